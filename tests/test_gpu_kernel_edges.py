@@ -1,0 +1,44 @@
+"""Each grouped-GEMM and routing kernel at the sizes where its tiling can go wrong (edges of tiles, remainders, the
+smallest and largest sizes of its range), against the fp64 oracle with the tolerance of tests/parity.py."""
+import numpy as np
+import pytest
+import torch
+
+import oracle
+from paper_2510_08055_amd import inputs
+from parity import assert_close
+
+pytestmark = pytest.mark.gpu
+
+DEV = "cuda:0"
+
+
+def dense_ffn(x_perm, offsets, L, dtype, E):
+    """The grouped FFN as each expert's dense SwiGLU FFN in the oracle (a one-expert layer with weight 1)."""
+    ref = np.zeros(tuple(x_perm.shape))
+    for e in range(E):
+        lo, hi = int(offsets[e]), int(offsets[e + 1])
+        if hi > lo:
+            ones = inputs.to_numpy(torch.ones((1, x_perm.shape[1]), dtype=inputs.torch_dtype(dtype)))
+            ref[lo:hi], _, _ = oracle.moe_layer(inputs.to_numpy(x_perm[lo:hi]), ones, None,
+                                                inputs.to_numpy(L["w_gate_up"][e:e + 1]),
+                                                inputs.to_numpy(L["w_down"][e:e + 1]), 1)
+    return ref
+
+
+# fp32: tiles of 32 rows x 16 columns, 16-wide k-chunks split over 4 waves
+@pytest.mark.parametrize("H,I,rows", [
+    (8, 8, [1]),                          # half a chunk, half a column tile
+    (16, 24, [31, 0, 33]),                # one chunk: three of the four waves have no work; a ragged second column tile
+    (72, 40, [32, 1, 64, 17]),            # 4.5 chunks: a ragged last chunk in the first wave
+    (264, 136, [0, 15, 100]),
+])
+def test_f32_grouped_ffn(gpu_lib, H, I, rows):
+    E, A = len(rows), sum(rows)
+    w = inputs.Workload("f32", H=H, E=E, K=1, I=I, n_layers=1, D=0, P=A, dtype="f32", seed=21)
+    L = inputs.make_layer(w, 0)
+    x_perm = inputs.randn((A, H), 1.0, 21, "x_perm", 0, "f32")
+    offsets = torch.tensor(np.concatenate([[0], np.cumsum(rows)]), dtype=torch.int32)
+    ctx = gpu_lib.Context(H, E, 1, I, torch.float32, max_tokens=A, device=DEV)
+    y = ctx.moe_grouped_ffn(x_perm.to(DEV), offsets.to(DEV), L["w_gate_up"].to(DEV), L["w_down"].to(DEV))
+    assert_close(y, dense_ffn(x_perm, offsets, L, "f32", E), "f32", "fp32 grouped_ffn")
