@@ -63,7 +63,7 @@ hipError_t launch_topk(const double* logits, int64_t T, int E, int K, int renorm
                        int32_t* tile_hist, hipStream_t s);
 
 // permute.hip
-constexpr int kPermTile = 8192;  // assignments per block of the permutation kernels
+constexpr int kPermTile = 2048;  // assignments per block of the permutation kernels
 // hist_ready: tile_hist already holds the per-tile histograms (the top-k kernel counted them)
 hipError_t launch_permute(const int32_t* idx, int64_t A, int E, int32_t* counts, int32_t* offsets,
                           int32_t* perm, int32_t* inv, int32_t* tile_hist, bool hist_ready,
