@@ -16,6 +16,7 @@ struct moe_ctx {
     int esz;  // bytes per element
     // workspace slices (device)
     unsigned long long* d_active_total;
+    uint32_t* d_tickets;     // of the one-launch routing of small batches: zero between launches
     double* logits;
     int32_t *idx, *counts, *offsets, *perm, *inv, *tile_hist;
     float* w;
@@ -143,23 +144,31 @@ moe_status run_layer(moe_ctx* c, const moe_layer& L, RowSrc x, int64_t T, void* 
     const int n_perm_tiles = (int)((A + kPermTile - 1) / kPermTile);
     const bool fused_hist = n_perm_tiles > 1;
     hipError_t e;
-    {
+    const bool small = route_is_small(T, g.E, g.K);
+    if (small) {
+        // (timed as the router's logits; the other two have no launch of their own)
+        Timed t(c, MOE_KERNEL_ROUTER_LOGITS, s);
+        e = launch_route_small(g.dtype, x, T, g.H, L.w_router, L.router_bias, g.E, g.K, g.renormalize, c->logits, c->idx,
+                               c->w, c->offsets, c->perm, c->inv, c->d_active_total, c->d_tickets, s);
+    } else {
         Timed t(c, MOE_KERNEL_ROUTER_LOGITS, s);
         e = launch_router_logits(g.dtype, x, T, g.H, L.w_router, L.router_bias, g.E, c->logits, c->tile_hist,
                                  fused_hist ? n_perm_tiles * g.E : 0, s);
     }
     if (e != hipSuccess) return MOE_ERR_DEVICE;
-    {
-        Timed t(c, MOE_KERNEL_TOPK, s);
-        e = launch_topk(c->logits, T, g.E, g.K, g.renormalize, c->idx, c->w, fused_hist ? c->tile_hist : nullptr, s);
+    if (!small) {
+        {
+            Timed t(c, MOE_KERNEL_TOPK, s);
+            e = launch_topk(c->logits, T, g.E, g.K, g.renormalize, c->idx, c->w, fused_hist ? c->tile_hist : nullptr, s);
+        }
+        if (e != hipSuccess) return MOE_ERR_DEVICE;
+        {
+            Timed t(c, MOE_KERNEL_PERMUTE, s);
+            e = launch_permute(c->idx, A, g.E, c->counts, c->offsets, c->perm, c->inv, c->tile_hist, fused_hist,
+                               c->d_active_total, s);
+        }
+        if (e != hipSuccess) return MOE_ERR_DEVICE;
     }
-    if (e != hipSuccess) return MOE_ERR_DEVICE;
-    {
-        Timed t(c, MOE_KERNEL_PERMUTE, s);
-        e = launch_permute(c->idx, A, g.E, c->counts, c->offsets, c->perm, c->inv, c->tile_hist, fused_hist,
-                           c->d_active_total, s);
-    }
-    if (e != hipSuccess) return MOE_ERR_DEVICE;
     // the activation rows are gathered inside the gate_up GEMM's tile loads: no x_perm round trip
     const bool w4 = g.weight_format == MOE_W_MXFP4;
     {
@@ -266,6 +275,8 @@ moe_status moe_create(const moe_config* cfg, int64_t max_tokens, void* workspace
     c->max_tokens = max_tokens;
     c->esz = cfg->dtype == MOE_BF16 ? 2 : 4;
     c->d_active_total = reinterpret_cast<unsigned long long*>(b + L.counters);
+    static_assert(128 + kSmallTickets * sizeof(uint32_t) <= 256, "the counter block");
+    c->d_tickets = reinterpret_cast<uint32_t*>(b + L.counters + 128);
     c->logits = reinterpret_cast<double*>(b + L.logits);
     c->idx = reinterpret_cast<int32_t*>(b + L.idx);
     c->w = reinterpret_cast<float*>(b + L.w);

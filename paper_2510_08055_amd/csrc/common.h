@@ -62,6 +62,16 @@ hipError_t launch_router_logits(int dtype, RowSrc x, int64_t T, int H, const voi
 hipError_t launch_topk(const double* logits, int64_t T, int E, int K, int renorm, int32_t* idx, float* w,
                        int32_t* tile_hist, hipStream_t s);
 
+// Batches whose routing (logits, top-k, permutation) is one launch: a single block can hold the permutation, and
+// 16 lanes a token's logits (at E > 256 they no longer fit the registers of a 16-wave block).
+constexpr int kSmallTokens = 256, kSmallExperts = 256;
+inline bool route_is_small(int64_t T, int E, int K) { return T <= kSmallTokens && E <= kSmallExperts && K <= 16; }
+// tickets: kSmallTickets counters that are zero before the first launch; every launch leaves them at zero
+constexpr int kSmallTickets = 1 + kSmallTokens / 16;
+hipError_t launch_route_small(int dtype, RowSrc x, int64_t T, int H, const void* w_router, const float* bias, int E, int K,
+                              int renorm, double* logits, int32_t* idx, float* w, int32_t* offsets, int32_t* perm, int32_t* inv,
+                              unsigned long long* active_total, uint32_t* tickets, hipStream_t s);
+
 // permute.hip
 constexpr int kPermTile = 2048;  // assignments per block of the permutation kernels
 // hist_ready: tile_hist already holds the per-tile histograms (the top-k kernel counted them)

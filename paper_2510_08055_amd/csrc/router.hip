@@ -7,6 +7,8 @@
 // realistic gap between neighbouring logits.  The reduction order of a token's
 // logits depends only on H, never on the batch, so routing is batch-invariant:
 // the chunked and the layered schedule route every token identically.
+#include <type_traits>
+
 #include "common.h"
 
 namespace moe {
@@ -84,9 +86,16 @@ __device__ __forceinline__ void wait_ring(vec8<float> (&x)[4], vec8<float> (&w)[
                  : "memory");
 }
 
-// One block: a 16-token x 16-expert tile of logits with v_mfma_f64_16x16x4; its 4 waves split the
-// hidden dimension (wave w takes the 32-wide k-chunks w, w+4, w+8, ...) and their partial tiles are
-// added in wave order 0,1,2,3 through LDS, so the summation order of a logit is fixed by H alone.
+// One block: a 16-token x 16-expert tile of logits with v_mfma_f64_16x16x4.  The hidden dimension is cut
+// into 32-wide chunks, chunk c belongs to partial sum c % 16, and the 16 partial sums are added in a fixed
+// tree (p, p + 4, p + 8, p + 12 in order for p = 0..3, then those four in order), so the summation order of a
+// logit is fixed by H alone, whichever of the two block shapes computes it:
+//   NW = 4:  wave w holds partial sums w, w + 4, w + 8, w + 12 (four independent MFMA chains).  The shape of the
+//            stand-alone logits kernel (16 waves per block were no faster there at 272 to 640 tokens: 11.5 against
+//            11.9 us and 16.4 against 18.4 us).
+//   NW = 16: one partial sum per wave.  The shape of the one-launch routing of a decode batch, whose few blocks are
+//            a serial chain of load latencies and 64-clock MFMAs: 1 us shorter than with 4 waves at H = 2048, 2 us
+//            at H = 2880.
 // Lane l supplies row (l % 16) of both operands; its quarter q = l / 16 owns the 8 consecutive
 // k-values [c*32 + q*8, c*32 + q*8 + 8) of chunk c and feeds them to 8 successive MFMAs (any fixed
 // pairing of k-slots is a valid summation order).  The raw operands of the next chunks are fetched
@@ -95,43 +104,57 @@ __device__ __forceinline__ void wait_ring(vec8<float> (&x)[4], vec8<float> (&w)[
 // many blocks leaves a 20 % tail on 256 compute units, and the matrix pipe, not the loads, is the limit.)
 constexpr int kRouterBufs = 4;      // (wait_ring names exactly four buffers)
 
-template <typename T>
-__global__ __launch_bounds__(256) void router_logits_kernel(RowSrc x, int64_t n_tok, int H,
-                                                            const T* __restrict__ wr,
-                                                            const float* __restrict__ bias, int E,
-                                                            double* __restrict__ logits,
-                                                            int32_t* __restrict__ zero_buf, int zero_n)
+// Stores and loads that meet at the level every block of the launch sees (past the caches of one XCD), for data
+// that one block hands to another inside a launch; the order between them comes from the ticket counters.
+template <typename V> __device__ __forceinline__ void store_shared(V* p, V v)
 {
-    __shared__ double part[3][4][64];   // partial tiles of waves 1..3: [wave-1][element v][lane]
-    // side job of block (0,0): clear the per-tile expert histogram that the top-k kernel, next on the
-    // stream, counts into (saves a separate fill launch)
-    if (blockIdx.x == 0 && blockIdx.y == 0)
-        for (int i = threadIdx.x; i < zero_n; i += 256) zero_buf[i] = 0;
+    __hip_atomic_store(p, v, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+}
+template <typename V> __device__ __forceinline__ V load_shared(const V* p)
+{
+    return __hip_atomic_load(p, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+}
+
+// The tile of logits at (t0, e0), written by wave 0 of the block; every thread of the block calls it.
+// SHARED: another block of the same launch reads the logits.
+template <typename T, int NW, bool SHARED>
+__device__ __forceinline__ void logits_tile(const RowSrc& x, int64_t n_tok, int H, const T* __restrict__ wr,
+                                            const float* __restrict__ bias, int E, double* __restrict__ logits, int64_t t0,
+                                            int e0)
+{
+    constexpr int NACC = 16 / NW;                // partial sums per wave
+    static_assert(NW == 4 || NW == 16, "16 partial sums over 4 or 16 waves");
+    __shared__ double part[NW - 1][4][64];       // [wave-1][element v][lane]: a wave's partial sums, already added up
     const int lane = lane_id();
-    const int wave = threadIdx.x >> 6;
+    const int wave = __builtin_amdgcn_readfirstlane((int)(threadIdx.x >> 6));
     const int r = lane & 15, q = lane >> 4;
-    const int64_t t0 = (int64_t)blockIdx.x * 16;
-    const int e0 = blockIdx.y * 16;
     const int64_t tr = (t0 + r < n_tok) ? (t0 + r) : (n_tok - 1);  // clamp: loads stay in bounds
     const int er = (e0 + r < E) ? (e0 + r) : (E - 1);
     const T* xp = row_ptr<T>(x, tr, H) + q * 8;
     const T* wp = wr + (int64_t)er * H + q * 8;
 
-    double4_t acc = {0.0, 0.0, 0.0, 0.0};
+    double4_t acc[NACC];
+#pragma unroll
+    for (int a = 0; a < NACC; ++a) acc[a] = double4_t{0.0, 0.0, 0.0, 0.0};
     // Ring of kRouterBufs operand buffers: the raw operands of this wave's next kRouterBufs - 1 chunks are
     // in flight while the MFMAs of the current chunk run.  Loads and waits of the ring are explicit (the
     // compiler would otherwise sink the loads next to their uses and wait for all of them); the look-ahead
     // index is clamped to the wave's last whole chunk rather than tested, so the loop body is branch-free.
     vec8<T> xa[kRouterBufs], wa[kRouterBufs];
-    auto multiply = [&](int buf) {
+    auto multiply = [&](int buf, double4_t& a) {
 #pragma unroll
         for (int j = 0; j < 8; ++j)
-            acc = __builtin_amdgcn_mfma_f64_16x16x4f64(xa[buf].get(j), wa[buf].get(j), acc, 0, 0, 0);
+            a = __builtin_amdgcn_mfma_f64_16x16x4f64(xa[buf].get(j), wa[buf].get(j), a, 0, 0, 0);
+    };
+    auto multiply_into = [&](int buf, int i) {   // the i-th chunk of this wave, i not known at compile time
+#pragma unroll
+        for (int a = 0; a < NACC; ++a)
+            if (a == i % NACC) multiply(buf, acc[a]);
     };
     const int n_whole = H / 32;                                            // whole 32-wide chunks of a row
-    const int mine = n_whole > wave ? (n_whole - wave + 3) / 4 : 0;         // of which this wave takes chunks wave, wave+4, ...
+    const int mine = n_whole > wave ? (n_whole - wave + NW - 1) / NW : 0;   // of which this wave takes chunks wave, wave + NW, ...
     auto fetch = [&](int buf, int i) {                                      // this wave's i-th chunk
-        const int k0 = (wave + 4 * i) * 32;
+        const int k0 = (wave + NW * i) * 32;
         xa[buf].load_async(xp + k0);
         wa[buf].load_async(wp + k0);
     };
@@ -146,7 +169,7 @@ __global__ __launch_bounds__(256) void router_logits_kernel(RowSrc x, int64_t n_
                 const int ahead = i + b + kRouterBufs - 1;
                 fetch((b + kRouterBufs - 1) % kRouterBufs, ahead < mine ? ahead : mine - 1);
                 wait_loads<(kRouterBufs - 1) * kPerChunk>(xa[b], wa[b]);
-                multiply(b);
+                multiply(b, acc[b % NACC]);      // (i is a multiple of kRouterBufs, which NACC divides)
             }
         }
         // the look-ahead loads of the last round are still in flight; they target ring registers
@@ -155,9 +178,9 @@ __global__ __launch_bounds__(256) void router_logits_kernel(RowSrc x, int64_t n_
     for (; i < mine; ++i) {        // the last few whole chunks, one at a time
         fetch(0, i);
         wait_loads<0>(xa[0], wa[0]);
-        multiply(0);
+        multiply_into(0, i);
     }
-    if (H % 32 != 0 && wave == n_whole % 4) {      // the row's partial chunk: lanes past the end feed zeros
+    if (H % 32 != 0 && wave == n_whole % NW) {      // the row's partial chunk: lanes past the end feed zeros
         const int k0 = n_whole * 32;
         if (k0 + q * 8 < H) {
             xa[0].load(xp + k0);
@@ -166,11 +189,14 @@ __global__ __launch_bounds__(256) void router_logits_kernel(RowSrc x, int64_t n_
             xa[0].zero();
             wa[0].zero();
         }
-        multiply(0);
+        multiply_into(0, n_whole / NW);
     }
+    double4_t mysum = acc[0];
+#pragma unroll
+    for (int a = 1; a < NACC; ++a) mysum += acc[a];
     if (wave > 0) {
 #pragma unroll
-        for (int v = 0; v < 4; ++v) part[wave - 1][v][lane] = acc[v];
+        for (int v = 0; v < 4; ++v) part[wave - 1][v][lane] = mysum[v];
     }
     __syncthreads();
     if (wave != 0) return;
@@ -181,10 +207,34 @@ __global__ __launch_bounds__(256) void router_logits_kernel(RowSrc x, int64_t n_
 #pragma unroll
         for (int v = 0; v < 4; ++v) {
             const int64_t t = t0 + v * 4 + q;
-            const double z = ((acc[v] + part[0][v][lane]) + part[1][v][lane]) + part[2][v][lane];
-            if (t < n_tok) logits[t * E + e] = z + b;
+            double z = 0.0;
+#pragma unroll
+            for (int p = 0; p < 4; ++p) {        // partial sums p, p + 4, p + 8, p + 12
+                double s = p == 0 ? mysum[v] : part[p - 1][v][lane];
+#pragma unroll
+                for (int w = p + 4; w < NW; w += 4) s += part[w - 1][v][lane];
+                z = p == 0 ? s : z + s;
+            }
+            if (t < n_tok) {
+                if (SHARED) store_shared(logits + t * E + e, z + b);
+                else logits[t * E + e] = z + b;
+            }
         }
     }
+}
+
+template <typename T, int NW>
+__global__ __launch_bounds__(NW * 64) void router_logits_kernel(RowSrc x, int64_t n_tok, int H,
+                                                                const T* __restrict__ wr,
+                                                                const float* __restrict__ bias, int E,
+                                                                double* __restrict__ logits,
+                                                                int32_t* __restrict__ zero_buf, int zero_n)
+{
+    // side job of block (0,0): clear the per-tile expert histogram that the top-k kernel, next on the
+    // stream, counts into (saves a separate fill launch)
+    if (blockIdx.x == 0 && blockIdx.y == 0)
+        for (int i = threadIdx.x; i < zero_n; i += NW * 64) zero_buf[i] = 0;
+    logits_tile<T, NW, false>(x, n_tok, H, wr, bias, E, logits, (int64_t)blockIdx.x * 16, (int)blockIdx.y * 16);
 }
 
 // (value, index) "greater" under the routing order: larger logit first, equal logits by lower index.
@@ -304,36 +354,22 @@ template <int CTRL> __device__ __forceinline__ void row_best_step(double& bv, in
 }
 template <int CTRL> __device__ __forceinline__ double row_sum_step(double v) { return v + dpp_mov<CTRL>(v); }
 
+// Top-k of token t by the 16 lanes of a row (c = lane % 16): lane c < K ends with the c-th winner and its
+// weight.  All lanes of the row hold the same t.
 template <int NPL>   // logits per lane: experts c + 16 i, i < NPL
-__global__ __launch_bounds__(kTopkWaves * 64) void topk_rows_kernel(const double* __restrict__ logits, int64_t n_tok,
-                                                                    int E, int K, int renorm, int32_t* __restrict__ idx,
-                                                                    float* __restrict__ w,
-                                                                    int32_t* __restrict__ tile_hist)
+__device__ __forceinline__ void topk_of_row(const double* z, int E, int K, int renorm, int c, bool shared, int& my_e,
+                                            float& my_w)
 {
-    // a block's assignments (32 tokens x K <= 512) touch at most two permutation tiles
-    __shared__ int32_t hist[2][kMaxExperts];
-    const int lane = lane_id();
-    const int wave = threadIdx.x >> 6;
-    const int c = lane & 15;
-    const int64_t tb0 = (int64_t)blockIdx.x * (kTopkWaves * 4);
-    const int64_t tile0 = tb0 * K / kPermTile;
-    if (tile_hist) {
-        for (int i = threadIdx.x; i < 2 * E; i += kTopkWaves * 64) hist[i / E][i % E] = 0;
-        __syncthreads();
-    }
-    const int64_t t = tb0 + wave * 4 + (lane >> 4);
-    const bool live = t < n_tok;
-    const int64_t tl = live ? t : n_tok - 1;      // rows past the end work on a copy of the last token, store nothing
     const double NEG = -__builtin_huge_val();
     double v[NPL];
 #pragma unroll
     for (int i = 0; i < NPL; ++i) {
         const int e = c + 16 * i;
-        v[i] = (e < E) ? logits[tl * E + e] : NEG;
+        v[i] = (e < E) ? (shared ? load_shared(z + e) : z[e]) : NEG;
     }
     double esum = 0.0;      // only without renormalisation: this lane's share of sum_e exp(z_e - z_max)
     double my_z = NEG, z_max = 0.0;
-    int my_e = 0;
+    my_e = 0;
     for (int j = 0; j < K; ++j) {
         double bv = v[0];
         int be = c;
@@ -366,9 +402,35 @@ __global__ __launch_bounds__(kTopkWaves * 64) void topk_rows_kernel(const double
     denom = row_sum_step<kDppXor2>(denom);
     denom = row_sum_step<kDppHalfMirror>(denom);
     denom = row_sum_step<kDppMirror>(denom);
+    my_w = (float)(p / denom);
+}
+
+template <int NPL>
+__global__ __launch_bounds__(kTopkWaves * 64) void topk_rows_kernel(const double* __restrict__ logits, int64_t n_tok,
+                                                                    int E, int K, int renorm, int32_t* __restrict__ idx,
+                                                                    float* __restrict__ w,
+                                                                    int32_t* __restrict__ tile_hist)
+{
+    // a block's assignments (32 tokens x K <= 512) touch at most two permutation tiles
+    __shared__ int32_t hist[2][kMaxExperts];
+    const int lane = lane_id();
+    const int wave = threadIdx.x >> 6;
+    const int c = lane & 15;
+    const int64_t tb0 = (int64_t)blockIdx.x * (kTopkWaves * 4);
+    const int64_t tile0 = tb0 * K / kPermTile;
+    if (tile_hist) {
+        for (int i = threadIdx.x; i < 2 * E; i += kTopkWaves * 64) hist[i / E][i % E] = 0;
+        __syncthreads();
+    }
+    const int64_t t = tb0 + wave * 4 + (lane >> 4);
+    const bool live = t < n_tok;
+    const int64_t tl = live ? t : n_tok - 1;      // rows past the end work on a copy of the last token, store nothing
+    int my_e;
+    float my_w;
+    topk_of_row<NPL>(logits + tl * E, E, K, renorm, c, false, my_e, my_w);
     if (live && c < K) {
         idx[t * K + c] = my_e;
-        w[t * K + c] = (float)(p / denom);
+        w[t * K + c] = my_w;
         if (tile_hist) atomicAdd(&hist[(t * K + c) / kPermTile - tile0][my_e], 1);
     }
     if (tile_hist) {
@@ -380,16 +442,174 @@ __global__ __launch_bounds__(kTopkWaves * 64) void topk_rows_kernel(const double
     }
 }
 
+// ----------------------------------------------------------------------------------------------
+// Router, top-k and permutation of a decode batch (at most kSmallTokens tokens, K <= 16) in one launch.
+//
+// On such a batch the three kernels are a chain of launches with almost nothing in each: one token through
+// E = 128 took 8.1 + 5.0 + 8.9 us, of which the arithmetic is a microsecond.  Here every block computes its
+// tile of logits and takes a ticket of its 16 tokens; the block that draws the last one finds their logits
+// written and does their top-k; of those blocks, the one that draws the last ticket of the batch does the
+// permutation (no block ever waits for another).  A token's experts are distinct, so the stable rank of an
+// assignment inside its expert is the number of earlier tokens that chose the expert: one bit per token and
+// expert in LDS, counted with popcounts.  What crosses between blocks goes past the XCD's caches by itself
+// (store_shared / load_shared): a fence would write back and drop the whole L2, 2 us with a few blocks and 15 us
+// with a hundred.  Every last drawer puts its counter back to zero.
+// Measured (H = 2048, E = 128, top-8; events around the launches, three launches -> one): 1 token 28.9 -> 15.4 us,
+// 32 tokens 29.3 -> 17.8 us, 128 tokens 30.2 -> 19.0 us; 256 tokens at H = 2880, top-4 31.0 -> 20.8 us.  A last
+// block that does the top-k of all tokens was slower from 32 tokens on (26 us; 46 us at 128).
+// ----------------------------------------------------------------------------------------------
+constexpr int kSmallWaves = 16;
+constexpr int kSmallWords = kSmallTokens / 64;
+
+// Draws a ticket for the block once everything it has stored is visible; true for the last of n drawers.
+// Every thread of the block calls it (`flag`: a word of LDS).
+__device__ __forceinline__ bool last_to_arrive(uint32_t* ticket, uint32_t n, int32_t* flag)
+{
+    asm volatile("s_waitcnt vmcnt(0)" ::: "memory");         // this wave's stores have reached the shared level
+    __syncthreads();
+    if (threadIdx.x == 0) {
+        const bool last = __hip_atomic_fetch_add(ticket, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) == n - 1;
+        if (last) store_shared(ticket, 0u);
+        *flag = last;
+    }
+    __syncthreads();
+    return *flag != 0;
+}
+
+template <typename T, int NPL>
+__global__ __launch_bounds__(kSmallWaves * 64) void route_small_kernel(
+    RowSrc x, int n_tok, int H, const T* __restrict__ wr, const float* __restrict__ bias, int E, int K, int renorm,
+    double* logits, int32_t* idx, float* __restrict__ w, int32_t* __restrict__ offsets, int32_t* __restrict__ perm,
+    int32_t* __restrict__ inv, unsigned long long* __restrict__ active_total, uint32_t* tickets)
+{
+    __shared__ unsigned long long chosen[kSmallExperts][kSmallWords];      // bit t of an expert: token t chose it
+    __shared__ int32_t count[kSmallExperts], start[kSmallExperts];
+    __shared__ int32_t own[16 * 16];                                       // the experts of this block's 16 tokens
+    __shared__ int32_t flag;
+    const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
+    const int t0 = (int)blockIdx.x * 16;
+    logits_tile<T, kSmallWaves, true>(x, n_tok, H, wr, bias, E, logits, t0, (int)blockIdx.y * 16);
+    for (int i = tid; i < E * kSmallWords; i += kSmallWaves * 64) (&chosen[0][0])[i] = 0ull;
+    if (tid < E) count[tid] = 0;
+    if (!last_to_arrive(tickets + 1 + blockIdx.x, gridDim.y, &flag)) return;
+
+    // top-k of this block's 16 tokens: 16 lanes per token, four waves
+    const bool single = gridDim.x == 1;       // a batch of one token tile: nothing to hand to another block
+    if (wave < 4) {
+        const int c = lane & 15, row = wave * 4 + (lane >> 4);
+        const int t = t0 + row;
+        int e;
+        float wt;
+        topk_of_row<NPL>(logits + (int64_t)(t < n_tok ? t : n_tok - 1) * E, E, K, renorm, c, true, e, wt);
+        if (t < n_tok && c < K) {
+            w[t * K + c] = wt;
+            if (single) own[row * K + c] = e;
+            else store_shared(idx + t * K + c, (int32_t)e);
+        }
+    }
+    if (single) __syncthreads();
+    else if (!last_to_arrive(tickets, gridDim.x, &flag)) return;
+
+    const int A = n_tok * K;
+    constexpr int PER = kSmallTokens * 16 / (kSmallWaves * 64);            // assignments per thread, at most
+    int my_e[PER];
+#pragma unroll
+    for (int p = 0; p < PER; ++p) {
+        const int f = p * kSmallWaves * 64 + tid;
+        my_e[p] = -1;
+        if (f < A) my_e[p] = single ? own[f] : load_shared(idx + f);
+    }
+#pragma unroll
+    for (int p = 0; p < PER; ++p) {
+        const int f = p * kSmallWaves * 64 + tid;
+        if (my_e[p] >= 0) {
+            const int t = f / K;
+            atomicOr(&chosen[my_e[p]][t >> 6], 1ull << (t & 63));
+            atomicAdd(&count[my_e[p]], 1);
+        }
+    }
+    __syncthreads();
+    // exclusive scan of the expert counts by wave 0: lane l owns experts [4 l, 4 l + 4)
+    if (wave == 0) {
+        constexpr int EPL = kSmallExperts / 64;
+        int cnt[EPL], sum = 0, act = 0;
+#pragma unroll
+        for (int i = 0; i < EPL; ++i) {
+            const int e = lane * EPL + i;
+            cnt[i] = e < E ? count[e] : 0;
+            sum += cnt[i];
+            act += cnt[i] > 0;
+        }
+        int incl = sum;
+#pragma unroll
+        for (int off = 1; off < 64; off <<= 1) {
+            const int o = __shfl_up(incl, off, 64);
+            if (lane >= off) incl += o;
+        }
+        int run = incl - sum;
+#pragma unroll
+        for (int i = 0; i < EPL; ++i) {
+            const int e = lane * EPL + i;
+            if (e < E) {
+                start[e] = run;
+                offsets[e] = run;
+            }
+            run += cnt[i];
+        }
+        if (lane == 63) offsets[E] = incl;
+#pragma unroll
+        for (int off = 32; off >= 1; off >>= 1) act += __shfl_xor(act, off, 64);
+        if (lane == 0) atomicAdd(active_total, (unsigned long long)act);
+    }
+    __syncthreads();
+#pragma unroll
+    for (int p = 0; p < PER; ++p) {
+        const int f = p * kSmallWaves * 64 + tid;
+        const int e = my_e[p];
+        if (e < 0) continue;
+        const int t = f / K;
+        int pos = start[e];
+        for (int j = 0; j <= (t >> 6); ++j) {
+            const unsigned long long m = chosen[e][j];
+            pos += __popcll(j < (t >> 6) ? m : m & ((1ull << (t & 63)) - 1));
+        }
+        perm[pos] = f;
+        inv[f] = pos;
+    }
+}
+
+hipError_t launch_route_small(int dtype, RowSrc x, int64_t T, int H, const void* w_router, const float* bias, int E, int K,
+                              int renorm, double* logits, int32_t* idx, float* w, int32_t* offsets, int32_t* perm, int32_t* inv,
+                              unsigned long long* active_total, uint32_t* tickets, hipStream_t s)
+{
+    if (!route_is_small(T, E, K)) return hipErrorInvalidValue;
+    const dim3 grid((unsigned)((T + 15) / 16), (unsigned)((E + 15) / 16));
+    const int npl = (E + 15) / 16;
+    auto go = [&](auto npl_const) {
+        constexpr int NPL = decltype(npl_const)::value;
+        if (dtype == MOE_BF16)
+            route_small_kernel<bf16_t, NPL><<<grid, kSmallWaves * 64, 0, s>>>(
+                x, (int)T, H, (const bf16_t*)w_router, bias, E, K, renorm, logits, idx, w, offsets, perm, inv, active_total, tickets);
+        else
+            route_small_kernel<float, NPL><<<grid, kSmallWaves * 64, 0, s>>>(
+                x, (int)T, H, (const float*)w_router, bias, E, K, renorm, logits, idx, w, offsets, perm, inv, active_total, tickets);
+        return hipGetLastError();
+    };
+    if (npl <= 1) return go(std::integral_constant<int, 1>{});
+    if (npl <= 2) return go(std::integral_constant<int, 2>{});
+    if (npl <= 8) return go(std::integral_constant<int, 8>{});
+    return go(std::integral_constant<int, 16>{});
+}
 
 hipError_t launch_router_logits(int dtype, RowSrc x, int64_t T, int H, const void* w_router, const float* bias,
                                 int E, double* logits, int32_t* zero_buf, int zero_n, hipStream_t s)
 {
     dim3 grid((unsigned)((T + 15) / 16), (unsigned)((E + 15) / 16));
     if (dtype == MOE_BF16)
-        router_logits_kernel<bf16_t><<<grid, 256, 0, s>>>(x, T, H, (const bf16_t*)w_router, bias, E, logits, zero_buf,
+        router_logits_kernel<bf16_t, 4><<<grid, 256, 0, s>>>(x, T, H, (const bf16_t*)w_router, bias, E, logits, zero_buf,
                                                           zero_n);
     else
-        router_logits_kernel<float><<<grid, 256, 0, s>>>(x, T, H, (const float*)w_router, bias, E, logits, zero_buf,
+        router_logits_kernel<float, 4><<<grid, 256, 0, s>>>(x, T, H, (const float*)w_router, bias, E, logits, zero_buf,
                                                          zero_n);
     return hipGetLastError();
 }

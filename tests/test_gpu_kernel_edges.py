@@ -42,3 +42,23 @@ def test_f32_grouped_ffn(gpu_lib, H, I, rows):
     ctx = gpu_lib.Context(H, E, 1, I, torch.float32, max_tokens=A, device=DEV)
     y = ctx.moe_grouped_ffn(x_perm.to(DEV), offsets.to(DEV), L["w_gate_up"].to(DEV), L["w_down"].to(DEV))
     assert_close(y, dense_ffn(x_perm, offsets, L, "f32", E), "f32", "fp32 grouped_ffn")
+
+
+# one-launch routing of small batches (at most 256 tokens, 256 experts, top-16): 16-token tiles, 64-token words of the
+# choice bitmask; the same layer through the step calls (three-launch routing) must give the same bits
+@pytest.mark.parametrize("E,K", [(8, 2), (128, 8), (40, 16), (256, 5), (257, 3)])
+@pytest.mark.parametrize("T", [1, 16, 17, 64, 65, 255, 256, 257])
+def test_one_launch_routing_equals_the_steps(gpu_lib, T, E, K):
+    H, I = 72, 64
+    w = inputs.Workload("small", H=H, E=E, K=K, I=I, n_layers=1, D=T, P=0, dtype="bf16", seed=100 * T + E)
+    L = {k: (v.to(DEV) if v is not None else None) for k, v in inputs.make_layer(w, 0).items()}
+    x = inputs.randn((T, H), 1.0, w.seed, "x", 0, "bf16").to(DEV)
+    for renorm in (True, False):
+        ctx = gpu_lib.Context(H, E, K, I, torch.bfloat16, max_tokens=T, renormalize=renorm, residual=False, device=DEV)
+        idx, wt = ctx.moe_router_topk(x, L["w_router"])
+        counts, offsets, perm, inv, x_perm = ctx.moe_permute(x, idx)
+        y_steps = ctx.moe_combine(ctx.moe_grouped_ffn(x_perm, offsets, L["w_gate_up"], L["w_down"]), inv, wt)
+        for _ in range(2):       # a second launch finds the ticket counters at zero again
+            y, _ = ctx.moe_group_forward([L], x, None)
+            assert torch.equal(y, y_steps)
+        assert ctx.moe_read_counters().active_experts_total == 2 * int((counts > 0).sum())
