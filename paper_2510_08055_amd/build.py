@@ -23,7 +23,7 @@ FLAGS = ["--offload-arch=gfx950", "-O3", "-std=c++17", "-fPIC", "-Wall",
 # register the load has not written yet, and the load would later land on whatever the register holds by
 # then (an address, say).  So these kernels must compile without any scratch memory; the build checks it.
 NO_SCRATCH = {"router.hip": ("router_logits_kernel", "route_small_kernel"), "ffn_w4.hip": ("grouped_gemm_w4_stream_kernel",),
-              "ffn.hip": ("grouped_gemm_bf16_pipe_kernel",)}
+              "ffn.hip": ("grouped_gemm_bf16_pipe_kernel", "grouped_gemm_bf16_big_kernel")}
 
 
 def _scratch_users(log, names):
@@ -66,6 +66,8 @@ def _foreign_m0_uses(asm):
 # between the compiler's #ASMSTART / #ASMEND markers) and pick the value up after an explicit
 # `s_waitcnt vmcnt`.  In the assembly, nothing between such a load and the next vmcnt wait may name vN.
 ASYNC_DWORD_LOADS = {"ffn.hip": "grouped_gemm_bf16_pipe_kernel", "ffn_w4.hip": "grouped_gemm_w4_stream_kernel"}
+# The same, following the branches (a persistent kernel's loads and waits are steps of a loop over tiles).
+ASYNC_DWORD_LOADS_ANY_PATH = {"ffn.hip": "grouped_gemm_bf16_big_kernel"}
 
 
 def _early_uses_of_async_loads(asm, kernel):
@@ -106,6 +108,64 @@ def _early_uses_of_async_loads(asm, kernel):
     return bad
 
 
+def _early_uses_on_any_path(asm, kernel):
+    """Instructions that name the destination of an asm-issued global_load_dword before the next vmcnt wait, in every
+    function whose (mangled) name contains `kernel`; every path from the load is followed, branches included (for kernels without
+    waits that only a repeated test of the same condition pairs with their loads)."""
+    import re
+    bad, funcs, cur = [], [], None
+    for line in asm.splitlines():
+        m = re.match(r"^(_Z\S+):", line)
+        if m:
+            cur = []
+            if kernel in m.group(1):
+                funcs.append((m.group(1), cur))
+            continue
+        if cur is not None:
+            cur.append(line)
+    for name, lines in funcs:
+        code, labels, in_asm = [], {}, False      # (text, issued from inline asm)
+        for line in lines:
+            m = re.match(r"^(\.?\w+):", line)
+            if m:
+                labels[m.group(1)] = len(code)
+                continue
+            if "#ASMSTART" in line or "#ASMEND" in line:
+                in_asm = "#ASMSTART" in line
+                continue
+            text = line.split(";")[0].strip()
+            if text and not text.startswith("."):
+                code.append((text, in_asm))
+        named = []
+        for text, _ in code:
+            regs = set(int(r) for r in re.findall(r"\bv(\d+)\b", text))
+            for lo, hi in re.findall(r"\bv\[(\d+):(\d+)\]", text):
+                regs.update(range(int(lo), int(hi) + 1))
+            named.append(regs)
+        for at, (text, is_asm) in enumerate(code):
+            m = re.match(r"global_load_dword v(\d+), v\[", text) if is_asm else None
+            if not m:
+                continue
+            reg, seen, todo = int(m.group(1)), set(), [at + 1]
+            while todo:
+                i = todo.pop()
+                if i in seen or i >= len(code):
+                    continue
+                seen.add(i)
+                t = code[i][0]
+                if ("s_waitcnt" in t and "vmcnt" in t) or t.startswith("s_endpgm"):
+                    continue
+                if reg in named[i]:
+                    bad.append(f"{name[:60]}...: v{reg} (loaded asynchronously) named by: {t}")
+                    continue
+                m = re.match(r"s_c?branch\w*\s+(\.?\w+)", t)
+                if m:
+                    todo.append(labels[m.group(1)])
+                if not t.startswith("s_branch"):
+                    todo.append(i + 1)
+    return bad
+
+
 def _compile(src, verbose):
     out = os.path.join(OBJ, src.replace(".hip", ".o"))
     extra = ["-Rpass-analysis=kernel-resource-usage"] if src in NO_SCRATCH else []
@@ -130,7 +190,10 @@ def _compile(src, verbose):
             raise RuntimeError(f"{src}: M0 is used outside the asm-issued direct-to-LDS loads:\n  " + "\n  ".join(bad[:10]))
         if src in ASYNC_DWORD_LOADS:
             with open(asm_path) as f:
-                bad = _early_uses_of_async_loads(f.read(), ASYNC_DWORD_LOADS[src])
+                asm = f.read()
+            bad = _early_uses_of_async_loads(asm, ASYNC_DWORD_LOADS[src])
+            if src in ASYNC_DWORD_LOADS_ANY_PATH:
+                bad += _early_uses_on_any_path(asm, ASYNC_DWORD_LOADS_ANY_PATH[src])
             if bad:
                 raise RuntimeError(f"{src}: an asynchronously loaded register is used before its wait:\n  "
                                    + "\n  ".join(bad[:10]))

@@ -3,6 +3,8 @@
 #include <hip/hip_runtime.h>
 #include <stdint.h>
 
+#include <atomic>
+
 #include "moe_lp.h"
 
 namespace moe {
@@ -113,6 +115,24 @@ template <typename K> inline hipError_t ensure_lds_limit(K kern, size_t lds_byte
                             (int)lds_bytes);
     if (e == hipSuccess) done[d] = true;
     return e;
+}
+
+// Compute units of the current device, looked up once per device.
+inline hipError_t compute_units(int* out)
+{
+    static std::atomic<int> known[kMaxDevices];
+    int d = 0;
+    hipError_t e = hipGetDevice(&d);
+    if (e != hipSuccess) return e;
+    if (d < 0 || d >= kMaxDevices) return hipErrorInvalidDevice;
+    int n = known[d].load(std::memory_order_relaxed);
+    if (n == 0) {
+        e = hipDeviceGetAttribute(&n, hipDeviceAttributeMultiprocessorCount, d);
+        if (e != hipSuccess) return e;
+        known[d].store(n, std::memory_order_relaxed);
+    }
+    *out = n;
+    return hipSuccess;
 }
 
 // ffn_w4.hip: the same two GEMMs with MXFP4 expert weights (codes + scale bytes), bf16 activations

@@ -170,17 +170,11 @@ __global__ __launch_bounds__(256) void grouped_gemm_bf16_kernel(
 
 
 // ----------------------------------------------------------------------------------------------
-// Pipelined grouped GEMM: global -> LDS copies issued as direct-to-LDS loads
-// (global_load_lds_dwordx4: no staging registers, no LDS store instructions) into two rings of LDS
-// slots, NSA stages of the activation rows and NSB stages of the weight rows, each stage PBK (64 or
-// 32) k-values deep; one barrier per stage.  Used for both regimes of Sec. 2.5:
-//   - weight streaming (few rows per expert): 64 x 128 tiles, 3 + 3 stages of 64 k-values (24 KB each);
-//   - compute bound (hundreds of rows per expert): up to 256-row tiles with 64 k-values per stage, so
-//     that every tile row asks for a whole 128-byte line per stage (fewer, larger requests measured
-//     faster than 64-byte ones); 2 activation + 3 weight stages fill the 160 KB of LDS, the deeper
-//     ring going to the operand that comes from HBM.
-// NW waves arranged WM x WN; with 8 waves (2 per SIMD) one wave's barrier and LDS waits are covered
-// by the other's MFMAs.
+// Weight-streaming shape (few rows per expert): global -> LDS copies issued as direct-to-LDS loads
+// (global_load_lds_dwordx4: no staging registers, no LDS store instructions) into two rings of NS LDS slots, one for
+// the activation rows and one for the weight rows, each stage PBK (64 or 32) k-values deep; one barrier per stage.
+// 64 x 128 tiles, 4 waves, 3 stages of 24 KB: two blocks share a compute unit.
+// NW waves arranged WM x WN.
 // One wave-level load moves 64 lanes x 16 B = 8 (or 16) whole tile rows into 1 KB of LDS.  LDS rows
 // are unpadded (the hardware writes lanes contiguously), so bank conflicts on the 16-byte operand
 // reads are avoided by an XOR swizzle applied on the SOURCE side: LDS chunk c of tile row r holds
@@ -193,8 +187,7 @@ __global__ __launch_bounds__(256) void grouped_gemm_bf16_kernel(
 // SPLIT: the intermediate is a pair of bf16 values, as in the kernel above.
 // MAPPED: the rows come through a row map (the fused gather of the gate_up GEMM); without one the look-ups and
 // their wait, a round trip to L2 at the start of every tile, are left out altogether.
-template <int RBM, int BN, int WM, int NSA, int NSB, int PBK, int MINW, int NW, int ORD, bool GATED, bool OUT_F32,
-          bool SPLIT, bool MAPPED>
+template <int RBM, int BN, int WM, int NS, int PBK, int MINW, int NW, bool GATED, bool OUT_F32, bool SPLIT, bool MAPPED>
 __global__ __launch_bounds__(NW * 64, MINW) void grouped_gemm_bf16_pipe_kernel(
     RowSrc X, int ldx, const int32_t* __restrict__ row_map, int map_div,
     const int32_t* __restrict__ offsets, int E, const bf16_t* __restrict__ W, int64_t w_expert_stride, int N, int K,
@@ -214,24 +207,15 @@ __global__ __launch_bounds__(NW * 64, MINW) void grouped_gemm_bf16_pipe_kernel(
     constexpr int A_LPW = BM / RPL / NW, B_LPW = BN / RPL / NW;   // load groups per wave and stage
     constexpr int LPS = A_LPW + B_LPW;                  // load instructions per thread and stage
     constexpr int A_SLOT = BM * ROWB, B_SLOT = BN * ROWB;   // bytes of one stage of either operand
-    constexpr int B_BASE = NSA * A_SLOT;                // the weight ring follows the activation ring
-    constexpr int NSMIN = NSA < NSB ? NSA : NSB, NSMAX = NSA < NSB ? NSB : NSA;
+    constexpr int B_BASE = NS * A_SLOT;                 // the weight ring follows the activation ring
     static_assert(PBK == 64 || PBK == 32, "stage depth must be 64 or 32");
-    static_assert(RBM % WM == 0 && TM <= 4 && TNO >= 1 && NSA >= 2 && NSB >= 2, "bad tile configuration");
-    static_assert(ORD == 0 ? NSA == NSB : ORD == 1 ? (NSB >= NSA) : ORD == 2 ? (NSA >= NSB) : (NSA + 1 == NSB),
-                  "the shallower ring loads first");
-    // ORD 3: the activation ring is one stage shallower than the weight ring, and all activation loads of
-    // stage g+NSA are issued at once, right behind the barrier at the end of step g that frees their slot
-    // (before the last MFMAs of that step); only the weight loads are spread over the next step.  The
-    // activation loads then have a whole step to land instead of half a step.
-    constexpr bool A_EARLY = (ORD == 3);
+    static_assert(RBM % WM == 0 && TM <= 4 && TNO >= 1, "bad tile configuration");
+    static_assert(NS == 2 || NS == 3, "the prologue's loads are not in stage order: the wait counts hold for these rings");
     static_assert(BM % (RPL * NW) == 0 && BN % (RPL * NW) == 0, "tile rows must split evenly over the waves");
-    // ORD 0-2: in a step the loads of activation stage g+NSA-1 are issued first, those of weight stage
-    // g+NSB-1 after them; loads return in issue order, so when stage g+1 is needed the loads that may
-    // still be in flight are the ones issued after activation stage g+1.  ORD 3: activation stage g+1 went
-    // out behind the previous barrier, before the weight loads of step g, which are the B_LPW that may stay.
-    constexpr int WAIT_MAIN = ORD == 3 ? B_LPW : (NSMIN - 2) * LPS + (NSA < NSB ? B_LPW : NSB < NSA ? A_LPW : 0);
-    constexpr int WAIT_FIRST = (NSA - 2) * A_LPW;   // prologue: all weight stages, then the activation stages
+    // In a step the loads of stage g+NS-1 are issued; loads return in issue order, so when stage g+1 is needed the
+    // loads that may still be in flight are the ones issued after it.
+    constexpr int WAIT_MAIN = (NS - 2) * LPS;
+    constexpr int WAIT_FIRST = (NS - 2) * A_LPW;   // prologue: all weight stages, then the activation stages
     static_assert(WAIT_MAIN < 64 && WAIT_FIRST < 64, "vmcnt is a 6-bit counter");
 
     extern __shared__ __attribute__((aligned(1024))) char smem[];
@@ -284,16 +268,16 @@ __global__ __launch_bounds__(NW * 64, MINW) void grouped_gemm_bf16_pipe_kernel(
     const uint32_t lds0 = lds_address(smem);
     auto issue_b = [&](int kt, int p) {
         const int kw = (SPLIT && !GATED && kt >= nk_w) ? kt - nk_w : kt;
-        load_lds_16(b_src[p] + kw * PBK, lds0 + B_BASE + (kt % NSB) * B_SLOT + (wave + NW * p) * 1024);
+        load_lds_16(b_src[p] + kw * PBK, lds0 + B_BASE + (kt % NS) * B_SLOT + (wave + NW * p) * 1024);
     };
 #pragma unroll
-    for (int st = 0; st < NSB - 1; ++st)
+    for (int st = 0; st < NS - 1; ++st)
         if (st < nk_)
 #pragma unroll
             for (int p = 0; p < B_LPW; ++p) issue_b(st, p);
     if (MAPPED) {
         // the lookups came before the weight loads of the prologue: wait for them alone
-        if (nk_ >= NSB - 1) wait_vmcnt<(NSB - 1) * B_LPW>();
+        if (nk_ >= NS - 1) wait_vmcnt<(NS - 1) * B_LPW>();
         else wait_vmcnt<0>();
 #pragma unroll
         for (int p = 0; p < A_LPW; ++p) {
@@ -314,40 +298,16 @@ __global__ __launch_bounds__(NW * 64, MINW) void grouped_gemm_bf16_pipe_kernel(
         a_src[p] = row_ptr<bf16_t>(X, src, ldx) + ((l_chunk ^ swz<PBK>(tr)) << 3);
     }
     // Loads of one stage, cut into KS parts that are issued in the shadow of the MFMAs of the KS
-    // k-slices of the stage being multiplied: load p of the step (activation loads first) goes with
-    // slice p * KS / LPS.
-    // Lanes whose tile row lies past the tile's last row load nothing when that is safe: with NSA = 2 and
-    // the activation loads issued first, no wait count includes an activation load, so it does not matter
-    // whether a fully masked load instruction is issued or branched around.  The LDS rows they would have
-    // filled feed only accumulator rows that are never stored.
-    constexpr bool MASK_A = (NSA == 2 && (ORD == 1 || ORD == 3));
-    bool a_live[A_LPW];
-#pragma unroll
-    for (int p = 0; p < A_LPW; ++p) a_live[p] = !MASK_A || ((wave + NW * p) * RPL + l_row) < rows_here;
+    // k-slices of the stage being multiplied: load q of the step (activation loads first) goes with slice q % KS.
     auto issue_a = [&](int kt, int p) {
-        if (a_live[p])
-            load_lds_16(a_src[p] + kt * PBK, lds0 + (kt % NSA) * A_SLOT + (wave + NW * p) * 1024);
+        load_lds_16(a_src[p] + kt * PBK, lds0 + (kt % NS) * A_SLOT + (wave + NW * p) * 1024);
     };
-    // Load q of a step: ORD 0 alternates over the parts as A0 B0 | A1 B1 ..., ORD 1 issues the activation
-    // loads first, ORD 2 the weight loads first; with ORD 3 a step's parts hold its weight loads only.
-    auto load_is_a = [](int q) { return ORD == 2 ? q >= B_LPW : q < A_LPW; };
-    auto load_idx = [](int q) { return ORD == 2 ? (q >= B_LPW ? q - B_LPW : q) : (q < A_LPW ? q : q - A_LPW); };
-    auto load_part = [](int q) { return ORD == 0 ? q % KS : q * KS / LPS; };
-    auto issue_part = [&](int g, int part, bool more_a, bool more_b) {
-        if (A_EARLY) {
-#pragma unroll
-            for (int p = 0; p < B_LPW; ++p)
-                if (p * KS / B_LPW == part && more_b) issue_b(g + NSB - 1, p);
-            return;
-        }
+    auto issue_part = [&](int kt, int part) {
 #pragma unroll
         for (int q = 0; q < LPS; ++q) {
-            if (load_part(q) != part) continue;
-            if (load_is_a(q)) {
-                if (more_a) issue_a(g + NSA - 1, load_idx(q));
-            } else {
-                if (more_b) issue_b(g + NSB - 1, load_idx(q));
-            }
+            if (q % KS != part) continue;
+            if (q < A_LPW) issue_a(kt, q);
+            else issue_b(kt, q - A_LPW);
         }
     };
     // ---- LDS byte offsets of the operand rows this lane feeds to the MFMAs ----
@@ -366,11 +326,9 @@ __global__ __launch_bounds__(NW * 64, MINW) void grouped_gemm_bf16_pipe_kernel(
 #pragma unroll
     for (int kk = 0; kk < KS; ++kk) k_off[kk] = ((kk * 2 + fq) ^ fsw) << 4;
 
-    // Software pipeline.  Global side: activation stages g+1 .. g+NSA-1 and weight stages g+1 ..
-    // g+NSB-1 are in flight while stage g is multiplied (the weight ring may be one stage deeper: the
-    // weights are what comes from HBM).  LDS side: the operand fragments of k-slice kk+1 are read while
-    // the MFMAs of slice kk run; the last slice of a stage runs after the barrier that hands over the
-    // next stage, under the reads of that stage's first slice.
+    // Software pipeline.  Global side: stages g+1 .. g+NS-1 are in flight while stage g is multiplied.  LDS side: the
+    // operand fragments of k-slice kk+1 are read while the MFMAs of slice kk run; the last slice of a stage runs after
+    // the barrier that hands over the next stage, under the reads of that stage's first slice.
     // The body is instantiated for the number TMV of row blocks this wave really has (0..TM), so the
     // hot loop is straight-line code; a wave with no row block still loads and synchronises.
     auto run = [&](auto tmv_const) {
@@ -386,8 +344,8 @@ __global__ __launch_bounds__(NW * 64, MINW) void grouped_gemm_bf16_pipe_kernel(
         bf16x8_t af[2][TMA], bfr[2][TN];
         auto read_frags = [&](int g, int kk, int set) {
             if (TMV == 0) return;
-            const char* base_a = smem + (g % NSA) * A_SLOT;
-            const char* base_b = smem + (g % NSB) * B_SLOT;
+            const char* base_a = smem + (g % NS) * A_SLOT;
+            const char* base_b = smem + (g % NS) * B_SLOT;
 #pragma unroll
             for (int i = 0; i < TMV; ++i)
                 af[set][i] = *reinterpret_cast<const bf16x8_t*>(base_a + a_row[i] + k_off[kk]);
@@ -408,22 +366,17 @@ __global__ __launch_bounds__(NW * 64, MINW) void grouped_gemm_bf16_pipe_kernel(
         // prologue: the weight stages are already in flight; the activation stages follow, and the first
         // wait lets through only the activation loads issued after stage 0's
 #pragma unroll
-        for (int st = 0; st < NSA - 1; ++st)
+        for (int st = 0; st < NS - 1; ++st)
             if (st < nk_)
 #pragma unroll
                 for (int p = 0; p < A_LPW; ++p) issue_a(st, p);
-        if (nk_ >= NSA - 1) wait_vmcnt<WAIT_FIRST>();
+        if (nk_ >= NS - 1) wait_vmcnt<WAIT_FIRST>();
         else wait_vmcnt<0>();
         block_barrier();
-        if (A_EARLY && NSA - 1 < nk_) {
-#pragma unroll
-            for (int p = 0; p < A_LPW; ++p) issue_a(NSA - 1, p);
-        }
         read_frags(0, 0, 0);
-        // One k-step.  MORE_A / MORE_B: activation stage g+NSA-1 / weight stage g+NSB-1 exists and is
-        // loaded (in parts, between the MFMAs) into the slot stage g-1 used, free since the last
-        // barrier.  NEXT: stage g+1 exists; it is waited for and handed over by the barrier before the
-        // last slice of this stage is multiplied.
+        // One k-step.  MORE: stage g+NS-1 exists and is loaded (in parts, between the MFMAs) into the slot stage g-1
+        // used, free since the last barrier.  NEXT: stage g+1 exists; it is waited for and handed over by the
+        // barrier before the last slice of this stage is multiplied.
         // Ask the scheduler to issue the LDS reads and the global loads of a region one by one between
         // its MFMAs (they then execute in the shadow of the matrix pipe) instead of in a clump.
         auto interleave = [](int n_ds, int n_vmem, int n_mfma) {
@@ -442,37 +395,23 @@ __global__ __launch_bounds__(NW * 64, MINW) void grouped_gemm_bf16_pipe_kernel(
                 }
             }
         };
-        auto parts_in = [&](int part, bool more_a, bool more_b) {
-            int n = 0;
-            if (A_EARLY) {
-                for (int p = 0; p < B_LPW; ++p) n += (p * KS / B_LPW == part) && more_b;
-                return n;
-            }
-            for (int q = 0; q < LPS; ++q)
-                if (load_part(q) == part) n += load_is_a(q) ? more_a : more_b;
-            return n;
-        };
-        auto step = [&](int g, auto more_a_c, auto more_b_c, auto next_c) {
-            constexpr bool MORE_A = decltype(more_a_c)::value, MORE_B = decltype(more_b_c)::value;
-            constexpr bool NEXT = decltype(next_c)::value;
+        auto parts_in = [](int part) { return (LPS - part + KS - 1) / KS; };
+        auto step = [&](int g, auto more_c, auto next_c) {
+            constexpr bool MORE = decltype(more_c)::value, NEXT = decltype(next_c)::value;
 #pragma unroll
             for (int kk = 0; kk < KS - 1; ++kk) {
                 read_frags(g, kk + 1, (kk + 1) & 1);
-                issue_part(g, kk, MORE_A, MORE_B);
+                if (MORE) issue_part(g + NS - 1, kk);
                 mfma_set(kk & 1);
-                interleave(TMV > 0 ? TMV + TN : 0, parts_in(kk, MORE_A, MORE_B), TMV * TN);
+                interleave(TMV > 0 ? TMV + TN : 0, MORE ? parts_in(kk) : 0, TMV * TN);
             }
-            issue_part(g, KS - 1, MORE_A, MORE_B);
+            if (MORE) issue_part(g + NS - 1, KS - 1);
             if (NEXT) {
-                if (A_EARLY ? MORE_B : (MORE_A && MORE_B)) wait_vmcnt<WAIT_MAIN>();
+                if (MORE) wait_vmcnt<WAIT_MAIN>();
                 else wait_vmcnt<0>();        // the pipeline drains: wait for everything
                 // all of this wave's reads of stage g have returned before its slots may be refilled
                 wait_lds_reads();
                 block_barrier();
-                if (A_EARLY && MORE_A) {
-#pragma unroll
-                    for (int p = 0; p < A_LPW; ++p) issue_a(g + NSA, p);
-                }
                 read_frags(g + 1, 0, 0);
             }
             mfma_set((KS - 1) & 1);
@@ -480,16 +419,11 @@ __global__ __launch_bounds__(NW * 64, MINW) void grouped_gemm_bf16_pipe_kernel(
         };
         using T = std::true_type;
         using F = std::false_type;
-        const int n_main = nk_ - (NSMAX - 1) > 0 ? nk_ - (NSMAX - 1) : 0;   // steps that still start both loads
+        const int n_main = nk_ - (NS - 1) > 0 ? nk_ - (NS - 1) : 0;   // steps that still start loads
         int g = 0;
-        for (; g < n_main; ++g) step(g, T{}, T{}, T{});
-        for (; g < nk_ - 1; ++g) {
-            // only the shallower ring may still have a stage to fetch
-            if (!A_EARLY && NSA < NSB && g + NSA - 1 < nk_) step(g, T{}, F{}, T{});
-            else if (NSB < NSA && g + NSB - 1 < nk_) step(g, F{}, T{}, T{});
-            else step(g, F{}, F{}, T{});
-        }
-        step(g, F{}, F{}, F{});
+        for (; g < n_main; ++g) step(g, T{}, T{});
+        for (; g < nk_ - 1; ++g) step(g, F{}, T{});
+        step(g, F{}, F{});
 
         // Epilogue.  A lane holds, for output row fr of a row block, groups of 4 consecutive columns
         // (accumulator element v of tile (i, j): column (v/4)*8 + fq*4 + v%4); storing them directly
@@ -497,21 +431,21 @@ __global__ __launch_bounds__(NW * 64, MINW) void grouped_gemm_bf16_pipe_kernel(
         // at a time (32 rows x WNO columns, at most 4 KB) through a private piece of LDS and writes it
         // out as whole 16-byte chunks, consecutive lanes along a row (64- or 128-byte runs per row).
         // The LDS used is an activation slot no stage occupies any more: stage nk-1, the last one, sits
-        // in slot (nk-1) % NSA, and the readers of the other slots passed their barrier long ago, so no
+        // in slot (nk-1) % NS, and the readers of the other slots passed their barrier long ago, so no
         // block barrier is needed; a wave's own LDS operations execute in program order.
         constexpr int RB = TNO * 64;              // bytes of one row of the wave's output tile
         constexpr int CPRW = TNO * 4;             // 16-byte chunks per such row
         constexpr int REG = 32 * RB;              // bytes per wave
         constexpr int WPS = A_SLOT / REG;         // waves per free activation slot
         constexpr int RPI = 64 / CPRW;            // rows one wave-level 16-byte access covers
-        static_assert(TNO <= 2 && WPS >= 1 && (NSA - 1) * WPS >= NW, "the epilogue staging does not fit the free slots");
+        static_assert(TNO <= 2 && WPS >= 1 && (NS - 1) * WPS >= NW, "the epilogue staging does not fit the free slots");
         static_assert(!OUT_F32 || REG >= 4096, "a 32 x 32 float tile must fit the wave's staging piece");
         if (TMV > 0 && OUT_F32) {
             // float output: one 32 x 32 tile (4 KB: 32 rows of 8 16-byte chunks) at a time through the same
             // private piece of LDS; a lane's 4 consecutive columns are one chunk, chunk c of row r sits in
             // chunk slot c ^ (r & 7), and the tile goes out as 128-byte runs per row.
             float* Out = static_cast<float*>(Out_);
-            char* epi = smem + ((nk_ + wave / WPS) % NSA) * A_SLOT + (wave % WPS) * REG;
+            char* epi = smem + ((nk_ + wave / WPS) % NS) * A_SLOT + (wave % WPS) * REG;
 #pragma unroll
             for (int i = 0; i < TMV; ++i) {
                 const int64_t row_base = (int64_t)tc.row0 + (wm + WM * i) * 32;
@@ -536,7 +470,7 @@ __global__ __launch_bounds__(NW * 64, MINW) void grouped_gemm_bf16_pipe_kernel(
             }
         } else if (TMV > 0) {
             bf16_t* Out = static_cast<bf16_t*>(Out_);
-            char* epi = smem + ((nk_ + wave / WPS) % NSA) * A_SLOT + (wave % WPS) * REG;
+            char* epi = smem + ((nk_ + wave / WPS) % NS) * A_SLOT + (wave % WPS) * REG;
             auto eswz = [](int r) { return (r >> (RB == 64 ? 2 : 1)) & (CPRW - 1); };
             constexpr int PARTS = (SPLIT && GATED) ? 2 : 1;      // the values, then what their bf16 rounding left over
 #pragma unroll
@@ -594,6 +528,634 @@ __global__ __launch_bounds__(NW * 64, MINW) void grouped_gemm_bf16_pipe_kernel(
     else if (TM >= 2 && tm_valid >= 2) run(std::integral_constant<int, (TM >= 2 ? 2 : 0)>{});
     else if (tm_valid >= 1) run(std::integral_constant<int, 1>{});
     else run(std::integral_constant<int, 0>{});
+}
+
+// ----------------------------------------------------------------------------------------------
+// Compute-bound shape: 256 x 256 tiles, 8 waves (2 per SIMD, 128 rows x 64 weight rows each), one persistent block
+// per compute unit.
+//
+// Per k-step of 64 values a block multiplies one stage of activation rows (ring of 2 LDS slots) by one stage of
+// weight rows (ring of 3: the weights are what comes from HBM); the two rings are all 160 KB of LDS.  Steps of one
+// tile and of the next one follow each other without a gap:
+//   - in step s the weight loads of stage s + 2 are issued between the MFMAs, and behind the barrier that ends
+//     step s the activation loads of stage s + 2 go into the slot stage s has just left; past the tile's last stage
+//     these are the first stages of the block's NEXT tile;
+//   - the epilogue works in the weight slot of the tile's last stage, which nobody needs until the next tile's first
+//     step;
+//   - the row ids of the next tile are looked up while the current tile is multiplied.
+// A block that started anew for every tile spent 7 us of each tile outside the k-loop (tile search 1.8, first loads
+// 2.6, epilogue 2.2, 1-3 until the next block ran) against k-loops of 17 us (K = 768) and 53 us (K = 2048); now it is
+// 3 us.  Before and after, us (same box, in turn): 66560 rows, 128 experts, H = 2048, I = 768: gate_up 405 -> 384, down
+// 245 -> 225; 8448 rows, 32 experts, H = I = 2880: 336 -> 317, 197 -> 170; 8256 rows, 8 skewed experts, H = 4096,
+// I = 14336: 1718 -> 1630, 1007 -> 911.  What bounds it: at 66560 rows the steps in the middle of a tile keep the
+// matrix pipes 77-82 % busy at a clock that the power limit holds at 1.55-1.75 GHz; at 132 rows per expert (16896 rows)
+// the weights arrive at 5.2-5.9 TB/s.
+//
+// Which tiles: experts are cut into m-tiles of at most `h` 32-row blocks, tiles are ordered by expert, n-tile, m-tile
+// (the m-tiles that share a weight tile run side by side on one XCD and share its L2), the list is cut into eight
+// pieces, one per XCD, and the blocks of an XCD walk its piece with a common stride.  A tile
+// costs a fixed part (big_tile_fixed) plus its row blocks.  `h` is the height,
+// 4 to 8, for which the rounds of tiles over the chip cost least; equal tiles are worth a few more of them, because
+// the blocks' shares are not evened out at run time.
+// ----------------------------------------------------------------------------------------------
+constexpr int kBigRows = 256, kBigBN = 256, kBigWaves = 8, kBigMinHeight = 4;
+
+// Fixed cost of a tile in units of one of its 32-row blocks: about 8 us (epilogue, next tile's search, the first
+// steps' waits) against 0.17 us per block and k-step, measured at nk = 12 and 32.
+__device__ __forceinline__ float big_tile_fixed(int nk) { return 48.0f / (float)nk + 0.35f; }
+
+// Inclusive scan over the wave's lanes in six register-to-register steps (row shifts, then the last lane of a row to
+// the next row, then lane 31 to the upper half).
+template <typename V> __device__ __forceinline__ V wave_scan(V v)
+{
+    auto step = [&](auto ctrl, auto row_mask) {
+        const int o = __builtin_amdgcn_update_dpp(0, __builtin_bit_cast(int, v), decltype(ctrl)::value,
+                                                  decltype(row_mask)::value, 0xF, true);
+        v += __builtin_bit_cast(V, o);
+    };
+    using std::integral_constant;
+    step(integral_constant<int, 0x111>{}, integral_constant<int, 0xF>{});      // from 1, 2, 4 and 8 lanes below, within 16
+    step(integral_constant<int, 0x112>{}, integral_constant<int, 0xF>{});
+    step(integral_constant<int, 0x114>{}, integral_constant<int, 0xF>{});
+    step(integral_constant<int, 0x118>{}, integral_constant<int, 0xF>{});
+    step(integral_constant<int, 0x142>{}, integral_constant<int, 0xA>{});      // rows 1 and 3: last lane of the row below
+    step(integral_constant<int, 0x143>{}, integral_constant<int, 0xC>{});      // upper half: lane 31
+    return v;
+}
+__device__ __forceinline__ int last_lane(int v) { return __builtin_amdgcn_readlane(v, 63); }
+__device__ __forceinline__ float last_lane(float v)
+{
+    return __builtin_bit_cast(float, __builtin_amdgcn_readlane(__builtin_bit_cast(int, v), 63));
+}
+
+struct BigTile {
+    int expert, row0, row_end, n_tile;
+};
+
+// ceil(x / h) for 0 <= x < 2^28 and 4 <= h <= 8 (inverse: ceil(2^32 / h), exact in this range)
+__device__ __forceinline__ uint32_t height_inverse(int h)
+{
+    return h == 8 ? 0x20000000u : h == 7 ? 0x24924925u : h == 6 ? 0x2aaaaaabu : h == 5 ? 0x33333334u : 0x40000000u;
+}
+__device__ __forceinline__ int div_up(int x, int h, uint32_t inverse) { return (int)__umulhi((uint32_t)(x + h - 1), inverse); }
+
+// The block's share of the tile list: a range of it with a stride, and the expert the walk has reached.  Everything
+// here is the same in all lanes.
+//
+// Every block works the list out for itself.  What that costs is instruction fetch (cold straight-line code runs at
+// about 1 KB per us: a first version, unrolled over the 8 experts of a lane, was 11 KB and took 10 us of every
+// launch), hence the loops that are kept loops and the walk over the experts in place of a search.
+struct BigQueue {
+    const int32_t* offsets;
+    int E, max_rows, n_tiles;
+    int h;                     // tile height limit in row blocks
+    uint32_t h_inv;
+    int end;                   // end of the block's range
+    int expert, before;        // the walk: an expert, tiles of the experts in front of it,
+    int lo, hi, mt, per;       // its rows, its number of m-tiles and the row blocks of each
+
+    __device__ __forceinline__ void load_expert()
+    {
+        // (one scalar load with its wait inside: through the compiler it might become a vector load, whose wait
+        // would also be a wait for every asm-issued load in flight)
+        unsigned long long pair;
+        asm volatile("s_load_dwordx2 %0, %1, 0x0\n\ts_waitcnt lgkmcnt(0)" : "=&s"(pair) : "s"(offsets + expert) : "memory");
+        lo = (int)(uint32_t)pair;
+        hi = (int)(uint32_t)(pair >> 32);
+        lo = lo < 0 ? 0 : (lo > max_rows ? max_rows : lo);
+        hi = hi < lo ? lo : (hi > max_rows ? max_rows : hi);
+        const int rb = (hi - lo + 31) / 32;
+        mt = div_up(rb, h, h_inv);
+        per = mt > 1 ? quotient(rb + mt - 1, mt) : rb;
+    }
+    // x / m for 0 <= x < 2^24 (the launch keeps lists of more tiles away), a few instructions instead of a division
+    static __device__ __forceinline__ int quotient(int x, int m)
+    {
+        int q = (int)((float)x * __builtin_amdgcn_rcpf((float)m));
+        if (q * m > x) q -= 1;
+        if (x - q * m >= m) q += 1;
+        return __builtin_amdgcn_readfirstlane(q);
+    }
+
+    // Tile j of the list; j never decreases from call to call and is below the number of tiles.
+    __device__ __forceinline__ BigTile take(int j)
+    {
+        while (j >= before + mt * n_tiles && expert + 1 < E) {
+            before += mt * n_tiles;
+            expert += 1;
+            load_expert();
+        }
+        const int m = mt > 0 ? mt : 1;
+        const int rem = j - before;
+        const int n = quotient(rem, m), t = rem - n * m;
+        BigTile tile;
+        tile.expert = expert;
+        tile.n_tile = n;
+        tile.row0 = lo + t * per * 32;
+        tile.row_end = tile.row0 + per * 32;
+        if (tile.row_end > hi) tile.row_end = hi;
+        if (tile.row0 > tile.row_end) tile.row0 = tile.row_end;
+        return tile;
+    }
+
+    // Every wave of the block calls it, with `scratch` a piece of LDS nothing else uses.  Returns the block's first tile.
+    __device__ __forceinline__ int init(const int32_t* offsets_, int E_, int n_tiles_, int max_rows_, float fixed, int* scratch)
+    {
+        offsets = offsets_;
+        E = E_;
+        max_rows = max_rows_;
+        n_tiles = n_tiles_;
+        const int lane = lane_id();
+        const int k = __builtin_amdgcn_readfirstlane((int)(threadIdx.x >> 6));       // wave
+        int* const tiles_at = scratch;              // [8] tiles at height 8 - k
+        float* const squares_at = reinterpret_cast<float*>(scratch + 600);   // [8] sum of their squared heights
+        int* const border = scratch + 8;            // [2][8] first tile of piece k: equal numbers, equal costs
+        int* const b_expert = scratch + 24;         // [2][8] the expert of that tile
+        int* const b_before = scratch + 40;         // [2][8] tiles of the experts in front of it
+        float* const b_cost = reinterpret_cast<float*>(scratch + 56);     // [8] cost in front of border[0][k]
+        int* const rb_of = scratch + 64;            // [E] row blocks
+
+        // wave k: number of tiles at height 8 - k
+        int rb_sum = 0, t_sum = 0;
+        float sq_sum = 0.f;                         // sum of the tiles' squared heights
+        {
+            const int hh = kBigRows / 32 - k >= kBigMinHeight ? kBigRows / 32 - k : kBigMinHeight;
+            const uint32_t inv = height_inverse(hh);
+#pragma unroll 1
+            for (int e = lane; e < E; e += 64) {
+                int r0 = offsets[e], r1 = offsets[e + 1];
+                r0 = r0 < 0 ? 0 : (r0 > max_rows ? max_rows : r0);
+                r1 = r1 < r0 ? r0 : (r1 > max_rows ? max_rows : r1);
+                const int rb = (r1 - r0 + 31) / 32;
+                if (k == 0) rb_of[e] = rb;
+                const int m = div_up(rb, hh, inv);
+                rb_sum += rb;
+                t_sum += m;
+                sq_sum += rb > 0 ? (float)rb * (float)rb * __builtin_amdgcn_rcpf((float)m) : 0.f;
+            }
+        }
+        t_sum = last_lane(wave_scan(t_sum));
+        sq_sum = last_lane(wave_scan(sq_sum));
+        const float rb_all = (float)last_lane(wave_scan(rb_sum)) * (float)n_tiles;
+        if (lane == 0) {
+            tiles_at[k] = t_sum;
+            squares_at[k] = sq_sum;
+        }
+        __syncthreads();
+        const float blocks = (float)gridDim.x;
+        float best = 0.f;
+        h = 0;
+#pragma unroll 1
+        for (int c = 0; c <= kBigRows / 32 - kBigMinHeight; ++c) {
+            const float tiles = fmaxf((float)tiles_at[c] * (float)n_tiles, 1.f), inv = __builtin_amdgcn_rcpf(tiles);
+            const float rounds = ceilf(tiles * __builtin_amdgcn_rcpf(blocks) - 1e-3f), mean = rb_all * inv;
+            const float var = fmaxf(squares_at[c] * (float)n_tiles * inv - mean * mean, 0.f);
+            // whole rounds of the mean tile, and what the unluckiest block gets on top of that by chance
+            const float cost = rounds * (fixed + mean) + 1.5f * __builtin_amdgcn_sqrtf(rounds * var);
+            if (c == 0 || cost < best) {
+                best = cost;
+                h = kBigRows / 32 - c;
+            }
+        }
+        h = __builtin_amdgcn_readfirstlane(h);
+        h_inv = height_inverse(h);
+        const int total = __builtin_amdgcn_readfirstlane(tiles_at[kBigRows / 32 - h]) * n_tiles;
+        const float ftotal = fixed * (float)total + rb_all;
+
+        // Border k of the eight pieces: after k / 8 of the tiles, or where the running cost passes k / 8 of the total.
+        // Pieces of equal cost suit tiles of different heights; pieces of equal number never need one more round
+        // than the whole list does.  Wave k works both out for k (and the cost in front of the first), they meet in
+        // LDS, and the kind whose slowest piece is estimated to end first is taken: whole rounds of its mean tile.
+        {
+            const float target = ftotal * (float)k * 0.125f;
+            const int by_count = (int)((int64_t)total * k / 8);
+            int sum = 0;
+            float fsum = 0.f;
+            bool found = false, found_n = false;
+#pragma unroll 1
+            for (int e0 = 0; e0 < E; e0 += 64) {
+                const int rb = e0 + lane < E ? rb_of[e0 + lane] : 0;
+                const int tiles = div_up(rb, h, h_inv) * n_tiles;
+                const float c = fixed * (float)tiles + (float)rb * (float)n_tiles;
+                const int cum = wave_scan(tiles) + sum;
+                const float fcum = wave_scan(c) + fsum;
+                const unsigned long long past_n = __ballot(cum > by_count), past = __ballot(fcum > target);
+                // (one lane is picked: one whose number of tiles and cost are not zero)
+                if (!found_n && past_n) {
+                    found_n = true;
+                    if (lane == __ffsll((long long)past_n) - 1) {
+                        border[k] = by_count;
+                        b_expert[k] = e0 + lane;
+                        b_before[k] = cum - tiles;
+                        b_cost[k] = fcum - c * (float)(cum - by_count) * __builtin_amdgcn_rcpf((float)tiles);
+                    }
+                }
+                if (!found && past) {
+                    found = true;
+                    if (lane == __ffsll((long long)past) - 1) {
+                        const float behind = fminf((fcum - target) * __builtin_amdgcn_rcpf(c), 1.f);
+                        border[8 + k] = k > 0 ? cum - (int)(behind * (float)tiles) : 0;
+                        b_expert[8 + k] = e0 + lane;
+                        b_before[8 + k] = cum - tiles;
+                    }
+                }
+                sum = last_lane(cum);
+                fsum = last_lane(fcum);
+            }
+            if (lane == 0) {     // (only if rounding puts the last borders behind the last expert, or nothing has rows)
+                if (!found_n) {
+                    border[k] = total;
+                    b_expert[k] = E - 1;
+                    b_before[k] = total;
+                    b_cost[k] = ftotal;
+                }
+                if (!found) {
+                    border[8 + k] = total;
+                    b_expert[8 + k] = E - 1;
+                    b_before[8 + k] = total;
+                }
+            }
+        }
+        __syncthreads();
+        // lane y < 8 of every wave: piece y, both ways
+        const int y = lane & 7;
+        const float n0 = (float)(y < 7 ? border[y + 1] : total) - (float)border[y];
+        const float n1 = (float)(y < 7 ? border[9 + y] : total) - (float)border[8 + y];
+        const float per_block = 8.f * __builtin_amdgcn_rcpf(blocks);
+        float slow0 = n0 > 0.f ? ceilf(n0 * per_block - 1e-3f) * ((y < 7 ? b_cost[y + 1] : ftotal) - b_cost[y]) * __builtin_amdgcn_rcpf(n0) : 0.f;
+        float slow1 = n1 > 0.f ? ceilf(n1 * per_block - 1e-3f) * (ftotal * 0.125f) * __builtin_amdgcn_rcpf(n1) : 0.f;
+#pragma unroll 1
+        for (int o = 4; o >= 1; o >>= 1) {
+            slow0 = fmaxf(slow0, __shfl_xor(slow0, o, 64));
+            slow1 = fmaxf(slow1, __shfl_xor(slow1, o, 64));
+        }
+        const int x = (int)(blockIdx.x % 8);
+        const int at = (__builtin_amdgcn_readfirstlane(slow1 < slow0) != 0 ? 8 : 0) + x;
+        const int first = __builtin_amdgcn_readfirstlane(border[at]) + (int)(blockIdx.x / 8);
+        end = x == 7 ? total : __builtin_amdgcn_readfirstlane(border[at + 1]);
+        expert = __builtin_amdgcn_readfirstlane(b_expert[at]);
+        before = __builtin_amdgcn_readfirstlane(b_before[at]);
+        load_expert();
+        __syncthreads();       // `scratch` is free again
+        return first;
+    }
+};
+
+template <bool GATED, bool OUT_F32, bool SPLIT, bool MAPPED>
+__global__ __launch_bounds__(kBigWaves * 64, 2) void grouped_gemm_bf16_big_kernel(
+    RowSrc X, int ldx, const int32_t* __restrict__ row_map, int map_div, uint32_t map_magic,
+    const int32_t* __restrict__ offsets, int E, const bf16_t* __restrict__ W, int64_t w_expert_stride, int N, int K,
+    void* __restrict__ Out_, int ldo, int a_rows)
+{
+    static_assert(!(GATED && OUT_F32), "the intermediate of the gated GEMM is always held in the activation dtype");
+    constexpr int BM = kBigRows, BN = kBigBN, NW = kBigWaves, WM = 2, WN = NW / WM, PBK = 64;
+    constexpr int NO = GATED ? BN / 2 : BN;     // output columns per block
+    constexpr int TM = BM / 32 / WM;            // row blocks per wave: rb = wm + WM * i
+    constexpr int WNO = NO / WN;                // output columns per wave
+    constexpr int TNO = WNO / 32;
+    constexpr int TN = GATED ? 2 * TNO : TNO;
+    constexpr int ROWB = PBK * 2;               // bytes per LDS tile row
+    constexpr int KS = PBK / 16;                // MFMA k-slices per stage
+    constexpr int LPW = BM / 8 / NW;            // load instructions per wave, stage and operand (8 rows of 128 bytes each)
+    constexpr uint32_t SLOT = BM * ROWB;        // bytes of one stage of either operand
+    constexpr uint32_t B_BASE = 2 * SLOT;       // the weight ring (3 slots) follows the activation ring (2 slots)
+    static_assert(BM == BN && LPW == 4 && TM == 4 && KS == 4, "tile configuration");
+
+    extern __shared__ __attribute__((aligned(1024))) char smem[];
+    const uint32_t lds0 = lds_address(smem);
+
+    const int lane = lane_id();
+    const int wave = __builtin_amdgcn_readfirstlane((int)(threadIdx.x >> 6));
+    const int wm = wave / WN, wn = wave % WN;
+    const int nk = K / PBK;
+    // stages per weight row: with a split intermediate the plain GEMM walks every weight row twice
+    const int nk_w = (SPLIT && !GATED) ? nk / 2 : nk;
+    const int ldw = (SPLIT && !GATED) ? K / 2 : K;
+
+    BigQueue queue;
+    int at = queue.init(offsets, E, (N + NO - 1) / NO, a_rows, big_tile_fixed(nk), reinterpret_cast<int*>(smem));
+    if (at >= queue.end) return;
+    const int stride = (int)gridDim.x / 8;
+
+    // Load p of this wave covers tile rows (wave + 8 p) * 8 .. + 7, lane = (row, 16-byte chunk); LDS chunk c of tile
+    // row r holds global chunk c ^ swz(r) (swz looks at the low four row bits only: the same for every p).
+    const int l_row = lane >> 3;
+    const uint32_t l_chunk = (uint32_t)((lane & 7) ^ swz<PBK>(wave * 8 + l_row)) * 16;
+
+    // ---- activation rows ----
+    int32_t row_id[LPW];               // looked-up rows of the next tile (asm-issued loads: see below)
+    const char* a_src[LPW];            // the lane's 16 bytes of stage 0 of the tile whose stages are being loaded
+    int a_live = 0;                    // of the wave's loads, how many hold rows of that tile
+    // The look-ups are loads issued from inline asm: through the compiler they would be waited for with vmcnt(0),
+    // i.e. together with all weight loads in flight.  They are picked up one step later, behind a wait that leaves only
+    // younger loads in flight.
+    auto look_up = [&](const BigTile& t) {
+#pragma unroll
+        for (int p = 0; p < LPW; ++p) {
+            int r = t.row0 + (wave + NW * p) * 8 + l_row;
+            if (r >= t.row_end) r = t.row_end - 1;
+            if (MAPPED) asm volatile("global_load_dword %0, %1, off" : "=v"(row_id[p]) : "v"(row_map + r) : "memory");
+            else row_id[p] = r;
+        }
+    };
+    auto use_rows = [&](const BigTile& t) {
+#pragma unroll
+        for (int p = 0; p < LPW; ++p) {
+            if (MAPPED) asm volatile("" : "+v"(row_id[p])::"memory");
+            // a row map holds indices below a_rows; the clamp keeps a bad entry from becoming a wild address
+            uint32_t id = row_id[p] < 0 ? 0u : (uint32_t)row_id[p];
+            id = id < (uint32_t)a_rows ? id : (uint32_t)a_rows - 1;
+            if (MAPPED && map_div > 1) {       // id / map_div: map_magic = ceil(2^32 / map_div) overshoots by at most one
+                uint32_t q = __umulhi(id, map_magic);
+                if (q * (uint32_t)map_div > id) q -= 1;
+                id = q;
+            }
+            a_src[p] = reinterpret_cast<const char*>(row_ptr<bf16_t>(X, (int64_t)id, ldx)) + l_chunk;
+        }
+        const int live = (t.row_end - t.row0 - wave * 8 + 63) / 64;
+        a_live = live < 0 ? 0 : (live > LPW ? LPW : live);
+    };
+    // (a load whose 8 rows all lie past the tile's last row is left out: no wait count includes an activation load)
+    auto issue_a = [&](int stage, uint32_t slot) {
+#pragma unroll
+        for (int p = 0; p < LPW; ++p)
+            if (p < a_live) load_lds_16(a_src[p] + (uint32_t)(stage * ROWB), lds0 + slot + (wave + NW * p) * 1024);
+    };
+
+    // ---- weight rows: a uniform base per half of the tile, small lane offsets ----
+    const char *b_gate = nullptr, *b_up = nullptr;      // next weight stage to load: rows n0 .. and, gated, N + n0 ..
+    uint32_t b_off[LPW];
+    auto use_weights = [&](const BigTile& t) {
+        const int n0 = t.n_tile * NO;
+        const bf16_t* We = W + (int64_t)t.expert * w_expert_stride;
+        b_gate = uniform(reinterpret_cast<const char*>(We + (int64_t)n0 * ldw));
+        b_up = uniform(reinterpret_cast<const char*>(We + ((int64_t)N + n0) * ldw));
+#pragma unroll
+        for (int p = 0; p < LPW; ++p) {
+            int r = (wave + NW * p) * 8 + l_row;
+            if (GATED && r >= NO) r -= NO;
+            if (n0 + r >= N) r = N - 1 - n0;            // past the matrix: a valid row, result unused
+            b_off[p] = (uint32_t)r * (uint32_t)ldw * 2u + l_chunk;
+        }
+    };
+    auto issue_b = [&](int p, uint32_t slot) {
+        load_lds_16_base(GATED && p >= LPW / 2 ? b_up : b_gate, b_off[p], lds0 + B_BASE + slot + (wave + NW * p) * 1024);
+    };
+    auto advance_b = [&](int stage) {      // after the loads of weight stage `stage` of a tile
+        const int64_t by = (SPLIT && !GATED && stage + 1 == nk_w) ? ROWB - (int64_t)ldw * 2 : ROWB;
+        b_gate += by;
+        if (GATED) b_up += by;
+    };
+    auto next_b_slot = [](uint32_t s) { return s == 2 * SLOT ? 0u : s + SLOT; };
+
+    // ---- LDS addresses of the operand rows this lane feeds to the MFMAs ----
+    // k-slice kk of tile row r sits at r * 128 + ((2 kk + fq) ^ swz(r)) * 16; the row blocks of a wave are constants
+    // apart and go into the read instructions.  (Addresses are integers in the LDS address space: the compiler then
+    // folds those constants instead of adding the array's base at every read.)
+    typedef __attribute__((address_space(3))) const bf16x8_t lds_bf16x8_t;
+    const int fr = lane & 31, fq = lane >> 5;
+    uint32_t k_lane[KS];
+#pragma unroll
+    for (int kk = 0; kk < KS; ++kk) k_lane[kk] = lds0 + fr * ROWB + (((kk * 2 + fq) ^ swz<PBK>(fr)) << 4);
+    const uint32_t a_wave = wm * 32 * ROWB, b_wave = B_BASE + wn * WNO * ROWB;
+
+    // ---- first tile: two weight stages and one activation stage ----
+    BigTile cur = queue.take(at), nxt = cur;
+    uint32_t a_slot = 0, b_slot = 0;       // slots of the stage being multiplied
+    look_up(cur);
+    use_weights(cur);
+#pragma unroll
+    for (int st = 0; st < 2; ++st) {
+#pragma unroll
+        for (int p = 0; p < LPW; ++p) issue_b(p, st * SLOT);
+        advance_b(st);
+    }
+    wait_vmcnt<2 * LPW>();                 // the look-ups came before the weight loads
+    use_rows(cur);
+    issue_a(0, 0);
+    wait_vmcnt<0>();
+    block_barrier();
+    issue_a(1, SLOT);
+
+    // One tile.  On entry stage 0 of both operands is in LDS for every wave, weight stage 1 is in flight and the
+    // activation loads of stage 1 have been issued.  The body is instantiated for the number TMV of row blocks this
+    // wave really has (0..TM), so the hot loop is straight-line code; a wave with no row block still loads and
+    // synchronises.
+    auto run = [&](auto tmv_const) {
+        constexpr int TMV = decltype(tmv_const)::value;
+        constexpr int TMA = TMV > 0 ? TMV : 1;
+        float16_t acc[TMA][TN];
+#pragma unroll
+        for (int i = 0; i < TMA; ++i)
+#pragma unroll
+            for (int j = 0; j < TN; ++j)
+#pragma unroll
+                for (int v = 0; v < 16; ++v) acc[i][j][v] = 0.f;
+        bf16x8_t af[2][TMA], bfr[2][TN];
+        auto read_frags = [&](uint32_t as, uint32_t bs, int kk, int set) {
+            if (TMV == 0) return;
+            const uint32_t av = k_lane[kk] + (as + a_wave), bv = k_lane[kk] + (bs + b_wave);
+#pragma unroll
+            for (int i = 0; i < TMV; ++i) af[set][i] = *(lds_bf16x8_t*)(uintptr_t)(av + i * (WM * 32 * ROWB));
+#pragma unroll
+            for (int j = 0; j < TN; ++j)
+                bfr[set][j] = *(lds_bf16x8_t*)(uintptr_t)(bv + (j < TNO ? j * 32 : NO + (j - TNO) * 32) * ROWB);
+        };
+        auto mfma_set = [&](int set) {
+#pragma unroll
+            for (int i = 0; i < TMV; ++i)
+#pragma unroll
+                for (int j = 0; j < TN; ++j)
+                    // weight rows as the MFMA's row operand, activation rows as its column operand: a lane then
+                    // holds 4 consecutive OUTPUT COLUMNS of one output row
+                    acc[i][j] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(bfr[set][j], af[set][i], acc[i][j], 0, 0, 0);
+        };
+        // Ask the scheduler to issue the LDS reads and the global loads of a region one by one between its MFMAs
+        // (they then execute in the shadow of the matrix pipe) instead of in a clump.
+        auto interleave = [](int n_ds, int n_vmem, int n_mfma) {
+#pragma unroll
+            for (int i = 0; i < 16; ++i) {
+                if (i < n_ds && i < n_mfma) {
+                    __builtin_amdgcn_sched_group_barrier(0x008, 1, 0);   // one MFMA
+                    __builtin_amdgcn_sched_group_barrier(0x100, 1, 0);   // one LDS read
+                }
+            }
+#pragma unroll
+            for (int i = 0; i < 16; ++i) {
+                if (i < n_vmem && n_ds + i < n_mfma) {
+                    __builtin_amdgcn_sched_group_barrier(0x008, 1, 0);   // one MFMA
+                    __builtin_amdgcn_sched_group_barrier(0x020, 1, 0);   // one global load
+                }
+            }
+        };
+        // The k-slices of step s but the last, with the weight loads of the stage two steps on; then the wait for
+        // the next stage and the barrier that hands it over.  On return the last slice's operands are in registers.
+        uint32_t b_ahead = next_b_slot(next_b_slot(b_slot));     // slot of the weight stage two steps on
+        auto step_head = [&](int stage_ahead) {
+#pragma unroll
+            for (int kk = 0; kk < KS - 1; ++kk) {
+                read_frags(a_slot, b_slot, kk + 1, (kk + 1) & 1);
+                issue_b(kk, b_ahead);
+                mfma_set(kk & 1);
+                interleave(TMV > 0 ? TMV + TN : 0, 1, TMV * TN);
+            }
+            issue_b(KS - 1, b_ahead);
+            advance_b(stage_ahead);
+            // Loads return in issue order.  Everything of the next stage was issued before this step's four weight
+            // loads (its activation loads behind the barrier that began this step), so those four may stay.
+            wait_vmcnt<LPW>();
+            wait_lds_reads();          // all of this wave's reads of the stage have returned before its slots are refilled
+            block_barrier();
+        };
+        auto step_tail = [&](bool read_next) {
+            const uint32_t a_next = a_slot ^ SLOT, b_next = next_b_slot(b_slot);
+            if (read_next) read_frags(a_next, b_next, 0, 0);
+            mfma_set((KS - 1) & 1);
+            interleave(read_next && TMV > 0 ? TMV + TN : 0, 0, TMV * TN);
+            a_slot = a_next;
+            b_ahead = b_slot;
+            b_slot = b_next;
+        };
+
+        read_frags(a_slot, b_slot, 0, 0);
+        for (int s = 0; s < nk - 3; ++s) {
+            step_head(s + 2);
+            issue_a(s + 2, a_slot);
+            step_tail(true);
+        }
+        // step nk - 3: the next tile's rows are looked up.  (Not earlier: the registers the look-ups land on must not
+        // be copied before they have landed, and the shorter they live the less reason the compiler has to; the
+        // build checks the listing.)
+        look_up(nxt);
+        step_head(nk - 1);
+        issue_a(nk - 1, a_slot);
+        step_tail(true);
+        // step nk - 2: from here on the loads are those of the next tile
+        use_weights(nxt);
+        use_rows(nxt);
+        step_head(0);
+        issue_a(0, a_slot);
+        step_tail(true);
+        // step nk - 1
+        step_head(1);
+        // every wave has read the last stage: its activation slot takes stage 1 of the next tile, its weight slot
+        // (free until the next tile's first step) is where the epilogue works
+        issue_a(1, a_slot);
+        const uint32_t epi_slot = B_BASE + b_slot;
+        step_tail(false);
+
+        // Epilogue.  A lane holds, for output row fr of a row block, groups of 4 consecutive columns
+        // (accumulator element v of tile (i, j): column (v/4)*8 + fq*4 + v%4); storing them directly
+        // would scatter 8-byte pieces over 32 rows per instruction.  Each wave instead turns one row block
+        // at a time (32 rows x WNO columns, at most 4 KB) through a private piece of LDS and writes it
+        // out as whole 16-byte chunks, consecutive lanes along a row (64- or 128-byte runs per row).
+        constexpr int RB = TNO * 64;              // bytes of one row of the wave's output tile
+        constexpr int CPRW = TNO * 4;             // 16-byte chunks per such row
+        constexpr int REG = 32 * RB;              // bytes per wave
+        constexpr int RPI = 64 / CPRW;            // rows one wave-level 16-byte access covers
+        static_assert(TNO <= 2 && NW * REG <= (int)SLOT, "the epilogue staging does not fit the free slot");
+        static_assert(!OUT_F32 || REG >= 4096, "a 32 x 32 float tile must fit the wave's staging piece");
+        const int n0 = cur.n_tile * NO;
+        if (TMV > 0 && OUT_F32) {
+            // float output: one 32 x 32 tile (4 KB: 32 rows of 8 16-byte chunks) at a time through the same
+            // private piece of LDS; a lane's 4 consecutive columns are one chunk, chunk c of row r sits in
+            // chunk slot c ^ (r & 7), and the tile goes out as 128-byte runs per row.
+            float* Out = static_cast<float*>(Out_);
+            char* epi = smem + epi_slot + wave * REG;
+#pragma unroll
+            for (int i = 0; i < TMV; ++i) {
+                const int64_t row_base = (int64_t)cur.row0 + (wm + WM * i) * 32;
+#pragma unroll
+                for (int j = 0; j < TNO; ++j) {
+#pragma unroll
+                    for (int a = 0; a < 4; ++a)
+                        *reinterpret_cast<float4*>(epi + fr * 128 + (((a * 2 + fq) ^ (fr & 7)) << 4)) =
+                            make_float4(acc[i][j][a * 4], acc[i][j][a * 4 + 1], acc[i][j][a * 4 + 2], acc[i][j][a * 4 + 3]);
+                    __builtin_amdgcn_wave_barrier();
+#pragma unroll
+                    for (int h = 0; h < 4; ++h) {
+                        const int r = h * 8 + (lane >> 3), c = lane & 7;
+                        const float4 v = *reinterpret_cast<const float4*>(epi + r * 128 + ((c ^ (r & 7)) << 4));
+                        const int64_t row = row_base + r;
+                        const int col = n0 + wn * WNO + j * 32 + c * 4;
+                        if (row < cur.row_end && col < N)    // N is a multiple of 8: the 4 columns are in or out together
+                            *reinterpret_cast<float4*>(Out + row * ldo + col) = v;
+                    }
+                    __builtin_amdgcn_wave_barrier();
+                }
+            }
+        } else if (TMV > 0) {
+            bf16_t* Out = static_cast<bf16_t*>(Out_);
+            char* epi = smem + epi_slot + wave * REG;
+            auto eswz = [](int r) { return (r >> (RB == 64 ? 2 : 1)) & (CPRW - 1); };
+            constexpr int PARTS = (SPLIT && GATED) ? 2 : 1;      // the values, then what their bf16 rounding left over
+#pragma unroll
+            for (int i = 0; i < TMV; ++i) {
+                if (GATED) {
+#pragma unroll
+                    for (int j = 0; j < TNO; ++j)
+#pragma unroll
+                        for (int v = 0; v < 16; ++v) {
+                            acc[i][j][v] = silu_mul(acc[i][j][v], acc[i][j + TNO][v]);
+                            if (SPLIT) acc[i][j][v] = opaque(acc[i][j][v]);
+                        }
+                }
+#pragma unroll
+                for (int part = 0; part < PARTS; ++part) {
+#pragma unroll
+                    for (int j = 0; j < TNO; ++j) {
+#pragma unroll
+                        for (int a = 0; a < 4; ++a) {
+                            float val[4];
+#pragma unroll
+                            for (int b = 0; b < 4; ++b) val[b] = acc[i][j][a * 4 + b];
+                            const uint32_t p01 = pack_bf16x2(val[0], val[1]), p23 = pack_bf16x2(val[2], val[3]);
+                            if (PARTS == 2 && part == 0) {      // keep the remainders for the second part
+                                acc[i][j][a * 4 + 0] = val[0] - __uint_as_float(p01 << 16);
+                                acc[i][j][a * 4 + 1] = val[1] - __uint_as_float(p01 & 0xffff0000u);
+                                acc[i][j][a * 4 + 2] = val[2] - __uint_as_float(p23 << 16);
+                                acc[i][j][a * 4 + 3] = val[3] - __uint_as_float(p23 & 0xffff0000u);
+                            }
+                            const int chunk = (j * 4 + a) ^ eswz(fr);
+                            *reinterpret_cast<uint2*>(epi + fr * RB + chunk * 16 + fq * 8) = make_uint2(p01, p23);
+                        }
+                    }
+                    __builtin_amdgcn_wave_barrier();
+                    const int64_t row_base = (int64_t)cur.row0 + (wm + WM * i) * 32;
+#pragma unroll
+                    for (int h = 0; h < 32 / RPI; ++h) {
+                        const int r = h * RPI + lane / CPRW, c = lane % CPRW;
+                        const uint4 v = *reinterpret_cast<const uint4*>(epi + r * RB + ((c ^ eswz(r)) * 16));
+                        const int64_t row = row_base + r;
+                        const int col = n0 + wn * WNO + c * 8;
+                        if (row < cur.row_end && col < N)    // N is a multiple of 8: a chunk is in or out as a whole
+                            *reinterpret_cast<uint4*>(Out + row * ldo + part * N + col) = v;
+                    }
+                    __builtin_amdgcn_wave_barrier();
+                }
+            }
+        }
+    };
+
+    for (;;) {
+        // (the last tile is followed by itself: its first stages are loaded once more and never used)
+        at += stride;
+        const bool more = at < queue.end;
+        if (more) nxt = queue.take(at);
+        const int rb_valid = (cur.row_end - cur.row0 + 31) / 32;
+        // row blocks wm, wm + WM, ... below rb_valid belong to this wave
+        const int tm_valid = (rb_valid - wm + WM - 1) / WM;
+        if (tm_valid >= 4) run(std::integral_constant<int, 4>{});
+        else if (tm_valid >= 3) run(std::integral_constant<int, 3>{});
+        else if (tm_valid >= 2) run(std::integral_constant<int, 2>{});
+        else if (tm_valid >= 1) run(std::integral_constant<int, 1>{});
+        else run(std::integral_constant<int, 0>{});
+        if (!more) break;
+        cur = nxt;
+        wait_lds_reads();
+        block_barrier();       // every wave has read its piece of the epilogue's slot: the next weight loads may overwrite it
+    }
+    wait_vmcnt<0>();           // a block must not end with loads into LDS outstanding
 }
 
 // ----------------------------------------------------------------------------------------------
@@ -735,10 +1297,11 @@ static Variant pick_variant(int variant, int64_t A, int E, int K)
     Variant v;
     const double mean_rows = (double)A / (double)E;
     if (mean_rows <= 64.0) v = V_PIPE_SMALL;   // weight streaming: 64 x 128 tiles, 3 stages of 64 k-values
-    else v = V_PIPE_BIG;                       // up to 256-row tiles, 2 + 3 stages of 64 k-values
+    else v = V_PIPE_BIG;                       // up to 256 x 256 tiles, persistent blocks
     if (variant == MOE_FFN_TILE128) v = V_TILE128;
     if (variant == MOE_FFN_PIPE_SMALL) v = V_PIPE_SMALL;
     if (variant == MOE_FFN_PIPE_BIG) v = V_PIPE_BIG;
+    if (v == V_PIPE_BIG && K < 256) v = V_PIPE_SMALL;   // the persistent kernel's pipeline is at least four stages long
     if (K % 64 != 0) v = V_TILE128;            // the pipelined kernels have no k-tail path
     return v;
 }
@@ -763,16 +1326,15 @@ static hipError_t launch_tile(RowSrc X, int ldx, const int32_t* row_map, int map
     return hipGetLastError();
 }
 
-template <int RBM, int BN, int WM, int NSA, int NSB, int PBK, int MINW, int NW, int ORD, bool GATED, bool OUT_F32,
-          bool SPLIT, bool MAPPED>
+template <bool GATED, bool OUT_F32, bool SPLIT, bool MAPPED>
 static hipError_t launch_pipe(RowSrc X, int ldx, const int32_t* row_map, int map_div, const int32_t* offsets,
                               int E, int64_t A, const bf16_t* W, int64_t w_expert_stride, int N, int K, void* Out,
                               int ldo, hipStream_t s)
 {
-    constexpr int BM = RBM * 32;
+    constexpr int BM = 64, BN = 128, NS = 3, PBK = 64, NW = 4;
     constexpr int NO = GATED ? BN / 2 : BN;
-    const size_t lds_bytes = ((size_t)NSA * BM + (size_t)NSB * BN) * PBK * 2;
-    auto kern = grouped_gemm_bf16_pipe_kernel<RBM, BN, WM, NSA, NSB, PBK, MINW, NW, ORD, GATED, OUT_F32, SPLIT, MAPPED>;
+    const size_t lds_bytes = (size_t)NS * (BM + BN) * PBK * 2;
+    auto kern = grouped_gemm_bf16_pipe_kernel<BM / 32, BN, 2, NS, PBK, 2, NW, GATED, OUT_F32, SPLIT, MAPPED>;
     static bool attr_set[kMaxDevices] = {};
     hipError_t e = ensure_lds_limit(kern, lds_bytes, attr_set);
     if (e != hipSuccess) return e;
@@ -785,6 +1347,33 @@ static hipError_t launch_pipe(RowSrc X, int ldx, const int32_t* row_map, int map
     return hipGetLastError();
 }
 
+template <bool GATED, bool OUT_F32, bool SPLIT, bool MAPPED>
+static hipError_t launch_big(RowSrc X, int ldx, const int32_t* row_map, int map_div, const int32_t* offsets, int E,
+                             int64_t A, const bf16_t* W, int64_t w_expert_stride, int N, int K, void* Out, int ldo,
+                             hipStream_t s)
+{
+    constexpr int NO = GATED ? kBigBN / 2 : kBigBN;
+    const size_t lds_bytes = (size_t)5 * kBigRows * 128;
+    auto kern = grouped_gemm_bf16_big_kernel<GATED, OUT_F32, SPLIT, MAPPED>;
+    static bool attr_set[kMaxDevices] = {};
+    hipError_t e = ensure_lds_limit(kern, lds_bytes, attr_set);
+    if (e != hipSuccess) return e;
+    const int64_t n_tiles = (N + NO - 1) / NO;
+    // (tiles of at least 4 row blocks: sum_e ceil(m_e / 128) never exceeds this; the device counts in floats here and there)
+    const int64_t tiles_max = ((A + 127) / 128 + (A < E ? A : E)) * n_tiles;
+    if (tiles_max >= ((int64_t)1 << 24) || A >= ((int64_t)1 << 28))
+        return launch_pipe<GATED, OUT_F32, SPLIT, MAPPED>(
+            X, ldx, row_map, map_div, offsets, E, A, W, w_expert_stride, N, K, Out, ldo, s);
+    int cus = 0;
+    e = compute_units(&cus);
+    if (e != hipSuccess) return e;
+    const int grid = cus / 8 * 8 > 0 ? cus / 8 * 8 : 8;      // one block per compute unit, the same number on every XCD
+    const uint32_t magic = map_div > 1 ? (uint32_t)((((uint64_t)1 << 32) + map_div - 1) / map_div) : 0;
+    kern<<<(unsigned)grid, kBigWaves * 64, lds_bytes, s>>>(X, ldx, row_map, map_div, magic, offsets, E, W, w_expert_stride,
+                                                           N, K, Out, ldo, (int)A);
+    return hipGetLastError();
+}
+
 // K: k-extent of the GEMM (twice the weight rows' length when the plain GEMM reads a split intermediate)
 template <bool GATED, bool OUT_F32, bool SPLIT>
 static hipError_t launch_bf16(int variant, RowSrc X, int ldx, const int32_t* row_map, int map_div,
@@ -793,20 +1382,19 @@ static hipError_t launch_bf16(int variant, RowSrc X, int ldx, const int32_t* row
 {
     // weight streaming: 64 x 128 tiles, 4 waves, 72 KB of LDS: two blocks share a compute unit, so one
     // block's prologue and epilogue are covered by the other's loads, and the many small tiles balance
-    // well over the chip.  compute bound: 256 x 256 tiles, 8 waves (2 per SIMD: one wave's barrier and
-    // LDS waits are covered by the other's MFMAs), 2 (rows) x 4 (columns).
+    // well over the chip.  compute bound: up to 256 x 256 tiles, one persistent block per compute unit.
     // (only the gate_up GEMM is ever called with a row map)
     const bool mapped = GATED && row_map != nullptr;
     if (!GATED && row_map != nullptr) return hipErrorInvalidValue;
     switch (pick_variant(variant, A, E, (SPLIT && !GATED) ? K / 2 : K)) {
         case V_PIPE_SMALL:
             if (mapped)
-                return launch_pipe<2, 128, 2, 3, 3, 64, 2, 4, 0, GATED, OUT_F32, SPLIT, GATED>(X, ldx, row_map, map_div, offsets, E, A, W, w_expert_stride, N, K, Out, ldo, s);
-            return launch_pipe<2, 128, 2, 3, 3, 64, 2, 4, 0, GATED, OUT_F32, SPLIT, false>(X, ldx, row_map, map_div, offsets, E, A, W, w_expert_stride, N, K, Out, ldo, s);
+                return launch_pipe<GATED, OUT_F32, SPLIT, GATED>(X, ldx, row_map, map_div, offsets, E, A, W, w_expert_stride, N, K, Out, ldo, s);
+            return launch_pipe<GATED, OUT_F32, SPLIT, false>(X, ldx, row_map, map_div, offsets, E, A, W, w_expert_stride, N, K, Out, ldo, s);
         case V_PIPE_BIG:
             if (mapped)
-                return launch_pipe<8, 256, 2, 2, 3, 64, 2, 8, 3, GATED, OUT_F32, SPLIT, GATED>(X, ldx, row_map, map_div, offsets, E, A, W, w_expert_stride, N, K, Out, ldo, s);
-            return launch_pipe<8, 256, 2, 2, 3, 64, 2, 8, 3, GATED, OUT_F32, SPLIT, false>(X, ldx, row_map, map_div, offsets, E, A, W, w_expert_stride, N, K, Out, ldo, s);
+                return launch_big<GATED, OUT_F32, SPLIT, GATED>(X, ldx, row_map, map_div, offsets, E, A, W, w_expert_stride, N, K, Out, ldo, s);
+            return launch_big<GATED, OUT_F32, SPLIT, false>(X, ldx, row_map, map_div, offsets, E, A, W, w_expert_stride, N, K, Out, ldo, s);
         default:
             if (OUT_F32)
                 return launch_tile<128, 128, GATED, float, SPLIT>(X, ldx, row_map, map_div, offsets, E, A, W,
@@ -853,8 +1441,8 @@ const char* ffn_variant_name(int dtype, int variant, int64_t A, int E, int H, in
     (void)I;
     if (dtype != MOE_BF16) return "grouped_gemm_f32_kernel<gated>";
     switch (pick_variant(variant, A, E, H)) {
-        case V_PIPE_SMALL: return "grouped_gemm_bf16_pipe_kernel<2,128,2,3,3,64,2,4,0,gated>";
-        case V_PIPE_BIG: return "grouped_gemm_bf16_pipe_kernel<8,256,2,2,3,64,2,8,3,gated>";
+        case V_PIPE_SMALL: return "grouped_gemm_bf16_pipe_kernel<2,128,2,3,64,2,4,gated>";
+        case V_PIPE_BIG: return "grouped_gemm_bf16_big_kernel<gated>";
         default: return "grouped_gemm_bf16_kernel<128,128,gated>";
     }
 }

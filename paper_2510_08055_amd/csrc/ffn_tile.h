@@ -160,6 +160,18 @@ template <int BYTES> __device__ __forceinline__ void load_lds(const void* src, u
         asm volatile("s_mov_b32 m0, %1\n\ts_nop 0\n\tglobal_load_lds_ushort %0, off" ::"v"(src), "s"(lds_base) : "memory");
 }
 __device__ __forceinline__ void load_lds_16(const void* src, uint32_t lds_base) { load_lds<16>(src, lds_base); }
+// An address that is the same in every lane, as a scalar (the compiler does not see every uniform value as one).
+__device__ __forceinline__ const char* uniform(const char* p)
+{
+    const uint64_t b = reinterpret_cast<uint64_t>(p);
+    return reinterpret_cast<const char*>((uint64_t)(uint32_t)__builtin_amdgcn_readfirstlane((int)(uint32_t)b) |
+                                         (uint64_t)(uint32_t)__builtin_amdgcn_readfirstlane((int)(uint32_t)(b >> 32)) << 32);
+}
+// The same load with a wave-uniform base address and a 32-bit byte offset per lane.
+__device__ __forceinline__ void load_lds_16_base(const void* base, uint32_t offset, uint32_t lds_base)
+{
+    asm volatile("s_mov_b32 m0, %2\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %0, %1" ::"v"(offset), "s"(base), "s"(lds_base) : "memory");
+}
 // LDS byte address of a pointer into the block's dynamic shared memory
 __device__ __forceinline__ uint32_t lds_address(const void* p)
 {

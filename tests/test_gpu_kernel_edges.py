@@ -62,3 +62,44 @@ def test_one_launch_routing_equals_the_steps(gpu_lib, T, E, K):
             y, _ = ctx.moe_group_forward([L], x, None)
             assert torch.equal(y, y_steps)
         assert ctx.moe_read_counters().active_experts_total == 2 * int((counts > 0).sum())
+
+
+# The persistent 256 x 256 kernel: tiles of 128 to 256 rows cut from experts of any size, at least four k-stages, next
+# tile's loads issued during the current one.  Checked against the oracle and, bit for bit, against the streaming shape.
+@pytest.mark.parametrize("H,I,rows", [
+    (256, 256, [1]),                                       # one row, four stages, one tile for the whole chip
+    (256, 264, [255, 256, 257, 0, 31, 32, 33]),            # tile edges; ragged column tiles in both GEMMs (264; 256)
+    (320, 512, [0] * 70 + [300] + [0] * 60 + [513]),       # experts in the second and third group of 64, the rest empty
+    (264 * 8, 320, [40, 700, 1]),                          # 33 stages, a wide ragged output
+    (256, 1024, [7 * i % 97 for i in range(130)]),         # many small experts: several tiles per block
+])
+def test_big_tiles_grouped_ffn(gpu_lib, H, I, rows):
+    E, A = len(rows), sum(rows)
+    w = inputs.Workload("big", H=H, E=E, K=1, I=I, n_layers=1, D=0, P=A, dtype="bf16", seed=31)
+    L = inputs.make_layer(w, 0)
+    x_perm = inputs.randn((A, H), 1.0, 31, "x_perm", 0, "bf16")
+    offsets = torch.tensor(np.concatenate([[0], np.cumsum(rows)]), dtype=torch.int32)
+    ctx = gpu_lib.Context(H, E, 1, I, torch.bfloat16, max_tokens=A, device=DEV)
+    args = (x_perm.to(DEV), offsets.to(DEV), L["w_gate_up"].to(DEV), L["w_down"].to(DEV))
+    ctx.moe_set_ffn_variant("small")
+    small = ctx.moe_grouped_ffn(*args)
+    ctx.moe_set_ffn_variant("big")
+    for _ in range(2):
+        assert torch.equal(ctx.moe_grouped_ffn(*args), small)
+    assert_close(small, dense_ffn(x_perm, offsets, L, "bf16", E), "bf16", "big tiles")
+
+
+@pytest.mark.parametrize("T,E,K,fmt", [(300, 5, 1, {}), (517, 9, 3, {}), (700, 65, 7, {"y_perm_f32": True}),
+                                       (259, 3, 3, {"y_perm_f32": True, "act_split": True})])
+def test_big_tiles_with_gathered_rows(gpu_lib, T, E, K, fmt):
+    """The rows come through the permutation (divided by K on the device), from two input buffers."""
+    H, I = 512, 384
+    w = inputs.Workload("bigmap", H=H, E=E, K=K, I=I, n_layers=1, D=T // 3, P=T - T // 3, dtype="bf16", seed=T)
+    L = {k: (v.to(DEV) if v is not None else None) for k, v in inputs.make_layer(w, 0).items()}
+    xd, xp = inputs.make_hidden(w, device=DEV)
+    ctx = gpu_lib.Context(H, E, K, I, torch.bfloat16, max_tokens=T, device=DEV, **fmt)
+    out = {}
+    for v in ("small", "big"):
+        ctx.moe_set_ffn_variant(v)
+        out[v] = [y.clone() for y in ctx.moe_group_forward([L], xd, xp)]
+    assert all(torch.equal(a, b) for a, b in zip(out["small"], out["big"]))
