@@ -289,7 +289,8 @@ typedef enum {
     MOE_FFN_PIPE_SMALL = 2, /* bf16: 64 x 128 tiles, weight streaming */
     MOE_FFN_PIPE_BIG = 3,   /* bf16: up to 256 x 256 tiles, compute bound */
     MOE_FFN_W4_TILE64 = 4,  /* MXFP4: 64-row tiles */
-    MOE_FFN_W4_STREAM = 5   /* MXFP4: 32-row weight-streaming tiles */
+    MOE_FFN_W4_STREAM = 5,  /* MXFP4: 32-row weight-streaming tiles */
+    MOE_FFN_W4_BIG = 6      /* MXFP4: up to 256 x 256 tiles, compute bound (K >= 512) */
 } moe_ffn_variant_id;
 moe_status moe_set_ffn_variant(moe_ctx *ctx, int32_t variant);
 

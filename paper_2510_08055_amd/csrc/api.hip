@@ -573,14 +573,14 @@ const char* moe_ffn_variant(const moe_ctx* ctx, int64_t T)
 {
     if (!ctx) return "";
     const moe_config& g = ctx->cfg;
-    if (g.weight_format == MOE_W_MXFP4) return ffn_w4_variant_name(ctx->ffn_variant, T * g.K, g.E);
+    if (g.weight_format == MOE_W_MXFP4) return ffn_w4_variant_name(ctx->ffn_variant, T * g.K, g.E, g.H);
     return ffn_variant_name(g.dtype, ctx->ffn_variant, T * g.K, g.E, g.H, g.I);
 }
 
 moe_status moe_set_ffn_variant(moe_ctx* ctx, int32_t variant)
 {
     if (!ctx) return MOE_ERR_NULL;
-    if (variant < MOE_FFN_AUTO || variant > MOE_FFN_W4_STREAM) return MOE_ERR_SHAPE;
+    if (variant < MOE_FFN_AUTO || variant > MOE_FFN_W4_BIG) return MOE_ERR_SHAPE;
     ctx->ffn_variant = variant;
     return MOE_OK;
 }

@@ -5,7 +5,7 @@
 //
 // Both operands are K-contiguous (activations [rows,K], weights [N,K]), which is exactly
 // the MFMA operand layout: each lane feeds 8 consecutive k-values of one row.
-#include "ffn_tile.h"
+#include "ffn_big.h"
 
 namespace moe {
 
@@ -558,249 +558,6 @@ __global__ __launch_bounds__(NW * 64, MINW) void grouped_gemm_bf16_pipe_kernel(
 // 4 to 8, for which the rounds of tiles over the chip cost least; equal tiles are worth a few more of them, because
 // the blocks' shares are not evened out at run time.
 // ----------------------------------------------------------------------------------------------
-constexpr int kBigRows = 256, kBigBN = 256, kBigWaves = 8, kBigMinHeight = 4;
-
-// Fixed cost of a tile in units of one of its 32-row blocks: about 8 us (epilogue, next tile's search, the first
-// steps' waits) against 0.17 us per block and k-step, measured at nk = 12 and 32.
-__device__ __forceinline__ float big_tile_fixed(int nk) { return 48.0f / (float)nk + 0.35f; }
-
-// Inclusive scan over the wave's lanes in six register-to-register steps (row shifts, then the last lane of a row to
-// the next row, then lane 31 to the upper half).
-template <typename V> __device__ __forceinline__ V wave_scan(V v)
-{
-    auto step = [&](auto ctrl, auto row_mask) {
-        const int o = __builtin_amdgcn_update_dpp(0, __builtin_bit_cast(int, v), decltype(ctrl)::value,
-                                                  decltype(row_mask)::value, 0xF, true);
-        v += __builtin_bit_cast(V, o);
-    };
-    using std::integral_constant;
-    step(integral_constant<int, 0x111>{}, integral_constant<int, 0xF>{});      // from 1, 2, 4 and 8 lanes below, within 16
-    step(integral_constant<int, 0x112>{}, integral_constant<int, 0xF>{});
-    step(integral_constant<int, 0x114>{}, integral_constant<int, 0xF>{});
-    step(integral_constant<int, 0x118>{}, integral_constant<int, 0xF>{});
-    step(integral_constant<int, 0x142>{}, integral_constant<int, 0xA>{});      // rows 1 and 3: last lane of the row below
-    step(integral_constant<int, 0x143>{}, integral_constant<int, 0xC>{});      // upper half: lane 31
-    return v;
-}
-__device__ __forceinline__ int last_lane(int v) { return __builtin_amdgcn_readlane(v, 63); }
-__device__ __forceinline__ float last_lane(float v)
-{
-    return __builtin_bit_cast(float, __builtin_amdgcn_readlane(__builtin_bit_cast(int, v), 63));
-}
-
-struct BigTile {
-    int expert, row0, row_end, n_tile;
-};
-
-// ceil(x / h) for 0 <= x < 2^28 and 4 <= h <= 8 (inverse: ceil(2^32 / h), exact in this range)
-__device__ __forceinline__ uint32_t height_inverse(int h)
-{
-    return h == 8 ? 0x20000000u : h == 7 ? 0x24924925u : h == 6 ? 0x2aaaaaabu : h == 5 ? 0x33333334u : 0x40000000u;
-}
-__device__ __forceinline__ int div_up(int x, int h, uint32_t inverse) { return (int)__umulhi((uint32_t)(x + h - 1), inverse); }
-
-// The block's share of the tile list: a range of it with a stride, and the expert the walk has reached.  Everything
-// here is the same in all lanes.
-//
-// Every block works the list out for itself.  What that costs is instruction fetch (cold straight-line code runs at
-// about 1 KB per us: a first version, unrolled over the 8 experts of a lane, was 11 KB and took 10 us of every
-// launch), hence the loops that are kept loops and the walk over the experts in place of a search.
-struct BigQueue {
-    const int32_t* offsets;
-    int E, max_rows, n_tiles;
-    int h;                     // tile height limit in row blocks
-    uint32_t h_inv;
-    int end;                   // end of the block's range
-    int expert, before;        // the walk: an expert, tiles of the experts in front of it,
-    int lo, hi, mt, per;       // its rows, its number of m-tiles and the row blocks of each
-
-    __device__ __forceinline__ void load_expert()
-    {
-        // (one scalar load with its wait inside: through the compiler it might become a vector load, whose wait
-        // would also be a wait for every asm-issued load in flight)
-        unsigned long long pair;
-        asm volatile("s_load_dwordx2 %0, %1, 0x0\n\ts_waitcnt lgkmcnt(0)" : "=&s"(pair) : "s"(offsets + expert) : "memory");
-        lo = (int)(uint32_t)pair;
-        hi = (int)(uint32_t)(pair >> 32);
-        lo = lo < 0 ? 0 : (lo > max_rows ? max_rows : lo);
-        hi = hi < lo ? lo : (hi > max_rows ? max_rows : hi);
-        const int rb = (hi - lo + 31) / 32;
-        mt = div_up(rb, h, h_inv);
-        per = mt > 1 ? quotient(rb + mt - 1, mt) : rb;
-    }
-    // x / m for 0 <= x < 2^24 (the launch keeps lists of more tiles away), a few instructions instead of a division
-    static __device__ __forceinline__ int quotient(int x, int m)
-    {
-        int q = (int)((float)x * __builtin_amdgcn_rcpf((float)m));
-        if (q * m > x) q -= 1;
-        if (x - q * m >= m) q += 1;
-        return __builtin_amdgcn_readfirstlane(q);
-    }
-
-    // Tile j of the list; j never decreases from call to call and is below the number of tiles.
-    __device__ __forceinline__ BigTile take(int j)
-    {
-        while (j >= before + mt * n_tiles && expert + 1 < E) {
-            before += mt * n_tiles;
-            expert += 1;
-            load_expert();
-        }
-        const int m = mt > 0 ? mt : 1;
-        const int rem = j - before;
-        const int n = quotient(rem, m), t = rem - n * m;
-        BigTile tile;
-        tile.expert = expert;
-        tile.n_tile = n;
-        tile.row0 = lo + t * per * 32;
-        tile.row_end = tile.row0 + per * 32;
-        if (tile.row_end > hi) tile.row_end = hi;
-        if (tile.row0 > tile.row_end) tile.row0 = tile.row_end;
-        return tile;
-    }
-
-    // Every wave of the block calls it, with `scratch` a piece of LDS nothing else uses.  Returns the block's first tile.
-    __device__ __forceinline__ int init(const int32_t* offsets_, int E_, int n_tiles_, int max_rows_, float fixed, int* scratch)
-    {
-        offsets = offsets_;
-        E = E_;
-        max_rows = max_rows_;
-        n_tiles = n_tiles_;
-        const int lane = lane_id();
-        const int k = __builtin_amdgcn_readfirstlane((int)(threadIdx.x >> 6));       // wave
-        int* const tiles_at = scratch;              // [8] tiles at height 8 - k
-        float* const squares_at = reinterpret_cast<float*>(scratch + 600);   // [8] sum of their squared heights
-        int* const border = scratch + 8;            // [2][8] first tile of piece k: equal numbers, equal costs
-        int* const b_expert = scratch + 24;         // [2][8] the expert of that tile
-        int* const b_before = scratch + 40;         // [2][8] tiles of the experts in front of it
-        float* const b_cost = reinterpret_cast<float*>(scratch + 56);     // [8] cost in front of border[0][k]
-        int* const rb_of = scratch + 64;            // [E] row blocks
-
-        // wave k: number of tiles at height 8 - k
-        int rb_sum = 0, t_sum = 0;
-        float sq_sum = 0.f;                         // sum of the tiles' squared heights
-        {
-            const int hh = kBigRows / 32 - k >= kBigMinHeight ? kBigRows / 32 - k : kBigMinHeight;
-            const uint32_t inv = height_inverse(hh);
-#pragma unroll 1
-            for (int e = lane; e < E; e += 64) {
-                int r0 = offsets[e], r1 = offsets[e + 1];
-                r0 = r0 < 0 ? 0 : (r0 > max_rows ? max_rows : r0);
-                r1 = r1 < r0 ? r0 : (r1 > max_rows ? max_rows : r1);
-                const int rb = (r1 - r0 + 31) / 32;
-                if (k == 0) rb_of[e] = rb;
-                const int m = div_up(rb, hh, inv);
-                rb_sum += rb;
-                t_sum += m;
-                sq_sum += rb > 0 ? (float)rb * (float)rb * __builtin_amdgcn_rcpf((float)m) : 0.f;
-            }
-        }
-        t_sum = last_lane(wave_scan(t_sum));
-        sq_sum = last_lane(wave_scan(sq_sum));
-        const float rb_all = (float)last_lane(wave_scan(rb_sum)) * (float)n_tiles;
-        if (lane == 0) {
-            tiles_at[k] = t_sum;
-            squares_at[k] = sq_sum;
-        }
-        __syncthreads();
-        const float blocks = (float)gridDim.x;
-        float best = 0.f;
-        h = 0;
-#pragma unroll 1
-        for (int c = 0; c <= kBigRows / 32 - kBigMinHeight; ++c) {
-            const float tiles = fmaxf((float)tiles_at[c] * (float)n_tiles, 1.f), inv = __builtin_amdgcn_rcpf(tiles);
-            const float rounds = ceilf(tiles * __builtin_amdgcn_rcpf(blocks) - 1e-3f), mean = rb_all * inv;
-            const float var = fmaxf(squares_at[c] * (float)n_tiles * inv - mean * mean, 0.f);
-            // whole rounds of the mean tile, and what the unluckiest block gets on top of that by chance
-            const float cost = rounds * (fixed + mean) + 1.5f * __builtin_amdgcn_sqrtf(rounds * var);
-            if (c == 0 || cost < best) {
-                best = cost;
-                h = kBigRows / 32 - c;
-            }
-        }
-        h = __builtin_amdgcn_readfirstlane(h);
-        h_inv = height_inverse(h);
-        const int total = __builtin_amdgcn_readfirstlane(tiles_at[kBigRows / 32 - h]) * n_tiles;
-        const float ftotal = fixed * (float)total + rb_all;
-
-        // Border k of the eight pieces: after k / 8 of the tiles, or where the running cost passes k / 8 of the total.
-        // Pieces of equal cost suit tiles of different heights; pieces of equal number never need one more round
-        // than the whole list does.  Wave k works both out for k (and the cost in front of the first), they meet in
-        // LDS, and the kind whose slowest piece is estimated to end first is taken: whole rounds of its mean tile.
-        {
-            const float target = ftotal * (float)k * 0.125f;
-            const int by_count = (int)((int64_t)total * k / 8);
-            int sum = 0;
-            float fsum = 0.f;
-            bool found = false, found_n = false;
-#pragma unroll 1
-            for (int e0 = 0; e0 < E; e0 += 64) {
-                const int rb = e0 + lane < E ? rb_of[e0 + lane] : 0;
-                const int tiles = div_up(rb, h, h_inv) * n_tiles;
-                const float c = fixed * (float)tiles + (float)rb * (float)n_tiles;
-                const int cum = wave_scan(tiles) + sum;
-                const float fcum = wave_scan(c) + fsum;
-                const unsigned long long past_n = __ballot(cum > by_count), past = __ballot(fcum > target);
-                // (one lane is picked: one whose number of tiles and cost are not zero)
-                if (!found_n && past_n) {
-                    found_n = true;
-                    if (lane == __ffsll((long long)past_n) - 1) {
-                        border[k] = by_count;
-                        b_expert[k] = e0 + lane;
-                        b_before[k] = cum - tiles;
-                        b_cost[k] = fcum - c * (float)(cum - by_count) * __builtin_amdgcn_rcpf((float)tiles);
-                    }
-                }
-                if (!found && past) {
-                    found = true;
-                    if (lane == __ffsll((long long)past) - 1) {
-                        const float behind = fminf((fcum - target) * __builtin_amdgcn_rcpf(c), 1.f);
-                        border[8 + k] = k > 0 ? cum - (int)(behind * (float)tiles) : 0;
-                        b_expert[8 + k] = e0 + lane;
-                        b_before[8 + k] = cum - tiles;
-                    }
-                }
-                sum = last_lane(cum);
-                fsum = last_lane(fcum);
-            }
-            if (lane == 0) {     // (only if rounding puts the last borders behind the last expert, or nothing has rows)
-                if (!found_n) {
-                    border[k] = total;
-                    b_expert[k] = E - 1;
-                    b_before[k] = total;
-                    b_cost[k] = ftotal;
-                }
-                if (!found) {
-                    border[8 + k] = total;
-                    b_expert[8 + k] = E - 1;
-                    b_before[8 + k] = total;
-                }
-            }
-        }
-        __syncthreads();
-        // lane y < 8 of every wave: piece y, both ways
-        const int y = lane & 7;
-        const float n0 = (float)(y < 7 ? border[y + 1] : total) - (float)border[y];
-        const float n1 = (float)(y < 7 ? border[9 + y] : total) - (float)border[8 + y];
-        const float per_block = 8.f * __builtin_amdgcn_rcpf(blocks);
-        float slow0 = n0 > 0.f ? ceilf(n0 * per_block - 1e-3f) * ((y < 7 ? b_cost[y + 1] : ftotal) - b_cost[y]) * __builtin_amdgcn_rcpf(n0) : 0.f;
-        float slow1 = n1 > 0.f ? ceilf(n1 * per_block - 1e-3f) * (ftotal * 0.125f) * __builtin_amdgcn_rcpf(n1) : 0.f;
-#pragma unroll 1
-        for (int o = 4; o >= 1; o >>= 1) {
-            slow0 = fmaxf(slow0, __shfl_xor(slow0, o, 64));
-            slow1 = fmaxf(slow1, __shfl_xor(slow1, o, 64));
-        }
-        const int x = (int)(blockIdx.x % 8);
-        const int at = (__builtin_amdgcn_readfirstlane(slow1 < slow0) != 0 ? 8 : 0) + x;
-        const int first = __builtin_amdgcn_readfirstlane(border[at]) + (int)(blockIdx.x / 8);
-        end = x == 7 ? total : __builtin_amdgcn_readfirstlane(border[at + 1]);
-        expert = __builtin_amdgcn_readfirstlane(b_expert[at]);
-        before = __builtin_amdgcn_readfirstlane(b_before[at]);
-        load_expert();
-        __syncthreads();       // `scratch` is free again
-        return first;
-    }
-};
-
 template <bool GATED, bool OUT_F32, bool SPLIT, bool MAPPED>
 __global__ __launch_bounds__(kBigWaves * 64, 2) void grouped_gemm_bf16_big_kernel(
     RowSrc X, int ldx, const int32_t* __restrict__ row_map, int map_div, uint32_t map_magic,
@@ -819,7 +576,7 @@ __global__ __launch_bounds__(kBigWaves * 64, 2) void grouped_gemm_bf16_big_kerne
     constexpr int LPW = BM / 8 / NW;            // load instructions per wave, stage and operand (8 rows of 128 bytes each)
     constexpr uint32_t SLOT = BM * ROWB;        // bytes of one stage of either operand
     constexpr uint32_t B_BASE = 2 * SLOT;       // the weight ring (3 slots) follows the activation ring (2 slots)
-    static_assert(BM == BN && LPW == 4 && TM == 4 && KS == 4, "tile configuration");
+    static_assert(BM == BN && LPW == 4 && TM == 4 && KS == 4 && NW * TNO * 2048 <= (int)SLOT, "tile configuration");
 
     extern __shared__ __attribute__((aligned(1024))) char smem[];
     const uint32_t lds0 = lds_address(smem);
@@ -837,50 +594,11 @@ __global__ __launch_bounds__(kBigWaves * 64, 2) void grouped_gemm_bf16_big_kerne
     if (at >= queue.end) return;
     const int stride = (int)gridDim.x / 8;
 
-    // Load p of this wave covers tile rows (wave + 8 p) * 8 .. + 7, lane = (row, 16-byte chunk); LDS chunk c of tile
-    // row r holds global chunk c ^ swz(r) (swz looks at the low four row bits only: the same for every p).
+    // Load p of this wave covers weight rows (wave + 8 p) * 8 .. + 7 of the tile, as on the activation side (BigRows).
     const int l_row = lane >> 3;
     const uint32_t l_chunk = (uint32_t)((lane & 7) ^ swz<PBK>(wave * 8 + l_row)) * 16;
 
-    // ---- activation rows ----
-    int32_t row_id[LPW];               // looked-up rows of the next tile (asm-issued loads: see below)
-    const char* a_src[LPW];            // the lane's 16 bytes of stage 0 of the tile whose stages are being loaded
-    int a_live = 0;                    // of the wave's loads, how many hold rows of that tile
-    // The look-ups are loads issued from inline asm: through the compiler they would be waited for with vmcnt(0),
-    // i.e. together with all weight loads in flight.  They are picked up one step later, behind a wait that leaves only
-    // younger loads in flight.
-    auto look_up = [&](const BigTile& t) {
-#pragma unroll
-        for (int p = 0; p < LPW; ++p) {
-            int r = t.row0 + (wave + NW * p) * 8 + l_row;
-            if (r >= t.row_end) r = t.row_end - 1;
-            if (MAPPED) asm volatile("global_load_dword %0, %1, off" : "=v"(row_id[p]) : "v"(row_map + r) : "memory");
-            else row_id[p] = r;
-        }
-    };
-    auto use_rows = [&](const BigTile& t) {
-#pragma unroll
-        for (int p = 0; p < LPW; ++p) {
-            if (MAPPED) asm volatile("" : "+v"(row_id[p])::"memory");
-            // a row map holds indices below a_rows; the clamp keeps a bad entry from becoming a wild address
-            uint32_t id = row_id[p] < 0 ? 0u : (uint32_t)row_id[p];
-            id = id < (uint32_t)a_rows ? id : (uint32_t)a_rows - 1;
-            if (MAPPED && map_div > 1) {       // id / map_div: map_magic = ceil(2^32 / map_div) overshoots by at most one
-                uint32_t q = __umulhi(id, map_magic);
-                if (q * (uint32_t)map_div > id) q -= 1;
-                id = q;
-            }
-            a_src[p] = reinterpret_cast<const char*>(row_ptr<bf16_t>(X, (int64_t)id, ldx)) + l_chunk;
-        }
-        const int live = (t.row_end - t.row0 - wave * 8 + 63) / 64;
-        a_live = live < 0 ? 0 : (live > LPW ? LPW : live);
-    };
-    // (a load whose 8 rows all lie past the tile's last row is left out: no wait count includes an activation load)
-    auto issue_a = [&](int stage, uint32_t slot) {
-#pragma unroll
-        for (int p = 0; p < LPW; ++p)
-            if (p < a_live) load_lds_16(a_src[p] + (uint32_t)(stage * ROWB), lds0 + slot + (wave + NW * p) * 1024);
-    };
+    BigRows<MAPPED> rows(X, ldx, row_map, map_div, map_magic, a_rows, wave);
 
     // ---- weight rows: a uniform base per half of the tile, small lane offsets ----
     const char *b_gate = nullptr, *b_up = nullptr;      // next weight stage to load: rows n0 .. and, gated, N + n0 ..
@@ -922,7 +640,7 @@ __global__ __launch_bounds__(kBigWaves * 64, 2) void grouped_gemm_bf16_big_kerne
     // ---- first tile: two weight stages and one activation stage ----
     BigTile cur = queue.take(at), nxt = cur;
     uint32_t a_slot = 0, b_slot = 0;       // slots of the stage being multiplied
-    look_up(cur);
+    rows.look_up(cur);
     use_weights(cur);
 #pragma unroll
     for (int st = 0; st < 2; ++st) {
@@ -931,11 +649,11 @@ __global__ __launch_bounds__(kBigWaves * 64, 2) void grouped_gemm_bf16_big_kerne
         advance_b(st);
     }
     wait_vmcnt<2 * LPW>();                 // the look-ups came before the weight loads
-    use_rows(cur);
-    issue_a(0, 0);
+    rows.use(cur);
+    rows.issue(0, lds0);
     wait_vmcnt<0>();
     block_barrier();
-    issue_a(1, SLOT);
+    rows.issue(1, lds0 + SLOT);
 
     // One tile.  On entry stage 0 of both operands is in LDS for every wave, weight stage 1 is in flight and the
     // activation loads of stage 1 have been issued.  The body is instantiated for the number TMV of row blocks this
@@ -1020,121 +738,32 @@ __global__ __launch_bounds__(kBigWaves * 64, 2) void grouped_gemm_bf16_big_kerne
         read_frags(a_slot, b_slot, 0, 0);
         for (int s = 0; s < nk - 3; ++s) {
             step_head(s + 2);
-            issue_a(s + 2, a_slot);
+            rows.issue(s + 2, lds0 + a_slot);
             step_tail(true);
         }
         // step nk - 3: the next tile's rows are looked up.  (Not earlier: the registers the look-ups land on must not
         // be copied before they have landed, and the shorter they live the less reason the compiler has to; the
         // build checks the listing.)
-        look_up(nxt);
+        rows.look_up(nxt);
         step_head(nk - 1);
-        issue_a(nk - 1, a_slot);
+        rows.issue(nk - 1, lds0 + a_slot);
         step_tail(true);
         // step nk - 2: from here on the loads are those of the next tile
         use_weights(nxt);
-        use_rows(nxt);
+        rows.use(nxt);
         step_head(0);
-        issue_a(0, a_slot);
+        rows.issue(0, lds0 + a_slot);
         step_tail(true);
         // step nk - 1
         step_head(1);
         // every wave has read the last stage: its activation slot takes stage 1 of the next tile, its weight slot
         // (free until the next tile's first step) is where the epilogue works
-        issue_a(1, a_slot);
+        rows.issue(1, lds0 + a_slot);
         const uint32_t epi_slot = B_BASE + b_slot;
         step_tail(false);
 
-        // Epilogue.  A lane holds, for output row fr of a row block, groups of 4 consecutive columns
-        // (accumulator element v of tile (i, j): column (v/4)*8 + fq*4 + v%4); storing them directly
-        // would scatter 8-byte pieces over 32 rows per instruction.  Each wave instead turns one row block
-        // at a time (32 rows x WNO columns, at most 4 KB) through a private piece of LDS and writes it
-        // out as whole 16-byte chunks, consecutive lanes along a row (64- or 128-byte runs per row).
-        constexpr int RB = TNO * 64;              // bytes of one row of the wave's output tile
-        constexpr int CPRW = TNO * 4;             // 16-byte chunks per such row
-        constexpr int REG = 32 * RB;              // bytes per wave
-        constexpr int RPI = 64 / CPRW;            // rows one wave-level 16-byte access covers
-        static_assert(TNO <= 2 && NW * REG <= (int)SLOT, "the epilogue staging does not fit the free slot");
-        static_assert(!OUT_F32 || REG >= 4096, "a 32 x 32 float tile must fit the wave's staging piece");
-        const int n0 = cur.n_tile * NO;
-        if (TMV > 0 && OUT_F32) {
-            // float output: one 32 x 32 tile (4 KB: 32 rows of 8 16-byte chunks) at a time through the same
-            // private piece of LDS; a lane's 4 consecutive columns are one chunk, chunk c of row r sits in
-            // chunk slot c ^ (r & 7), and the tile goes out as 128-byte runs per row.
-            float* Out = static_cast<float*>(Out_);
-            char* epi = smem + epi_slot + wave * REG;
-#pragma unroll
-            for (int i = 0; i < TMV; ++i) {
-                const int64_t row_base = (int64_t)cur.row0 + (wm + WM * i) * 32;
-#pragma unroll
-                for (int j = 0; j < TNO; ++j) {
-#pragma unroll
-                    for (int a = 0; a < 4; ++a)
-                        *reinterpret_cast<float4*>(epi + fr * 128 + (((a * 2 + fq) ^ (fr & 7)) << 4)) =
-                            make_float4(acc[i][j][a * 4], acc[i][j][a * 4 + 1], acc[i][j][a * 4 + 2], acc[i][j][a * 4 + 3]);
-                    __builtin_amdgcn_wave_barrier();
-#pragma unroll
-                    for (int h = 0; h < 4; ++h) {
-                        const int r = h * 8 + (lane >> 3), c = lane & 7;
-                        const float4 v = *reinterpret_cast<const float4*>(epi + r * 128 + ((c ^ (r & 7)) << 4));
-                        const int64_t row = row_base + r;
-                        const int col = n0 + wn * WNO + j * 32 + c * 4;
-                        if (row < cur.row_end && col < N)    // N is a multiple of 8: the 4 columns are in or out together
-                            *reinterpret_cast<float4*>(Out + row * ldo + col) = v;
-                    }
-                    __builtin_amdgcn_wave_barrier();
-                }
-            }
-        } else if (TMV > 0) {
-            bf16_t* Out = static_cast<bf16_t*>(Out_);
-            char* epi = smem + epi_slot + wave * REG;
-            auto eswz = [](int r) { return (r >> (RB == 64 ? 2 : 1)) & (CPRW - 1); };
-            constexpr int PARTS = (SPLIT && GATED) ? 2 : 1;      // the values, then what their bf16 rounding left over
-#pragma unroll
-            for (int i = 0; i < TMV; ++i) {
-                if (GATED) {
-#pragma unroll
-                    for (int j = 0; j < TNO; ++j)
-#pragma unroll
-                        for (int v = 0; v < 16; ++v) {
-                            acc[i][j][v] = silu_mul(acc[i][j][v], acc[i][j + TNO][v]);
-                            if (SPLIT) acc[i][j][v] = opaque(acc[i][j][v]);
-                        }
-                }
-#pragma unroll
-                for (int part = 0; part < PARTS; ++part) {
-#pragma unroll
-                    for (int j = 0; j < TNO; ++j) {
-#pragma unroll
-                        for (int a = 0; a < 4; ++a) {
-                            float val[4];
-#pragma unroll
-                            for (int b = 0; b < 4; ++b) val[b] = acc[i][j][a * 4 + b];
-                            const uint32_t p01 = pack_bf16x2(val[0], val[1]), p23 = pack_bf16x2(val[2], val[3]);
-                            if (PARTS == 2 && part == 0) {      // keep the remainders for the second part
-                                acc[i][j][a * 4 + 0] = val[0] - __uint_as_float(p01 << 16);
-                                acc[i][j][a * 4 + 1] = val[1] - __uint_as_float(p01 & 0xffff0000u);
-                                acc[i][j][a * 4 + 2] = val[2] - __uint_as_float(p23 << 16);
-                                acc[i][j][a * 4 + 3] = val[3] - __uint_as_float(p23 & 0xffff0000u);
-                            }
-                            const int chunk = (j * 4 + a) ^ eswz(fr);
-                            *reinterpret_cast<uint2*>(epi + fr * RB + chunk * 16 + fq * 8) = make_uint2(p01, p23);
-                        }
-                    }
-                    __builtin_amdgcn_wave_barrier();
-                    const int64_t row_base = (int64_t)cur.row0 + (wm + WM * i) * 32;
-#pragma unroll
-                    for (int h = 0; h < 32 / RPI; ++h) {
-                        const int r = h * RPI + lane / CPRW, c = lane % CPRW;
-                        const uint4 v = *reinterpret_cast<const uint4*>(epi + r * RB + ((c ^ eswz(r)) * 16));
-                        const int64_t row = row_base + r;
-                        const int col = n0 + wn * WNO + c * 8;
-                        if (row < cur.row_end && col < N)    // N is a multiple of 8: a chunk is in or out as a whole
-                            *reinterpret_cast<uint4*>(Out + row * ldo + part * N + col) = v;
-                    }
-                    __builtin_amdgcn_wave_barrier();
-                }
-            }
-        }
+        big_epilogue<GATED, OUT_F32, SPLIT, TMV, TNO>(acc, cur, wm, cur.n_tile * NO + wn * WNO,
+                                                      smem + epi_slot + wave * (TNO * 2048), Out_, ldo, N);
     };
 
     for (;;) {
@@ -1295,8 +924,10 @@ enum Variant { V_TILE128 = 0, V_PIPE_SMALL, V_PIPE_BIG };
 static Variant pick_variant(int variant, int64_t A, int E, int K)
 {
     Variant v;
-    const double mean_rows = (double)A / (double)E;
-    if (mean_rows <= 64.0) v = V_PIPE_SMALL;   // weight streaming: 64 x 128 tiles, 3 stages of 64 k-values
+    // Weight streaming with 64 x 128 tiles up to 56 rows per expert on average.  Layer, us, streaming against big tiles:
+    // 128 experts, H = 2048, I = 768: 47 rows 277 / 280, 56 rows 299 / 299, 64 rows 320 / 304; 32 experts, H = I = 2880:
+    // 32 rows 318 / 316, 50 rows 339 / 336, 64 rows 385 / 344.
+    if (A <= (int64_t)56 * E) v = V_PIPE_SMALL;
     else v = V_PIPE_BIG;                       // up to 256 x 256 tiles, persistent blocks
     if (variant == MOE_FFN_TILE128) v = V_TILE128;
     if (variant == MOE_FFN_PIPE_SMALL) v = V_PIPE_SMALL;
@@ -1358,18 +989,13 @@ static hipError_t launch_big(RowSrc X, int ldx, const int32_t* row_map, int map_
     static bool attr_set[kMaxDevices] = {};
     hipError_t e = ensure_lds_limit(kern, lds_bytes, attr_set);
     if (e != hipSuccess) return e;
-    const int64_t n_tiles = (N + NO - 1) / NO;
-    // (tiles of at least 4 row blocks: sum_e ceil(m_e / 128) never exceeds this; the device counts in floats here and there)
-    const int64_t tiles_max = ((A + 127) / 128 + (A < E ? A : E)) * n_tiles;
-    if (tiles_max >= ((int64_t)1 << 24) || A >= ((int64_t)1 << 28))
-        return launch_pipe<GATED, OUT_F32, SPLIT, MAPPED>(
-            X, ldx, row_map, map_div, offsets, E, A, W, w_expert_stride, N, K, Out, ldo, s);
-    int cus = 0;
-    e = compute_units(&cus);
+    if (!big_list_fits(A, E, (N + NO - 1) / NO))
+        return launch_pipe<GATED, OUT_F32, SPLIT, MAPPED>(X, ldx, row_map, map_div, offsets, E, A, W, w_expert_stride, N, K,
+                                                          Out, ldo, s);
+    int grid = 0;
+    e = big_grid(&grid);
     if (e != hipSuccess) return e;
-    const int grid = cus / 8 * 8 > 0 ? cus / 8 * 8 : 8;      // one block per compute unit, the same number on every XCD
-    const uint32_t magic = map_div > 1 ? (uint32_t)((((uint64_t)1 << 32) + map_div - 1) / map_div) : 0;
-    kern<<<(unsigned)grid, kBigWaves * 64, lds_bytes, s>>>(X, ldx, row_map, map_div, magic, offsets, E, W, w_expert_stride,
+    kern<<<(unsigned)grid, kBigWaves * 64, lds_bytes, s>>>(X, ldx, row_map, map_div, map_magic_of(map_div), offsets, E, W, w_expert_stride,
                                                            N, K, Out, ldo, (int)A);
     return hipGetLastError();
 }

@@ -7,19 +7,19 @@
 // 32 consecutive elements along k.  A dequantised weight is exactly representable in bf16, so the GEMM
 // is the bf16 MFMA GEMM of ffn.hip on weights widened on the fly (v_cvt_scalef32_pk_bf16_fp4).
 //
-// Two kernel shapes.  The first, for batches with more than 96 rows per expert on average: 64-row x
+// Three kernel shapes.  The first, for short rows (K < 512) and batches of many rows per expert: 64-row x
 // 256-weight-row tiles, 4 waves side by side along the weight rows (each widens and multiplies its own
 // 64 weight rows against the tile's one or two 32-row blocks), 64 k-values per stage; activation rows
 // come through a 2-stage LDS ring as in ffn.hip.  The packed weight rows and their scale bytes are
 // fetched for TWO stages at a time (64 bytes of codes and 4 scale bytes per row) into a ring of 3 such
 // double stages: the layer is bound by the number of memory requests, not their bytes, when every row
 // contributes 32 + 2 bytes per stage (measured: 2.7x slower).  72 KB of LDS: two blocks share a compute
-// unit.  The second, the weight-streaming shape for decode-heavy batches, is described further down.
-// In both, within a 64-wide stage lane (row, q) feeds k-block q (32 values) to four successive MFMAs, 8
+// unit.  The second, the weight-streaming shape for decode-heavy batches, and the third, the compute-bound one, are
+// described further down.  In all, within a 64-wide stage lane (row, q) feeds k-block q (32 values) to four successive MFMAs, 8
 // values each, and the activation fragments follow the same k assignment; stages and MFMAs run in the
-// same ascending order, so the two shapes produce bit-identical results and a chunked and a layered pass
+// same ascending order, so the shapes produce bit-identical results and a chunked and a layered pass
 // may pick different ones.
-#include "ffn_tile.h"
+#include "ffn_big.h"
 
 namespace moe {
 
@@ -29,6 +29,7 @@ typedef uint32_t u32x4_t __attribute__((ext_vector_type(4)));
 namespace {
 
 constexpr int kW4Rows = 64, kW4BN = 256, kW4Waves = 4, kW4K = 64;
+constexpr size_t kW4BigLds = (size_t)(2 * 256 * 128 + 4 * 256 * 64 + 3 * 256 * 16);     // see the kernel
 constexpr int kW4NSA = 2, kW4NSB = 3;     // activation stages; weight DOUBLE stages (two stages each)
 
 // Loads that may still be in flight while the wave goes on: the pipeline keeps count of the load
@@ -71,7 +72,12 @@ __device__ __forceinline__ bf16x8_t widen_fp4x8(uint32_t v, float scale)
 }
 
 // E8M0 scale byte -> float 2^(s - 127); s = 0 is 2^-127, a subnormal float.
-__device__ __forceinline__ float e8m0_to_float(uint32_t s) { return __uint_as_float(s ? s << 23 : 0x00400000u); }
+// (any other byte gives at least 0x00800000.)
+__device__ __forceinline__ float e8m0_to_float(uint32_t s)
+{
+    const uint32_t bits = s << 23;
+    return __uint_as_float(bits > 0x00400000u ? bits : 0x00400000u);
+}
 
 // The same for byte SH / 8 of a word, in three instructions: the byte is moved into the exponent field
 // in place, and 2^-127 = 0x00400000 exceeds the result only when the byte is 0.  (Written as a compare
@@ -351,7 +357,7 @@ __global__ __launch_bounds__(kW4Waves * 64, 2) void grouped_gemm_w4_kernel(
 }
 
 // ----------------------------------------------------------------------------------------------
-// The weight-streaming shape for decode-heavy batches (on average at most 96 rows per expert).
+// The weight-streaming shape for decode-heavy batches (on average at most 48 rows per expert).
 //
 // With 4-bit weights a 64-value stage is 32 bytes of a weight row: fetched stage by stage (or two
 // stages at a time) every 128-byte line of the weights is requested several times, a few stages
@@ -767,15 +773,315 @@ __global__ __launch_bounds__(kS4Waves * 64, 4) void grouped_gemm_w4_stream_kerne
     }
 }
 
-// Which kernel shape a launch uses: the streaming shape up to 96 rows per expert on average.  Its
-// 32-row tiles re-read (from L2) and re-widen the weights once per 32 rows, which a prefill-heavy batch
-// pays for: measured on 32 experts x 5760 x 2880 the two shapes are level at 40 rows per expert, the
-// streaming shape 3 % ahead at 72, 5 % behind at 136 and 13 % behind at 264.
-bool w4_use_stream(int variant, int64_t A, int E)
+// ----------------------------------------------------------------------------------------------
+// Compute-bound shape: the persistent 256 x 256 kernel of ffn.hip (its tile list, activation path and epilogue) on
+// weights that stay packed in LDS and are widened by the wave that multiplies them.
+//
+// A stage of weights is 8 KB instead of 32, so a wave reads 2 x 16 bytes of codes per stage where it read 8 x 16 bytes
+// of bf16, and two conversions per MFMA take the matrix pipe's shadow.  Codes are fetched for two stages at a time (64
+// bytes per row; a request per row and stage would be the limit) into a ring of four double stages, one 8 KB piece
+// (128 rows) per step, five pieces ahead of the step that loads it: the next tile's first pieces go out in the last
+// five steps of a tile.  When a row is an odd number of stages its last double stage is half empty (the lanes behind
+// the row's end repeat what is in front of it) and an extra piece is issued between two tiles, so that every tile
+// starts with the same lead.  Scale bytes come 16 per row and 8 stages into a ring of three 4 KB slots.
+// Within a stage lane (row, q) feeds MX block q (32 k-values) to four successive MFMAs, as in the other two shapes.
+// 140 KB of LDS: 2 x 32 activations, 4 x 16 codes, 3 x 4 scales.  Needs K >= 512 (16 scale bytes per row).
+// 32 experts, H = I = 2880, top-4, against the 64-row shape, us: 2112 tokens (264 rows per expert) gate_up 375 -> 300,
+// down 215 -> 156; 900 tokens 170 -> 136, 116 -> 88.  What bounds it: the matrix pipe at the clock the power limit
+// leaves, as in ffn.hip (bf16 weights take 312 and 166 us); the conversions hide under it.
+// ----------------------------------------------------------------------------------------------
+template <bool GATED, bool OUT_F32, bool MAPPED>
+__global__ __launch_bounds__(kBigWaves * 64, 2) void grouped_gemm_w4_big_kernel(
+    RowSrc X, int ldx, const int32_t* __restrict__ row_map, int map_div, uint32_t map_magic,
+    const int32_t* __restrict__ offsets, int E, const uint8_t* __restrict__ W, const uint8_t* __restrict__ S,
+    int64_t rows_per_expert, int N, int K, void* __restrict__ Out_, int ldo, int a_rows)
 {
-    if (variant == MOE_FFN_W4_TILE64) return false;
-    if (variant == MOE_FFN_W4_STREAM) return true;
-    return A <= (int64_t)96 * E;
+    static_assert(!(GATED && OUT_F32), "the intermediate of the gated GEMM is always bf16");
+    constexpr int BM = kBigRows, BN = kBigBN, NW = kBigWaves, WM = 2, WN = NW / WM, PBK = 64;
+    constexpr int NO = GATED ? BN / 2 : BN;     // output columns per block
+    constexpr int TM = BM / 32 / WM;            // row blocks per wave: rb = wm + WM * i
+    constexpr int WNO = NO / WN;                // output columns per wave
+    constexpr int TNO = WNO / 32;
+    constexpr int TN = GATED ? 2 * TNO : TNO;
+    constexpr int ROWB = PBK * 2;               // bytes per activation row and stage
+    constexpr int KS = PBK / 16;                // MFMA k-slices per stage
+    constexpr uint32_t A_SLOT = BM * ROWB;                       // activation stage
+    constexpr uint32_t B_BASE = 2 * A_SLOT, B_SLOT = BN * 64;    // double stage of codes, four of them
+    constexpr uint32_t B_PIECE = B_SLOT / 2;
+    constexpr uint32_t S_BASE = B_BASE + 4 * B_SLOT, S_SLOT = BN * 16;   // scale bytes of 8 stages, three of them
+    constexpr int LEAD = 5;                     // pieces in front of the one a step would need if it waited
+    static_assert(TN == 2 && TM == 4 && KS == 4 && NW * TNO * 2048 <= (int)A_SLOT, "tile configuration");
+    static_assert(S_BASE + 3 * S_SLOT == kW4BigLds, "LDS layout");
+
+    extern __shared__ __attribute__((aligned(1024))) char smem[];
+    const uint32_t lds0 = lds_address(smem);
+
+    const int lane = lane_id();
+    const int wave = __builtin_amdgcn_readfirstlane((int)(threadIdx.x >> 6));
+    const int wm = wave / WN, wn = wave % WN;
+    const int nk = K / PBK, nd = (nk + 1) / 2, n_chunks = (nk + 7) / 8;
+    const bool odd = (nk & 1) != 0;
+    const uint32_t row_bytes = (uint32_t)K / 2, row_scales = (uint32_t)K / 32;
+
+    BigQueue queue;
+    int at = queue.init(offsets, E, (N + NO - 1) / NO, a_rows, big_tile_fixed(nk), reinterpret_cast<int*>(smem));
+    if (at >= queue.end) return;
+    const int stride = (int)gridDim.x / 8;
+
+    BigRows<MAPPED> rows(X, ldx, row_map, map_div, map_magic, a_rows, wave);
+
+    // ---- codes: piece p of a double stage holds tile rows 128 p + 16 wave .. + 15, lane = (row, 16-byte block); LDS
+    // block slot c of row r holds block c ^ ((r >> 2) & 3) ----
+    const int b_row = wave * 16 + (lane >> 2);
+    const uint32_t b_blk = (uint32_t)((lane & 3) ^ ((b_row >> 2) & 3));
+    const int b_tail = odd && b_blk >= 2 ? -32 : 0;      // in a half-empty double stage: the block two in front
+    const char *b0 = nullptr, *b1 = nullptr;             // next double stage of the rows of piece 0 and of piece 1
+    uint32_t b_off0 = 0, b_off1 = 0, b_slot = 0;         // b_slot: where the double stage being loaded goes
+    int np = 0;                                          // next piece (2 per double stage) of the tile being loaded
+    auto use_weights = [&](const BigTile& t) {
+        const int n0 = t.n_tile * NO, last = N - 1 - n0;
+        const uint8_t* We = W + (int64_t)t.expert * rows_per_expert * row_bytes;
+        b0 = uniform(reinterpret_cast<const char*>(We + (int64_t)n0 * row_bytes));
+        b1 = GATED ? uniform(reinterpret_cast<const char*>(We + ((int64_t)N + n0) * row_bytes)) : b0;
+        const int r0 = b_row < last ? b_row : last;      // past the matrix: a valid row, result unused
+        const int r1 = GATED ? r0 : (BN / 2 + b_row < last ? BN / 2 + b_row : last);
+        b_off0 = (uint32_t)r0 * row_bytes + b_blk * 16;
+        b_off1 = (uint32_t)r1 * row_bytes + b_blk * 16;
+        np = 0;
+    };
+    auto issue_piece = [&]() {
+        const bool second = (np & 1) != 0;
+        const uint32_t off = (second ? b_off1 : b_off0) + (uint32_t)((np >> 1) == nd - 1 ? b_tail : 0);
+        load_lds_16_base(second ? b1 : b0, off, lds0 + B_BASE + b_slot + (second ? B_PIECE : 0) + wave * 1024);
+        np += 1;
+        if (second) {
+            b0 += 64;
+            b1 += 64;
+            b_slot = (b_slot + B_SLOT) & (3 * B_SLOT);
+        }
+    };
+    static_assert((B_SLOT & (B_SLOT - 1)) == 0, "the ring of four wraps with a mask");
+
+    // ---- scales: lanes 0 .. 31 of a wave fetch 16 bytes of rows 32 wave + lane ----
+    const char* s_base = nullptr;
+    uint32_t s_off = 0, s_load = 0;                      // s_load: ring slot of the next chunk to load
+    auto use_scales = [&](const BigTile& t) {
+        const int n0 = t.n_tile * NO, last = N - 1 - n0;
+        s_base = uniform(reinterpret_cast<const char*>(S + (int64_t)t.expert * rows_per_expert * row_scales));
+        int r = wave * 32 + (lane & 31);
+        const bool up = GATED && r >= NO;
+        if (up) r -= NO;
+        r = r < last ? r : last;
+        s_off = (uint32_t)(n0 + r + (up ? N : 0)) * row_scales;
+    };
+    auto chunk_start = [&](int c) {      // first scale byte of chunk c within the row: a chunk never runs past the row
+        const uint32_t b = (uint32_t)c * 16;
+        return b + 16 <= row_scales ? b : row_scales - 16;
+    };
+    auto issue_scales = [&](int c) {
+        if (lane < 32) load_lds_16_base(s_base + chunk_start(c), s_off, lds0 + S_BASE + s_load + wave * 512);
+        s_load = s_load == 2 * S_SLOT ? 0u : s_load + S_SLOT;
+    };
+    // ---- LDS addresses of the operands this lane feeds to the MFMAs ----
+    typedef __attribute__((address_space(3))) const bf16x8_t lds_bf16x8_t;
+    typedef __attribute__((address_space(3))) const u32x4_t lds_u32x4_t;
+    typedef __attribute__((address_space(3))) const uint8_t lds_u8_t;
+    const int fr = lane & 31, fq = lane >> 5;
+    uint32_t k_lane[KS];                 // activation chunk of slice kk: k-values 32 fq + 8 kk .. + 7 of the stage
+#pragma unroll
+    for (int kk = 0; kk < KS; ++kk) k_lane[kk] = lds0 + fr * ROWB + (((fq * 4 + kk) ^ swz<PBK>(fr)) << 4);
+    const uint32_t w_lane = lds0 + B_BASE + fr * 64 + ((fq ^ ((fr >> 2) & 3)) << 4);    // the even stage's block; odd: ^ 32
+    const uint32_t s_lane = lds0 + S_BASE + fr * 16 + fq;
+    const uint32_t a_wave = wm * 32 * ROWB;
+    const uint32_t row_of[2] = {(uint32_t)(wn * WNO), (uint32_t)(GATED ? NO + wn * WNO : wn * WNO + 32)};   // first tile row of a fragment
+
+    // ---- first tile ----
+    BigTile cur = queue.take(at), nxt = cur;
+    uint32_t a_slot = 0, w_slot = 0, s_slot = 0;         // slots of the stage being multiplied
+    rows.look_up(cur);
+    use_weights(cur);
+    use_scales(cur);
+#pragma unroll 1
+    for (int i = 0; i < LEAD; ++i) issue_piece();
+    issue_scales(0);
+    wait_vmcnt<LEAD + 1>();                // the look-ups came first
+    rows.use(cur);
+    rows.issue(0, lds0);
+    wait_vmcnt<0>();
+    block_barrier();
+
+    auto run = [&](auto tmv_const) {
+        constexpr int TMV = decltype(tmv_const)::value;
+        constexpr int TMA = TMV > 0 ? TMV : 1;
+        float16_t acc[TMA][TN];
+#pragma unroll
+        for (int i = 0; i < TMA; ++i)
+#pragma unroll
+            for (int j = 0; j < TN; ++j)
+#pragma unroll
+                for (int v = 0; v < 16; ++v) acc[i][j][v] = 0.f;
+        bf16x8_t af[2][TMA], bfr[2][TN];
+        u32x4_t codes[TN];
+        uint32_t scale[TN];
+        auto read_rows = [&](uint32_t as, int kk, int set) {
+            if (TMV == 0) return;
+            const uint32_t av = k_lane[kk] + (as + a_wave);
+#pragma unroll
+            for (int i = 0; i < TMV; ++i) af[set][i] = *(lds_bf16x8_t*)(uintptr_t)(av + i * (WM * 32 * ROWB));
+        };
+        auto read_weights = [&](int stage) {     // a whole stage of this wave's weight rows
+            if (TMV == 0) return;
+            const uint32_t wv = (w_lane ^ ((stage & 1) * 32u)) + w_slot;
+            const uint32_t sv = s_lane + (s_slot + 2u * (uint32_t)stage - chunk_start(stage >> 3));
+#pragma unroll
+            for (int j = 0; j < TN; ++j) {
+                codes[j] = *(lds_u32x4_t*)(uintptr_t)(wv + row_of[j] * 64);
+                scale[j] = *(lds_u8_t*)(uintptr_t)(sv + row_of[j] * 16);
+            }
+        };
+        auto widen = [&](int kk, int set) {
+            if (TMV == 0) return;
+#pragma unroll
+            for (int j = 0; j < TN; ++j) bfr[set][j] = widen_fp4x8(codes[j][kk], e8m0_to_float(scale[j]));
+        };
+        auto mfma_set = [&](int set) {
+#pragma unroll
+            for (int i = 0; i < TMV; ++i)
+#pragma unroll
+                for (int j = 0; j < TN; ++j)
+                    acc[i][j] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(bfr[set][j], af[set][i], acc[i][j], 0, 0, 0);
+        };
+        // (as in ffn.hip: the LDS reads of a region one by one between its MFMAs)
+        auto interleave = [](int n_ds, int n_mfma) {
+#pragma unroll
+            for (int i = 0; i < 16; ++i) {
+                if (i < n_ds && i < n_mfma) {
+                    __builtin_amdgcn_sched_group_barrier(0x008, 1, 0);   // one MFMA
+                    __builtin_amdgcn_sched_group_barrier(0x100, 1, 0);   // one LDS read
+                }
+            }
+        };
+        // Step s but its last slice.  `loads`: load instructions this step issues (all of them younger than the next
+        // stage's activation loads, so that many may stay in flight).
+        auto step_head = [&](auto loads) {
+#pragma unroll
+            for (int kk = 0; kk < KS - 1; ++kk) {
+                read_rows(a_slot, kk + 1, (kk + 1) & 1);
+                mfma_set(kk & 1);
+                widen(kk + 1, (kk + 1) & 1);
+                interleave(TMV, TMV * TN);
+            }
+            if constexpr (std::is_same<decltype(loads), int>::value) {
+                if (loads == 1) wait_vmcnt<1>();
+                else wait_vmcnt<2>();
+            } else {
+                wait_vmcnt<decltype(loads)::value>();
+            }
+            wait_lds_reads();          // all of this wave's reads of the stage have returned before its slots are refilled
+            block_barrier();
+        };
+        // Behind the barrier: the last slice, under the reads of stage `next` (< 0: the tile ends here).
+        auto step_tail = [&](int stage, int next) {
+            a_slot ^= A_SLOT;
+            if ((stage & 1) != 0 || next < 0) w_slot = (w_slot + B_SLOT) & (3 * B_SLOT);
+            if ((stage & 7) == 7 || next < 0) s_slot = s_slot == 2 * S_SLOT ? 0u : s_slot + S_SLOT;
+            if (next >= 0) {
+                read_weights(next);
+                read_rows(a_slot, 0, 0);
+            }
+            mfma_set((KS - 1) & 1);
+            interleave(next >= 0 && TMV > 0 ? TMV + 2 * TN : 0, TMV * TN);
+            if (next >= 0) widen(0, 0);
+        };
+
+        read_weights(0);
+        read_rows(a_slot, 0, 0);
+        widen(0, 0);
+        for (int s = 0; s < nk - 3; ++s) {
+            if (np == 2 * nd) use_weights(nxt);
+            const bool more_scales = (s & 7) == 4 && s + 4 < nk;        // chunk s / 8 + 1 exists
+            if (more_scales) issue_scales((s >> 3) + 1);
+            issue_piece();
+            step_head(more_scales ? 2 : 1);
+            rows.issue(s + 2, lds0 + a_slot);
+            step_tail(s, s + 1);
+        }
+        // step nk - 3: look-ups and scales of the next tile
+        rows.look_up(nxt);
+        if (np == 2 * nd) use_weights(nxt);
+        use_scales(nxt);
+        issue_scales(0);
+        issue_piece();
+        step_head(std::integral_constant<int, 2>{});
+        rows.issue(nk - 1, lds0 + a_slot);
+        step_tail(nk - 3, nk - 2);
+        // step nk - 2
+        rows.use(nxt);
+        issue_piece();
+        step_head(std::integral_constant<int, 1>{});
+        rows.issue(0, lds0 + a_slot);
+        step_tail(nk - 2, nk - 1);
+        // step nk - 1
+        issue_piece();
+        step_head(std::integral_constant<int, 1>{});
+        const uint32_t epi_slot = a_slot;        // every wave has read the last stage: its activation slot is free
+        step_tail(nk - 1, -1);
+        big_epilogue<GATED, OUT_F32, false, TMV, TNO>(acc, cur, wm, cur.n_tile * NO + wn * WNO,
+                                                      smem + epi_slot + wave * (TNO * 2048), Out_, ldo, N);
+    };
+
+    for (;;) {
+        // (the last tile is followed by itself: its first stages are loaded once more and never used)
+        rows.issue(1, lds0 + (a_slot ^ A_SLOT));
+        at += stride;
+        const bool more = at < queue.end;
+        if (more) nxt = queue.take(at);
+        const int rb_valid = (cur.row_end - cur.row0 + 31) / 32;
+        const int tm_valid = (rb_valid - wm + WM - 1) / WM;      // row blocks wm, wm + WM, ... below rb_valid belong to this wave
+        if (tm_valid >= 4) run(std::integral_constant<int, 4>{});
+        else if (tm_valid >= 3) run(std::integral_constant<int, 3>{});
+        else if (tm_valid >= 2) run(std::integral_constant<int, 2>{});
+        else if (tm_valid >= 1) run(std::integral_constant<int, 1>{});
+        else run(std::integral_constant<int, 0>{});
+        if (!more) break;
+        cur = nxt;
+        if (odd) issue_piece();
+        wait_lds_reads();
+        block_barrier();       // every wave has read its piece of the epilogue's slot: the next activation loads may overwrite it
+    }
+    wait_vmcnt<0>();           // a block must not end with loads into LDS outstanding
+}
+
+// Which kernel shape a launch uses: the streaming shape up to 48 rows per expert on average.  Its 32-row tiles re-read
+// (from L2) and re-widen the weights once per 32 rows.  Layer, us, streaming against big tiles (32 experts, H = I =
+// 2880): 32 rows per expert 170 / 185, 41 rows 183 / 186, 50 rows 192 / 189, 64 rows 211 / 210, 77 rows 249 / 220.
+// The 64-row shape serves what the big tiles do not take (K < 512).
+enum W4Shape { W4_TILE64, W4_STREAM, W4_BIG };
+W4Shape w4_shape(int variant, int64_t A, int E, int K)
+{
+    W4Shape v = A <= (int64_t)48 * E ? W4_STREAM : W4_BIG;
+    if (variant == MOE_FFN_W4_TILE64) v = W4_TILE64;
+    if (variant == MOE_FFN_W4_STREAM) v = W4_STREAM;
+    if (variant == MOE_FFN_W4_BIG) v = W4_BIG;
+    if (v == W4_BIG && K < 512) v = W4_TILE64;      // 16 scale bytes per row, eight stages
+    return v;
+}
+
+template <bool GATED, bool OUT_F32, bool MAPPED>
+hipError_t launch_w4_big(RowSrc X, int ldx, const int32_t* row_map, int map_div, const int32_t* offsets, int E, int64_t A,
+                         const uint8_t* W, const uint8_t* S, int64_t rows_per_expert, int N, int K, void* Out, int ldo,
+                         hipStream_t s)
+{
+    auto kern = grouped_gemm_w4_big_kernel<GATED, OUT_F32, MAPPED>;
+    static bool attr_set[kMaxDevices] = {};
+    hipError_t e = ensure_lds_limit(kern, kW4BigLds, attr_set);
+    if (e != hipSuccess) return e;
+    int grid = 0;
+    e = big_grid(&grid);
+    if (e != hipSuccess) return e;
+    kern<<<(unsigned)grid, kBigWaves * 64, kW4BigLds, s>>>(X, ldx, row_map, map_div, map_magic_of(map_div), offsets, E, W, S,
+                                                           rows_per_expert, N, K, Out, ldo, (int)A);
+    return hipGetLastError();
 }
 
 template <bool GATED, bool OUT_F32>
@@ -784,9 +1090,18 @@ hipError_t launch_w4(int variant, RowSrc X, int ldx, const int32_t* row_map, int
                      int ldo, hipStream_t s)
 {
     constexpr int NO = GATED ? kW4BN / 2 : kW4BN;
+    if (!GATED && row_map != nullptr) return hipErrorInvalidValue;      // (only the gate_up GEMM is ever called with a row map)
     // the streaming kernel takes a row's address mod 128 for a multiple of 32 (the callers check it)
     if ((reinterpret_cast<uintptr_t>(W) & 31u) != 0) return hipErrorInvalidValue;
-    const bool stream = w4_use_stream(variant, A, E);
+    W4Shape shape = w4_shape(variant, A, E, K);
+    if (shape == W4_BIG && !big_list_fits(A, E, (N + (GATED ? kBigBN / 2 : kBigBN) - 1) / (GATED ? kBigBN / 2 : kBigBN)))
+        shape = W4_TILE64;
+    if (shape == W4_BIG) {
+        if (row_map)
+            return launch_w4_big<GATED, OUT_F32, GATED>(X, ldx, row_map, map_div, offsets, E, A, W, S, rows_per_expert, N, K, Out, ldo, s);
+        return launch_w4_big<GATED, OUT_F32, false>(X, ldx, row_map, map_div, offsets, E, A, W, S, rows_per_expert, N, K, Out, ldo, s);
+    }
+    const bool stream = shape == W4_STREAM;
     const int tile_rows = stream ? kS4Rows : kW4Rows;
     const size_t lds_bytes = stream ? (size_t)kS4NSA * kS4Rows * kW4K * 2 + (size_t)2 * kW4BN * 128
                                     : (size_t)kW4NSA * kW4Rows * kW4K * 2 + (size_t)kW4NSB * kW4BN * kW4K +
@@ -828,9 +1143,13 @@ hipError_t launch_ffn_down_w4(int variant, bool out_f32, const void* act, const 
                                    y_perm, H, s);
 }
 
-const char* ffn_w4_variant_name(int variant, int64_t A, int E)
+const char* ffn_w4_variant_name(int variant, int64_t A, int E, int H)
 {
-    return w4_use_stream(variant, A, E) ? "grouped_gemm_w4_stream_kernel<gated>" : "grouped_gemm_w4_kernel<gated>";
+    switch (w4_shape(variant, A, E, H)) {
+        case W4_STREAM: return "grouped_gemm_w4_stream_kernel<gated>";
+        case W4_BIG: return "grouped_gemm_w4_big_kernel<gated>";
+        default: return "grouped_gemm_w4_kernel<gated>";
+    }
 }
 
 }  // namespace moe

@@ -103,3 +103,53 @@ def test_big_tiles_with_gathered_rows(gpu_lib, T, E, K, fmt):
         ctx.moe_set_ffn_variant(v)
         out[v] = [y.clone() for y in ctx.moe_group_forward([L], xd, xp)]
     assert all(torch.equal(a, b) for a, b in zip(out["small"], out["big"]))
+
+
+# MXFP4, compute-bound shape: double stages of codes (rows of an odd or even number of stages), chunks of 8 stages of
+# scale bytes (the row's last chunk starts early), 256 x 256 tiles.  Checked against the 64-row shape bit for bit (it is
+# checked against the oracle elsewhere), and against the oracle once.
+@pytest.mark.parametrize("H,I,rows", [
+    (512, 512, [1]),                                        # the smallest K: eight stages, one chunk of scales
+    (576, 640, [33, 0, 255, 257, 96]),                      # 9 and 10 stages; ragged column tiles
+    (1024 + 64, 960, [300, 7, 128]),                        # 17 stages: the last scale chunk holds one stage
+    (2880, 576, [0] * 66 + [140, 3] + [0] * 3 + [511]),     # 45 stages, rows of 90 scale bytes
+    (512, 1536, [40 + 3 * i % 50 for i in range(90)]),      # several tiles per block
+])
+def test_w4_big_tiles(gpu_lib, H, I, rows):
+    E, A = len(rows), sum(rows)
+    w = inputs.Workload("w4big", H=H, E=E, K=1, I=I, n_layers=1, D=0, P=A, dtype="bf16", seed=41, weight_format="mxfp4")
+    L = {k: (v.to(DEV) if v is not None else None) for k, v in inputs.make_layer(w, 0).items()}
+    L["s_gate_up"][0, 0, 0] = 0                             # 2^-127: the one scale byte that is not an exponent field
+    x_perm = inputs.randn((A, H), 1.0, 41, "x_perm", 0, "bf16").to(DEV)
+    offsets = torch.tensor(np.concatenate([[0], np.cumsum(rows)]), dtype=torch.int32).to(DEV)
+    for f32 in (False, True):
+        ctx = gpu_lib.Context(H, E, 1, I, torch.bfloat16, max_tokens=A, device=DEV, weight_format="mxfp4", y_perm_f32=f32)
+        out = {}
+        for v in ("w4_tile64", "w4_big", "w4_big"):
+            ctx.moe_set_ffn_variant(v)
+            y = ctx.moe_grouped_ffn_mxfp4(x_perm, offsets, L["w_gate_up"], L["s_gate_up"], L["w_down"], L["s_down"])
+            assert torch.equal(out.setdefault("y", y), y), v
+    # rows through the permutation, from two buffers
+    T, K = 150, min(3, E)
+    ctx = gpu_lib.Context(H, E, K, I, torch.bfloat16, max_tokens=T, device=DEV, weight_format="mxfp4")
+    xd, xp = (inputs.randn((n, H), 1.0, 42, s, 0, "bf16").to(DEV) for n, s in ((50, "d"), (100, "p")))
+    ys = {}
+    for v in ("w4_tile64", "w4_big"):
+        ctx.moe_set_ffn_variant(v)
+        ys[v] = [y.clone() for y in ctx.moe_group_forward([L], xd, xp)]
+    assert all(torch.equal(a, b) for a, b in zip(ys["w4_tile64"], ys["w4_big"]))
+
+
+def test_w4_big_tiles_against_the_oracle(gpu_lib):
+    H, I, E, K, T = 640, 576, 4, 2, 300
+    w = inputs.Workload("w4o", H=H, E=E, K=K, I=I, n_layers=1, D=0, P=T, dtype="bf16", seed=43, residual=False,
+                        weight_format="mxfp4")
+    L = inputs.make_layer(w, 0)
+    _, x = inputs.make_hidden(w)
+    ctx = gpu_lib.Context(H, E, K, I, torch.bfloat16, max_tokens=T, residual=False, device=DEV, weight_format="mxfp4")
+    ctx.moe_set_ffn_variant("w4_big")
+    _, y = ctx.moe_group_forward([{k: (v.to(DEV) if v is not None else None) for k, v in L.items()}], None, x.to(DEV))
+    n = inputs.layer_to_numpy(L)
+    ref, _, _ = oracle.moe_layer(inputs.to_numpy(x), n["w_router"], None, n["w_gate_up"], n["w_down"], K, residual=False,
+                                 s_gate_up=n["s_gate_up"], s_down=n["s_down"])
+    assert_close(y, ref, "bf16", "w4 big tiles")
