@@ -173,7 +173,7 @@ __global__ __launch_bounds__(256) void grouped_gemm_bf16_kernel(
 // Weight-streaming shape (few rows per expert): global -> LDS copies issued as direct-to-LDS loads
 // (global_load_lds_dwordx4: no staging registers, no LDS store instructions) into two rings of NS LDS slots, one for
 // the activation rows and one for the weight rows, each stage PBK (64 or 32) k-values deep; one barrier per stage.
-// 64 x 128 tiles, 4 waves, 3 stages of 24 KB: two blocks share a compute unit.
+// 64 x 128 tiles, 4 waves, 3 stages of 24 KB: two blocks share a compute unit (launches of few tiles: see kFewTiles).
 // NW waves arranged WM x WN.
 // One wave-level load moves 64 lanes x 16 B = 8 (or 16) whole tile rows into 1 KB of LDS.  LDS rows
 // are unpadded (the hardware writes lanes contiguously), so bank conflicts on the 16-byte operand
@@ -210,13 +210,17 @@ __global__ __launch_bounds__(NW * 64, MINW) void grouped_gemm_bf16_pipe_kernel(
     constexpr int B_BASE = NS * A_SLOT;                 // the weight ring follows the activation ring
     static_assert(PBK == 64 || PBK == 32, "stage depth must be 64 or 32");
     static_assert(RBM % WM == 0 && TM <= 4 && TNO >= 1, "bad tile configuration");
-    static_assert(NS == 2 || NS == 3, "the prologue's loads are not in stage order: the wait counts hold for these rings");
+    static_assert(NS >= 2, "a stage is loaded while another is multiplied");
     static_assert(BM % (RPL * NW) == 0 && BN % (RPL * NW) == 0, "tile rows must split evenly over the waves");
     // In a step the loads of stage g+NS-1 are issued; loads return in issue order, so when stage g+1 is needed the
     // loads that may still be in flight are the ones issued after it.
     constexpr int WAIT_MAIN = (NS - 2) * LPS;
     constexpr int WAIT_FIRST = (NS - 2) * A_LPW;   // prologue: all weight stages, then the activation stages
-    static_assert(WAIT_MAIN < 64 && WAIT_FIRST < 64, "vmcnt is a 6-bit counter");
+    // The prologue's loads are not in stage order: while stage g + 1 is one of the prologue's, the loads issued after it
+    // are its later activation stages and the steps' own; the fewest, at g = 0, serve all of these steps.  (With up
+    // to three stages this is no fewer than WAIT_MAIN.)
+    constexpr int WAIT_EARLY = NS > 3 ? (NS - 3) * A_LPW + LPS : WAIT_MAIN;
+    static_assert(WAIT_MAIN + LPS < 64 && (NS - 1) * LPS + A_LPW < 64, "vmcnt is a 6-bit counter");
 
     extern __shared__ __attribute__((aligned(1024))) char smem[];
 
@@ -407,7 +411,8 @@ __global__ __launch_bounds__(NW * 64, MINW) void grouped_gemm_bf16_pipe_kernel(
             }
             if (MORE) issue_part(g + NS - 1, KS - 1);
             if (NEXT) {
-                if (MORE) wait_vmcnt<WAIT_MAIN>();
+                if (MORE && NS > 3 && g < NS - 2) wait_vmcnt<WAIT_EARLY>();
+                else if (MORE) wait_vmcnt<WAIT_MAIN>();
                 else wait_vmcnt<0>();        // the pipeline drains: wait for everything
                 // all of this wave's reads of stage g have returned before its slots may be refilled
                 wait_lds_reads();
@@ -957,15 +962,15 @@ static hipError_t launch_tile(RowSrc X, int ldx, const int32_t* row_map, int map
     return hipGetLastError();
 }
 
-template <bool GATED, bool OUT_F32, bool SPLIT, bool MAPPED>
-static hipError_t launch_pipe(RowSrc X, int ldx, const int32_t* row_map, int map_div, const int32_t* offsets,
-                              int E, int64_t A, const bf16_t* W, int64_t w_expert_stride, int N, int K, void* Out,
-                              int ldo, hipStream_t s)
+template <int BM, int BN, int WM, int NS, int MINW, int NW, bool GATED, bool OUT_F32, bool SPLIT, bool MAPPED>
+static hipError_t launch_pipe_shape(RowSrc X, int ldx, const int32_t* row_map, int map_div, const int32_t* offsets,
+                                    int E, int64_t A, const bf16_t* W, int64_t w_expert_stride, int N, int K, void* Out,
+                                    int ldo, hipStream_t s)
 {
-    constexpr int BM = 64, BN = 128, NS = 3, PBK = 64, NW = 4;
+    constexpr int PBK = 64;
     constexpr int NO = GATED ? BN / 2 : BN;
     const size_t lds_bytes = (size_t)NS * (BM + BN) * PBK * 2;
-    auto kern = grouped_gemm_bf16_pipe_kernel<BM / 32, BN, 2, NS, PBK, 2, NW, GATED, OUT_F32, SPLIT, MAPPED>;
+    auto kern = grouped_gemm_bf16_pipe_kernel<BM / 32, BN, WM, NS, PBK, MINW, NW, GATED, OUT_F32, SPLIT, MAPPED>;
     static bool attr_set[kMaxDevices] = {};
     hipError_t e = ensure_lds_limit(kern, lds_bytes, attr_set);
     if (e != hipSuccess) return e;
@@ -976,6 +981,29 @@ static hipError_t launch_pipe(RowSrc X, int ldx, const int32_t* row_map, int map
     kern<<<(unsigned)grid, NW * 64, lds_bytes, s>>>(X, ldx, row_map, map_div, offsets, E, W, w_expert_stride, N, K, Out,
                                                 ldo, (int)A);
     return hipGetLastError();
+}
+
+// Up to this many 64 x 128 tiles (an upper bound; one per compute unit) the launch takes narrow tiles: 32 x 64, one wave,
+// five stages of 12 KB.  What bounds such a launch is how much it has in flight: 96 tiles for one token at 8 of 128
+// experts (H = 2048, I = 768) with two stages of weights each, 16 KB, ask for 2.6 TB/s; 192 narrow ones keep four
+// stages of 8 KB.  gate_up 19.1 -> 15.4 us, down 10.1 -> 9.3.  Above one tile per unit twice as many blocks, and every
+// activation row read twice, cost more than they bring.  Layer of that shape, us, 64 x 128 against narrow tiles: 1 token
+// (108 and 144 tiles) 49.9 / 41.9, 2 tokens (204 and 272) 57.1 / 53.8, 3 tokens (300 and 400) 73.2 / 75.7, 4 tokens (396 and
+// 528) 82.2 / 85.6; 32 experts, top-4, H = I = 2880: 1 token (225 and 115) 70.3 / 63.8, 2 tokens (405 and 207) 96.0 / 99.6.
+constexpr int64_t kFewTiles = 256;
+
+template <bool GATED, bool OUT_F32, bool SPLIT, bool MAPPED>
+static hipError_t launch_pipe(RowSrc X, int ldx, const int32_t* row_map, int map_div, const int32_t* offsets,
+                              int E, int64_t A, const bf16_t* W, int64_t w_expert_stride, int N, int K, void* Out,
+                              int ldo, hipStream_t s)
+{
+    constexpr int NO = GATED ? 64 : 128;
+    const int64_t tiles = ((A + 63) / 64 + (A < E ? A : E)) * ((N + NO - 1) / NO);
+    if (tiles <= kFewTiles)
+        return launch_pipe_shape<32, 64, 1, 5, 1, 1, GATED, OUT_F32, SPLIT, MAPPED>(X, ldx, row_map, map_div, offsets, E, A,
+                                                                                  W, w_expert_stride, N, K, Out, ldo, s);
+    return launch_pipe_shape<64, 128, 2, 3, 2, 4, GATED, OUT_F32, SPLIT, MAPPED>(X, ldx, row_map, map_div, offsets, E, A, W,
+                                                                                w_expert_stride, N, K, Out, ldo, s);
 }
 
 template <bool GATED, bool OUT_F32, bool SPLIT, bool MAPPED>

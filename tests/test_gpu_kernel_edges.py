@@ -64,6 +64,35 @@ def test_one_launch_routing_equals_the_steps(gpu_lib, T, E, K):
         assert ctx.moe_read_counters().active_experts_total == 2 * int((counts > 0).sum())
 
 
+# The narrow streaming shape (32 x 64 tiles, one wave, a ring of five stages), taken when the launch has few tiles: k-extents
+# around the length of the ring, row and column edges, a plain and a split intermediate.  Against the register-staged
+# kernel bit for bit (the order of a sum is the same in every shape) and against the oracle.
+@pytest.mark.parametrize("H,I,rows", [
+    (64, 128, [1]),                        # one and two stages
+    (192, 256, [31, 32, 33]),              # three and four stages (the ring's look-ahead)
+    (320, 384, [0, 5, 0, 64, 65]),         # five and six
+    (448, 72 * 8, [1, 0, 2]),              # seven and nine
+    (1280, 64, [3] * 9),                   # 20 stages and one
+])
+def test_few_tiles_grouped_ffn(gpu_lib, H, I, rows):
+    E, A = len(rows), sum(rows)
+    w = inputs.Workload("few", H=H, E=E, K=1, I=I, n_layers=1, D=0, P=A, dtype="bf16", seed=51)
+    L = inputs.make_layer(w, 0)
+    x_perm = inputs.randn((A, H), 1.0, 51, "x_perm", 0, "bf16")
+    offsets = torch.tensor(np.concatenate([[0], np.cumsum(rows)]), dtype=torch.int32)
+    args = (x_perm.to(DEV), offsets.to(DEV), L["w_gate_up"].to(DEV), L["w_down"].to(DEV))
+    for fmt in ({}, {"y_perm_f32": True}, {"y_perm_f32": True, "act_split": True}):
+        ctx = gpu_lib.Context(H, E, 1, I, torch.bfloat16, max_tokens=A, device=DEV, **fmt)
+        ctx.moe_set_ffn_variant("tile128")
+        ref = ctx.moe_grouped_ffn(*args)
+        ctx.moe_set_ffn_variant("small")
+        for _ in range(2):
+            assert torch.equal(ctx.moe_grouped_ffn(*args), ref), fmt
+    ctx = gpu_lib.Context(H, E, 1, I, torch.bfloat16, max_tokens=A, device=DEV)
+    ctx.moe_set_ffn_variant("small")
+    assert_close(ctx.moe_grouped_ffn(*args), dense_ffn(x_perm, offsets, L, "bf16", E), "bf16", "few tiles")
+
+
 # The persistent 256 x 256 kernel: tiles of 128 to 256 rows cut from experts of any size, at least four k-stages, next
 # tile's loads issued during the current one.  Checked against the oracle and, bit for bit, against the streaming shape.
 @pytest.mark.parametrize("H,I,rows", [
