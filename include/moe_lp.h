@@ -116,7 +116,8 @@ moe_status moe_workspace_bytes(const moe_config *cfg, int64_t max_tokens, size_t
 
 /* Create a context over a caller-owned device workspace (256-byte aligned, at least
  * moe_workspace_bytes; it must stay alive and untouched until moe_destroy).  The
- * workspace's counter block is cleared on `stream`. */
+ * moe_counters kept on the device are cleared on `stream`; nothing else in the workspace
+ * needs that, so passes on other streams give their results whether or not it has run. */
 moe_status moe_create(const moe_config *cfg, int64_t max_tokens, void *workspace, size_t workspace_bytes,
                       void *stream, moe_ctx **out_ctx);
 moe_status moe_destroy(moe_ctx *ctx);

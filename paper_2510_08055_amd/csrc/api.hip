@@ -16,7 +16,8 @@ struct moe_ctx {
     int esz;  // bytes per element
     // workspace slices (device)
     unsigned long long* d_active_total;
-    uint32_t* d_tickets;     // of the one-launch routing of small batches: zero between launches
+    uint32_t* d_tickets;     // of the one-launch routing of small batches: zero between launches, once cleared
+    bool tickets_clear;      // a pass of this context has cleared them (see clear_tickets)
     double* logits;
     int32_t *idx, *counts, *offsets, *perm, *inv, *tile_hist;
     float* w;
@@ -133,6 +134,24 @@ inline bool misaligned(const void* p) { return (reinterpret_cast<uintptr_t>(p) &
 // the packed codes of MXFP4 weights: rows must start a multiple of 32 bytes into a 128-byte line
 inline bool misaligned32(const void* p) { return (reinterpret_cast<uintptr_t>(p) & 31u) != 0; }
 inline moe_status dev(hipError_t e) { return e == hipSuccess ? MOE_OK : MOE_ERR_DEVICE; }
+
+// The tickets of the one-launch routing have to be zero when its first launch starts.  The first pass of a context clears
+// them, on its own stream: the clear is then ordered in front of the routing whatever stream the context was made on (and
+// whether or not moe_create's own work has run).  Later passes find them as the launch before left them, at zero.
+// A pass that is being captured runs only when its graph is replayed, so it carries the clear along and the next pass
+// clears again.
+hipError_t clear_tickets(moe_ctx* c, hipStream_t s)
+{
+    if (c->tickets_clear) return hipSuccess;
+    hipStreamCaptureStatus capture = hipStreamCaptureStatusNone;
+    if (hipStreamIsCapturing(s, &capture) != hipSuccess) {
+        (void)hipGetLastError();        // (the legacy stream while another one is captured)
+        capture = hipStreamCaptureStatusActive;
+    }
+    const hipError_t e = launch_fill_zero(c->d_tickets, kSmallTickets, s);
+    if (e == hipSuccess && capture == hipStreamCaptureStatusNone) c->tickets_clear = true;
+    return e;
+}
 
 // One layer on the batch `x` [T,H]; output rows [0,rows0) -> y0, the rest -> y1.
 moe_status run_layer(moe_ctx* c, const moe_layer& L, RowSrc x, int64_t T, void* y0, int64_t rows0, void* y1,
@@ -277,6 +296,7 @@ moe_status moe_create(const moe_config* cfg, int64_t max_tokens, void* workspace
     c->d_active_total = reinterpret_cast<unsigned long long*>(b + L.counters);
     static_assert(128 + kSmallTickets * sizeof(uint32_t) <= 256, "the counter block");
     c->d_tickets = reinterpret_cast<uint32_t*>(b + L.counters + 128);
+    c->tickets_clear = false;
     c->logits = reinterpret_cast<double*>(b + L.logits);
     c->idx = reinterpret_cast<int32_t*>(b + L.idx);
     c->w = reinterpret_cast<float*>(b + L.w);
@@ -293,7 +313,8 @@ moe_status moe_create(const moe_config* cfg, int64_t max_tokens, void* workspace
     c->iterations = c->layer_passes = 0;
     c->timing_mask = 0;
     c->ffn_variant = MOE_FFN_AUTO;
-    if (hipMemsetAsync(b + L.counters, 0, 256, static_cast<hipStream_t>(stream)) != hipSuccess) {
+    // the counters only: the tickets behind them belong to the first pass, which may already run on another stream
+    if (hipMemsetAsync(b + L.counters, 0, 128, static_cast<hipStream_t>(stream)) != hipSuccess) {
         delete c;
         return MOE_ERR_DEVICE;
     }
@@ -483,6 +504,7 @@ moe_status moe_stack_forward(moe_ctx* ctx, const moe_layer* layers, int32_t n_la
     if (D + (P < step ? P : step) > ctx->max_tokens) return MOE_ERR_SHAPE;
 
     hipStream_t s = static_cast<hipStream_t>(stream);
+    if (clear_tickets(ctx, s) != hipSuccess) return MOE_ERR_DEVICE;
     const size_t row_bytes = (size_t)ctx->cfg.H * ctx->esz;
     std::vector<int32_t> first((size_t)n_layers + 1);
     for (int64_t sl = 0; sl < n_slices; ++sl) {

@@ -1,5 +1,7 @@
 """The drivers enqueue kernels only (no allocation, no memset, no host synchronisation), so a caller may
 capture them in a HIP graph: every replay must reproduce the eager result for the inputs then in place."""
+import ctypes
+
 import pytest
 import torch
 
@@ -55,3 +57,64 @@ def test_replays_match_eager(gpu_lib, w, kind):
         graph.replay()
         torch.cuda.synchronize()
         assert torch.equal(yd, ed) and torch.equal(yp, ep), f"replay {rep}"
+
+
+# A batch small enough for the one-launch routing, whose ticket counters live in the workspace.
+SMALL = inputs.Workload("first_pass", H=256, E=16, K=4, I=192, n_layers=2, D=40, P=0, dtype="bf16", seed=74)
+
+
+def small_case(gpu_lib):
+    layers = [{k: (v.to(DEV) if v is not None else None) for k, v in inputs.make_layer(SMALL, l).items()}
+              for l in range(SMALL.n_layers)]
+    xd = inputs.make_hidden(SMALL)[0].to(DEV)
+    ref = gpu_lib.Context(SMALL.H, SMALL.E, SMALL.K, SMALL.I, torch.bfloat16, max_tokens=SMALL.D, device=DEV)
+    want = ref.moe_group_forward(layers, xd, None)[0].clone()
+    torch.cuda.synchronize()
+    return layers, xd, want
+
+
+def test_first_pass_does_not_wait_for_the_context_s_stream(gpu_lib):
+    """The context is made on a stream that is still busy, over a workspace of arbitrary bytes; a pass on another stream
+    gives its result at once, and so does one behind the creation's own work."""
+    layers, xd, want = small_case(gpu_lib)
+    ctx = gpu_lib.Context(SMALL.H, SMALL.E, SMALL.K, SMALL.I, torch.bfloat16, max_tokens=SMALL.D, device=DEV)
+    out = [torch.empty_like(xd) for _ in range(3)]
+    busy, other = torch.cuda.Stream(), torch.cuda.Stream()
+    base = (ctx.workspace.data_ptr() + 255) // 256 * 256
+    ctx.workspace.fill_(0xA5)
+    torch.cuda.synchronize()
+    with torch.cuda.stream(busy):
+        torch.cuda._sleep(50_000_000)           # tens of milliseconds
+        ctx.close()
+        assert ctx.lib.moe_create(ctypes.byref(ctx.cfg), SMALL.D, ctypes.c_void_p(base), ctx.workspace.numel() - 256,
+                                  ctypes.c_void_p(busy.cuda_stream), ctypes.byref(ctx._ctx)) == 0
+    with torch.cuda.stream(other):
+        ctx.moe_group_forward(layers, xd, None, y_decode=out[0])
+        ctx.moe_group_forward(layers, xd, None, y_decode=out[1])
+        other.synchronize()
+    assert not busy.query()                     # the creation's work has not run yet
+    assert torch.equal(out[0], want) and torch.equal(out[1], want)
+    busy.synchronize()
+    ctx.moe_group_forward(layers, xd, None, y_decode=out[2])
+    assert torch.equal(out[2], want)
+
+
+def test_first_pass_under_capture(gpu_lib):
+    """The first pass of a context is captured: eager passes in front of the first replay, and every replay, are right."""
+    layers, xd, want = small_case(gpu_lib)
+    ctx = gpu_lib.Context(SMALL.H, SMALL.E, SMALL.K, SMALL.I, torch.bfloat16, max_tokens=SMALL.D, device=DEV)
+    ctx.workspace.fill_(0xA5)                   # (behind the creation, in front of every pass)
+    packed = ctx.pack_layers(layers)
+    y, eager = torch.empty_like(xd), torch.empty_like(xd)
+    torch.cuda.synchronize()
+    graph = torch.cuda.CUDAGraph()
+    with torch.cuda.graph(graph):
+        ctx.moe_group_forward(layers, xd, None, packed=packed, y_decode=y)
+    for _ in range(3):
+        ctx.moe_group_forward(layers, xd, None, packed=packed, y_decode=eager)
+        torch.cuda.synchronize()
+        assert torch.equal(eager, want)
+        y.zero_()
+        graph.replay()
+        torch.cuda.synchronize()
+        assert torch.equal(y, want)
