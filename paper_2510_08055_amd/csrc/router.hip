@@ -449,9 +449,11 @@ __global__ __launch_bounds__(kTopkWaves * 64) void topk_rows_kernel(const double
 // E = 128 took 8.1 + 5.0 + 8.9 us, of which the arithmetic is a microsecond.  Here every block computes its
 // tile of logits and takes a ticket of its 16 tokens; the block that draws the last one finds their logits
 // written and does their top-k; of those blocks, the one that draws the last ticket of the batch does the
-// permutation (no block ever waits for another).  A token's experts are distinct, so the stable rank of an
-// assignment inside its expert is the number of earlier tokens that chose the expert: one bit per token and
-// expert in LDS, counted with popcounts.  What crosses between blocks goes past the XCD's caches by itself
+// permutation (no block ever waits for another).  A token's experts are distinct as long as K of its logits are finite;
+// the stable rank of an assignment inside its expert is then the number of earlier tokens that chose the expert: one
+// bit per token and expert in LDS, counted with popcounts.  A bit that is set twice (a removed expert and one with a
+// logit of -infinity compare equal, NaN compares with nothing) sends the batch to a count of the earlier assignments
+// one by one.  What crosses between blocks goes past the XCD's caches by itself
 // (store_shared / load_shared): a fence would write back and drop the whole L2, 2 us with a few blocks and 15 us
 // with a hundred.  Every last drawer puts its counter back to zero.
 // Measured (H = 2048, E = 128, top-8; events around the launches, three launches -> one): 1 token 28.9 -> 15.4 us,
@@ -485,12 +487,15 @@ __global__ __launch_bounds__(kSmallWaves * 64) void route_small_kernel(
     __shared__ unsigned long long chosen[kSmallExperts][kSmallWords];      // bit t of an expert: token t chose it
     __shared__ int32_t count[kSmallExperts], start[kSmallExperts];
     __shared__ int32_t own[16 * 16];                                       // the experts of this block's 16 tokens
-    __shared__ int32_t flag;
+    __shared__ uint8_t expert_of[kSmallTokens * 16];                       // only when a token chose an expert twice
+    __shared__ int32_t flag, twice;
+    static_assert(kSmallExperts <= 256, "an expert is one byte of expert_of");
     const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
     const int t0 = (int)blockIdx.x * 16;
     logits_tile<T, kSmallWaves, true>(x, n_tok, H, wr, bias, E, logits, t0, (int)blockIdx.y * 16);
     for (int i = tid; i < E * kSmallWords; i += kSmallWaves * 64) (&chosen[0][0])[i] = 0ull;
     if (tid < E) count[tid] = 0;
+    if (tid == 0) twice = 0;
     if (!last_to_arrive(tickets + 1 + blockIdx.x, gridDim.y, &flag)) return;
 
     // top-k of this block's 16 tokens: 16 lanes per token, four waves
@@ -524,7 +529,8 @@ __global__ __launch_bounds__(kSmallWaves * 64) void route_small_kernel(
         const int f = p * kSmallWaves * 64 + tid;
         if (my_e[p] >= 0) {
             const int t = f / K;
-            atomicOr(&chosen[my_e[p]][t >> 6], 1ull << (t & 63));
+            const unsigned long long bit = 1ull << (t & 63);
+            if (atomicOr(&chosen[my_e[p]][t >> 6], bit) & bit) twice = 1;
             atomicAdd(&count[my_e[p]], 1);
         }
     }
@@ -562,6 +568,21 @@ __global__ __launch_bounds__(kSmallWaves * 64) void route_small_kernel(
         if (lane == 0) atomicAdd(active_total, (unsigned long long)act);
     }
     __syncthreads();
+    if (twice) {
+#pragma unroll
+        for (int p = 0; p < PER; ++p)
+            if (my_e[p] >= 0) expert_of[p * kSmallWaves * 64 + tid] = (uint8_t)my_e[p];
+        __syncthreads();
+#pragma unroll 1
+        for (int f = tid; f < A; f += kSmallWaves * 64) {
+            const int e = expert_of[f];
+            int pos = start[e];
+            for (int g = 0; g < f; ++g) pos += expert_of[g] == e;
+            perm[pos] = f;
+            inv[f] = pos;
+        }
+        return;
+    }
 #pragma unroll
     for (int p = 0; p < PER; ++p) {
         const int f = p * kSmallWaves * 64 + tid;

@@ -64,6 +64,41 @@ def test_one_launch_routing_equals_the_steps(gpu_lib, T, E, K):
         assert ctx.moe_read_counters().active_experts_total == 2 * int((counts > 0).sum())
 
 
+# Fewer than K finite logits: a removed expert and one at -infinity compare equal, so a token may list an expert twice (the
+# second time with weight 0); NaN compares with nothing.  The permutation stays one, on either routing path.
+@pytest.mark.parametrize("E,K,T", [(8, 3, 5), (40, 16, 16), (128, 8, 70), (256, 5, 256), (257, 3, 256), (128, 8, 300)])
+@pytest.mark.parametrize("kind", ["bias", "nan"])
+def test_routing_of_logits_that_are_not_finite(gpu_lib, E, K, T, kind):
+    H, I = 72, 64
+    w = inputs.Workload("odd", H=H, E=E, K=K, I=I, n_layers=1, D=T, P=0, dtype="bf16", seed=T + E)
+    L = {k: (v.to(DEV) if v is not None else None) for k, v in inputs.make_layer(w, 0).items()}
+    x = inputs.randn((T, H), 1.0, w.seed, "x", 0, "bf16").to(DEV)
+    if kind == "bias":
+        L["router_bias"] = torch.full((E,), float("-inf"), device=DEV)
+        L["router_bias"][[1, E - 1]] = 0.25                     # two experts are left
+    else:
+        x[::3, 5] = float("nan")
+        x[1::3] = x[1::3].abs()                                 # and rows whose logit of expert 2 is infinite
+        L["w_router"][2] = float("inf")
+    ctx = gpu_lib.Context(H, E, K, I, torch.bfloat16, max_tokens=T, residual=False, device=DEV)
+    idx, wt = ctx.moe_router_topk(x, L["w_router"], L["router_bias"])
+    assert int(idx.min()) >= 0 and int(idx.max()) < E
+    counts, offsets, perm, inv, x_perm = ctx.moe_permute(x, idx)
+    y_steps = ctx.moe_combine(ctx.moe_grouped_ffn(x_perm, offsets, L["w_gate_up"], L["w_down"]), inv, wt)
+    fresh = gpu_lib.Context(H, E, K, I, torch.bfloat16, max_tokens=T, residual=False, device=DEV)
+    fresh.workspace[256:].fill_(0xA5)                           # behind the counters: whatever a pass does not write shows
+    y, _ = fresh.moe_group_forward([L], x, None)
+    assert torch.equal(y.view(torch.int16), y_steps.view(torch.int16))
+    # the permutation the pass used, in the context's workspace (slices of whole 256 bytes: counters, logits, indices,
+    # weights, counts, offsets, perm, inverse)
+    at = (fresh.workspace.data_ptr() + 255) // 256 * 256 - fresh.workspace.data_ptr() + 256
+    sizes = [T * E * 8, T * K * 4, T * K * 4, E * 4, (E + 1) * 4]
+    at += sum((n + 255) // 256 * 256 for n in sizes)
+    got = fresh.workspace[at:at + T * K * 4].view(torch.int32)
+    assert torch.equal(got, perm)
+    assert torch.equal(torch.sort(perm).values, torch.arange(T * K, dtype=torch.int32, device=DEV))
+
+
 # The narrow streaming shape (32 x 64 tiles, one wave, a ring of five stages), taken when the launch has few tiles: k-extents
 # around the length of the ring, row and column edges, a plain and a split intermediate.  Against the register-staged
 # kernel bit for bit (the order of a sum is the same in every shape) and against the oracle.
