@@ -278,20 +278,21 @@ const char *moe_ffn_variant(const moe_ctx *ctx, int64_t T);
 
 /*
  * Test and tuning aid (not part of the method): the grouped GEMMs come in several kernel shapes, all of
- * which compute the same bits for any batch; the library picks one from the mean rows per expert of a
- * launch.  moe_set_ffn_variant pins the shape for every later launch on this context (MOE_FFN_AUTO
+ * which compute the same bits for any batch; the library picks one from the mean rows per expert and the
+ * number of tiles of a launch.  moe_set_ffn_variant pins the shape for every later launch on this context (MOE_FFN_AUTO
  * restores the rule), so that tests can run every shape on every case.  A shape that cannot run the
- * context's weight format or a launch's K (the pipelined bf16 shapes need K % 64 == 0) is ignored for
- * that launch.  MOE_ERR_SHAPE for an unknown id.
+ * context's weight format or a launch's K (its weight rows' length; the pipelined bf16 shapes need
+ * K % 64 == 0) is ignored for that launch.  MOE_ERR_SHAPE for an unknown id.
  */
 typedef enum {
     MOE_FFN_AUTO = 0,
     MOE_FFN_TILE128 = 1,    /* bf16: 128 x 128 register-staged tiles (any K) */
     MOE_FFN_PIPE_SMALL = 2, /* bf16: 64 x 128 tiles, weight streaming */
-    MOE_FFN_PIPE_BIG = 3,   /* bf16: up to 256 x 256 tiles, compute bound */
+    MOE_FFN_PIPE_BIG = 3,   /* bf16: up to 256 x 256 tiles, compute bound (K >= 256) */
     MOE_FFN_W4_TILE64 = 4,  /* MXFP4: 64-row tiles */
     MOE_FFN_W4_STREAM = 5,  /* MXFP4: 32-row weight-streaming tiles */
-    MOE_FFN_W4_BIG = 6      /* MXFP4: up to 256 x 256 tiles, compute bound (K >= 512) */
+    MOE_FFN_W4_BIG = 6,     /* MXFP4: up to 256 x 256 tiles, compute bound (K >= 512) */
+    MOE_FFN_PIPE_FEW = 7    /* bf16: 32 x 64 tiles, weight streaming with few tiles */
 } moe_ffn_variant_id;
 moe_status moe_set_ffn_variant(moe_ctx *ctx, int32_t variant);
 

@@ -602,7 +602,7 @@ const char* moe_ffn_variant(const moe_ctx* ctx, int64_t T)
 moe_status moe_set_ffn_variant(moe_ctx* ctx, int32_t variant)
 {
     if (!ctx) return MOE_ERR_NULL;
-    if (variant < MOE_FFN_AUTO || variant > MOE_FFN_W4_BIG) return MOE_ERR_SHAPE;
+    if (variant < MOE_FFN_AUTO || variant > MOE_FFN_PIPE_FEW) return MOE_ERR_SHAPE;
     ctx->ffn_variant = variant;
     return MOE_OK;
 }

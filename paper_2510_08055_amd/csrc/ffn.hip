@@ -173,7 +173,7 @@ __global__ __launch_bounds__(256) void grouped_gemm_bf16_kernel(
 // Weight-streaming shape (few rows per expert): global -> LDS copies issued as direct-to-LDS loads
 // (global_load_lds_dwordx4: no staging registers, no LDS store instructions) into two rings of NS LDS slots, one for
 // the activation rows and one for the weight rows, each stage PBK (64 or 32) k-values deep; one barrier per stage.
-// 64 x 128 tiles, 4 waves, 3 stages of 24 KB: two blocks share a compute unit (launches of few tiles: see kFewTiles).
+// 64 x 128 tiles, 4 waves, 3 stages of 24 KB: two blocks share a compute unit (launches of few tiles take 32 x 64, see pick_variant).
 // NW waves arranged WM x WN.
 // One wave-level load moves 64 lanes x 16 B = 8 (or 16) whole tile rows into 1 KB of LDS.  LDS rows
 // are unpadded (the hardware writes lanes contiguously), so bank conflicts on the 16-byte operand
@@ -924,22 +924,39 @@ static hipError_t launch_f32(RowSrc X, int ldx, const int32_t* row_map, int map_
 // the device), so the variant is chosen from the mean rows per expert A/E; every variant is correct
 // for any distribution of rows.
 // ----------------------------------------------------------------------------------------------
-enum Variant { V_TILE128 = 0, V_PIPE_SMALL, V_PIPE_BIG };
+enum Variant { V_TILE128 = 0, V_PIPE_SMALL, V_PIPE_FEW, V_PIPE_BIG };
 
-static Variant pick_variant(int variant, int64_t A, int E, int K)
+// The shape of a launch: the one `pinned` names if it can run, else the library's rule.  K: length of a weight row.
+static hipError_t pick_variant(int pinned, bool gated, int64_t A, int E, int N, int K, Variant* v)
 {
-    Variant v;
+    *v = V_TILE128;
+    if (K % 64 != 0 || pinned == MOE_FFN_TILE128) return hipSuccess;      // the pipelined kernels have no k-tail path
+    *v = V_PIPE_SMALL;
+    if (pinned == MOE_FFN_PIPE_SMALL) return hipSuccess;
+    *v = V_PIPE_FEW;
+    if (pinned == MOE_FFN_PIPE_FEW) return hipSuccess;
+    // (the persistent kernel's pipeline is at least four stages long, and its tile list has a limit)
+    const int big_cols = gated ? kBigBN / 2 : kBigBN;
+    const bool big_runs = K >= 256 && big_list_fits(A, E, (N + big_cols - 1) / big_cols);
+    *v = V_PIPE_BIG;
+    if (pinned == MOE_FFN_PIPE_BIG && big_runs) return hipSuccess;
     // Weight streaming with 64 x 128 tiles up to 56 rows per expert on average.  Layer, us, streaming against big tiles:
     // 128 experts, H = 2048, I = 768: 47 rows 277 / 280, 56 rows 299 / 299, 64 rows 320 / 304; 32 experts, H = I = 2880:
     // 32 rows 318 / 316, 50 rows 339 / 336, 64 rows 385 / 344.
-    if (A <= (int64_t)56 * E) v = V_PIPE_SMALL;
-    else v = V_PIPE_BIG;                       // up to 256 x 256 tiles, persistent blocks
-    if (variant == MOE_FFN_TILE128) v = V_TILE128;
-    if (variant == MOE_FFN_PIPE_SMALL) v = V_PIPE_SMALL;
-    if (variant == MOE_FFN_PIPE_BIG) v = V_PIPE_BIG;
-    if (v == V_PIPE_BIG && K < 256) v = V_PIPE_SMALL;   // the persistent kernel's pipeline is at least four stages long
-    if (K % 64 != 0) v = V_TILE128;            // the pipelined kernels have no k-tail path
-    return v;
+    if (A > (int64_t)56 * E && big_runs) return hipSuccess;
+    // Up to one 64 x 128 tile per compute unit (an upper bound of their number) the launch takes narrow tiles: 32 x 64, one
+    // wave, five stages of 12 KB.  What bounds such a launch is how much it has in flight: 96 tiles for one token at 8 of
+    // 128 experts (H = 2048, I = 768) with two stages of weights each, 16 KB, ask for 2.6 TB/s; 192 narrow ones keep four
+    // stages of 8 KB.  gate_up 19.1 -> 15.4 us, down 10.1 -> 9.3.  Above one tile per unit twice as many blocks, and every
+    // activation row read twice, cost more than they bring.  Layer of that shape, us, 64 x 128 against narrow tiles: 1 token
+    // (108 and 144 tiles) 49.9 / 41.9, 2 tokens (204 and 272) 57.1 / 53.8, 3 tokens (300 and 400) 73.2 / 75.7, 4 tokens (396
+    // and 528) 82.2 / 85.6; 32 experts, top-4, H = I = 2880: 1 token (225 and 115) 70.3 / 63.8, 2 tokens (405 and 207) 96.0 /
+    // 99.6.
+    int cus = 0;
+    const hipError_t e = compute_units(&cus);
+    const int cols = gated ? 64 : 128;
+    *v = ((A + 63) / 64 + (A < E ? A : E)) * ((N + cols - 1) / cols) <= cus ? V_PIPE_FEW : V_PIPE_SMALL;
+    return e;
 }
 
 template <int BM, int BN, bool GATED, typename OT, bool SPLIT>
@@ -963,7 +980,7 @@ static hipError_t launch_tile(RowSrc X, int ldx, const int32_t* row_map, int map
 }
 
 template <int BM, int BN, int WM, int NS, int MINW, int NW, bool GATED, bool OUT_F32, bool SPLIT, bool MAPPED>
-static hipError_t launch_pipe_shape(RowSrc X, int ldx, const int32_t* row_map, int map_div, const int32_t* offsets,
+static hipError_t launch_pipe(RowSrc X, int ldx, const int32_t* row_map, int map_div, const int32_t* offsets,
                                     int E, int64_t A, const bf16_t* W, int64_t w_expert_stride, int N, int K, void* Out,
                                     int ldo, hipStream_t s)
 {
@@ -983,43 +1000,16 @@ static hipError_t launch_pipe_shape(RowSrc X, int ldx, const int32_t* row_map, i
     return hipGetLastError();
 }
 
-// Up to this many 64 x 128 tiles (an upper bound; one per compute unit) the launch takes narrow tiles: 32 x 64, one wave,
-// five stages of 12 KB.  What bounds such a launch is how much it has in flight: 96 tiles for one token at 8 of 128
-// experts (H = 2048, I = 768) with two stages of weights each, 16 KB, ask for 2.6 TB/s; 192 narrow ones keep four
-// stages of 8 KB.  gate_up 19.1 -> 15.4 us, down 10.1 -> 9.3.  Above one tile per unit twice as many blocks, and every
-// activation row read twice, cost more than they bring.  Layer of that shape, us, 64 x 128 against narrow tiles: 1 token
-// (108 and 144 tiles) 49.9 / 41.9, 2 tokens (204 and 272) 57.1 / 53.8, 3 tokens (300 and 400) 73.2 / 75.7, 4 tokens (396 and
-// 528) 82.2 / 85.6; 32 experts, top-4, H = I = 2880: 1 token (225 and 115) 70.3 / 63.8, 2 tokens (405 and 207) 96.0 / 99.6.
-constexpr int64_t kFewTiles = 256;
-
-template <bool GATED, bool OUT_F32, bool SPLIT, bool MAPPED>
-static hipError_t launch_pipe(RowSrc X, int ldx, const int32_t* row_map, int map_div, const int32_t* offsets,
-                              int E, int64_t A, const bf16_t* W, int64_t w_expert_stride, int N, int K, void* Out,
-                              int ldo, hipStream_t s)
-{
-    constexpr int NO = GATED ? 64 : 128;
-    const int64_t tiles = ((A + 63) / 64 + (A < E ? A : E)) * ((N + NO - 1) / NO);
-    if (tiles <= kFewTiles)
-        return launch_pipe_shape<32, 64, 1, 5, 1, 1, GATED, OUT_F32, SPLIT, MAPPED>(X, ldx, row_map, map_div, offsets, E, A,
-                                                                                  W, w_expert_stride, N, K, Out, ldo, s);
-    return launch_pipe_shape<64, 128, 2, 3, 2, 4, GATED, OUT_F32, SPLIT, MAPPED>(X, ldx, row_map, map_div, offsets, E, A, W,
-                                                                                w_expert_stride, N, K, Out, ldo, s);
-}
-
 template <bool GATED, bool OUT_F32, bool SPLIT, bool MAPPED>
 static hipError_t launch_big(RowSrc X, int ldx, const int32_t* row_map, int map_div, const int32_t* offsets, int E,
                              int64_t A, const bf16_t* W, int64_t w_expert_stride, int N, int K, void* Out, int ldo,
                              hipStream_t s)
 {
-    constexpr int NO = GATED ? kBigBN / 2 : kBigBN;
     const size_t lds_bytes = (size_t)5 * kBigRows * 128;
     auto kern = grouped_gemm_bf16_big_kernel<GATED, OUT_F32, SPLIT, MAPPED>;
     static bool attr_set[kMaxDevices] = {};
     hipError_t e = ensure_lds_limit(kern, lds_bytes, attr_set);
     if (e != hipSuccess) return e;
-    if (!big_list_fits(A, E, (N + NO - 1) / NO))
-        return launch_pipe<GATED, OUT_F32, SPLIT, MAPPED>(X, ldx, row_map, map_div, offsets, E, A, W, w_expert_stride, N, K,
-                                                          Out, ldo, s);
     int grid = 0;
     e = big_grid(&grid);
     if (e != hipSuccess) return e;
@@ -1036,15 +1026,23 @@ static hipError_t launch_bf16(int variant, RowSrc X, int ldx, const int32_t* row
 {
     // weight streaming: 64 x 128 tiles, 4 waves, 72 KB of LDS: two blocks share a compute unit, so one
     // block's prologue and epilogue are covered by the other's loads, and the many small tiles balance
-    // well over the chip.  compute bound: up to 256 x 256 tiles, one persistent block per compute unit.
+    // well over the chip.  launches of few tiles: 32 x 64, 1 wave, five stages.  compute bound: up to 256 x 256 tiles,
+    // one persistent block per compute unit.
     // (only the gate_up GEMM is ever called with a row map)
     const bool mapped = GATED && row_map != nullptr;
     if (!GATED && row_map != nullptr) return hipErrorInvalidValue;
-    switch (pick_variant(variant, A, E, (SPLIT && !GATED) ? K / 2 : K)) {
+    Variant v;
+    const hipError_t e = pick_variant(variant, GATED, A, E, N, (SPLIT && !GATED) ? K / 2 : K, &v);
+    if (e != hipSuccess) return e;
+    switch (v) {
         case V_PIPE_SMALL:
             if (mapped)
-                return launch_pipe<GATED, OUT_F32, SPLIT, GATED>(X, ldx, row_map, map_div, offsets, E, A, W, w_expert_stride, N, K, Out, ldo, s);
-            return launch_pipe<GATED, OUT_F32, SPLIT, false>(X, ldx, row_map, map_div, offsets, E, A, W, w_expert_stride, N, K, Out, ldo, s);
+                return launch_pipe<64, 128, 2, 3, 2, 4, GATED, OUT_F32, SPLIT, GATED>(X, ldx, row_map, map_div, offsets, E, A, W, w_expert_stride, N, K, Out, ldo, s);
+            return launch_pipe<64, 128, 2, 3, 2, 4, GATED, OUT_F32, SPLIT, false>(X, ldx, row_map, map_div, offsets, E, A, W, w_expert_stride, N, K, Out, ldo, s);
+        case V_PIPE_FEW:
+            if (mapped)
+                return launch_pipe<32, 64, 1, 5, 1, 1, GATED, OUT_F32, SPLIT, GATED>(X, ldx, row_map, map_div, offsets, E, A, W, w_expert_stride, N, K, Out, ldo, s);
+            return launch_pipe<32, 64, 1, 5, 1, 1, GATED, OUT_F32, SPLIT, false>(X, ldx, row_map, map_div, offsets, E, A, W, w_expert_stride, N, K, Out, ldo, s);
         case V_PIPE_BIG:
             if (mapped)
                 return launch_big<GATED, OUT_F32, SPLIT, GATED>(X, ldx, row_map, map_div, offsets, E, A, W, w_expert_stride, N, K, Out, ldo, s);
@@ -1092,10 +1090,12 @@ hipError_t launch_ffn_down(int dtype, int variant, bool out_f32, bool split, con
 
 const char* ffn_variant_name(int dtype, int variant, int64_t A, int E, int H, int I)
 {
-    (void)I;
     if (dtype != MOE_BF16) return "grouped_gemm_f32_kernel<gated>";
-    switch (pick_variant(variant, A, E, H)) {
+    Variant v;
+    if (pick_variant(variant, true, A, E, I, H, &v) != hipSuccess) return "";
+    switch (v) {
         case V_PIPE_SMALL: return "grouped_gemm_bf16_pipe_kernel<2,128,2,3,64,2,4,gated>";
+        case V_PIPE_FEW: return "grouped_gemm_bf16_pipe_kernel<1,64,1,5,64,1,1,gated>";
         case V_PIPE_BIG: return "grouped_gemm_bf16_big_kernel<gated>";
         default: return "grouped_gemm_bf16_kernel<128,128,gated>";
     }

@@ -99,9 +99,10 @@ def test_routing_of_logits_that_are_not_finite(gpu_lib, E, K, T, kind):
     assert torch.equal(torch.sort(perm).values, torch.arange(T * K, dtype=torch.int32, device=DEV))
 
 
-# The narrow streaming shape (32 x 64 tiles, one wave, a ring of five stages), taken when the launch has few tiles: k-extents
-# around the length of the ring, row and column edges, a plain and a split intermediate.  Against the register-staged
-# kernel bit for bit (the order of a sum is the same in every shape) and against the oracle.
+# The two streaming shapes: 64 x 128 tiles (four waves, a ring of three stages) and, taken when the launch has few tiles, 32 x 64
+# (one wave, five stages).  k-extents around the length of the ring, row and column edges, a plain and a split
+# intermediate.  Against the register-staged kernel bit for bit (the order of a sum is the same in every shape) and against
+# the oracle.
 @pytest.mark.parametrize("H,I,rows", [
     (64, 128, [1]),                        # one and two stages
     (192, 256, [31, 32, 33]),              # three and four stages (the ring's look-ahead)
@@ -120,12 +121,24 @@ def test_few_tiles_grouped_ffn(gpu_lib, H, I, rows):
         ctx = gpu_lib.Context(H, E, 1, I, torch.bfloat16, max_tokens=A, device=DEV, **fmt)
         ctx.moe_set_ffn_variant("tile128")
         ref = ctx.moe_grouped_ffn(*args)
-        ctx.moe_set_ffn_variant("small")
-        for _ in range(2):
-            assert torch.equal(ctx.moe_grouped_ffn(*args), ref), fmt
+        for shape in ("few", "small", "few"):
+            ctx.moe_set_ffn_variant(shape)
+            assert torch.equal(ctx.moe_grouped_ffn(*args), ref), (shape, fmt)
     ctx = gpu_lib.Context(H, E, 1, I, torch.bfloat16, max_tokens=A, device=DEV)
-    ctx.moe_set_ffn_variant("small")
+    ctx.moe_set_ffn_variant("few")
     assert_close(ctx.moe_grouped_ffn(*args), dense_ffn(x_perm, offsets, L, "bf16", E), "bf16", "few tiles")
+
+
+# The shape a launch takes is the one moe_ffn_variant names: pinned, or by the rule (rows per expert, then tiles: one 64 x 128
+# tile per compute unit is the border of the narrow shape; 256 units: 8 of 128 experts have 96 + 12 tiles at one token)
+@pytest.mark.parametrize("T,want", [(1, "<1,64,1,5,64,1,1,"), (2, "<1,64,1,5,64,1,1,"), (3, "<2,128,2,3,64,2,4,"),
+                                    (896, "<2,128,2,3,64,2,4,"), (1100, "big")])
+def test_shape_names(gpu_lib, T, want):
+    ctx = gpu_lib.Context(2048, 128, 8, 768, torch.bfloat16, max_tokens=2, device=DEV)
+    assert want in ctx.moe_ffn_variant(T)
+    for pin, name in (("few", "<1,64,1,5,64,1,1,"), ("small", "<2,128,2,3,64,2,4,"), ("big", "big"), ("tile128", "<128,128,")):
+        ctx.moe_set_ffn_variant(pin)
+        assert name in ctx.moe_ffn_variant(T)
 
 
 # The persistent 256 x 256 kernel: tiles of 128 to 256 rows cut from experts of any size, at least four k-stages, next

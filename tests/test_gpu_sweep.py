@@ -51,6 +51,11 @@ def test_layer_against_oracle_and_schedules(gpu_lib, w):
     idx, _ = ctx.moe_router_topk(x.to(DEV), Ld["w_router"], Ld["router_bias"])
     assert (idx.cpu().numpy() == o_idx).all()
     assert_close(y, o_y, "bf16", w.name)
+    if not w.weight_format:                        # launches this small take the narrow streaming shape by themselves
+        ctx.moe_set_ffn_variant("small")
+        yd1, yp1 = ctx.moe_group_forward([Ld], xdd, xpd, "layered")
+        assert torch.equal(torch.cat([t for t in (yd1, yp1) if t.shape[0]]), y), "64 x 128 tiles"
+        ctx.moe_set_ffn_variant("auto")
     if w.P:
         for chunk in (7, 64):
             yd2, yp2 = ctx.moe_group_forward([Ld], xdd, xpd, "chunked", chunk)
