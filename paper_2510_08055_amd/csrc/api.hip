@@ -18,6 +18,7 @@ struct moe_ctx {
     unsigned long long* d_active_total;
     uint32_t* d_tickets;     // of the one-launch routing of small batches: zero between launches, once cleared
     bool tickets_clear;      // a pass of this context has cleared them (see clear_tickets)
+    bool tickets_clear_now;  // the call in progress finds them clear
     double* logits;
     int32_t *idx, *counts, *offsets, *perm, *inv, *tile_hist;
     float* w;
@@ -135,21 +136,23 @@ inline bool misaligned(const void* p) { return (reinterpret_cast<uintptr_t>(p) &
 inline bool misaligned32(const void* p) { return (reinterpret_cast<uintptr_t>(p) & 31u) != 0; }
 inline moe_status dev(hipError_t e) { return e == hipSuccess ? MOE_OK : MOE_ERR_DEVICE; }
 
-// The tickets of the one-launch routing have to be zero when its first launch starts.  The first pass of a context clears
-// them, on its own stream: the clear is then ordered in front of the routing whatever stream the context was made on (and
-// whether or not moe_create's own work has run).  Later passes find them as the launch before left them, at zero.
-// A pass that is being captured runs only when its graph is replayed, so it carries the clear along and the next pass
-// clears again.
+// The tickets of the one-launch routing have to be zero when its first launch starts.  The first pass that needs them
+// clears them, on its own stream: the clear is then ordered in front of the routing whatever stream the context was made
+// on, and whether or not moe_create's own work has run.  It is one launch in a context's life (12 us of a first pass of
+// 211 us on an idle GPU); later passes find the tickets as the launch before left them, at zero.
+// A pass that is being captured runs only when its graph is replayed, so it carries the clear along, once, and the next
+// pass clears again.
 hipError_t clear_tickets(moe_ctx* c, hipStream_t s)
 {
-    if (c->tickets_clear) return hipSuccess;
+    if (c->tickets_clear_now) return hipSuccess;
     hipStreamCaptureStatus capture = hipStreamCaptureStatusNone;
     if (hipStreamIsCapturing(s, &capture) != hipSuccess) {
         (void)hipGetLastError();        // (the legacy stream while another one is captured)
         capture = hipStreamCaptureStatusActive;
     }
     const hipError_t e = launch_fill_zero(c->d_tickets, kSmallTickets, s);
-    if (e == hipSuccess && capture == hipStreamCaptureStatusNone) c->tickets_clear = true;
+    c->tickets_clear_now = e == hipSuccess;
+    c->tickets_clear = c->tickets_clear_now && capture == hipStreamCaptureStatusNone;
     return e;
 }
 
@@ -166,6 +169,8 @@ moe_status run_layer(moe_ctx* c, const moe_layer& L, RowSrc x, int64_t T, void* 
     const bool small = route_is_small(T, g.E, g.K);
     if (small) {
         // (timed as the router's logits; the other two have no launch of their own)
+        e = clear_tickets(c, s);
+        if (e != hipSuccess) return MOE_ERR_DEVICE;
         Timed t(c, MOE_KERNEL_ROUTER_LOGITS, s);
         e = launch_route_small(g.dtype, x, T, g.H, L.w_router, L.router_bias, g.E, g.K, g.renormalize, c->logits, c->idx,
                                c->w, c->offsets, c->perm, c->inv, c->d_active_total, c->d_tickets, s);
@@ -296,7 +301,7 @@ moe_status moe_create(const moe_config* cfg, int64_t max_tokens, void* workspace
     c->d_active_total = reinterpret_cast<unsigned long long*>(b + L.counters);
     static_assert(128 + kSmallTickets * sizeof(uint32_t) <= 256, "the counter block");
     c->d_tickets = reinterpret_cast<uint32_t*>(b + L.counters + 128);
-    c->tickets_clear = false;
+    c->tickets_clear = c->tickets_clear_now = false;
     c->logits = reinterpret_cast<double*>(b + L.logits);
     c->idx = reinterpret_cast<int32_t*>(b + L.idx);
     c->w = reinterpret_cast<float*>(b + L.w);
@@ -504,7 +509,7 @@ moe_status moe_stack_forward(moe_ctx* ctx, const moe_layer* layers, int32_t n_la
     if (D + (P < step ? P : step) > ctx->max_tokens) return MOE_ERR_SHAPE;
 
     hipStream_t s = static_cast<hipStream_t>(stream);
-    if (clear_tickets(ctx, s) != hipSuccess) return MOE_ERR_DEVICE;
+    ctx->tickets_clear_now = ctx->tickets_clear;
     const size_t row_bytes = (size_t)ctx->cfg.H * ctx->esz;
     std::vector<int32_t> first((size_t)n_layers + 1);
     for (int64_t sl = 0; sl < n_slices; ++sl) {
