@@ -921,8 +921,8 @@ static hipError_t launch_f32(RowSrc X, int ldx, const int32_t* row_map, int map_
 
 // ----------------------------------------------------------------------------------------------
 // Host side: variant choice and launches.  The host never sees the per-expert counts (they live on
-// the device), so the variant is chosen from the mean rows per expert A/E; every variant is correct
-// for any distribution of rows.
+// the device), so the variant is chosen from the mean rows per expert A/E and from the number of tiles these
+// make; every variant is correct for any distribution of rows.
 // ----------------------------------------------------------------------------------------------
 enum Variant { V_TILE128 = 0, V_PIPE_SMALL, V_PIPE_FEW, V_PIPE_BIG };
 
@@ -940,23 +940,29 @@ static hipError_t pick_variant(int pinned, bool gated, int64_t A, int E, int N, 
     const bool big_runs = K >= 256 && big_list_fits(A, E, (N + big_cols - 1) / big_cols);
     *v = V_PIPE_BIG;
     if (pinned == MOE_FFN_PIPE_BIG && big_runs) return hipSuccess;
-    // Weight streaming with 64 x 128 tiles up to 56 rows per expert on average.  Layer, us, streaming against big tiles:
-    // 128 experts, H = 2048, I = 768: 47 rows 277 / 280, 56 rows 299 / 299, 64 rows 320 / 304; 32 experts, H = I = 2880:
-    // 32 rows 318 / 316, 50 rows 339 / 336, 64 rows 385 / 344.
-    if (A > (int64_t)56 * E && big_runs) return hipSuccess;
-    // Up to one 64 x 128 tile per compute unit (an upper bound of their number) the launch takes narrow tiles: 32 x 64, one
-    // wave, five stages of 12 KB.  What bounds such a launch is how much it has in flight: 96 tiles for one token at 8 of
-    // 128 experts (H = 2048, I = 768) with two stages of weights each, 16 KB, ask for 2.6 TB/s; 192 narrow ones keep four
-    // stages of 8 KB.  gate_up 19.1 -> 15.4 us, down 10.1 -> 9.3.  Above one tile per unit twice as many blocks, and every
-    // activation row read twice, cost more than they bring.  Layer of that shape, us, 64 x 128 against narrow tiles: 1 token
-    // (108 and 144 tiles) 49.9 / 41.9, 2 tokens (204 and 272) 57.1 / 53.8, 3 tokens (300 and 400) 73.2 / 75.7, 4 tokens (396
-    // and 528) 82.2 / 85.6; 32 experts, top-4, H = I = 2880: 1 token (225 and 115) 70.3 / 63.8, 2 tokens (405 and 207) 96.0 /
-    // 99.6.
     int cus = 0;
     const hipError_t e = compute_units(&cus);
+    if (e != hipSuccess) return e;
+    // Two blocks of either streaming shape share a compute unit: up to two tiles per unit a launch is one round of
+    // blocks, whatever the number of rows per expert; the first tile beyond that costs a second round.
     const int cols = gated ? 64 : 128;
-    *v = ((A + 63) / 64 + (A < E ? A : E)) * ((N + cols - 1) / cols) <= cus ? V_PIPE_FEW : V_PIPE_SMALL;
-    return e;
+    const bool small_is_one_round = tiles_expected(A, E, 64, (N + cols - 1) / cols) <= 2 * cus;
+    const bool few_is_one_round = tiles_expected(A, E, 32, (N + cols / 2 - 1) / (cols / 2)) < 2 * cus;
+    // Big tiles from 56 rows per expert on average, unless the 64 x 128 tiles are one round.  With many tiles (layer, us,
+    // streaming against big): 128 experts, H = 2048, I = 768: 47 rows 277 / 280, 56 rows 299 / 299, 64 rows 320 / 304; 32
+    // experts, H = I = 2880: 32 rows 318 / 316, 50 rows 339 / 336, 64 rows 385 / 344.  Around one round of 512 (gate_up, us):
+    // 8 experts, H = I = 1024, 200 rows, 464 tiles expected 16.2 / 20.5, 400 rows, 864 tiles 26.4 / 23.3; 8 experts, H = I =
+    // 2048, 80 rows, 448 tiles 26.4 / 29.5, 130 rows, 648 tiles 37.4 / 32.2; 2 experts, H = I = 512, 1000 rows, 256 tiles 11.0 /
+    // 15.7.
+    if (A > (int64_t)56 * E && big_runs && !small_is_one_round) return hipSuccess;
+    // Narrow tiles (32 x 64, one wave, five stages of 12 KB) while they are one round.  What bounds such a launch is how
+    // much it has in flight: 96 tiles of 64 x 128 for one token at 8 of 128 experts (H = 2048, I = 768) with two stages of
+    // weights each, 16 KB, ask for 2.6 TB/s; 192 narrow ones keep four stages of 8 KB: gate_up 19.1 -> 15.4 us, down 10.1 ->
+    // 9.3.  64 x 128 against narrow tiles, us: layer of that shape, 2 tokens (384 and 512 narrow tiles) 57.1 / 53.8, 3 tokens
+    // (576 and 768) 73.2 / 75.7; gate_up, 8 experts, H = I = 1024, 40 rows (448) 12.6 / 13.3, 56 rows (576) 12.9 / 20.1; H = I =
+    // 512, 100 rows (464) 9.5 / 10.0, 130 rows (584) 9.9 / 14.8.
+    *v = few_is_one_round ? V_PIPE_FEW : V_PIPE_SMALL;
+    return hipSuccess;
 }
 
 template <int BM, int BN, bool GATED, typename OT, bool SPLIT>

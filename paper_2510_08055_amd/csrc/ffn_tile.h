@@ -112,6 +112,14 @@ __device__ __forceinline__ TileCoord find_tile(const int32_t* __restrict__ offse
     return tc;
 }
 
+// Host side: tiles of `rows` rows a launch is expected to have when its A rows spread evenly over the experts (an
+// expert's last tile is half full on average, and an expert with a row has a tile).
+inline int64_t tiles_expected(int64_t A, int E, int rows, int64_t n_tiles)
+{
+    const int64_t used = A < E ? A : E, m_tiles = A / rows + used / 2;
+    return (m_tiles > used ? m_tiles : used) * n_tiles;
+}
+
 // silu(g) * u with silu(g) = g / (1 + e^-g); hardware exp2 and reciprocal (1 ulp each), far inside the
 // rounding of the bf16 (or the tolerance of the fp32) result.
 __device__ __forceinline__ float silu_mul(float g, float u)

@@ -129,14 +129,31 @@ def test_few_tiles_grouped_ffn(gpu_lib, H, I, rows):
     assert_close(ctx.moe_grouped_ffn(*args), dense_ffn(x_perm, offsets, L, "bf16", E), "bf16", "few tiles")
 
 
-# The shape a launch takes is the one moe_ffn_variant names: pinned, or by the rule (rows per expert, then tiles: one 64 x 128
-# tile per compute unit is the border of the narrow shape; 256 units: 8 of 128 experts have 96 + 12 tiles at one token)
-@pytest.mark.parametrize("T,want", [(1, "<1,64,1,5,64,1,1,"), (2, "<1,64,1,5,64,1,1,"), (3, "<2,128,2,3,64,2,4,"),
-                                    (896, "<2,128,2,3,64,2,4,"), (1100, "big")])
-def test_shape_names(gpu_lib, T, want):
-    ctx = gpu_lib.Context(2048, 128, 8, 768, torch.bfloat16, max_tokens=2, device=DEV)
+# The shape a launch takes is the one moe_ffn_variant names: pinned, or by the rule.  By the rule: a streaming shape up to 56
+# rows per expert, and beyond as long as its tiles are one round (two per compute unit, 512 on 256 units); narrow tiles while
+# these are less than one round.
+FEW, SMALL, BIG = "<1,64,1,5,64,1,1,", "<2,128,2,3,64,2,4,", "big"
+
+
+@pytest.mark.parametrize("H,E,K,I,T,want", [
+    (2048, 128, 8, 768, 1, FEW),           # 8 experts x 24 narrow tiles
+    (2048, 128, 8, 768, 2, FEW),           # 384
+    (2048, 128, 8, 768, 3, SMALL),         # 576
+    (2048, 128, 8, 768, 896, SMALL),       # 56 rows per expert
+    (2048, 128, 8, 768, 897, BIG),
+    (512, 4, 1, 512, 60 * 4, FEW),         # few experts of many rows: (7 + 2) x 16 narrow tiles
+    (512, 4, 1, 512, 4 * 500, SMALL),      # (62 + 2) x 16 narrow tiles, (31 + 2) x 8 of 64 x 128
+    (1024, 8, 2, 1024, 4 * 56, SMALL),     # (14 + 4) x 32 narrow tiles
+    (1024, 8, 2, 1024, 4 * 224, SMALL),    # (28 + 4) x 16 tiles: one round
+    (1024, 8, 2, 1024, 4 * 232, BIG),      # (29 + 4) x 16
+    (512, 2, 1, 512, 8192, BIG),           # 129 x 8
+])
+def test_shape_rule_and_names(gpu_lib, H, E, K, I, T, want):
+    if torch.cuda.get_device_properties(0).multi_processor_count != 256:
+        pytest.skip("the rule counts compute units")
+    ctx = gpu_lib.Context(H, E, K, I, torch.bfloat16, max_tokens=2, device=DEV)
     assert want in ctx.moe_ffn_variant(T)
-    for pin, name in (("few", "<1,64,1,5,64,1,1,"), ("small", "<2,128,2,3,64,2,4,"), ("big", "big"), ("tile128", "<128,128,")):
+    for pin, name in (("few", FEW), ("small", SMALL), ("big", BIG), ("tile128", "<128,128,")):
         ctx.moe_set_ffn_variant(pin)
         assert name in ctx.moe_ffn_variant(T)
 
