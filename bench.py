@@ -71,7 +71,7 @@ def parse_args():
     ap.add_argument("--time-all-kernels", action="store_true",
                     help="bracket all six kernels of a layer with events (default: the two grouped GEMMs)")
     ap.add_argument("--ffn-variant", default="auto",
-                    choices=["auto", "tile128", "small", "few", "big", "w4_tile64", "w4_stream", "w4_big"],
+                    choices=["auto", "tile128", "small", "few", "big", "wide", "w4_tile64", "w4_stream", "w4_big"],
                     help="tuning aid: pin the grouped-GEMM kernel shape (moe_set_ffn_variant); auto = the library's own choice")
     ap.add_argument("--copy-calibration", action="store_true",
                     help="only run a plain 1 GiB device-to-device copy kernel a few times (reference for scaling "

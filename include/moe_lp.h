@@ -292,7 +292,8 @@ typedef enum {
     MOE_FFN_W4_TILE64 = 4,  /* MXFP4: 64-row tiles */
     MOE_FFN_W4_STREAM = 5,  /* MXFP4: 32-row weight-streaming tiles */
     MOE_FFN_W4_BIG = 6,     /* MXFP4: up to 256 x 256 tiles, compute bound (K >= 512) */
-    MOE_FFN_PIPE_FEW = 7    /* bf16: 32 x 64 tiles, weight streaming with few tiles */
+    MOE_FFN_PIPE_FEW = 7,   /* bf16: 32 x 64 tiles, weight streaming with few tiles */
+    MOE_FFN_PIPE_WIDE = 8   /* bf16: 256 x 256 tiles, short rows (K < 256) */
 } moe_ffn_variant_id;
 moe_status moe_set_ffn_variant(moe_ctx *ctx, int32_t variant);
 

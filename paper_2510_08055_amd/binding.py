@@ -26,7 +26,7 @@ EXPORTS = ["moe_workspace_bytes", "moe_create", "moe_destroy", "moe_router_topk"
            "moe_kernel_timing", "moe_read_kernel_timing", "moe_ffn_variant", "moe_set_ffn_variant",
            "moe_status_string"]
 
-FFN_VARIANTS = {"auto": 0, "tile128": 1, "small": 2, "big": 3, "w4_tile64": 4, "w4_stream": 5, "w4_big": 6, "few": 7}
+FFN_VARIANTS = {"auto": 0, "tile128": 1, "small": 2, "big": 3, "w4_tile64": 4, "w4_stream": 5, "w4_big": 6, "few": 7, "wide": 8}
 
 KERNELS = {"router_logits": 0, "topk": 1, "permute": 2, "gate_up": 3, "down": 4, "combine": 5}
 

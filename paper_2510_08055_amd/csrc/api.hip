@@ -607,7 +607,7 @@ const char* moe_ffn_variant(const moe_ctx* ctx, int64_t T)
 moe_status moe_set_ffn_variant(moe_ctx* ctx, int32_t variant)
 {
     if (!ctx) return MOE_ERR_NULL;
-    if (variant < MOE_FFN_AUTO || variant > MOE_FFN_PIPE_FEW) return MOE_ERR_SHAPE;
+    if (variant < MOE_FFN_AUTO || variant > MOE_FFN_PIPE_WIDE) return MOE_ERR_SHAPE;
     ctx->ffn_variant = variant;
     return MOE_OK;
 }

@@ -173,7 +173,8 @@ __global__ __launch_bounds__(256) void grouped_gemm_bf16_kernel(
 // Weight-streaming shape (few rows per expert): global -> LDS copies issued as direct-to-LDS loads
 // (global_load_lds_dwordx4: no staging registers, no LDS store instructions) into two rings of NS LDS slots, one for
 // the activation rows and one for the weight rows, each stage PBK (64 or 32) k-values deep; one barrier per stage.
-// 64 x 128 tiles, 4 waves, 3 stages of 24 KB: two blocks share a compute unit (launches of few tiles take 32 x 64, see pick_variant).
+// 64 x 128 tiles, 4 waves, 3 stages of 24 KB: two blocks share a compute unit.  Launches of few tiles take 32 x 64 tiles (one wave, 5 stages), short rows 256 x 256 (8
+// waves, 2 stages): see pick_variant.
 // NW waves arranged WM x WN.
 // One wave-level load moves 64 lanes x 16 B = 8 (or 16) whole tile rows into 1 KB of LDS.  LDS rows
 // are unpadded (the hardware writes lanes contiguously), so bank conflicts on the 16-byte operand
@@ -924,7 +925,7 @@ static hipError_t launch_f32(RowSrc X, int ldx, const int32_t* row_map, int map_
 // the device), so the variant is chosen from the mean rows per expert A/E and from the number of tiles these
 // make; every variant is correct for any distribution of rows.
 // ----------------------------------------------------------------------------------------------
-enum Variant { V_TILE128 = 0, V_PIPE_SMALL, V_PIPE_FEW, V_PIPE_BIG };
+enum Variant { V_TILE128 = 0, V_PIPE_SMALL, V_PIPE_FEW, V_PIPE_BIG, V_PIPE_WIDE };
 
 // The shape of a launch: the one `pinned` names if it can run, else the library's rule.  K: length of a weight row.
 static hipError_t pick_variant(int pinned, bool gated, int64_t A, int E, int N, int K, Variant* v)
@@ -935,6 +936,8 @@ static hipError_t pick_variant(int pinned, bool gated, int64_t A, int E, int N, 
     if (pinned == MOE_FFN_PIPE_SMALL) return hipSuccess;
     *v = V_PIPE_FEW;
     if (pinned == MOE_FFN_PIPE_FEW) return hipSuccess;
+    *v = V_PIPE_WIDE;
+    if (pinned == MOE_FFN_PIPE_WIDE) return hipSuccess;
     // (the persistent kernel's pipeline is at least four stages long, and its tile list has a limit)
     const int big_cols = gated ? kBigBN / 2 : kBigBN;
     const bool big_runs = K >= 256 && big_list_fits(A, E, (N + big_cols - 1) / big_cols);
@@ -955,6 +958,13 @@ static hipError_t pick_variant(int pinned, bool gated, int64_t A, int E, int N, 
     // 2048, 80 rows, 448 tiles 26.4 / 29.5, 130 rows, 648 tiles 37.4 / 32.2; 2 experts, H = I = 512, 1000 rows, 256 tiles 11.0 /
     // 15.7.
     if (A > (int64_t)56 * E && big_runs && !small_is_one_round) return hipSuccess;
+    // Rows too short for the persistent kernel (K < 256): 256 x 256 tiles, a block each, from 64 rows per expert on average.
+    // Such a GEMM is bound by its outputs and the activation rows it reads per column tile.  gate_up, us, 64 x 128 against
+    // 256 x 256 tiles: 64 experts, K = 192, N = 2048: 58 rows 32.1 / 34.3, 64 rows 34.3 / 34.9, 80 rows 41.2 / 37.5, 300 rows
+    // 96 / 71, 1000 rows 311 / 206; K = 64, N = 1024, 1000 rows 120 / 63; 8 experts, K = 128, N = 1024, one round of 64 x 128
+    // tiles at 150 rows 8.3 / 10.3, more than one at 300 rows 11.5 / 10.6.
+    *v = V_PIPE_WIDE;
+    if (K < 256 && A > (int64_t)64 * E && !small_is_one_round) return hipSuccess;
     // Narrow tiles (32 x 64, one wave, five stages of 12 KB) while they are one round.  What bounds such a launch is how
     // much it has in flight: 96 tiles of 64 x 128 for one token at 8 of 128 experts (H = 2048, I = 768) with two stages of
     // weights each, 16 KB, ask for 2.6 TB/s; 192 narrow ones keep four stages of 8 KB: gate_up 19.1 -> 15.4 us, down 10.1 ->
@@ -1033,7 +1043,7 @@ static hipError_t launch_bf16(int variant, RowSrc X, int ldx, const int32_t* row
     // weight streaming: 64 x 128 tiles, 4 waves, 72 KB of LDS: two blocks share a compute unit, so one
     // block's prologue and epilogue are covered by the other's loads, and the many small tiles balance
     // well over the chip.  launches of few tiles: 32 x 64, 1 wave, five stages.  compute bound: up to 256 x 256 tiles,
-    // one persistent block per compute unit.
+    // one persistent block per compute unit; for rows of fewer than four stages the same tiles, a block each, two stages.
     // (only the gate_up GEMM is ever called with a row map)
     const bool mapped = GATED && row_map != nullptr;
     if (!GATED && row_map != nullptr) return hipErrorInvalidValue;
@@ -1049,6 +1059,10 @@ static hipError_t launch_bf16(int variant, RowSrc X, int ldx, const int32_t* row
             if (mapped)
                 return launch_pipe<32, 64, 1, 5, 1, 1, GATED, OUT_F32, SPLIT, GATED>(X, ldx, row_map, map_div, offsets, E, A, W, w_expert_stride, N, K, Out, ldo, s);
             return launch_pipe<32, 64, 1, 5, 1, 1, GATED, OUT_F32, SPLIT, false>(X, ldx, row_map, map_div, offsets, E, A, W, w_expert_stride, N, K, Out, ldo, s);
+        case V_PIPE_WIDE:
+            if (mapped)
+                return launch_pipe<256, 256, 2, 2, 2, 8, GATED, OUT_F32, SPLIT, GATED>(X, ldx, row_map, map_div, offsets, E, A, W, w_expert_stride, N, K, Out, ldo, s);
+            return launch_pipe<256, 256, 2, 2, 2, 8, GATED, OUT_F32, SPLIT, false>(X, ldx, row_map, map_div, offsets, E, A, W, w_expert_stride, N, K, Out, ldo, s);
         case V_PIPE_BIG:
             if (mapped)
                 return launch_big<GATED, OUT_F32, SPLIT, GATED>(X, ldx, row_map, map_div, offsets, E, A, W, w_expert_stride, N, K, Out, ldo, s);
@@ -1102,6 +1116,7 @@ const char* ffn_variant_name(int dtype, int variant, int64_t A, int E, int H, in
     switch (v) {
         case V_PIPE_SMALL: return "grouped_gemm_bf16_pipe_kernel<2,128,2,3,64,2,4,gated>";
         case V_PIPE_FEW: return "grouped_gemm_bf16_pipe_kernel<1,64,1,5,64,1,1,gated>";
+        case V_PIPE_WIDE: return "grouped_gemm_bf16_pipe_kernel<8,256,2,2,64,2,8,gated>";
         case V_PIPE_BIG: return "grouped_gemm_bf16_big_kernel<gated>";
         default: return "grouped_gemm_bf16_kernel<128,128,gated>";
     }

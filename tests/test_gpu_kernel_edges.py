@@ -129,10 +129,37 @@ def test_few_tiles_grouped_ffn(gpu_lib, H, I, rows):
     assert_close(ctx.moe_grouped_ffn(*args), dense_ffn(x_perm, offsets, L, "bf16", E), "bf16", "few tiles")
 
 
+# 256 x 256 tiles with a block each (short rows): one to three stages on either GEMM, and longer rows when pinned; row blocks per
+# wave from none to four, ragged columns, both output formats and the split intermediate
+@pytest.mark.parametrize("H,I,rows", [
+    (64, 192, [1, 0, 33]),
+    (128, 128, [255, 256, 257, 31, 0, 95, 160]),
+    (192, 64, [300] + [0] * 70 + [7]),
+    (192, 320, [129, 64]),
+    (8 * 41, 128, [200, 97]),                                   # gate_up takes another kernel, down has 328 columns
+])
+def test_wide_tiles_grouped_ffn(gpu_lib, H, I, rows):
+    E, A = len(rows), sum(rows)
+    w = inputs.Workload("wide", H=H, E=E, K=1, I=I, n_layers=1, D=0, P=A, dtype="bf16", seed=61)
+    L = inputs.make_layer(w, 0)
+    x_perm = inputs.randn((A, H), 1.0, 61, "x_perm", 0, "bf16")
+    offsets = torch.tensor(np.concatenate([[0], np.cumsum(rows)]), dtype=torch.int32)
+    args = (x_perm.to(DEV), offsets.to(DEV), L["w_gate_up"].to(DEV), L["w_down"].to(DEV))
+    for fmt in ({}, {"y_perm_f32": True}, {"y_perm_f32": True, "act_split": True}):
+        ctx = gpu_lib.Context(H, E, 1, I, torch.bfloat16, max_tokens=A, device=DEV, **fmt)
+        ctx.moe_set_ffn_variant("tile128")
+        ref = ctx.moe_grouped_ffn(*args)
+        ctx.moe_set_ffn_variant("wide")
+        for _ in range(2):
+            assert torch.equal(ctx.moe_grouped_ffn(*args), ref), fmt
+        if not fmt:
+            assert_close(ref, dense_ffn(x_perm, offsets, L, "bf16", E), "bf16", "wide tiles")
+
+
 # The shape a launch takes is the one moe_ffn_variant names: pinned, or by the rule.  By the rule: a streaming shape up to 56
 # rows per expert, and beyond as long as its tiles are one round (two per compute unit, 512 on 256 units); narrow tiles while
 # these are less than one round.
-FEW, SMALL, BIG = "<1,64,1,5,64,1,1,", "<2,128,2,3,64,2,4,", "big"
+FEW, SMALL, BIG, WIDE = "<1,64,1,5,64,1,1,", "<2,128,2,3,64,2,4,", "big", "<8,256,2,2,64,2,8,"
 
 
 @pytest.mark.parametrize("H,E,K,I,T,want", [
@@ -147,13 +174,16 @@ FEW, SMALL, BIG = "<1,64,1,5,64,1,1,", "<2,128,2,3,64,2,4,", "big"
     (1024, 8, 2, 1024, 4 * 224, SMALL),    # (28 + 4) x 16 tiles: one round
     (1024, 8, 2, 1024, 4 * 232, BIG),      # (29 + 4) x 16
     (512, 2, 1, 512, 8192, BIG),           # 129 x 8
+    (192, 64, 1, 2048, 64 * 64, SMALL),    # short rows: 256 x 256 tiles above 64 rows per expert
+    (192, 64, 1, 2048, 64 * 64 + 1, WIDE),
+    (192, 2, 1, 512, 2 * 900, SMALL),      # (28 + 1) x 8
 ])
 def test_shape_rule_and_names(gpu_lib, H, E, K, I, T, want):
     if torch.cuda.get_device_properties(0).multi_processor_count != 256:
         pytest.skip("the rule counts compute units")
     ctx = gpu_lib.Context(H, E, K, I, torch.bfloat16, max_tokens=2, device=DEV)
     assert want in ctx.moe_ffn_variant(T)
-    for pin, name in (("few", FEW), ("small", SMALL), ("big", BIG), ("tile128", "<128,128,")):
+    for pin, name in (("few", FEW), ("small", SMALL), ("wide", WIDE), ("big", BIG if H >= 256 else want), ("tile128", "<128,128,")):
         ctx.moe_set_ffn_variant(pin)
         assert name in ctx.moe_ffn_variant(T)
 

@@ -298,7 +298,7 @@ def test_output_side_formats_on_every_kernel_shape(gpu_lib, w, fmt):
     ctx = gpu_lib.Context(w.H, w.E, w.K, w.I, torch.bfloat16, max_tokens=w.D + w.P, residual=w.residual, device=DEV,
                           **FORMATS[fmt])
     outs = {}
-    for variant in ("tile128", "small", "few", "big", "auto"):
+    for variant in ("tile128", "small", "few", "wide", "big", "auto"):
         ctx.moe_set_ffn_variant(variant)
         idx, wt = ctx.moe_router_topk(x, Ld["w_router"])
         _, offsets, _, inv, x_perm = ctx.moe_permute(x, idx)
@@ -310,7 +310,7 @@ def test_output_side_formats_on_every_kernel_shape(gpu_lib, w, fmt):
         yd, yp = ctx.moe_group_forward([Ld], x[:w.D] if w.D else None, x[w.D:], "chunked", 100)
         assert torch.equal(torch.cat([t for t in (yd, yp) if t.shape[0]]), y), variant
         outs[variant] = y
-    for variant in ("small", "few", "big", "auto"):
+    for variant in ("small", "few", "wide", "big", "auto"):
         assert torch.equal(outs[variant], outs["tile128"]), variant
     st = assert_close(outs["auto"], o_y, "bf16", f"{w.name} {FORMATS[fmt]}")
     # what each format is for: the error that is left
