@@ -141,6 +141,6 @@ hipError_t launch_ffn_gate_up_w4(int variant, RowSrc x, const int32_t* row_map, 
                                  void* act, hipStream_t s);
 hipError_t launch_ffn_down_w4(int variant, bool out_f32, const void* act, const int32_t* offsets, int64_t A, int E, int H,
                               int I, const uint8_t* w_down, const uint8_t* s_down, void* y_perm, hipStream_t s);
-const char* ffn_w4_variant_name(int variant, int64_t A, int E, int H);
+const char* ffn_w4_variant_name(int variant, int64_t A, int E, int H, int I);
 
 }  // namespace moe

@@ -7,7 +7,7 @@
 // 32 consecutive elements along k.  A dequantised weight is exactly representable in bf16, so the GEMM
 // is the bf16 MFMA GEMM of ffn.hip on weights widened on the fly (v_cvt_scalef32_pk_bf16_fp4).
 //
-// Three kernel shapes.  The first, for short rows (K < 512) and batches of many rows per expert: 64-row x
+// Three kernel shapes.  The first, for many rows per expert in few tiles or with short rows (K < 512): 64-row x
 // 256-weight-row tiles, 4 waves side by side along the weight rows (each widens and multiplies its own
 // 64 weight rows against the tile's one or two 32-row blocks), 64 k-values per stage; activation rows
 // come through a 2-stage LDS ring as in ffn.hip.  The packed weight rows and their scale bytes are
@@ -357,7 +357,7 @@ __global__ __launch_bounds__(kW4Waves * 64, 2) void grouped_gemm_w4_kernel(
 }
 
 // ----------------------------------------------------------------------------------------------
-// The weight-streaming shape for decode-heavy batches (on average at most 48 rows per expert).
+// The weight-streaming shape for decode-heavy batches (on average at most 48 rows per expert) and launches of few tiles.
 //
 // With 4-bit weights a 64-value stage is 32 bytes of a weight row: fetched stage by stage (or two
 // stages at a time) every 128-byte line of the weights is requested several times, a few stages
@@ -1052,19 +1052,43 @@ __global__ __launch_bounds__(kBigWaves * 64, 2) void grouped_gemm_w4_big_kernel(
     wait_vmcnt<0>();           // a block must not end with loads into LDS outstanding
 }
 
-// Which kernel shape a launch uses: the streaming shape up to 48 rows per expert on average.  Its 32-row tiles re-read
-// (from L2) and re-widen the weights once per 32 rows.  Layer, us, streaming against big tiles (32 experts, H = I =
-// 2880): 32 rows per expert 170 / 185, 41 rows 183 / 186, 50 rows 192 / 189, 64 rows 211 / 210, 77 rows 249 / 220.
-// The 64-row shape serves what the big tiles do not take (K < 512).
+// Which kernel shape a launch uses.  K: length of a weight row.
 enum W4Shape { W4_TILE64, W4_STREAM, W4_BIG };
-W4Shape w4_shape(int variant, int64_t A, int E, int K)
+hipError_t w4_shape(int pinned, bool gated, int64_t A, int E, int N, int K, W4Shape* v)
 {
-    W4Shape v = A <= (int64_t)48 * E ? W4_STREAM : W4_BIG;
-    if (variant == MOE_FFN_W4_TILE64) v = W4_TILE64;
-    if (variant == MOE_FFN_W4_STREAM) v = W4_STREAM;
-    if (variant == MOE_FFN_W4_BIG) v = W4_BIG;
-    if (v == W4_BIG && K < 512) v = W4_TILE64;      // 16 scale bytes per row, eight stages
-    return v;
+    const int cols = gated ? kW4BN / 2 : kW4BN;      // per tile, in all three shapes
+    static_assert(kW4BN == kBigBN, "one number of columns");
+    const int64_t n_tiles = (N + cols - 1) / cols;
+    // (the big tiles read 16 scale bytes of a row at a time and run eight stages ahead; their tile list has a limit)
+    const bool big_runs = K >= 512 && big_list_fits(A, E, n_tiles);
+    *v = W4_TILE64;
+    if (pinned == MOE_FFN_W4_TILE64 || (pinned == MOE_FFN_W4_BIG && !big_runs)) return hipSuccess;
+    *v = W4_BIG;
+    if (pinned == MOE_FFN_W4_BIG) return hipSuccess;
+    // The streaming shape up to 48 rows per expert on average.  Its 32-row tiles re-read (from L2) and re-widen the weights
+    // once per 32 rows.  Layer, us, streaming against big tiles (32 experts, H = I = 2880): 32 rows per expert 170 / 185,
+    // 41 rows 183 / 186, 50 rows 192 / 189, 64 rows 211 / 210, 77 rows 249 / 220.
+    *v = W4_STREAM;
+    if (pinned == MOE_FFN_W4_STREAM || A <= (int64_t)48 * E) return hipSuccess;
+    int cus = 0;
+    const hipError_t e = compute_units(&cus);
+    if (e != hipSuccess) return e;
+    // Few tiles: a launch that leaves compute units without a block is bound by the chain of one tile, which is shortest
+    // with 32 rows and longest with the big tiles' start and end.  Up to one streaming tile per unit (gate_up, us,
+    // streaming / 64-row / big): 8 experts, H = I = 1024, 96 rows, 224 tiles expected 18.5 / 19.8 / 23.6, 130 rows, 292 tiles
+    // 23.0 / 20.6 / 24.3; H = 2048, I = 768, 130 rows, 219 tiles 26.8 / 31.7 / 35.3.  Rows of up to four stages are level or
+    // better with 64 rows (down, 95 rows, 224 tiles: K = 256 13.0 / 12.9; K = 448 13.2 / 15.5).
+    if (K >= 320 && tiles_expected(A, E, kS4Rows, n_tiles) <= cus) return hipSuccess;
+    // 64-row tiles up to one per unit, unless the experts' rows fit one tile of either shape, and up to two (which share a
+    // unit) for rows of up to eleven stages: K = 1024, 8 experts, 200 rows, 232 tiles 21.4 / 24.0 (64-row / big), 400 rows, 432
+    // tiles 25.9 / 25.2, 32 experts, 48 rows, 164 tiles 20.6 / 19.1; K = 2048, 130 rows, 324 tiles 41.5 / 36.3; K = 512, 8 experts,
+    // 1000 rows, 516 tiles 18.4 / 20.7, 64 experts, 96 rows, 512 tiles 18.0 / 20.8, 130 rows, 648 tiles 26.1 / 21.7; K = 704,
+    // 32 experts, 130 rows, 486 tiles 21.4 / 22.7.
+    *v = W4_TILE64;
+    const int64_t limit = K < 768 ? 2 * cus : A > (int64_t)64 * E ? cus : 0;
+    if (!big_runs || tiles_expected(A, E, kW4Rows, n_tiles) <= limit) return hipSuccess;
+    *v = W4_BIG;
+    return hipSuccess;
 }
 
 template <bool GATED, bool OUT_F32, bool MAPPED>
@@ -1093,9 +1117,9 @@ hipError_t launch_w4(int variant, RowSrc X, int ldx, const int32_t* row_map, int
     if (!GATED && row_map != nullptr) return hipErrorInvalidValue;      // (only the gate_up GEMM is ever called with a row map)
     // the streaming kernel takes a row's address mod 128 for a multiple of 32 (the callers check it)
     if ((reinterpret_cast<uintptr_t>(W) & 31u) != 0) return hipErrorInvalidValue;
-    W4Shape shape = w4_shape(variant, A, E, K);
-    if (shape == W4_BIG && !big_list_fits(A, E, (N + (GATED ? kBigBN / 2 : kBigBN) - 1) / (GATED ? kBigBN / 2 : kBigBN)))
-        shape = W4_TILE64;
+    W4Shape shape;
+    hipError_t e = w4_shape(variant, GATED, A, E, N, K, &shape);
+    if (e != hipSuccess) return e;
     if (shape == W4_BIG) {
         if (row_map)
             return launch_w4_big<GATED, OUT_F32, GATED>(X, ldx, row_map, map_div, offsets, E, A, W, S, rows_per_expert, N, K, Out, ldo, s);
@@ -1112,7 +1136,7 @@ hipError_t launch_w4(int variant, RowSrc X, int ldx, const int32_t* row_map, int
                        : grouped_gemm_w4_kernel<GATED, OUT_F32>;
     static bool attr_set[3][kMaxDevices] = {};
     const int which = stream ? (odd ? 2 : 1) : 0;
-    hipError_t e = ensure_lds_limit(kern, lds_bytes, attr_set[which]);
+    e = ensure_lds_limit(kern, lds_bytes, attr_set[which]);
     if (e != hipSuccess) return e;
     const int64_t n_tiles = (N + NO - 1) / NO;
     const int64_t m_tiles_max = (A + tile_rows - 1) / tile_rows + (A < E ? A : E);
@@ -1143,9 +1167,11 @@ hipError_t launch_ffn_down_w4(int variant, bool out_f32, const void* act, const 
                                    y_perm, H, s);
 }
 
-const char* ffn_w4_variant_name(int variant, int64_t A, int E, int H)
+const char* ffn_w4_variant_name(int variant, int64_t A, int E, int H, int I)
 {
-    switch (w4_shape(variant, A, E, H)) {
+    W4Shape v;
+    if (w4_shape(variant, true, A, E, I, H, &v) != hipSuccess) return "";
+    switch (v) {
         case W4_STREAM: return "grouped_gemm_w4_stream_kernel<gated>";
         case W4_BIG: return "grouped_gemm_w4_big_kernel<gated>";
         default: return "grouped_gemm_w4_kernel<gated>";

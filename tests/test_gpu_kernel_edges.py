@@ -264,6 +264,34 @@ def test_w4_big_tiles(gpu_lib, H, I, rows):
     assert all(torch.equal(a, b) for a, b in zip(ys["w4_tile64"], ys["w4_big"]))
 
 
+# The MXFP4 rule: streaming up to 48 rows per expert, and beyond up to one of its tiles per compute unit (256 units); then 64-row
+# tiles up to one per unit (from 64 rows per expert; two for rows of up to eleven stages) and for rows under 512 values; else the big ones
+STREAM4, TILE4, BIG4 = "w4_stream", "w4_kernel", "w4_big"
+
+
+@pytest.mark.parametrize("H,E,I,T,want", [
+    (2880, 32, 2880, 32 * 48, STREAM4),
+    (2880, 32, 2880, 32 * 48 + 1, BIG4),
+    (1024, 8, 1024, 8 * 112, STREAM4),         # (28 + 4) x 8 streaming tiles
+    (1024, 8, 1024, 8 * 116, TILE4),           # (29 + 4) x 8
+    (1024, 8, 1024, 8 * 224, TILE4),           # (28 + 4) x 8 tiles of 64 rows
+    (1024, 8, 1024, 8 * 232, BIG4),
+    (512, 4, 512, 4 * 500, STREAM4),           # (62 + 2) x 4 streaming tiles
+    (512, 8, 512, 8 * 900, TILE4),             # (112 + 4) x 4
+    (512, 8, 512, 8 * 1100, BIG4),             # (137 + 4) x 4
+    (1024, 32, 640, 32 * 60, BIG4),            # (30 + 16) x 5, but an expert's rows fit one tile
+    (256, 8, 2048, 8 * 60, TILE4),             # short rows
+])
+def test_w4_shape_rule_and_names(gpu_lib, H, E, I, T, want):
+    if torch.cuda.get_device_properties(0).multi_processor_count != 256:
+        pytest.skip("the rule counts compute units")
+    ctx = gpu_lib.Context(H, E, 1, I, torch.bfloat16, max_tokens=2, device=DEV, weight_format="mxfp4")
+    assert want in ctx.moe_ffn_variant(T)
+    for pin, name in (("w4_stream", STREAM4), ("w4_tile64", TILE4), ("w4_big", BIG4 if H >= 512 else TILE4)):
+        ctx.moe_set_ffn_variant(pin)
+        assert name in ctx.moe_ffn_variant(T)
+
+
 def test_w4_big_tiles_against_the_oracle(gpu_lib):
     H, I, E, K, T = 640, 576, 4, 2, 300
     w = inputs.Workload("w4o", H=H, E=E, K=K, I=I, n_layers=1, D=0, P=T, dtype="bf16", seed=43, residual=False,
