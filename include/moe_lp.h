@@ -261,8 +261,8 @@ moe_status moe_reset_counters(moe_ctx *ctx, void *stream);
  * moe_group_forward with HIP events on the caller's stream.  kernel_mask has bit (1 << id) set for
  * every moe_kernel_id to time; 0 switches timing off.  Setting the mask discards earlier records.
  * moe_read_kernel_timing synchronises `stream` and returns the summed duration (milliseconds) and
- * the number of timed launches of one kernel since the mask was set.  (The permutation may be two
- * launches; they are timed as one.  The routing of a small batch is a single launch, timed as
+ * the number of timed launches of one kernel since the mask was set.  (The permutation may be up to
+ * three launches; they are timed as one.  The routing of a small batch is a single launch, timed as
  * MOE_KERNEL_ROUTER_LOGITS.)
  */
 typedef enum {

@@ -38,9 +38,46 @@ __global__ __launch_bounds__(kPermThreads) void permute_hist_kernel(const int32_
     for (int e = threadIdx.x; e < E; e += kPermThreads) tile_hist[(int64_t)blockIdx.x * E + e] = hist[e];
 }
 
+// Between the passes, for many tiles (see launch_permute): tile_hist[tile][e] becomes the sum over the tiles in front,
+// tile_hist[n_tiles][e] the sum over all.  A block takes 64 experts, one per lane; each wave sums a run of tiles, the
+// waves' sums meet in LDS, then the wave writes its run's running sums.
+__global__ __launch_bounds__(kPermThreads) void permute_scan_kernel(int32_t* __restrict__ tile_hist, int n_tiles, int E)
+{
+    __shared__ int32_t wave_sum[kPermWaves][64];
+    const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
+    const int e = (int)blockIdx.x * 64 + lane;
+    const int run = (n_tiles + kPermWaves - 1) / kPermWaves;
+    const int first = wave * run < n_tiles ? wave * run : n_tiles;
+    const int last = first + run < n_tiles ? first + run : n_tiles;
+    int sum = 0;
+    if (e < E)
+#pragma unroll 8
+        for (int t = first; t < last; ++t) sum += tile_hist[(int64_t)t * E + e];
+    wave_sum[wave][lane] = sum;
+    __syncthreads();
+    int before = 0;
+    for (int w = 0; w < wave; ++w) before += wave_sum[w][lane];
+    if (e < E) {
+        constexpr int AHEAD = 8;       // rows fetched in front of the chain of sums
+        for (int t0 = first; t0 < last; t0 += AHEAD) {
+            int h[AHEAD];
+#pragma unroll
+            for (int i = 0; i < AHEAD; ++i) h[i] = t0 + i < last ? tile_hist[(int64_t)(t0 + i) * E + e] : 0;
+#pragma unroll
+            for (int i = 0; i < AHEAD; ++i) {
+                if (t0 + i < last) tile_hist[(int64_t)(t0 + i) * E + e] = before;
+                before += h[i];
+            }
+        }
+        if (wave == kPermWaves - 1) tile_hist[(int64_t)n_tiles * E + e] = before;
+    }
+}
+
 // Pass 2: every block derives the global offsets (all tiles' histograms are tiny) and the
 // start of its own tile inside each expert, then ranks and scatters its assignments.
 // With a single tile the block builds the histogram itself and pass 1 is skipped.
+// SCANNED: the sums over the tiles are already in tile_hist.
+template <bool SCANNED>
 __global__ __launch_bounds__(kPermThreads) void permute_scatter_kernel(
     const int32_t* __restrict__ idx, int64_t A, int E, int n_tiles, const int32_t* __restrict__ tile_hist,
     int32_t* __restrict__ counts, int32_t* __restrict__ offsets, int32_t* __restrict__ perm,
@@ -60,7 +97,12 @@ __global__ __launch_bounds__(kPermThreads) void permute_scatter_kernel(
     }
     for (int i = tid; i < kPermWaves * kMaxExperts; i += kPermThreads) (&wave_cnt[0][0])[i] = 0;
     __syncthreads();
-    if (n_tiles == 1) {
+    if (SCANNED) {
+        for (int e = tid; e < E; e += kPermThreads) {
+            total[e] = tile_hist[(int64_t)n_tiles * E + e];
+            start[e] = tile_hist[(int64_t)tile * E + e];
+        }
+    } else if (n_tiles == 1) {
         for (int i = tid; i < kPermTile; i += kPermThreads)
             if (base + i < A) atomicAdd(&total[clamp_expert(idx[base + i], E)], 1);
     } else {
@@ -120,7 +162,7 @@ __global__ __launch_bounds__(kPermThreads) void permute_scatter_kernel(
     }
     __syncthreads();
 
-    // Rank inside the wave's 512-assignment region, chunk by chunk in index order.
+    // Rank inside the wave's region of kPermRounds * 64 assignments, chunk by chunk in index order.
     int nbits = 0;
     while ((1 << nbits) < E) ++nbits;
     int my_e[kPermRounds], my_rank[kPermRounds];
@@ -201,8 +243,20 @@ hipError_t launch_permute(const int32_t* idx, int64_t A, int E, int32_t* counts,
         hipError_t e = hipGetLastError();
         if (e != hipSuccess) return e;
     }
-    permute_scatter_kernel<<<n_tiles, kPermThreads, 0, s>>>(idx, A, E, n_tiles, tile_hist, counts, offsets, perm,
-                                                            inv, active_total);
+    // Every block of the scatter reads all histograms, which grows with the square of their number: beyond 2^25 words read in
+    // all, a pass over the tiles (one more launch) is cheaper.  Permutation alone, us, without / with it: 512 experts:
+    // 786432 assignments 37.4 / 20.3, 2 M 140 / 38, 8 M 1628 / 127; 128 experts: 2 M 49.4 / 32.7, 8 M 435 / 109.  At the border
+    // (524288 and 1 M) the direct sums take 23 and 21 us.
+    if ((int64_t)n_tiles * n_tiles * E > ((int64_t)1 << 25)) {
+        permute_scan_kernel<<<(E + 63) / 64, kPermThreads, 0, s>>>(tile_hist, n_tiles, E);
+        const hipError_t e = hipGetLastError();
+        if (e != hipSuccess) return e;
+        permute_scatter_kernel<true><<<n_tiles, kPermThreads, 0, s>>>(idx, A, E, n_tiles, tile_hist, counts, offsets, perm,
+                                                                      inv, active_total);
+    } else {
+        permute_scatter_kernel<false><<<n_tiles, kPermThreads, 0, s>>>(idx, A, E, n_tiles, tile_hist, counts, offsets, perm,
+                                                                       inv, active_total);
+    }
     return hipGetLastError();
 }
 

@@ -64,6 +64,39 @@ def test_one_launch_routing_equals_the_steps(gpu_lib, T, E, K):
         assert ctx.moe_read_counters().active_experts_total == 2 * int((counts > 0).sum())
 
 
+# Many permutation tiles: from 2^25 histogram words read in all (tiles squared times experts), the tiles' running sums come from
+# a pass of their own; one tile to either side of the border, 64-expert groups that are not whole
+@pytest.mark.parametrize("T,K,E", [(65536, 8, 512), (65537, 8, 512), (300000, 5, 65), (1 << 20, 8, 3)])
+def test_permute_many_tiles(gpu_lib, T, K, E):
+    gen = torch.Generator(device=DEV).manual_seed(T + E)
+    idx = torch.randint(0, E, (T, K), generator=gen, dtype=torch.int32, device=DEV)
+    idx = torch.minimum(idx, torch.randint(0, E, (T, K), generator=gen, dtype=torch.int32, device=DEV))      # skewed
+    ctx = gpu_lib.Context(8, E, min(K, E), 8, torch.bfloat16, max_tokens=T * K // min(K, E) + 1, device=DEV)
+    flat = idx.reshape(-1)[:T * K // ctx.K * ctx.K].reshape(-1, ctx.K)
+    counts, offsets, perm, inv, _ = ctx.moe_permute(None, flat, want_x_perm=False)
+    order = torch.sort(flat.reshape(-1).long(), stable=True)
+    assert torch.equal(perm.long(), order.indices)
+    assert torch.equal(flat.reshape(-1)[perm.long()].long(), order.values)
+    assert torch.equal(inv[perm.long()].long(), torch.arange(perm.numel(), device=DEV))
+    want = torch.bincount(flat.reshape(-1).long(), minlength=E)
+    assert torch.equal(counts.long(), want)
+    assert torch.equal(offsets.long(), torch.cat([torch.zeros(1, dtype=torch.long, device=DEV), want.cumsum(0)]))
+
+
+def test_layer_of_many_permutation_tiles(gpu_lib):
+    """The same with the histograms counted by the top-k kernel: a layer against its steps."""
+    T, K, E, H, I = 65600, 8, 512, 8, 8
+    w = inputs.Workload("tiles", H=H, E=E, K=K, I=I, n_layers=1, D=0, P=T, dtype="bf16", seed=81, residual=False)
+    L = inputs.make_layer(w, 0, device=DEV)
+    x = inputs.randn((T, H), 1.0, 81, "x", 0, "bf16", DEV)
+    ctx = gpu_lib.Context(H, E, K, I, torch.bfloat16, max_tokens=T, residual=False, device=DEV)
+    idx, wt = ctx.moe_router_topk(x, L["w_router"])
+    _, offsets, _, inv, x_perm = ctx.moe_permute(x, idx)
+    y = ctx.moe_combine(ctx.moe_grouped_ffn(x_perm, offsets, L["w_gate_up"], L["w_down"]), inv, wt)
+    for _ in range(2):
+        assert torch.equal(ctx.moe_group_forward([L], None, x)[1], y)
+
+
 # Fewer than K finite logits: a removed expert and one at -infinity compare equal, so a token may list an expert twice (the
 # second time with weight 0); NaN compares with nothing.  The permutation stays one, on either routing path.
 @pytest.mark.parametrize("E,K,T", [(8, 3, 5), (40, 16, 16), (128, 8, 70), (256, 5, 256), (257, 3, 256), (128, 8, 300)])
