@@ -64,6 +64,29 @@ def test_one_launch_routing_equals_the_steps(gpu_lib, T, E, K):
         assert ctx.moe_read_counters().active_experts_total == 2 * int((counts > 0).sum())
 
 
+# The same at hidden sizes whose rows are long enough for the ring of asynchronous loads (16 waves take 32-wide chunks in turn:
+# four chunks per wave and more from H = 1568 on): the ring once, with a tail and a partial chunk, twice; both types; a bias;
+# rows from two buffers
+@pytest.mark.parametrize("H,dtype", [(2048, "bf16"), (2888, "bf16"), (4096, "bf16"), (2048, "f32"), (2888, "f32")])
+@pytest.mark.parametrize("T", [1, 40, 256])
+def test_one_launch_routing_of_long_rows(gpu_lib, H, dtype, T):
+    E, K, I = 72, 4, 64
+    w = inputs.Workload("long", H=H, E=E, K=K, I=I, n_layers=1, D=T // 2, P=T - T // 2, dtype=dtype, seed=H + T)
+    L = {k: (v.to(DEV) if v is not None else None) for k, v in inputs.make_layer(w, 0).items()}
+    L["router_bias"] = inputs.randn((E,), 0.3, w.seed, "bias", 0, "f32").to(DEV)
+    xd, xp = inputs.make_hidden(w, device=DEV)
+    x = torch.cat([xd, xp])
+    ctx = gpu_lib.Context(H, E, K, I, inputs.torch_dtype(dtype), max_tokens=T, residual=False, device=DEV)
+    idx, wt = ctx.moe_router_topk(x, L["w_router"], L["router_bias"])
+    o_idx, _ = oracle.router_topk(inputs.to_numpy(x), inputs.to_numpy(L["w_router"]), inputs.to_numpy(L["router_bias"]), K)
+    assert (idx.cpu().numpy() == o_idx).all()
+    _, offsets, _, inv, x_perm = ctx.moe_permute(x, idx)
+    y_steps = ctx.moe_combine(ctx.moe_grouped_ffn(x_perm, offsets, L["w_gate_up"], L["w_down"]), inv, wt)
+    for _ in range(2):
+        yd, yp = ctx.moe_group_forward([L], xd if w.D else None, xp)
+        assert torch.equal(torch.cat([yd, yp]), y_steps)
+
+
 # Many permutation tiles: from 2^25 histogram words read in all (tiles squared times experts), the tiles' running sums come from
 # a pass of their own; one tile to either side of the border, 64-expert groups that are not whole
 @pytest.mark.parametrize("T,K,E", [(65536, 8, 512), (65537, 8, 512), (300000, 5, 65), (1 << 20, 8, 3)])
@@ -225,7 +248,7 @@ def test_shape_rule_and_names(gpu_lib, H, E, K, I, T, want):
 # tile's loads issued during the current one.  Checked against the oracle and, bit for bit, against the streaming shape.
 @pytest.mark.parametrize("H,I,rows", [
     (256, 256, [1]),                                       # one row, four stages, one tile for the whole chip
-    (256, 264, [255, 256, 257, 0, 31, 32, 33]),            # tile edges; ragged column tiles in both GEMMs (264; 256)
+    (256, 264, [255, 256, 257, 0, 31, 32, 33]),            # tile edges; a ragged column tile in gate_up (K = 264 keeps down off)
     (320, 512, [0] * 70 + [300] + [0] * 60 + [513]),       # experts in the second and third group of 64, the rest empty
     (264 * 8, 320, [40, 700, 1]),                          # 33 stages, a wide ragged output
     (256, 1024, [7 * i % 97 for i in range(130)]),         # many small experts: several tiles per block
@@ -244,6 +267,25 @@ def test_big_tiles_grouped_ffn(gpu_lib, H, I, rows):
     for _ in range(2):
         assert torch.equal(ctx.moe_grouped_ffn(*args), small)
     assert_close(small, dense_ffn(x_perm, offsets, L, "bf16", E), "bf16", "big tiles")
+
+
+# Columns that are a multiple of 8 only in the down GEMM (H = 328: K = 328 keeps gate_up off the pipelined kernels), in every
+# output format: the last 32-column block of a tile is stored in part
+@pytest.mark.parametrize("fmt", [{}, {"y_perm_f32": True}, {"y_perm_f32": True, "act_split": True}])
+@pytest.mark.parametrize("H,rows", [(328, [255, 0, 257, 40]), (264, [1, 300]), (8 * 67, [128] * 3)])
+def test_big_tiles_ragged_columns(gpu_lib, H, rows, fmt):
+    I, E, A = 512, len(rows), sum(rows)
+    w = inputs.Workload("ragged", H=H, E=E, K=1, I=I, n_layers=1, D=0, P=A, dtype="bf16", seed=33)
+    L = inputs.make_layer(w, 0)
+    x_perm = inputs.randn((A, H), 1.0, 33, "x_perm", 0, "bf16")
+    offsets = torch.tensor(np.concatenate([[0], np.cumsum(rows)]), dtype=torch.int32)
+    args = (x_perm.to(DEV), offsets.to(DEV), L["w_gate_up"].to(DEV), L["w_down"].to(DEV))
+    ctx = gpu_lib.Context(H, E, 1, I, torch.bfloat16, max_tokens=A, device=DEV, **fmt)
+    ctx.moe_set_ffn_variant("tile128")
+    ref = ctx.moe_grouped_ffn(*args)
+    ctx.moe_set_ffn_variant("big")
+    assert torch.equal(ctx.moe_grouped_ffn(*args), ref)
+    assert_close(ref, dense_ffn(x_perm, offsets, L, "bf16", E), "bf16", "ragged columns")
 
 
 @pytest.mark.parametrize("T,E,K,fmt", [(300, 5, 1, {}), (517, 9, 3, {}), (700, 65, 7, {"y_perm_f32": True}),

@@ -114,11 +114,13 @@ def test_step_calls_on_an_empty_batch(gpu_lib):
     (256, 512, 4, [130, 0, 1, 64], "bf16"),       # an empty expert, a 1-row expert, a ragged tile
     (256, 512, 3, [5, 200, 33], "f32"),
     (192, 72, 2, [257, 31], "bf16"),              # N and K tails: I = 72, H = 192
-    (256, 320, 5, [3, 0, 70, 1, 33], "bf16"),     # mean 21 rows/expert: streaming variant, one 32-row block per pass
+    (256, 320, 5, [3, 0, 70, 1, 33], "bf16"),     # mean 21 rows/expert: streaming
     (2880, 2880, 3, [8, 5, 11], "bf16"),          # decode-like: H = I = 2880 (tails in N), 8 rows per expert
-    (256, 328, 5, [40, 64, 65, 0, 100], "bf16"),  # mean 54 rows/expert: streaming variant, two row blocks per pass
+    (256, 328, 5, [40, 64, 65, 0, 100], "bf16"),  # mean 54 rows/expert: streaming, experts of several tiles
 ])
 def test_grouped_ffn_is_the_dense_swiglu_of_each_expert(gpu_lib, H, I, E, rows, dtype):
+    """On the kernels the library chooses: launches this small take the narrow streaming shape (every shape is pinned in
+    turn in test_gpu_kernel_edges.py)."""
     A = sum(rows)
     w = inputs.Workload("f", H=H, E=E, K=1, I=I, n_layers=1, D=0, P=A, dtype=dtype, seed=11)
     L = inputs.make_layer(w, 0)
