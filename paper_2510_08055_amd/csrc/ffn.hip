@@ -172,11 +172,11 @@ __global__ __launch_bounds__(256) void grouped_gemm_bf16_kernel(
 // ----------------------------------------------------------------------------------------------
 // Weight-streaming shape (few rows per expert): global -> LDS copies issued as direct-to-LDS loads
 // (global_load_lds_dwordx4: no staging registers, no LDS store instructions) into two rings of NS LDS slots, one for
-// the activation rows and one for the weight rows, each stage PBK (64 or 32) k-values deep; one barrier per stage.
+// the activation rows and one for the weight rows, each stage 64 k-values deep; one barrier per stage.
 // 64 x 128 tiles, 4 waves, 3 stages of 24 KB: two blocks share a compute unit.  Launches of few tiles take 32 x 64 tiles (one wave, 5 stages), short rows 256 x 256 (8
 // waves, 2 stages): see pick_variant.
 // NW waves arranged WM x WN.
-// One wave-level load moves 64 lanes x 16 B = 8 (or 16) whole tile rows into 1 KB of LDS.  LDS rows
+// One wave-level load moves 64 lanes x 16 B = 8 whole tile rows into 1 KB of LDS.  LDS rows
 // are unpadded (the hardware writes lanes contiguously), so bank conflicts on the 16-byte operand
 // reads are avoided by an XOR swizzle applied on the SOURCE side: LDS chunk c of tile row r holds
 // global 16-byte chunk c ^ swz(r).
@@ -188,13 +188,14 @@ __global__ __launch_bounds__(256) void grouped_gemm_bf16_kernel(
 // SPLIT: the intermediate is a pair of bf16 values, as in the kernel above.
 // MAPPED: the rows come through a row map (the fused gather of the gate_up GEMM); without one the look-ups and
 // their wait, a round trip to L2 at the start of every tile, are left out altogether.
-template <int RBM, int BN, int WM, int NS, int PBK, int MINW, int NW, bool GATED, bool OUT_F32, bool SPLIT, bool MAPPED>
+template <int RBM, int BN, int WM, int NS, int MINW, int NW, bool GATED, bool OUT_F32, bool SPLIT, bool MAPPED>
 __global__ __launch_bounds__(NW * 64, MINW) void grouped_gemm_bf16_pipe_kernel(
     RowSrc X, int ldx, const int32_t* __restrict__ row_map, int map_div,
     const int32_t* __restrict__ offsets, int E, const bf16_t* __restrict__ W, int64_t w_expert_stride, int N, int K,
     void* __restrict__ Out_, int ldo, int a_rows)
 {
     static_assert(!(GATED && OUT_F32), "the intermediate of the gated GEMM is always held in the activation dtype");
+    constexpr int PBK = 64;                      // k-values per stage
     constexpr int BM = RBM * 32, WN = NW / WM;   // NW waves arranged WM (rows) x WN (columns)
     constexpr int NO = GATED ? BN / 2 : BN;     // output columns per block
     constexpr int TM = RBM / WM;                // row blocks per wave: rb = wm + WM * i
@@ -209,7 +210,6 @@ __global__ __launch_bounds__(NW * 64, MINW) void grouped_gemm_bf16_pipe_kernel(
     constexpr int LPS = A_LPW + B_LPW;                  // load instructions per thread and stage
     constexpr int A_SLOT = BM * ROWB, B_SLOT = BN * ROWB;   // bytes of one stage of either operand
     constexpr int B_BASE = NS * A_SLOT;                 // the weight ring follows the activation ring
-    static_assert(PBK == 64 || PBK == 32, "stage depth must be 64 or 32");
     static_assert(RBM % WM == 0 && TM <= 4 && TNO >= 1, "bad tile configuration");
     static_assert(NS >= 2, "a stage is loaded while another is multiplied");
     static_assert(BM % (RPL * NW) == 0 && BN % (RPL * NW) == 0, "tile rows must split evenly over the waves");
@@ -268,7 +268,7 @@ __global__ __launch_bounds__(NW * 64, MINW) void grouped_gemm_bf16_pipe_kernel(
         else n = n0 + rb;
         if (n >= N) n = N - 1;
         if (GATED && rb >= NO) n += N;
-        b_src[p] = We + (int64_t)n * ldw + ((l_chunk ^ swz<PBK>(rb)) << 3);
+        b_src[p] = We + (int64_t)n * ldw + ((l_chunk ^ swz(rb)) << 3);
     }
     const uint32_t lds0 = lds_address(smem);
     auto issue_b = [&](int kt, int p) {
@@ -300,7 +300,7 @@ __global__ __launch_bounds__(NW * 64, MINW) void grouped_gemm_bf16_pipe_kernel(
     for (int p = 0; p < A_LPW; ++p) {
         const int tr = (wave + NW * p) * RPL + l_row;      // row inside the tile
         const int64_t src = MAPPED ? (int64_t)(a_row_id[p] / map_div) : (int64_t)a_row_id[p];
-        a_src[p] = row_ptr<bf16_t>(X, src, ldx) + ((l_chunk ^ swz<PBK>(tr)) << 3);
+        a_src[p] = row_ptr<bf16_t>(X, src, ldx) + ((l_chunk ^ swz(tr)) << 3);
     }
     // Loads of one stage, cut into KS parts that are issued in the shadow of the MFMAs of the KS
     // k-slices of the stage being multiplied: load q of the step (activation loads first) goes with slice q % KS.
@@ -317,7 +317,7 @@ __global__ __launch_bounds__(NW * 64, MINW) void grouped_gemm_bf16_pipe_kernel(
     };
     // ---- LDS byte offsets of the operand rows this lane feeds to the MFMAs ----
     const int fr = lane & 31, fq = lane >> 5;
-    const int fsw = swz<PBK>(fr);     // the swizzle only looks at the low 4 row bits; row blocks are 32 rows
+    const int fsw = swz(fr);     // the swizzle only looks at the low 4 row bits; row blocks are 32 rows
     int a_row[TM], b_row[TN], k_off[KS];
 #pragma unroll
     for (int i = 0; i < TM; ++i) a_row[i] = ((wm + WM * i) * 32 + fr) * ROWB;
@@ -431,100 +431,13 @@ __global__ __launch_bounds__(NW * 64, MINW) void grouped_gemm_bf16_pipe_kernel(
         for (; g < nk_ - 1; ++g) step(g, F{}, T{});
         step(g, F{}, F{});
 
-        // Epilogue.  A lane holds, for output row fr of a row block, groups of 4 consecutive columns
-        // (accumulator element v of tile (i, j): column (v/4)*8 + fq*4 + v%4); storing them directly
-        // would scatter 8-byte pieces over 32 rows per instruction.  Each wave instead turns one row block
-        // at a time (32 rows x WNO columns, at most 4 KB) through a private piece of LDS and writes it
-        // out as whole 16-byte chunks, consecutive lanes along a row (64- or 128-byte runs per row).
-        // The LDS used is an activation slot no stage occupies any more: stage nk-1, the last one, sits
-        // in slot (nk-1) % NS, and the readers of the other slots passed their barrier long ago, so no
-        // block barrier is needed; a wave's own LDS operations execute in program order.
-        constexpr int RB = TNO * 64;              // bytes of one row of the wave's output tile
-        constexpr int CPRW = TNO * 4;             // 16-byte chunks per such row
-        constexpr int REG = 32 * RB;              // bytes per wave
+        // The epilogue's LDS is an activation slot no stage occupies any more: stage nk-1, the last one, sits in slot
+        // (nk-1) % NS, and the readers of the other slots passed their barrier long ago.
+        constexpr int REG = TNO * 2048;           // bytes per wave
         constexpr int WPS = A_SLOT / REG;         // waves per free activation slot
-        constexpr int RPI = 64 / CPRW;            // rows one wave-level 16-byte access covers
-        static_assert(TNO <= 2 && WPS >= 1 && (NS - 1) * WPS >= NW, "the epilogue staging does not fit the free slots");
-        static_assert(!OUT_F32 || REG >= 4096, "a 32 x 32 float tile must fit the wave's staging piece");
-        if (TMV > 0 && OUT_F32) {
-            // float output: one 32 x 32 tile (4 KB: 32 rows of 8 16-byte chunks) at a time through the same
-            // private piece of LDS; a lane's 4 consecutive columns are one chunk, chunk c of row r sits in
-            // chunk slot c ^ (r & 7), and the tile goes out as 128-byte runs per row.
-            float* Out = static_cast<float*>(Out_);
-            char* epi = smem + ((nk_ + wave / WPS) % NS) * A_SLOT + (wave % WPS) * REG;
-#pragma unroll
-            for (int i = 0; i < TMV; ++i) {
-                const int64_t row_base = (int64_t)tc.row0 + (wm + WM * i) * 32;
-#pragma unroll
-                for (int j = 0; j < TNO; ++j) {
-#pragma unroll
-                    for (int a = 0; a < 4; ++a)
-                        *reinterpret_cast<float4*>(epi + fr * 128 + (((a * 2 + fq) ^ (fr & 7)) << 4)) =
-                            make_float4(acc[i][j][a * 4], acc[i][j][a * 4 + 1], acc[i][j][a * 4 + 2], acc[i][j][a * 4 + 3]);
-                    __builtin_amdgcn_wave_barrier();
-#pragma unroll
-                    for (int h = 0; h < 4; ++h) {
-                        const int r = h * 8 + (lane >> 3), c = lane & 7;
-                        const float4 v = *reinterpret_cast<const float4*>(epi + r * 128 + ((c ^ (r & 7)) << 4));
-                        const int64_t row = row_base + r;
-                        const int col = n0 + wn * WNO + j * 32 + c * 4;
-                        if (row < tc.row_end && col < N)    // N is a multiple of 8: the 4 columns are in or out together
-                            *reinterpret_cast<float4*>(Out + row * ldo + col) = v;
-                    }
-                    __builtin_amdgcn_wave_barrier();
-                }
-            }
-        } else if (TMV > 0) {
-            bf16_t* Out = static_cast<bf16_t*>(Out_);
-            char* epi = smem + ((nk_ + wave / WPS) % NS) * A_SLOT + (wave % WPS) * REG;
-            auto eswz = [](int r) { return (r >> (RB == 64 ? 2 : 1)) & (CPRW - 1); };
-            constexpr int PARTS = (SPLIT && GATED) ? 2 : 1;      // the values, then what their bf16 rounding left over
-#pragma unroll
-            for (int i = 0; i < TMV; ++i) {
-                if (GATED) {
-#pragma unroll
-                    for (int j = 0; j < TNO; ++j)
-#pragma unroll
-                        for (int v = 0; v < 16; ++v) {
-                            acc[i][j][v] = silu_mul(acc[i][j][v], acc[i][j + TNO][v]);
-                            if (SPLIT) acc[i][j][v] = opaque(acc[i][j][v]);
-                        }
-                }
-#pragma unroll
-                for (int part = 0; part < PARTS; ++part) {
-#pragma unroll
-                    for (int j = 0; j < TNO; ++j) {
-#pragma unroll
-                        for (int a = 0; a < 4; ++a) {
-                            float val[4];
-#pragma unroll
-                            for (int b = 0; b < 4; ++b) val[b] = acc[i][j][a * 4 + b];
-                            const uint32_t p01 = pack_bf16x2(val[0], val[1]), p23 = pack_bf16x2(val[2], val[3]);
-                            if (PARTS == 2 && part == 0) {      // keep the remainders for the second part
-                                acc[i][j][a * 4 + 0] = val[0] - __uint_as_float(p01 << 16);
-                                acc[i][j][a * 4 + 1] = val[1] - __uint_as_float(p01 & 0xffff0000u);
-                                acc[i][j][a * 4 + 2] = val[2] - __uint_as_float(p23 << 16);
-                                acc[i][j][a * 4 + 3] = val[3] - __uint_as_float(p23 & 0xffff0000u);
-                            }
-                            const int chunk = (j * 4 + a) ^ eswz(fr);
-                            *reinterpret_cast<uint2*>(epi + fr * RB + chunk * 16 + fq * 8) = make_uint2(p01, p23);
-                        }
-                    }
-                    __builtin_amdgcn_wave_barrier();
-                    const int64_t row_base = (int64_t)tc.row0 + (wm + WM * i) * 32;
-#pragma unroll
-                    for (int h = 0; h < 32 / RPI; ++h) {
-                        const int r = h * RPI + lane / CPRW, c = lane % CPRW;
-                        const uint4 v = *reinterpret_cast<const uint4*>(epi + r * RB + ((c ^ eswz(r)) * 16));
-                        const int64_t row = row_base + r;
-                        const int col = n0 + wn * WNO + c * 8;
-                        if (row < tc.row_end && col < N)    // N is a multiple of 8: a chunk is in or out as a whole
-                            *reinterpret_cast<uint4*>(Out + row * ldo + part * N + col) = v;
-                    }
-                    __builtin_amdgcn_wave_barrier();
-                }
-            }
-        }
+        static_assert(WPS >= 1 && (NS - 1) * WPS >= NW, "the epilogue staging does not fit the free slots");
+        store_tile<GATED, OUT_F32, SPLIT, TMV, TNO, WM>(acc, tc.row0, tc.row_end, wm, n0 + wn * WNO,
+                                                        smem + ((nk_ + wave / WPS) % NS) * A_SLOT + (wave % WPS) * REG, Out_, ldo, N);
     };
 
     // row blocks wm, wm + WM, ... below rb_valid belong to this wave
@@ -602,7 +515,7 @@ __global__ __launch_bounds__(kBigWaves * 64, 2) void grouped_gemm_bf16_big_kerne
 
     // Load p of this wave covers weight rows (wave + 8 p) * 8 .. + 7 of the tile, as on the activation side (BigRows).
     const int l_row = lane >> 3;
-    const uint32_t l_chunk = (uint32_t)((lane & 7) ^ swz<PBK>(wave * 8 + l_row)) * 16;
+    const uint32_t l_chunk = (uint32_t)((lane & 7) ^ swz(wave * 8 + l_row)) * 16;
 
     BigRows<MAPPED> rows(X, ldx, row_map, map_div, map_magic, a_rows, wave);
 
@@ -640,7 +553,7 @@ __global__ __launch_bounds__(kBigWaves * 64, 2) void grouped_gemm_bf16_big_kerne
     const int fr = lane & 31, fq = lane >> 5;
     uint32_t k_lane[KS];
 #pragma unroll
-    for (int kk = 0; kk < KS; ++kk) k_lane[kk] = lds0 + fr * ROWB + (((kk * 2 + fq) ^ swz<PBK>(fr)) << 4);
+    for (int kk = 0; kk < KS; ++kk) k_lane[kk] = lds0 + fr * ROWB + (((kk * 2 + fq) ^ swz(fr)) << 4);
     const uint32_t a_wave = wm * 32 * ROWB, b_wave = B_BASE + wn * WNO * ROWB;
 
     // ---- first tile: two weight stages and one activation stage ----
@@ -768,8 +681,8 @@ __global__ __launch_bounds__(kBigWaves * 64, 2) void grouped_gemm_bf16_big_kerne
         const uint32_t epi_slot = B_BASE + b_slot;
         step_tail(false);
 
-        big_epilogue<GATED, OUT_F32, SPLIT, TMV, TNO>(acc, cur, wm, cur.n_tile * NO + wn * WNO,
-                                                      smem + epi_slot + wave * (TNO * 2048), Out_, ldo, N);
+        store_tile<GATED, OUT_F32, SPLIT, TMV, TNO, WM>(acc, cur.row0, cur.row_end, wm, cur.n_tile * NO + wn * WNO,
+                                                        smem + epi_slot + wave * (TNO * 2048), Out_, ldo, N);
     };
 
     for (;;) {
@@ -1003,7 +916,7 @@ static hipError_t launch_pipe(RowSrc X, int ldx, const int32_t* row_map, int map
     constexpr int PBK = 64;
     constexpr int NO = GATED ? BN / 2 : BN;
     const size_t lds_bytes = (size_t)NS * (BM + BN) * PBK * 2;
-    auto kern = grouped_gemm_bf16_pipe_kernel<BM / 32, BN, WM, NS, PBK, MINW, NW, GATED, OUT_F32, SPLIT, MAPPED>;
+    auto kern = grouped_gemm_bf16_pipe_kernel<BM / 32, BN, WM, NS, MINW, NW, GATED, OUT_F32, SPLIT, MAPPED>;
     static bool attr_set[kMaxDevices] = {};
     hipError_t e = ensure_lds_limit(kern, lds_bytes, attr_set);
     if (e != hipSuccess) return e;
@@ -1114,9 +1027,9 @@ const char* ffn_variant_name(int dtype, int variant, int64_t A, int E, int H, in
     Variant v;
     if (pick_variant(variant, true, A, E, I, H, &v) != hipSuccess) return "";
     switch (v) {
-        case V_PIPE_SMALL: return "grouped_gemm_bf16_pipe_kernel<2,128,2,3,64,2,4,gated>";
-        case V_PIPE_FEW: return "grouped_gemm_bf16_pipe_kernel<1,64,1,5,64,1,1,gated>";
-        case V_PIPE_WIDE: return "grouped_gemm_bf16_pipe_kernel<8,256,2,2,64,2,8,gated>";
+        case V_PIPE_SMALL: return "grouped_gemm_bf16_pipe_kernel<2,128,2,3,2,4,gated>";
+        case V_PIPE_FEW: return "grouped_gemm_bf16_pipe_kernel<1,64,1,5,1,1,gated>";
+        case V_PIPE_WIDE: return "grouped_gemm_bf16_pipe_kernel<8,256,2,2,2,8,gated>";
         case V_PIPE_BIG: return "grouped_gemm_bf16_big_kernel<gated>";
         default: return "grouped_gemm_bf16_kernel<128,128,gated>";
     }

@@ -1,5 +1,5 @@
 // What the persistent 256 x 256 grouped GEMMs share (bf16 weights in ffn.hip, 4-bit weights in ffn_w4.hip): the tile
-// list a block works through, the activation rows of its tiles and the epilogue.
+// list a block works through and the activation rows of its tiles.
 #pragma once
 #include "ffn_tile.h"
 
@@ -274,7 +274,7 @@ template <bool MAPPED> struct BigRows {
         : X(X_), ldx(ldx_), row_map(row_map_), map_div(map_div_), map_magic(map_magic_), a_rows(a_rows_), wave(wave_),
           l_row(lane_id() >> 3), base(nullptr), live(0)
     {
-        l_chunk = (uint32_t)((lane_id() & 7) ^ swz<64>(wave * 8 + l_row)) * 16;
+        l_chunk = (uint32_t)((lane_id() & 7) ^ swz(wave * 8 + l_row)) * 16;
     }
 
     // The look-ups are loads issued from inline asm: through the compiler they would be waited for with vmcnt(0),
@@ -347,107 +347,6 @@ inline bool big_list_fits(int64_t A, int E, int64_t n_tiles)
 inline uint32_t map_magic_of(int map_div)
 {
     return map_div > 1 ? (uint32_t)((((uint64_t)1 << 32) + map_div - 1) / map_div) : 0;
-}
-
-// Stores a wave's accumulators of tile `cur`: TMV row blocks (wm, wm + 2, ...) by TNO * 32 output columns from `col0`
-// on.  `epi`: 32 * TNO * 64 bytes of LDS only this wave uses.
-template <bool GATED, bool OUT_F32, bool SPLIT, int TMV, int TNO, typename ACC>
-__device__ __forceinline__ void big_epilogue(ACC& acc, const BigTile& cur, int wm, int col0, char* epi, void* Out_, int ldo,
-                                             int N)
-{
-    if (TMV == 0) return;
-    constexpr int WM = 2;
-    // (the lane number as an unknown value: the compiler would otherwise work the addresses below out once, in front of
-    // the block's loop over its tiles, and hold them in registers the k-loop needs)
-    int lane = lane_id();
-    asm volatile("" : "+v"(lane));
-    const int fr = lane & 31, fq = lane >> 5;
-            // Epilogue.  A lane holds, for output row fr of a row block, groups of 4 consecutive columns
-            // (accumulator element v of tile (i, j): column (v/4)*8 + fq*4 + v%4); storing them directly
-            // would scatter 8-byte pieces over 32 rows per instruction.  Each wave instead turns one row block
-            // at a time (32 rows x WNO columns, at most 4 KB) through a private piece of LDS and writes it
-            // out as whole 16-byte chunks, consecutive lanes along a row (64- or 128-byte runs per row).
-            constexpr int RB = TNO * 64;              // bytes of one row of the wave's output tile
-            constexpr int CPRW = TNO * 4;             // 16-byte chunks per such row
-                    constexpr int RPI = 64 / CPRW;            // rows one wave-level 16-byte access covers
-            static_assert(TNO <= 2 && (!OUT_F32 || TNO == 2), "a 32 x 32 float tile must fit the wave's staging piece");
-            if constexpr (OUT_F32) {
-                // float output: one 32 x 32 tile (4 KB: 32 rows of 8 16-byte chunks) at a time through the same
-                // private piece of LDS; a lane's 4 consecutive columns are one chunk, chunk c of row r sits in
-                // chunk slot c ^ (r & 7), and the tile goes out as 128-byte runs per row.
-                float* Out = static_cast<float*>(Out_);
-            #pragma unroll
-                for (int i = 0; i < TMV; ++i) {
-                    const int64_t row_base = (int64_t)cur.row0 + (wm + WM * i) * 32;
-    #pragma unroll
-                    for (int j = 0; j < TNO; ++j) {
-    #pragma unroll
-                        for (int a = 0; a < 4; ++a)
-                            *reinterpret_cast<float4*>(epi + fr * 128 + (((a * 2 + fq) ^ (fr & 7)) << 4)) =
-                                make_float4(acc[i][j][a * 4], acc[i][j][a * 4 + 1], acc[i][j][a * 4 + 2], acc[i][j][a * 4 + 3]);
-                        __builtin_amdgcn_wave_barrier();
-    #pragma unroll
-                        for (int h = 0; h < 4; ++h) {
-                            const int r = h * 8 + (lane >> 3), c = lane & 7;
-                            const float4 v = *reinterpret_cast<const float4*>(epi + r * 128 + ((c ^ (r & 7)) << 4));
-                            const int64_t row = row_base + r;
-                            const int col = col0 + j * 32 + c * 4;
-                            if (row < cur.row_end && col < N)    // N is a multiple of 8: the 4 columns are in or out together
-                                *reinterpret_cast<float4*>(Out + row * ldo + col) = v;
-                        }
-                        __builtin_amdgcn_wave_barrier();
-                    }
-                }
-            } else {
-                bf16_t* Out = static_cast<bf16_t*>(Out_);
-                        auto eswz = [](int r) { return (r >> (RB == 64 ? 2 : 1)) & (CPRW - 1); };
-                constexpr int PARTS = (SPLIT && GATED) ? 2 : 1;      // the values, then what their bf16 rounding left over
-    #pragma unroll
-                for (int i = 0; i < TMV; ++i) {
-                    if (GATED) {
-    #pragma unroll
-                        for (int j = 0; j < TNO; ++j)
-    #pragma unroll
-                            for (int v = 0; v < 16; ++v) {
-                                acc[i][j][v] = silu_mul(acc[i][j][v], acc[i][j + TNO][v]);
-                                if (SPLIT) acc[i][j][v] = opaque(acc[i][j][v]);
-                            }
-                    }
-    #pragma unroll
-                    for (int part = 0; part < PARTS; ++part) {
-    #pragma unroll
-                        for (int j = 0; j < TNO; ++j) {
-    #pragma unroll
-                            for (int a = 0; a < 4; ++a) {
-                                float val[4];
-    #pragma unroll
-                                for (int b = 0; b < 4; ++b) val[b] = acc[i][j][a * 4 + b];
-                                const uint32_t p01 = pack_bf16x2(val[0], val[1]), p23 = pack_bf16x2(val[2], val[3]);
-                                if (PARTS == 2 && part == 0) {      // keep the remainders for the second part
-                                    acc[i][j][a * 4 + 0] = val[0] - __uint_as_float(p01 << 16);
-                                    acc[i][j][a * 4 + 1] = val[1] - __uint_as_float(p01 & 0xffff0000u);
-                                    acc[i][j][a * 4 + 2] = val[2] - __uint_as_float(p23 << 16);
-                                    acc[i][j][a * 4 + 3] = val[3] - __uint_as_float(p23 & 0xffff0000u);
-                                }
-                                const int chunk = (j * 4 + a) ^ eswz(fr);
-                                *reinterpret_cast<uint2*>(epi + fr * RB + chunk * 16 + fq * 8) = make_uint2(p01, p23);
-                            }
-                        }
-                        __builtin_amdgcn_wave_barrier();
-                        const int64_t row_base = (int64_t)cur.row0 + (wm + WM * i) * 32;
-    #pragma unroll
-                        for (int h = 0; h < 32 / RPI; ++h) {
-                            const int r = h * RPI + lane / CPRW, c = lane % CPRW;
-                            const uint4 v = *reinterpret_cast<const uint4*>(epi + r * RB + ((c ^ eswz(r)) * 16));
-                            const int64_t row = row_base + r;
-                            const int col = col0 + c * 8;
-                            if (row < cur.row_end && col < N)    // N is a multiple of 8: a chunk is in or out as a whole
-                                *reinterpret_cast<uint4*>(Out + row * ldo + part * N + col) = v;
-                        }
-                        __builtin_amdgcn_wave_barrier();
-                    }
-                }
-            }
 }
 
 }  // namespace moe

@@ -226,7 +226,7 @@ __global__ __launch_bounds__(kW4Waves * 64, 2) void grouped_gemm_w4_kernel(
     for (int p = 0; p < A_LPW; ++p) {
         const int tr = (wave + NW * p) * 8 + a_lrow;
         const int64_t src = row_map ? (int64_t)(a_row_id[p] / map_div) : (int64_t)a_row_id[p];
-        a_src[p] = row_ptr<bf16_t>(X, src, ldx) + ((a_chunk ^ swz<64>(tr)) << 3);
+        a_src[p] = row_ptr<bf16_t>(X, src, ldx) + ((a_chunk ^ swz(tr)) << 3);
     }
     // A load whose 8 tile rows all lie past the tile's last row is left out (a decode batch puts a
     // handful of rows into a 64-row tile; with 4-bit weights the activation tile would otherwise be most
@@ -252,7 +252,7 @@ __global__ __launch_bounds__(kW4Waves * 64, 2) void grouped_gemm_w4_kernel(
 
     // ---- LDS offsets of the operand rows this lane feeds to the MFMAs ----
     const int fr = lane & 31, fq = lane >> 5;
-    const int fsw = swz<64>(fr);
+    const int fsw = swz(fr);
     const int a_off = fr * A_ROWB;                 // row block i: + i * 32 * A_ROWB
     int b_off[TN], s_row[TN], b_sw[TN];
 #pragma unroll
@@ -622,7 +622,7 @@ __global__ __launch_bounds__(kS4Waves * 64, 4) void grouped_gemm_w4_stream_kerne
         for (int i = 0; i < 8; ++i) keep_piece(s_raw[i], i < s_row_pieces ? i : s_row_pieces - 1, s_lo[i], s_hi[i]);
         const int tr = wave * 8 + a_lrow;
         const int64_t src = row_map ? (int64_t)(a_row_id / map_div) : (int64_t)a_row_id;
-        a_src = row_ptr<bf16_t>(X, src, ldx) + ((a_chunk ^ swz<64>(tr)) << 3);
+        a_src = row_ptr<bf16_t>(X, src, ldx) + ((a_chunk ^ swz(tr)) << 3);
     }
     issue_stage(-3, 0);
     issue_stage(-2, 1);
@@ -637,7 +637,7 @@ __global__ __launch_bounds__(kS4Waves * 64, 4) void grouped_gemm_w4_stream_kerne
     const uint32_t lds0 = (uint32_t)(uintptr_t)(lds_ptr_t*)smem;
     uint32_t a_rd[4];
 #pragma unroll
-    for (int j4 = 0; j4 < 4; ++j4) a_rd[j4] = lds0 + fr * A_ROWB + (((fq * 4 + j4) ^ swz<64>(fr)) << 4);
+    for (int j4 = 0; j4 < 4; ++j4) a_rd[j4] = lds0 + fr * A_ROWB + (((fq * 4 + j4) ^ swz(fr)) << 4);
     const uint32_t b_rd = lds0 + B_BASE + b_off;
     const uint32_t b_rd_odd = b_rd + ((fq ^ (b_sw & 1)) << 4);
     // token columns past the tile's rows are never stored: their lanes skip the activation reads (with a
@@ -819,7 +819,7 @@ __global__ __launch_bounds__(kBigWaves * 64, 2) void grouped_gemm_w4_big_kernel(
     const int lane = lane_id();
     const int wave = __builtin_amdgcn_readfirstlane((int)(threadIdx.x >> 6));
     const int wm = wave / WN, wn = wave % WN;
-    const int nk = K / PBK, nd = (nk + 1) / 2, n_chunks = (nk + 7) / 8;
+    const int nk = K / PBK, nd = (nk + 1) / 2;
     const bool odd = (nk & 1) != 0;
     const uint32_t row_bytes = (uint32_t)K / 2, row_scales = (uint32_t)K / 32;
 
@@ -889,7 +889,7 @@ __global__ __launch_bounds__(kBigWaves * 64, 2) void grouped_gemm_w4_big_kernel(
     const int fr = lane & 31, fq = lane >> 5;
     uint32_t k_lane[KS];                 // activation chunk of slice kk: k-values 32 fq + 8 kk .. + 7 of the stage
 #pragma unroll
-    for (int kk = 0; kk < KS; ++kk) k_lane[kk] = lds0 + fr * ROWB + (((fq * 4 + kk) ^ swz<PBK>(fr)) << 4);
+    for (int kk = 0; kk < KS; ++kk) k_lane[kk] = lds0 + fr * ROWB + (((fq * 4 + kk) ^ swz(fr)) << 4);
     const uint32_t w_lane = lds0 + B_BASE + fr * 64 + ((fq ^ ((fr >> 2) & 3)) << 4);    // the even stage's block; odd: ^ 32
     const uint32_t s_lane = lds0 + S_BASE + fr * 16 + fq;
     const uint32_t a_wave = wm * 32 * ROWB;
@@ -1006,9 +1006,9 @@ __global__ __launch_bounds__(kBigWaves * 64, 2) void grouped_gemm_w4_big_kernel(
             rows.issue(s + 2, lds0 + a_slot);
             step_tail(s, s + 1);
         }
-        // step nk - 3: look-ups and scales of the next tile
+        // step nk - 3: look-ups and scales of the next tile (its first codes are on their way: the last piece of this tile went
+        // out two steps ago or earlier)
         rows.look_up(nxt);
-        if (np == 2 * nd) use_weights(nxt);
         use_scales(nxt);
         issue_scales(0);
         issue_piece();
@@ -1026,8 +1026,8 @@ __global__ __launch_bounds__(kBigWaves * 64, 2) void grouped_gemm_w4_big_kernel(
         step_head(std::integral_constant<int, 1>{});
         const uint32_t epi_slot = a_slot;        // every wave has read the last stage: its activation slot is free
         step_tail(nk - 1, -1);
-        big_epilogue<GATED, OUT_F32, false, TMV, TNO>(acc, cur, wm, cur.n_tile * NO + wn * WNO,
-                                                      smem + epi_slot + wave * (TNO * 2048), Out_, ldo, N);
+        store_tile<GATED, OUT_F32, false, TMV, TNO, WM>(acc, cur.row0, cur.row_end, wm, cur.n_tile * NO + wn * WNO,
+                                                        smem + epi_slot + wave * (TNO * 2048), Out_, ldo, N);
     };
 
     for (;;) {

@@ -223,18 +223,18 @@ __device__ __forceinline__ void logits_tile(const RowSrc& x, int64_t n_tok, int 
     }
 }
 
-template <typename T, int NW>
-__global__ __launch_bounds__(NW * 64) void router_logits_kernel(RowSrc x, int64_t n_tok, int H,
-                                                                const T* __restrict__ wr,
-                                                                const float* __restrict__ bias, int E,
-                                                                double* __restrict__ logits,
-                                                                int32_t* __restrict__ zero_buf, int zero_n)
+template <typename T>
+__global__ __launch_bounds__(256) void router_logits_kernel(RowSrc x, int64_t n_tok, int H,
+                                                            const T* __restrict__ wr,
+                                                            const float* __restrict__ bias, int E,
+                                                            double* __restrict__ logits,
+                                                            int32_t* __restrict__ zero_buf, int zero_n)
 {
     // side job of block (0,0): clear the per-tile expert histogram that the top-k kernel, next on the
     // stream, counts into (saves a separate fill launch)
     if (blockIdx.x == 0 && blockIdx.y == 0)
-        for (int i = threadIdx.x; i < zero_n; i += NW * 64) zero_buf[i] = 0;
-    logits_tile<T, NW, false>(x, n_tok, H, wr, bias, E, logits, (int64_t)blockIdx.x * 16, (int)blockIdx.y * 16);
+        for (int i = threadIdx.x; i < zero_n; i += 256) zero_buf[i] = 0;
+    logits_tile<T, 4, false>(x, n_tok, H, wr, bias, E, logits, (int64_t)blockIdx.x * 16, (int)blockIdx.y * 16);
 }
 
 // (value, index) "greater" under the routing order: larger logit first, equal logits by lower index.
@@ -627,10 +627,10 @@ hipError_t launch_router_logits(int dtype, RowSrc x, int64_t T, int H, const voi
 {
     dim3 grid((unsigned)((T + 15) / 16), (unsigned)((E + 15) / 16));
     if (dtype == MOE_BF16)
-        router_logits_kernel<bf16_t, 4><<<grid, 256, 0, s>>>(x, T, H, (const bf16_t*)w_router, bias, E, logits, zero_buf,
+        router_logits_kernel<bf16_t><<<grid, 256, 0, s>>>(x, T, H, (const bf16_t*)w_router, bias, E, logits, zero_buf,
                                                           zero_n);
     else
-        router_logits_kernel<float, 4><<<grid, 256, 0, s>>>(x, T, H, (const float*)w_router, bias, E, logits, zero_buf,
+        router_logits_kernel<float><<<grid, 256, 0, s>>>(x, T, H, (const float*)w_router, bias, E, logits, zero_buf,
                                                          zero_n);
     return hipGetLastError();
 }

@@ -215,7 +215,7 @@ def test_wide_tiles_grouped_ffn(gpu_lib, H, I, rows):
 # The shape a launch takes is the one moe_ffn_variant names: pinned, or by the rule.  By the rule: a streaming shape up to 56
 # rows per expert, and beyond as long as its tiles are one round (two per compute unit, 512 on 256 units); narrow tiles while
 # these are less than one round.
-FEW, SMALL, BIG, WIDE = "<1,64,1,5,64,1,1,", "<2,128,2,3,64,2,4,", "big", "<8,256,2,2,64,2,8,"
+FEW, SMALL, BIG, WIDE = "<1,64,1,5,1,1,", "<2,128,2,3,2,4,", "big", "<8,256,2,2,2,8,"
 
 
 @pytest.mark.parametrize("H,E,K,I,T,want", [
