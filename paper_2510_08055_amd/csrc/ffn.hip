@@ -462,13 +462,14 @@ __global__ __launch_bounds__(NW * 64, MINW) void grouped_gemm_bf16_pipe_kernel(
 //   - the epilogue works in the weight slot of the tile's last stage, which nobody needs until the next tile's first
 //     step;
 //   - the row ids of the next tile are looked up while the current tile is multiplied.
-// A block that started anew for every tile spent 7 us of each tile outside the k-loop (tile search 1.8, first loads
-// 2.6, epilogue 2.2, 1-3 until the next block ran) against k-loops of 17 us (K = 768) and 53 us (K = 2048); now it is
-// 3 us.  Before and after, us (same box, in turn): 66560 rows, 128 experts, H = 2048, I = 768: gate_up 405 -> 384, down
+// A block that started anew for every tile spent 7 us of each tile outside the k-loop (timestamps written by the kernel:
+// tile search 1.8, first loads 2.6, epilogue 2.2, 1-3 until the next block ran) against k-loops of 17 us (K = 768) and 53
+// us (K = 2048); now it is 3 us.  Before and after, us (same box, in turn): 66560 rows, 128 experts, H = 2048, I = 768: gate_up 405 -> 384, down
 // 245 -> 225; 8448 rows, 32 experts, H = I = 2880: 336 -> 317, 197 -> 170; 8256 rows, 8 skewed experts, H = 4096,
-// I = 14336: 1718 -> 1630, 1007 -> 911.  What bounds it: at 66560 rows the steps in the middle of a tile keep the
-// matrix pipes 77-82 % busy at a clock that the power limit holds at 1.55-1.75 GHz; at 132 rows per expert (16896 rows)
-// the weights arrive at 5.2-5.9 TB/s.
+// I = 14336: 1718 -> 1630, 1007 -> 911.  What bounds it, by the counters of whole launches: at 66560 rows the
+// matrix pipes are busy 62 % of the gate_up and 47 % of the down GEMM (70 and 72 % of the skewed layer's), at the clock that
+// the power limit leaves, with waves waiting 30 and 35 % of their cycles; at 132 rows per expert (16896 rows) they are busy
+// 28 and 24 %, and 919 and 516 MB cross the fabric at 4.5 and 5.0 TB/s.
 //
 // Which tiles: experts are cut into m-tiles of at most `h` 32-row blocks, tiles are ordered by expert, n-tile, m-tile
 // (the m-tiles that share a weight tile run side by side on one XCD and share its L2), the list is cut into eight

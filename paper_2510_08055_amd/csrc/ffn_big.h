@@ -7,8 +7,9 @@ namespace moe {
 
 constexpr int kBigRows = 256, kBigBN = 256, kBigWaves = 8, kBigMinHeight = 4;
 
-// Fixed cost of a tile in units of one of its 32-row blocks: about 8 us (epilogue, next tile's search, the first
-// steps' waits) against 0.17 us per block and k-step, measured at nk = 12 and 32.
+// Cost of a tile that does not depend on its height, in units of one of its 32-row blocks: about 8 us against 0.17 us per
+// block and k-step, fitted to launches of different heights at nk = 12 and 32.  3 us of it lie between two k-loops
+// (epilogue, change of tile); the rest are waits inside the k-loop that the MFMAs of the blocks do not cover.
 __device__ __forceinline__ float big_tile_fixed(int nk) { return 48.0f / (float)nk + 0.35f; }
 
 // Inclusive scan over the wave's lanes in six register-to-register steps (row shifts, then the last lane of a row to
