@@ -16,9 +16,12 @@ struct moe_ctx {
     int esz;  // bytes per element
     // workspace slices (device)
     unsigned long long* d_active_total;
-    uint32_t* d_tickets;     // of the one-launch routing of small batches: zero between launches, once cleared
-    bool tickets_clear;      // a pass of this context has cleared them (see clear_tickets)
-    bool tickets_clear_now;  // the call in progress finds them clear
+    // tickets of the one-launch routing of small batches (see clear_tickets): zero between launches, once cleared
+    uint32_t* d_tickets;
+    uint32_t* d_tickets_own;  // the set only passes clear (d_tickets starts out as the set that moe_create clears)
+    int create_device;        // >= 0: the context was made on the null stream of this device
+    bool tickets_clear;       // cleared in front of every later pass
+    bool tickets_clear_now;   // the call in progress finds them clear
     double* logits;
     int32_t *idx, *counts, *offsets, *perm, *inv, *tile_hist;
     float* w;
@@ -136,15 +139,22 @@ inline bool misaligned(const void* p) { return (reinterpret_cast<uintptr_t>(p) &
 inline bool misaligned32(const void* p) { return (reinterpret_cast<uintptr_t>(p) & 31u) != 0; }
 inline moe_status dev(hipError_t e) { return e == hipSuccess ? MOE_OK : MOE_ERR_DEVICE; }
 
-// The tickets of the one-launch routing have to be zero when its first launch starts.  The first pass that needs them
-// clears them, on its own stream: the clear is then ordered in front of the routing whatever stream the context was made
-// on, and whether or not moe_create's own work has run.  It is one launch in a context's life (12 us of a first pass of
-// 211 us on an idle GPU); later passes find the tickets as the launch before left them, at zero.
+// The tickets of the one-launch routing have to be zero when its first launch starts; later passes find them as the launch
+// before left them, at zero.  A context made on a device's null stream has a set cleared there, and a first pass on that
+// stream is ordered behind it.  Any other first pass may run before moe_create's work has, so it takes a set that
+// moe_create never touches and clears it on its own stream (one launch in a context's life; 7 to 12 us of a first pass on an
+// idle GPU).  (Only the null stream is told by its handle: another stream's may be a destroyed one's used again.)
 // A pass that is being captured runs only when its graph is replayed, so it carries the clear along, once, and the next
 // pass clears again.
 hipError_t clear_tickets(moe_ctx* c, hipStream_t s)
 {
     if (c->tickets_clear_now) return hipSuccess;
+    int device = -1;
+    if (s == nullptr && c->d_tickets != c->d_tickets_own && hipGetDevice(&device) == hipSuccess && device == c->create_device) {
+        c->tickets_clear = c->tickets_clear_now = true;
+        return hipSuccess;
+    }
+    c->d_tickets = c->d_tickets_own;
     hipStreamCaptureStatus capture = hipStreamCaptureStatusNone;
     if (hipStreamIsCapturing(s, &capture) != hipSuccess) {
         (void)hipGetLastError();        // (the legacy stream while another one is captured)
@@ -299,8 +309,11 @@ moe_status moe_create(const moe_config* cfg, int64_t max_tokens, void* workspace
     c->max_tokens = max_tokens;
     c->esz = cfg->dtype == MOE_BF16 ? 2 : 4;
     c->d_active_total = reinterpret_cast<unsigned long long*>(b + L.counters);
-    static_assert(128 + kSmallTickets * sizeof(uint32_t) <= 256, "the counter block");
-    c->d_tickets = reinterpret_cast<uint32_t*>(b + L.counters + 128);
+    static_assert(kSmallTickets * sizeof(uint32_t) <= 96, "the counter block: counters, two sets of tickets at 32 and at 128");
+    c->d_tickets = reinterpret_cast<uint32_t*>(b + L.counters + 32);
+    c->d_tickets_own = reinterpret_cast<uint32_t*>(b + L.counters + 128);
+    c->create_device = -1;
+    if (stream == nullptr && hipGetDevice(&c->create_device) != hipSuccess) c->create_device = -1;
     c->tickets_clear = c->tickets_clear_now = false;
     c->logits = reinterpret_cast<double*>(b + L.logits);
     c->idx = reinterpret_cast<int32_t*>(b + L.idx);
@@ -318,7 +331,7 @@ moe_status moe_create(const moe_config* cfg, int64_t max_tokens, void* workspace
     c->iterations = c->layer_passes = 0;
     c->timing_mask = 0;
     c->ffn_variant = MOE_FFN_AUTO;
-    // the counters only: the tickets behind them belong to the first pass, which may already run on another stream
+    // the counters and the first set of tickets: the second belongs to a first pass that may already run on another stream
     if (hipMemsetAsync(b + L.counters, 0, 128, static_cast<hipStream_t>(stream)) != hipSuccess) {
         delete c;
         return MOE_ERR_DEVICE;

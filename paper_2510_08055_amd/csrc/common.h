@@ -68,7 +68,7 @@ hipError_t launch_topk(const double* logits, int64_t T, int E, int K, int renorm
 // 16 lanes a token's logits (at E > 256 they no longer fit the registers of a 16-wave block).
 constexpr int kSmallTokens = 256, kSmallExperts = 256;
 inline bool route_is_small(int64_t T, int E, int K) { return T <= kSmallTokens && E <= kSmallExperts && K <= 16; }
-// tickets: kSmallTickets counters, zero before the first launch (the caller's pass clears them); every launch leaves them at zero
+// tickets: kSmallTickets counters, zero before the first launch; every launch leaves them at zero
 constexpr int kSmallTickets = 1 + kSmallTokens / 16;
 hipError_t launch_route_small(int dtype, RowSrc x, int64_t T, int H, const void* w_router, const float* bias, int E, int K,
                               int renorm, double* logits, int32_t* idx, float* w, int32_t* offsets, int32_t* perm, int32_t* inv,

@@ -73,13 +73,14 @@ def small_case(gpu_lib):
     return layers, xd, want
 
 
-def test_first_pass_does_not_wait_for_the_context_s_stream(gpu_lib):
+@pytest.mark.parametrize("made_on", ["side stream", "null stream"])
+def test_first_pass_does_not_wait_for_the_context_s_stream(gpu_lib, made_on):
     """The context is made on a stream that is still busy, over a workspace of arbitrary bytes; a pass on another stream
     gives its result at once, and so does one behind the creation's own work."""
     layers, xd, want = small_case(gpu_lib)
     ctx = gpu_lib.Context(SMALL.H, SMALL.E, SMALL.K, SMALL.I, torch.bfloat16, max_tokens=SMALL.D, device=DEV)
     out = [torch.empty_like(xd) for _ in range(3)]
-    busy, other = torch.cuda.Stream(), torch.cuda.Stream()
+    busy, other = (torch.cuda.Stream() if made_on == "side stream" else torch.cuda.default_stream()), torch.cuda.Stream()
     base = (ctx.workspace.data_ptr() + 255) // 256 * 256
     ctx.workspace.fill_(0xA5)
     torch.cuda.synchronize()
@@ -97,6 +98,25 @@ def test_first_pass_does_not_wait_for_the_context_s_stream(gpu_lib):
     busy.synchronize()
     ctx.moe_group_forward(layers, xd, None, y_decode=out[2])
     assert torch.equal(out[2], want)
+
+
+def test_first_pass_behind_the_creation(gpu_lib):
+    """Made and first used on the null stream, nothing in between, over a workspace of arbitrary bytes; then on another one."""
+    layers, xd, want = small_case(gpu_lib)
+    ctx = gpu_lib.Context(SMALL.H, SMALL.E, SMALL.K, SMALL.I, torch.bfloat16, max_tokens=SMALL.D, device=DEV)
+    base = (ctx.workspace.data_ptr() + 255) // 256 * 256
+    ctx.close()
+    ctx.workspace.fill_(0xA5)
+    assert ctx.lib.moe_create(ctypes.byref(ctx.cfg), SMALL.D, ctypes.c_void_p(base), ctx.workspace.numel() - 256, None,
+                              ctypes.byref(ctx._ctx)) == 0
+    for _ in range(2):
+        assert torch.equal(ctx.moe_group_forward(layers, xd, None)[0], want)
+    side = torch.cuda.Stream()
+    side.wait_stream(torch.cuda.current_stream())
+    with torch.cuda.stream(side):
+        y = ctx.moe_group_forward(layers, xd, None)[0]
+        side.synchronize()
+    assert torch.equal(y, want)
 
 
 def test_first_pass_under_capture(gpu_lib):
