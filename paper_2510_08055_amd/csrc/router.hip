@@ -568,7 +568,23 @@ __global__ __launch_bounds__(kSmallWaves * 64) void route_small_kernel(
         if (lane == 0) atomicAdd(active_total, (unsigned long long)act);
     }
     __syncthreads();
-    if (twice) {
+    const bool recount = twice != 0;
+#pragma unroll
+    for (int p = 0; p < PER; ++p) {
+        const int f = p * kSmallWaves * 64 + tid;
+        const int e = my_e[p];
+        if (e < 0) continue;
+        const int t = f / K;
+        int pos = start[e];
+        for (int j = 0; j <= (t >> 6); ++j) {
+            const unsigned long long m = chosen[e][j];
+            pos += __popcll(j < (t >> 6) ? m : m & ((1ull << (t & 63)) - 1));
+        }
+        if (recount) continue;                // (asked this late: the answer is here when the position is)
+        perm[pos] = f;
+        inv[f] = pos;
+    }
+    if (__builtin_expect(recount, 0)) {
 #pragma unroll
         for (int p = 0; p < PER; ++p)
             if (my_e[p] >= 0) expert_of[p * kSmallWaves * 64 + tid] = (uint8_t)my_e[p];
@@ -581,21 +597,6 @@ __global__ __launch_bounds__(kSmallWaves * 64) void route_small_kernel(
             perm[pos] = f;
             inv[f] = pos;
         }
-        return;
-    }
-#pragma unroll
-    for (int p = 0; p < PER; ++p) {
-        const int f = p * kSmallWaves * 64 + tid;
-        const int e = my_e[p];
-        if (e < 0) continue;
-        const int t = f / K;
-        int pos = start[e];
-        for (int j = 0; j <= (t >> 6); ++j) {
-            const unsigned long long m = chosen[e][j];
-            pos += __popcll(j < (t >> 6) ? m : m & ((1ull << (t & 63)) - 1));
-        }
-        perm[pos] = f;
-        inv[f] = pos;
     }
 }
 
