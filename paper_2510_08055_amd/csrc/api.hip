@@ -25,6 +25,10 @@ struct moe_ctx {
     double* logits;
     int32_t *idx, *counts, *offsets, *perm, *inv, *tile_hist;
     float* w;
+    uint8_t* digits;          // w_router as digits, of digit_slots layers
+    char* digit_forms;          // and what else describes its rows
+    int digit_slots;
+    int64_t tile_hist_words;  // of one slot
     void *xa, *xb, *act, *y_perm;
     // host-side counters (everything the host already knows)
     uint64_t router_bytes, tokens_processed;
@@ -67,7 +71,9 @@ moe_status check_cfg(const moe_config* c)
 }
 
 struct Layout {
-    size_t counters, logits, idx, w, counts, offsets, perm, inv, tile_hist, xa, xb, act, y_perm, total;
+    size_t counters, logits, idx, w, counts, offsets, perm, inv, tile_hist, digits, digit_forms, xa, xb, act, y_perm, total;
+    int digit_slots;
+    size_t tile_hist_words;
 };
 
 Layout carve(const moe_config& c, int64_t Tm)
@@ -86,7 +92,17 @@ Layout carve(const moe_config& c, int64_t Tm)
     L.offsets = take((size_t)(c.E + 1) * 4);
     L.perm = take(Am * 4);
     L.inv = take(Am * 4);
-    L.tile_hist = take(n_tiles * c.E * 4);
+    // the router's digits: layers of a group at a time, in at most 32 MB
+    const size_t digit_bytes = (size_t)router_digit_bytes(c.H, c.E);
+    L.digit_slots = 0;
+    if (route_is_exact(c.dtype, Tm, c.H, c.E, c.K)) {
+        const size_t fit = ((size_t)32 << 20) / digit_bytes;
+        L.digit_slots = fit < 1 ? 1 : (fit > (size_t)kDigitLayers ? kDigitLayers : (int)fit);
+    }
+    L.tile_hist_words = n_tiles * c.E;       // of a layer
+    L.tile_hist = take((L.digit_slots > 1 ? L.digit_slots : 1) * L.tile_hist_words * 4);
+    L.digits = take(L.digit_slots * digit_bytes);
+    L.digit_forms = take((size_t)L.digit_slots * router_form_bytes(c.E));
     L.xa = take((size_t)Tm * c.H * esz);
     L.xb = take((size_t)Tm * c.H * esz);
     L.act = take(Am * c.I * esz * (c.act_split ? 2 : 1));
@@ -167,7 +183,7 @@ hipError_t clear_tickets(moe_ctx* c, hipStream_t s)
 }
 
 // One layer on the batch `x` [T,H]; output rows [0,rows0) -> y0, the rest -> y1.
-moe_status run_layer(moe_ctx* c, const moe_layer& L, RowSrc x, int64_t T, void* y0, int64_t rows0, void* y1,
+moe_status run_layer(moe_ctx* c, const moe_layer& L, RowSrc x, int64_t T, int slot, void* y0, int64_t rows0, void* y1,
                      hipStream_t s)
 {
     const moe_config& g = c->cfg;
@@ -177,6 +193,8 @@ moe_status run_layer(moe_ctx* c, const moe_layer& L, RowSrc x, int64_t T, void* 
     const bool fused_hist = n_perm_tiles > 1;
     hipError_t e;
     const bool small = route_is_small(T, g.E, g.K);
+    const bool exact = route_is_exact(g.dtype, T, g.H, g.E, g.K);
+    int32_t* const tile_hist = c->tile_hist + slot * c->tile_hist_words;
     if (small) {
         // (timed as the router's logits; the other two have no launch of their own)
         e = clear_tickets(c, s);
@@ -186,19 +204,24 @@ moe_status run_layer(moe_ctx* c, const moe_layer& L, RowSrc x, int64_t T, void* 
                                c->w, c->offsets, c->perm, c->inv, c->d_active_total, c->d_tickets, s);
     } else {
         Timed t(c, MOE_KERNEL_ROUTER_LOGITS, s);
-        e = launch_router_logits(g.dtype, x, T, g.H, L.w_router, L.router_bias, g.E, c->logits, c->tile_hist,
-                                 fused_hist ? n_perm_tiles * g.E : 0, s);
+        if (exact)      // (timed as the router's logits; the top-k has no launch of its own)
+            e = launch_route_exact(x, T, g.H, L.w_router, L.router_bias, g.E, g.K, g.renormalize,
+                                   c->digits + slot * router_digit_bytes(g.H, g.E), c->digit_forms + slot * router_form_bytes(g.E),
+                                   c->idx, c->w, fused_hist ? tile_hist : nullptr, s);
+        else
+            e = launch_router_logits(g.dtype, x, T, g.H, L.w_router, L.router_bias, g.E, c->logits, tile_hist,
+                                     fused_hist ? n_perm_tiles * g.E : 0, s);
     }
     if (e != hipSuccess) return MOE_ERR_DEVICE;
     if (!small) {
-        {
+        if (!exact) {
             Timed t(c, MOE_KERNEL_TOPK, s);
-            e = launch_topk(c->logits, T, g.E, g.K, g.renormalize, c->idx, c->w, fused_hist ? c->tile_hist : nullptr, s);
+            e = launch_topk(c->logits, T, g.E, g.K, g.renormalize, c->idx, c->w, fused_hist ? tile_hist : nullptr, s);
         }
         if (e != hipSuccess) return MOE_ERR_DEVICE;
         {
             Timed t(c, MOE_KERNEL_PERMUTE, s);
-            e = launch_permute(c->idx, A, g.E, c->counts, c->offsets, c->perm, c->inv, c->tile_hist, fused_hist,
+            e = launch_permute(c->idx, A, g.E, c->counts, c->offsets, c->perm, c->inv, tile_hist, fused_hist,
                                c->d_active_total, s);
         }
         if (e != hipSuccess) return MOE_ERR_DEVICE;
@@ -242,11 +265,20 @@ moe_status run_group(moe_ctx* c, const moe_layer* layers, int n, RowSrc in, int6
 {
     char* cur = static_cast<char*>(c->xa);
     char* nxt = static_cast<char*>(c->xb);
+    const moe_config& g = c->cfg;
+    const int slots = route_is_exact(g.dtype, T, g.H, g.E, g.K) ? c->digit_slots : 0;
     for (int l = 0; l < n; ++l) {
         const RowSrc src = (l == 0) ? in : single_src(cur);
+        const int slot = slots > 0 ? l % slots : 0;
+        if (slots > 0 && slot == 0) {
+            RouterWeights w = {};
+            const int here = n - l < slots ? n - l : slots;
+            for (int i = 0; i < here; ++i) w.p[i] = layers[l + i].w_router;
+            if (launch_router_digits(w, here, g.H, g.E, c->digits, c->digit_forms, c->tile_hist, here * c->tile_hist_words, s) != hipSuccess) return MOE_ERR_DEVICE;
+        }
         moe_status st;
-        if (l + 1 < n) st = run_layer(c, layers[l], src, T, nxt, T, nxt, s);
-        else st = run_layer(c, layers[l], src, T, y0, rows0, y1, s);
+        if (l + 1 < n) st = run_layer(c, layers[l], src, T, slot, nxt, T, nxt, s);
+        else st = run_layer(c, layers[l], src, T, slot, y0, rows0, y1, s);
         if (st != MOE_OK) return st;
         char* t = cur; cur = nxt; nxt = t;
         c->layer_passes += 1;
@@ -323,6 +355,10 @@ moe_status moe_create(const moe_config* cfg, int64_t max_tokens, void* workspace
     c->perm = reinterpret_cast<int32_t*>(b + L.perm);
     c->inv = reinterpret_cast<int32_t*>(b + L.inv);
     c->tile_hist = reinterpret_cast<int32_t*>(b + L.tile_hist);
+    c->digits = reinterpret_cast<uint8_t*>(b + L.digits);
+    c->digit_forms = b + L.digit_forms;
+    c->digit_slots = L.digit_slots;
+    c->tile_hist_words = (int64_t)L.tile_hist_words;
     c->xa = b + L.xa;
     c->xb = b + L.xb;
     c->act = b + L.act;
@@ -358,6 +394,12 @@ moe_status moe_router_topk(moe_ctx* ctx, const void* x, int64_t T, const void* w
     if (misaligned(x) || misaligned(w_router)) return MOE_ERR_ALIGN;
     hipStream_t s = static_cast<hipStream_t>(stream);
     const moe_config& g = ctx->cfg;
+    if (route_is_exact(g.dtype, T, g.H, g.E, g.K)) {
+        const RouterWeights w = {{w_router}};
+        if (launch_router_digits(w, 1, g.H, g.E, ctx->digits, ctx->digit_forms, nullptr, 0, s) != hipSuccess) return MOE_ERR_DEVICE;
+        return dev(launch_route_exact(single_src(x), T, g.H, w_router, bias, g.E, g.K, g.renormalize, ctx->digits,
+                                      ctx->digit_forms, topk_idx, topk_w, nullptr, s));
+    }
     hipError_t e = launch_router_logits(g.dtype, single_src(x), T, g.H, w_router, bias, g.E, ctx->logits, nullptr, 0, s);
     if (e != hipSuccess) return MOE_ERR_DEVICE;
     return dev(launch_topk(ctx->logits, T, g.E, g.K, g.renormalize, topk_idx, topk_w, nullptr, s));

@@ -60,14 +60,40 @@ template <typename T> __device__ __forceinline__ const T* row_ptr(const RowSrc& 
 // router.hip
 hipError_t launch_router_logits(int dtype, RowSrc x, int64_t T, int H, const void* w_router, const float* bias,
                                 int E, double* logits, int32_t* zero_buf, int zero_n, hipStream_t s);
-// tile_hist (or NULL): [ceil(T*K / kPermTile), E] counters, already zero, that receive the expert histogram
-hipError_t launch_topk(const double* logits, int64_t T, int E, int K, int renorm, int32_t* idx, float* w,
-                       int32_t* tile_hist, hipStream_t s);
-
 // Batches whose routing (logits, top-k, permutation) is one launch: a single block can hold the permutation, and
 // 16 lanes a token's logits (at E > 256 they no longer fit the registers of a 16-wave block).
 constexpr int kSmallTokens = 256, kSmallExperts = 256;
 inline bool route_is_small(int64_t T, int E, int K) { return T <= kSmallTokens && E <= kSmallExperts && K <= 16; }
+
+// Router and top-k of larger bf16 batches with logits that are exact integer sums (see router.hip): a launch that makes the
+// digits of the layers' w_router (router_digit_bytes and router_form_bytes for each) and clears zero_n words, then a launch
+// per layer; tile_hist as for launch_topk.
+constexpr int kDigitLayers = 8;      // layers per digits launch
+struct RouterWeights {
+    const void* p[kDigitLayers];
+};
+int64_t router_digit_bytes(int H, int E);
+inline int64_t router_form_bytes(int E) { return (int64_t)((E + 31) / 32 * 32) * 16; }
+hipError_t launch_router_digits(const RouterWeights& w, int layers, int H, int E, uint8_t* digits, void* forms, int32_t* zero_buf,
+                                int64_t zero_n, hipStream_t s);
+hipError_t launch_route_exact(RowSrc x, int64_t T, int H, const void* w_router, const float* bias, int E, int K, int renorm,
+                              const uint8_t* digits, const void* forms, int32_t* idx, float* w, int32_t* tile_hist,
+                              hipStream_t s);
+// (its sums are at most 4 H 2^14; a block holds all experts' logits of its tokens.)  It takes 25 us and more however few the
+// tokens, the fp64 pass grows with T E H.  Logits and top-k, fp64 / exact with the digits of one layer, us: H = 2048, E = 128: 1389
+// tokens 26.6 / 31, 2112 36.4 / 31.2 (as part of a layer, with one launch boundary less or more, the two are level), 4128
+// 57.5 / 34; E = 64: 3000 tokens 25.9 / 31, 4128 36.4 / 32; H = 2880, E = 32: 4128 30.6 / 30, 8320 45 / 42.  Up to 16 experts the
+// fp64 pass does a group of 16 where this one does 32: H = 4096, E = 8, 8320 tokens 39 / 61.
+constexpr int kExactMaxH = 16384, kExactExperts = 128;
+inline bool route_is_exact(int dtype, int64_t T, int H, int E, int K)
+{
+    return dtype == MOE_BF16 && !route_is_small(T, E, K) && H <= kExactMaxH && E > 16 && E <= kExactExperts && K <= 16 &&
+           T * ((E + 15) / 16 * 16) * H >= (int64_t)600000000;
+}
+// tile_hist (or NULL): [ceil(T*K / kPermTile), E] counters, already zero, that receive the expert histogram
+hipError_t launch_topk(const double* logits, int64_t T, int E, int K, int renorm, int32_t* idx, float* w,
+                       int32_t* tile_hist, hipStream_t s);
+
 // tickets: kSmallTickets counters, zero before the first launch; every launch leaves them at zero
 constexpr int kSmallTickets = 1 + kSmallTokens / 16;
 hipError_t launch_route_small(int dtype, RowSrc x, int64_t T, int H, const void* w_router, const float* bias, int E, int K,

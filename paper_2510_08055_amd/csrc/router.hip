@@ -5,8 +5,10 @@
 // agree with an fp64 definition: products of two bf16 (or two fp32) values are
 // exact in fp64 and the summation error (~1e-16 relative) is far below any
 // realistic gap between neighbouring logits.  The reduction order of a token's
-// logits depends only on H, never on the batch, so routing is batch-invariant:
-// the chunked and the layered schedule route every token identically.
+// logits depends only on H, never on the batch.  Large bf16 batches take exact
+// integer sums instead (route_exact_kernel), rounded once: their logits can differ
+// from the fp64 chain's by its own rounding, a part in 10^15, and from nothing else
+// in the batch.
 #include <type_traits>
 
 #include "common.h"
@@ -115,12 +117,11 @@ template <typename V> __device__ __forceinline__ V load_shared(const V* p)
     return __hip_atomic_load(p, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
 }
 
-// The tile of logits at (t0, e0), written by wave 0 of the block; every thread of the block calls it.
-// SHARED: another block of the same launch reads the logits.
-template <typename T, int NW, bool SHARED>
+// The tile of logits at (t0, e0), computed by the first NW waves of the block and stored by wave 0; every thread of the
+// block calls it.  store(i, j, z) takes the logit z of token t0 + i < n_tok and expert e0 + j < E.
+template <typename T, int NW, typename Store>
 __device__ __forceinline__ void logits_tile(const RowSrc& x, int64_t n_tok, int H, const T* __restrict__ wr,
-                                            const float* __restrict__ bias, int E, double* __restrict__ logits, int64_t t0,
-                                            int e0)
+                                            const float* __restrict__ bias, int E, int64_t t0, int e0, Store store)
 {
     constexpr int NACC = 16 / NW;                // partial sums per wave
     static_assert(NW == 4 || NW == 16, "16 partial sums over 4 or 16 waves");
@@ -152,7 +153,8 @@ __device__ __forceinline__ void logits_tile(const RowSrc& x, int64_t n_tok, int 
             if (a == i % NACC) multiply(buf, acc[a]);
     };
     const int n_whole = H / 32;                                            // whole 32-wide chunks of a row
-    const int mine = n_whole > wave ? (n_whole - wave + NW - 1) / NW : 0;   // of which this wave takes chunks wave, wave + NW, ...
+    // of which this wave takes chunks wave, wave + NW, ... (a wave past the first NW none)
+    const int mine = wave < NW && n_whole > wave ? (n_whole - wave + NW - 1) / NW : 0;
     auto fetch = [&](int buf, int i) {                                      // this wave's i-th chunk
         const int k0 = (wave + NW * i) * 32;
         xa[buf].load_async(xp + k0);
@@ -194,7 +196,7 @@ __device__ __forceinline__ void logits_tile(const RowSrc& x, int64_t n_tok, int 
     double4_t mysum = acc[0];
 #pragma unroll
     for (int a = 1; a < NACC; ++a) mysum += acc[a];
-    if (wave > 0) {
+    if (wave > 0 && wave < NW) {
 #pragma unroll
         for (int v = 0; v < 4; ++v) part[wave - 1][v][lane] = mysum[v];
     }
@@ -215,10 +217,7 @@ __device__ __forceinline__ void logits_tile(const RowSrc& x, int64_t n_tok, int 
                 for (int w = p + 4; w < NW; w += 4) s += part[w - 1][v][lane];
                 z = p == 0 ? s : z + s;
             }
-            if (t < n_tok) {
-                if (SHARED) store_shared(logits + t * E + e, z + b);
-                else logits[t * E + e] = z + b;
-            }
+            if (t < n_tok) store(v * 4 + q, r, z + b);
         }
     }
 }
@@ -234,7 +233,9 @@ __global__ __launch_bounds__(256) void router_logits_kernel(RowSrc x, int64_t n_
     // stream, counts into (saves a separate fill launch)
     if (blockIdx.x == 0 && blockIdx.y == 0)
         for (int i = threadIdx.x; i < zero_n; i += 256) zero_buf[i] = 0;
-    logits_tile<T, 4, false>(x, n_tok, H, wr, bias, E, logits, (int64_t)blockIdx.x * 16, (int)blockIdx.y * 16);
+    const int64_t t0 = (int64_t)blockIdx.x * 16;
+    const int e0 = (int)blockIdx.y * 16;
+    logits_tile<T, 4>(x, n_tok, H, wr, bias, E, t0, e0, [&](int i, int j, double z) { logits[(t0 + i) * E + e0 + j] = z; });
 }
 
 // (value, index) "greater" under the routing order: larger logit first, equal logits by lower index.
@@ -354,55 +355,116 @@ template <int CTRL> __device__ __forceinline__ void row_best_step(double& bv, in
 }
 template <int CTRL> __device__ __forceinline__ double row_sum_step(double v) { return v + dpp_mov<CTRL>(v); }
 
-// Top-k of token t by the 16 lanes of a row (c = lane % 16): lane c < K ends with the c-th winner and its
-// weight.  All lanes of the row hold the same t.
-template <int NPL>   // logits per lane: experts c + 16 i, i < NPL
-__device__ __forceinline__ void topk_of_row(const double* z, int E, int K, int renorm, int c, bool shared, int& my_e,
-                                            float& my_w)
+// The best of a lane's logits, experts c + 16 i; the lower index stays among equal values.  TREE: as a tree over i in place of a
+// chain (shorter, but more instructions: worth it where several tokens share the lanes).  As in the chain, a NaN is best
+// as the first of them and never elsewhere: in the tree the others count as -infinity.
+template <int NPL, bool TREE> __device__ __forceinline__ void lane_best(const double (&v)[NPL], int c, double& bv, int& be)
 {
-    const double NEG = -__builtin_huge_val();
-    double v[NPL];
-#pragma unroll
-    for (int i = 0; i < NPL; ++i) {
-        const int e = c + 16 * i;
-        v[i] = (e < E) ? (shared ? load_shared(z + e) : z[e]) : NEG;
-    }
-    double esum = 0.0;      // only without renormalisation: this lane's share of sum_e exp(z_e - z_max)
-    double my_z = NEG, z_max = 0.0;
-    my_e = 0;
-    for (int j = 0; j < K; ++j) {
-        double bv = v[0];
-        int be = c;
+    if (!TREE) {
+        bv = v[0];
+        be = c;
 #pragma unroll
         for (int i = 1; i < NPL; ++i)
-            if (v[i] > bv) { bv = v[i]; be = c + 16 * i; }     // equal values: the lower index stays
-        row_best_step<kDppXor1>(bv, be);
-        row_best_step<kDppXor2>(bv, be);
-        row_best_step<kDppHalfMirror>(bv, be);
-        row_best_step<kDppMirror>(bv, be);
-        if (j == 0) {
-            z_max = bv;
-            if (!renorm) {
+            if (v[i] > bv) { bv = v[i]; be = c + 16 * i; }
+        return;
+    }
+    double t[NPL];
+    int e[NPL];
 #pragma unroll
-                for (int i = 0; i < NPL; ++i)
-                    if (c + 16 * i < E) esum += exp(v[i] - z_max);
+    for (int i = 0; i < NPL; ++i) {
+        t[i] = i == 0 ? v[i] : __builtin_fmax(v[i], -__builtin_huge_val());
+        e[i] = c + 16 * i;
+    }
+#pragma unroll
+    for (int d = 1; d < NPL; d *= 2)
+#pragma unroll
+        for (int i = 0; i + d < NPL; i += 2 * d)
+            if (t[i + d] > t[i]) {
+                t[i] = t[i + d];
+                e[i] = e[i + d];
+            }
+    bv = t[0];
+    be = e[0];
+}
+
+// Top-k of R tokens by the 16 lanes of a row (c = lane % 16): lane c < K ends with the c-th winner of each and its weight.
+// All lanes of the row hold the same z[0 .. R).  (A round is a chain of dependent instructions; two tokens fill its gaps.)
+template <int NPL, int R>   // logits per lane: experts c + 16 i, i < NPL
+__device__ __forceinline__ void topk_of_rows(const double* const (&z)[R], int E, int K, int renorm, int c, bool shared,
+                                             int (&my_e)[R], float (&my_w)[R])
+{
+    const double NEG = -__builtin_huge_val();
+    double v[R][NPL];
+#pragma unroll
+    for (int r = 0; r < R; ++r)
+#pragma unroll
+        for (int i = 0; i < NPL; ++i) {
+            const int e = c + 16 * i;
+            v[r][i] = (e < E) ? (shared ? load_shared(z[r] + e) : z[r][e]) : NEG;
+        }
+    double esum[R];         // only without renormalisation: this lane's share of sum_e exp(z_e - z_max)
+    double my_z[R], z_max[R];
+#pragma unroll
+    for (int r = 0; r < R; ++r) {
+        esum[r] = z_max[r] = 0.0;
+        my_z[r] = NEG;
+        my_e[r] = 0;
+    }
+    for (int j = 0; j < K; ++j) {
+        double bv[R];
+        int be[R];
+#pragma unroll
+        for (int r = 0; r < R; ++r) lane_best<NPL, (R > 1)>(v[r], c, bv[r], be[r]);
+#pragma unroll
+        for (int r = 0; r < R; ++r) row_best_step<kDppXor1>(bv[r], be[r]);
+#pragma unroll
+        for (int r = 0; r < R; ++r) row_best_step<kDppXor2>(bv[r], be[r]);
+#pragma unroll
+        for (int r = 0; r < R; ++r) row_best_step<kDppHalfMirror>(bv[r], be[r]);
+#pragma unroll
+        for (int r = 0; r < R; ++r) row_best_step<kDppMirror>(bv[r], be[r]);
+        if (j == 0) {
+#pragma unroll
+            for (int r = 0; r < R; ++r) {
+                z_max[r] = bv[r];
+                if (!renorm) {
+#pragma unroll
+                    for (int i = 0; i < NPL; ++i)
+                        if (c + 16 * i < E) esum[r] += exp(v[r][i] - bv[r]);
+                }
             }
         }
-        if (c == j) { my_z = bv; my_e = be; }
-        if ((be & 15) == c) {
-            const int slot = be >> 4;
 #pragma unroll
-            for (int i = 0; i < NPL; ++i)
-                if (i == slot) v[i] = NEG;
+        for (int r = 0; r < R; ++r) {
+            if (c == j) { my_z[r] = bv[r]; my_e[r] = be[r]; }
+            if ((be[r] & 15) == c) {
+                const int slot = be[r] >> 4;
+#pragma unroll
+                for (int i = 0; i < NPL; ++i)
+                    if (i == slot) v[r][i] = NEG;
+            }
         }
     }
-    const double p = (c < K) ? exp(my_z - z_max) : 0.0;
-    double denom = renorm ? p : esum;
-    denom = row_sum_step<kDppXor1>(denom);
-    denom = row_sum_step<kDppXor2>(denom);
-    denom = row_sum_step<kDppHalfMirror>(denom);
-    denom = row_sum_step<kDppMirror>(denom);
-    my_w = (float)(p / denom);
+#pragma unroll
+    for (int r = 0; r < R; ++r) {
+        const double p = (c < K) ? exp(my_z[r] - z_max[r]) : 0.0;
+        double denom = renorm ? p : esum[r];
+        denom = row_sum_step<kDppXor1>(denom);
+        denom = row_sum_step<kDppXor2>(denom);
+        denom = row_sum_step<kDppHalfMirror>(denom);
+        denom = row_sum_step<kDppMirror>(denom);
+        my_w[r] = (float)(p / denom);
+    }
+}
+template <int NPL>
+__device__ __forceinline__ void topk_of_row(const double* z, int E, int K, int renorm, int c, bool shared, int& my_e, float& my_w)
+{
+    const double* zs[1] = {z};
+    int e[1];
+    float w[1];
+    topk_of_rows<NPL, 1>(zs, E, K, renorm, c, shared, e, w);
+    my_e = e[0];
+    my_w = w[0];
 }
 
 template <int NPL>
@@ -436,6 +498,512 @@ __global__ __launch_bounds__(kTopkWaves * 64) void topk_rows_kernel(const double
     if (tile_hist) {
         __syncthreads();
         for (int i = threadIdx.x; i < 2 * E; i += kTopkWaves * 64) {
+            const int cnt = hist[i / E][i % E];
+            if (cnt) atomicAdd(&tile_hist[(tile0 + i / E) * E + i % E], cnt);
+        }
+    }
+}
+
+// ----------------------------------------------------------------------------------------------
+// Router and top-k of larger batches of bf16 rows (at most kExactExperts experts, K <= 16): the logits are exact integer
+// sums on the i8 matrix cores.
+//
+// The fp64 pass above is bound by the fp64 matrix pipe (two widenings beside every MFMA).  Here a row of x, and a row
+// of w_router, becomes 32-bit fixed point under the row's own power of two, v = trunc(x 2^(156 - eb)) (eb: largest
+// biased exponent of the row, so |v| < 2^30), and v is written in four balanced base-256 digits: the bytes of
+// (v + 0x80808080) ^ 0x80808080.  A logit is then sum_ij 2^(8 (i + j)) sum_k d_i d_j, and every sum over k is a chain of
+// v_mfma_i32_32x32x32_i8 that cannot overflow (7 sums for i + j = 0 .. 6, each at most 4 H 2^14 < 2^31).  Nothing is rounded
+// until the 7 sums meet: one rounding to fp64, closer to the true sum than the fp64 chain's H of them, and the same
+// whatever the tile, the order of the chain or the rest of the batch.
+// The lowest digit of most values is zero (it is used by values 2^13 and more below their row's largest, one in 10^4 of
+// normally distributed ones): a chunk of 32 k-values whose lowest digits are all zero on either side leaves
+// those products out, which makes 10 of 16.
+// A value with bits below the window (2^22 and more below the row's largest: one in 2 10^6) leaves a remainder that the
+// digits do not hold.  Such values of a row are listed, up to kStray of them, and their remainders times the other
+// operand are added to the logit in fp64.  A row with more of them, with infinities or NaN, or of largest exponents that no
+// fp32 scale reaches, takes its logits from the fp64 pass, tile by tile, at the end of the block.  Which way a logit is
+// made depends on its two rows alone.
+//
+// A block takes 32 tokens and all experts, WE groups of 32; its waves are WE x WK: WK shares of the k-range, in each of
+// them one wave per group; the WE waves of a share turn 32 tokens x 64 k-values at a time into digits (whole 128-byte
+// lines, each value once) and hand them to each other through LDS, a step ahead of the MFMAs that use them.  w_router's
+// digits come from a launch of their own (for several layers at once), laid out as the operands' registers.  The logits
+// stay in LDS, where the top-k reads them.
+// Measured (kernel times; logits and top-k before -> this launch, and 5 us for the digits of up to 8 layers), H = 2048,
+// E = 128, top-8: 2112 tokens 36.4 -> 26.4 us, 4128 57.5 -> 29, 8320 100.9 -> 43.7; H = 2880, E = 32, top-4, 8320 tokens
+// 45 -> 37.  What bounds it: the MFMAs alone take 10.5 us of the 24 of the k-loop at 8320 tokens; the rest is the 36 KB per
+// step that a compute unit's address unit and L2 deliver (eight loads issued in a row, in place of one by one between the
+// MFMAs, cost 6 us, the branches around four groups of MFMAs in place of one 5 us; the conversions are hidden).  The row maxima
+// take 4 us, the sums and the logits 2, the top-k 6.
+// ----------------------------------------------------------------------------------------------
+typedef int i32x4_t __attribute__((ext_vector_type(4)));
+typedef int i32x16_t __attribute__((ext_vector_type(16)));
+typedef uint16_t u16x2_t __attribute__((ext_vector_type(2)));
+
+constexpr int kDigitK = 64;           // k-values per step: rows are padded to it with zeros
+constexpr int kWindow = 22;           // exponents below the row's largest that the fixed point holds exactly
+constexpr int kStray = 3;             // values of a row that may lie below it
+constexpr uint32_t kBalance = 0x80808080u, kNoStray = 0xffffffffu;
+
+// How a row is held: the biased exponent eb of its scale (-1: not at all), and the k-values whose remainders it misses.
+struct RowForm {
+    int eb;
+    uint32_t stray[kStray];           // in ascending order, kNoStray past the last
+};
+// 2^(156 - eb); any scale will do for a row that is not held
+__device__ __forceinline__ float digit_scale(int eb) { return __uint_as_float((uint32_t)(283 - (eb < 0 ? 127 : eb)) << 23); }
+// value = what the digits hold + remainder
+__device__ __forceinline__ double digit_part(bf16_t v, int eb) { return (double)truncf(bf16_to_f32(v) * digit_scale(eb)) / digit_scale(eb); }
+__device__ __forceinline__ double remainder_part(bf16_t v, int eb) { return (double)bf16_to_f32(v) - digit_part(v, eb); }
+
+// The largest and the smallest non-zero magnitude of a row, as bf16 bits, gathered 8 values at a time (zero counts as
+// 0xffff on the small side).
+struct RowRange {
+    u16x2_t top, low;
+    __device__ __forceinline__ void clear()
+    {
+        top = u16x2_t{0, 0};
+        low = u16x2_t{0xffff, 0xffff};
+    }
+    __device__ __forceinline__ void add(const u32x4_t& raw)
+    {
+#pragma unroll
+        for (int i = 0; i < 4; ++i) {
+            const u16x2_t m = __builtin_bit_cast(u16x2_t, raw[i] & 0x7fff7fffu);
+            top = __builtin_elementwise_max(top, m);
+            low = __builtin_elementwise_min(low, m - u16x2_t{1, 1});       // zero wraps to 0xffff
+        }
+    }
+    // Over W neighbouring lanes that hold the row; strays: some value lies below the window.
+    template <int W> __device__ __forceinline__ int exponent(bool& strays) const
+    {
+        int hi = top[0] > top[1] ? top[0] : top[1], lo = low[0] < low[1] ? low[0] : low[1];
+#pragma unroll
+        for (int o = 1; o < W; o <<= 1) {
+            const int h2 = __shfl_xor(hi, o, 64), l2 = __shfl_xor(lo, o, 64);
+            hi = h2 > hi ? h2 : hi;
+            lo = l2 < lo ? l2 : lo;
+        }
+        const int eb = hi == 0 ? 127 : hi >> 7;      // (a row of zeros: any)
+        strays = ((lo + 1) >> 7) < eb - kWindow;
+        return eb >= 29 && eb <= 254 ? eb : -1;
+    }
+};
+
+// Lists the strays of a row; called by one whole wave.  (Rare: short rather than fast.)
+__device__ __forceinline__ void list_strays(const bf16_t* row, int H, RowForm* form)
+{
+    const int lane = lane_id();
+    const int eb = form->eb;
+    int n = 0;
+#pragma unroll 1
+    for (int k0 = 0; k0 < H; k0 += 512) {
+        const int k = k0 + lane * 8;
+        u32x4_t raw = {0, 0, 0, 0};
+        if (k < H) raw = *reinterpret_cast<const u32x4_t*>(row + k);
+        uint32_t mine = 0;                // bit j: value k + j is a stray
+#pragma unroll
+        for (int j = 0; j < 8; ++j) {
+            const uint32_t m = (raw[j / 2] >> (16 * (j & 1))) & 0x7fffu;
+            if (m != 0 && (int)(m >> 7) < eb - kWindow) mine |= 1u << j;
+        }
+        unsigned long long hit = __ballot(mine != 0);
+#pragma unroll 1
+        while (hit) {
+            const int from = __ffsll((long long)hit) - 1;
+            uint32_t bits = (uint32_t)__builtin_amdgcn_readlane((int)mine, from);
+#pragma unroll 1
+            for (; bits; bits &= bits - 1, ++n)
+                if (n < kStray && lane == 0) form->stray[n] = (uint32_t)(k0 + from * 8 + __ffs((int)bits) - 1);
+            hit &= hit - 1;
+        }
+    }
+    if (n > kStray && lane == 0) form->eb = -1;
+}
+
+// The digits of 8 consecutive values: digit p of values 0 .. 3 in d[p][0], of values 4 .. 7 in d[p][1].
+__device__ __forceinline__ void digits_of_8(const u32x4_t& raw, float scale, uint32_t (&d)[4][2])
+{
+    uint32_t u[8];
+#pragma unroll
+    for (int i = 0; i < 4; ++i) {
+        u[2 * i] = (uint32_t)(int)(__uint_as_float(raw[i] << 16) * scale) + kBalance;
+        u[2 * i + 1] = (uint32_t)(int)(__uint_as_float(raw[i] & 0xffff0000u) * scale) + kBalance;
+    }
+#pragma unroll
+    for (int g = 0; g < 2; ++g) {       // 4 x 4 bytes, transposed
+        const uint32_t a = u[4 * g], b = u[4 * g + 1], c = u[4 * g + 2], e = u[4 * g + 3];
+        const uint32_t ab01 = __builtin_amdgcn_perm(b, a, 0x05010400u), ce01 = __builtin_amdgcn_perm(e, c, 0x05010400u);
+        const uint32_t ab23 = __builtin_amdgcn_perm(b, a, 0x07030602u), ce23 = __builtin_amdgcn_perm(e, c, 0x07030602u);
+        d[0][g] = __builtin_amdgcn_perm(ce01, ab01, 0x05040100u) ^ kBalance;
+        d[1][g] = __builtin_amdgcn_perm(ce01, ab01, 0x07060302u) ^ kBalance;
+        d[2][g] = __builtin_amdgcn_perm(ce23, ab23, 0x05040100u) ^ kBalance;
+        d[3][g] = __builtin_amdgcn_perm(ce23, ab23, 0x07060302u) ^ kBalance;
+    }
+}
+
+// Digits of w_router, in the order in which the waves below load them: [64 k-values][group of 32 experts][32 k-values][digit]
+// [lane][16 bytes], lane (r, q) = expert r, k-values 16 q .. + 15.  A block per expert (the last group is padded with rows
+// of zeros) and layer.
+constexpr int kPrepThreads = 128;
+__global__ __launch_bounds__(kPrepThreads) void router_digits_kernel(RouterWeights w, int H, int E, uint8_t* digits,
+                                                                      int64_t layer_bytes, RowForm* forms, int32_t* zero_buf,
+                                                                      int64_t zero_n)
+{
+    __shared__ int s_hi[kPrepThreads / 64], s_lo[kPrepThreads / 64];
+    __shared__ RowForm s_form;
+    // side job: clear the expert histograms that the layers' top-k counts into
+    for (int64_t i = ((int64_t)blockIdx.y * gridDim.x + blockIdx.x) * kPrepThreads + threadIdx.x; i < zero_n;
+         i += (int64_t)gridDim.x * gridDim.y * kPrepThreads)
+        zero_buf[i] = 0;
+    const int e = (int)blockIdx.x, layer = (int)blockIdx.y, groups = (int)gridDim.x / 32;
+    const bf16_t* row = static_cast<const bf16_t*>(w.p[layer]) + (int64_t)(e < E ? e : 0) * H;
+    const int pieces = e < E ? H / 8 : 0;
+    const u32x4_t zero = {0, 0, 0, 0};
+    RowRange range;
+    range.clear();
+    for (int p = threadIdx.x; p < pieces; p += kPrepThreads) range.add(*reinterpret_cast<const u32x4_t*>(row + p * 8));
+    int hi = range.top[0] > range.top[1] ? range.top[0] : range.top[1];
+    int lo = range.low[0] < range.low[1] ? range.low[0] : range.low[1];
+#pragma unroll
+    for (int o = 1; o < 64; o <<= 1) {
+        const int h2 = __shfl_xor(hi, o, 64), l2 = __shfl_xor(lo, o, 64);
+        hi = h2 > hi ? h2 : hi;
+        lo = l2 < lo ? l2 : lo;
+    }
+    if ((threadIdx.x & 63) == 0) {
+        s_hi[threadIdx.x >> 6] = hi;
+        s_lo[threadIdx.x >> 6] = lo;
+    }
+    __syncthreads();
+    range.top = u16x2_t{(uint16_t)s_hi[0], (uint16_t)s_hi[1]};
+    range.low = u16x2_t{(uint16_t)s_lo[0], (uint16_t)s_lo[1]};
+    bool strays;
+    const int eb = range.exponent<1>(strays);
+    if (threadIdx.x < 64) {
+        if (threadIdx.x == 0) s_form = RowForm{eb, {kNoStray, kNoStray, kNoStray}};
+        if (strays && eb >= 0) list_strays(row, H, &s_form);
+        __builtin_amdgcn_wave_barrier();
+        if (threadIdx.x == 0) forms[layer * (int)gridDim.x + e] = s_form;
+    }
+    const float scale = digit_scale(eb);
+    const int steps = (H + kDigitK - 1) / kDigitK;
+    for (int i = threadIdx.x; i < steps * 4; i += kPrepThreads) {        // 16 k-values: step i / 4, half (i / 2) % 2, q = i % 2
+        uint32_t a[4][2], b[4][2];
+        digits_of_8(2 * i < pieces ? *reinterpret_cast<const u32x4_t*>(row + i * 16) : zero, scale, a);
+        digits_of_8(2 * i + 1 < pieces ? *reinterpret_cast<const u32x4_t*>(row + i * 16 + 8) : zero, scale, b);
+        uint8_t* out = digits + layer * layer_bytes + (((int64_t)(i >> 2) * groups + e / 32) * 2 + ((i >> 1) & 1)) * 4096 +
+                       ((i & 1) * 32 + (e & 31)) * 16;
+#pragma unroll
+        for (int p = 0; p < 4; ++p) *reinterpret_cast<u32x4_t*>(out + p * 1024) = u32x4_t{a[p][0], a[p][1], b[p][0], b[p][1]};
+    }
+}
+
+// sum_s 2^(8 s) S[s], rounded once: either half is exact (|S[s]| <= 4 H 2^14 and, its digits being at most 64, |S[6]| <= H 2^12,
+// H <= 16384: the halves stay below 2^52)
+__device__ __forceinline__ double join_sums(const int (&s)[7])
+{
+    double hi = (double)s[6], lo = (double)s[2];
+    hi = __builtin_fma(hi, 256.0, (double)s[5]);
+    hi = __builtin_fma(hi, 256.0, (double)s[4]);
+    hi = __builtin_fma(hi, 256.0, (double)s[3]);
+    lo = __builtin_fma(lo, 256.0, (double)s[1]);
+    lo = __builtin_fma(lo, 256.0, (double)s[0]);
+    return __builtin_fma(hi, 16777216.0, lo);
+}
+
+// LDS traffic of the block is visible to all its waves; loads from global memory stay in flight.
+__device__ __forceinline__ void lds_barrier() { asm volatile("s_waitcnt lgkmcnt(0)\n\ts_barrier" ::: "memory"); }
+
+template <int WE, int WK>
+__global__ __launch_bounds__(WE * WK * 64, 2) void route_exact_kernel(
+    RowSrc x, int64_t n_tok, int H, const bf16_t* __restrict__ wr, const float* __restrict__ bias, int E, int K, int renorm,
+    const uint8_t* __restrict__ digits, const RowForm* __restrict__ forms, int32_t* __restrict__ idx, float* __restrict__ w,
+    int32_t* __restrict__ tile_hist)
+{
+    constexpr int NW = WE * WK, NT = NW * 64;    // waves, threads
+    constexpr int XL = 4 / WE;                   // 16-byte loads per lane and step: 32 rows x 128 bytes over WE waves
+    constexpr int SHARE = 2 * 8192;              // digits of one share of the k-range: [buffer][digit][32 rows][64 bytes]
+    constexpr int SUMS = (WK / 2) * WE * 28672;  // then: the sums of half the waves
+    constexpr int ZLD = WE * 32 + 1, LOGITS = 32 * ZLD * 8;      // then: the logits
+    constexpr int LDS = SUMS > WK * SHARE ? SUMS : WK * SHARE;
+    __shared__ __attribute__((aligned(16))) uint8_t lds[LDS > LOGITS ? LDS : LOGITS];
+    __shared__ RowForm form[32];                 // of the token rows
+    __shared__ int32_t hist[2][WE * 32];
+    const int tid = threadIdx.x, lane = tid & 63;
+    const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+    const int we = wave % WE, wk = wave / WE;
+    const int64_t t0 = (int64_t)blockIdx.x * 32;
+    const int groups = (E + 31) / 32;
+    auto token_row = [&](int r) {
+        const int64_t t = t0 + r < n_tok ? t0 + r : n_tok - 1;
+        return row_ptr<bf16_t>(x, t, H);
+    };
+    const int pieces = H / 8;                                // 16-byte pieces of a row
+
+    // ---- w_router: two steps of digits in registers, the next one's on their way ----
+    const int steps = (H + kDigitK - 1) / kDigitK;
+    const int mine = (steps + WK - 1) / WK;                  // steps of every share (its last ones may be empty: zeros)
+    const uint8_t* w_src = digits + (int64_t)(we < groups ? we : groups - 1) * 8192 + lane * 16;
+    constexpr int WB = WE > 1 ? 2 : 1;           // (one group's waves hold four rows' worth of x: no room for a second step)
+    i32x4_t wd[WB][2][4];
+    auto load_w = [&](int i, int buf) {
+        const int c = i * WK + wk;
+        const uint8_t* p = w_src + (int64_t)(c < steps ? c : steps - 1) * groups * 8192;
+#pragma unroll
+        for (int d = 0; d < 8; ++d) wd[buf][d / 4][d % 4] = *reinterpret_cast<const i32x4_t*>(p + d * 1024);
+    };
+
+    // ---- the form of the token rows: NT / 32 neighbouring lanes per row ----
+    for (int i = tid; i < 2 * WE * 32; i += NT) (&hist[0][0])[i] = 0;
+    {
+        constexpr int W = NT / 32, AHEAD = 8;
+        const bf16_t* row = token_row(tid / W);
+        RowRange range;
+        range.clear();
+#pragma unroll 1
+        for (int p0 = tid % W; p0 < pieces; p0 += AHEAD * W) {
+            u32x4_t v[AHEAD];
+#pragma unroll
+            for (int i = 0; i < AHEAD; ++i) {
+                const int p = p0 + i * W < pieces ? p0 + i * W : pieces - 1;      // (a piece may count twice)
+                v[i] = *reinterpret_cast<const u32x4_t*>(row + p * 8);
+            }
+#pragma unroll
+            for (int i = 0; i < AHEAD; ++i) range.add(v[i]);
+        }
+        bool strays;
+        const int eb = range.exponent<W>(strays);
+        // (a stray, if there is one, is looked for at the end)
+        if (tid % W == 0) form[tid / W] = RowForm{eb, {strays ? 0u : kNoStray, kNoStray, kNoStray}};
+    }
+    lds_barrier();
+
+    // ---- x: load p of this wave covers rows (we + WE p) * 8 .. + 7 of the tile, lane = (row, 16-byte piece of the step) ----
+    const int piece = lane & 7;
+    const bf16_t* x_src[XL];
+    float x_scale[XL];
+    uint32_t x_dst[XL];
+    // 16-byte slot c of a row's 64 digit bytes sits at slot c ^ f(row): 8, and 16, consecutive rows then fall into
+    // different banks
+    auto slot = [](int r, int c) { return (uint32_t)(r * 64 + ((c ^ (((r >> 1) & 1) * 2) ^ ((r >> 2) & 3)) << 4)); };
+#pragma unroll
+    for (int p = 0; p < XL; ++p) {
+        const int r = (we + WE * p) * 8 + (lane >> 3);
+        x_src[p] = token_row(r);
+        x_scale[p] = digit_scale(form[r].eb);
+        x_dst[p] = slot(r, piece >> 1) + (piece & 1) * 8;
+    }
+    constexpr int XB = WE > 1 ? 2 : 1;   // (issued in front of the step's weights, so that waiting for one is not waiting for the other)
+    u32x4_t xr[XB][XL];
+    auto load_x = [&](int i, int buf) {
+        const int at = (i * WK + wk) * 8 + piece;
+        // (past the row: a valid piece, turned into zeros below; a load under a condition would make the compiler wait for
+        // every load in flight)
+        const int from = at < pieces ? at : pieces - 1;
+#pragma unroll
+        for (int p = 0; p < XL; ++p) xr[buf][p] = *reinterpret_cast<const u32x4_t*>(x_src[p] + from * 8);
+    };
+    auto store_digits = [&](int i, int buf) {                // of this share's step i
+        const bool in = (i * WK + wk) * 8 + piece < pieces;
+        uint8_t* dig = lds + wk * SHARE + (i & 1) * 8192;
+#pragma unroll
+        for (int p = 0; p < XL; ++p) {
+            uint32_t d[4][2];
+            digits_of_8(xr[buf][p], in ? x_scale[p] : 0.f, d);
+#pragma unroll
+            for (int q = 0; q < 4; ++q) *reinterpret_cast<uint2*>(dig + q * 2048 + x_dst[p]) = make_uint2(d[q][0], d[q][1]);
+        }
+    };
+    const int fr = lane & 31, fq = lane >> 5;
+
+    i32x16_t acc[7];
+#pragma unroll
+    for (int s = 0; s < 7; ++s)
+#pragma unroll
+        for (int v = 0; v < 16; ++v) acc[s][v] = 0;
+    auto step = [&](int i, auto buf_const) {
+        constexpr int BUF = decltype(buf_const)::value;
+        lds_barrier();                   // the digits of step i are there, and those of step i - 1 have been read
+        if (XB == 2) load_x(i + 2, BUF);
+        if (WB == 2) load_w(i + 1, BUF ^ 1);
+        const uint8_t* dig = lds + wk * SHARE + (i & 1) * 8192;
+        i32x4_t xd[2][4];
+#pragma unroll
+        for (int half = 0; half < 2; ++half)
+#pragma unroll
+            for (int d = 0; d < 4; ++d) xd[half][d] = *reinterpret_cast<const i32x4_t*>(dig + d * 2048 + slot(fr, half * 2 + fq));
+        // expert rows as the MFMA's row operand: a lane ends up with 4 consecutive experts of one token
+        auto multiply = [&](int half, int a, int b) {
+            acc[a + b] = __builtin_amdgcn_mfma_i32_32x32x32_i8(wd[BUF][half][a], xd[half][b], acc[a + b], 0, 0, 0);
+        };
+#pragma unroll
+        for (int half = 0; half < 2; ++half) {
+            // (neighbours in this order belong to different sums)
+            multiply(half, 3, 3); multiply(half, 1, 1); multiply(half, 3, 2); multiply(half, 1, 2); multiply(half, 1, 3);
+            multiply(half, 2, 3); multiply(half, 2, 1); multiply(half, 2, 2); multiply(half, 3, 1);
+        }
+        auto any_of = [](const i32x4_t& d) { return __ballot((d[0] | d[1] | d[2] | d[3]) != 0) != 0; };
+        // bits 0, 1: lowest digits of the weights' halves that are not zero; 2, 3: of x's
+        const int low = (any_of(wd[BUF][0][0]) ? 1 : 0) | (any_of(wd[BUF][1][0]) ? 2 : 0) | (any_of(xd[0][0]) ? 4 : 0) |
+                        (any_of(xd[1][0]) ? 8 : 0);
+        store_digits(i + 1, XB == 2 ? BUF ^ 1 : 0);          // (past the last step: zeros nobody reads)
+        if (XB == 1) load_x(i + 2, 0);
+        // The loads one by one between the MFMAs: a wave issues in order, and eight loads in a row keep its MFMAs waiting
+        // for the address unit, which takes 16 clocks of each of the four waves' loads.
+        __builtin_amdgcn_sched_group_barrier(0x100, 4, 0);           // LDS reads of the first half
+#pragma unroll
+        for (int n = 0; n < 9; ++n) {
+            __builtin_amdgcn_sched_group_barrier(0x008, 1, 0);       // one MFMA
+            if (n < (WB == 2 ? 8 : 0) + (XB == 2 ? XL : 0)) __builtin_amdgcn_sched_group_barrier(0x020, 1, 0);   // one global load
+            if (n < 4) __builtin_amdgcn_sched_group_barrier(0x100, 1, 0);
+            __builtin_amdgcn_sched_group_barrier(0x008, 1, 0);
+        }
+        if (__builtin_expect(low != 0, 0)) {
+#pragma unroll
+            for (int half = 0; half < 2; ++half) {
+                const bool w_low = (low >> half & 1) != 0, x_low = (low >> half & 4) != 0;
+                if (w_low) { multiply(half, 0, 1); multiply(half, 0, 2); multiply(half, 0, 3); }
+                if (x_low) { multiply(half, 1, 0); multiply(half, 2, 0); multiply(half, 3, 0); }
+                if (w_low && x_low) multiply(half, 0, 0);
+            }
+        }
+        if (WB == 1) load_w(i + 1, 0);
+    };
+    load_x(0, 0);
+    if (XB == 2) load_x(1, 1);
+    load_w(0, 0);                        // (in the loop's order: the compiler's waits in the loop allow for what comes before it)
+    store_digits(0, 0);
+    if (XB == 1) load_x(1, 0);
+#pragma unroll 1
+    for (int i = 0; i < mine; i += 2) {
+        step(i, std::integral_constant<int, 0>{});
+        step(i + 1, std::integral_constant<int, WB - 1>{});
+    }
+
+    // ---- the shares' sums meet, the upper half of them handing theirs to the lower half ----
+#pragma unroll
+    for (int half = WK / 2; half >= 1; half /= 2) {
+        __syncthreads();
+        if (wk >= half && wk < 2 * half) {
+            i32x4_t* to = reinterpret_cast<i32x4_t*>(lds) + ((wk - half) * WE + we) * 1792 + lane;
+#pragma unroll
+            for (int s = 0; s < 7; ++s)
+#pragma unroll
+                for (int v = 0; v < 4; ++v)
+                    to[(s * 4 + v) * 64] = i32x4_t{acc[s][4 * v], acc[s][4 * v + 1], acc[s][4 * v + 2], acc[s][4 * v + 3]};
+        }
+        __syncthreads();
+        if (wk < half) {
+            const i32x4_t* from = reinterpret_cast<const i32x4_t*>(lds) + (wk * WE + we) * 1792 + lane;
+#pragma unroll
+            for (int s = 0; s < 7; ++s)
+#pragma unroll
+                for (int v = 0; v < 4; ++v) {
+                    const i32x4_t o = from[(s * 4 + v) * 64];
+#pragma unroll
+                    for (int u = 0; u < 4; ++u) acc[s][4 * v + u] += o[u];
+                }
+        }
+    }
+    __syncthreads();
+    double* const z = reinterpret_cast<double*>(lds);        // [32][ZLD]
+    // what is not in the digits (bit = token row, or expert of this wave's group; the same in every wave of a share)
+    const int rows = n_tok - t0 < 32 ? (int)(n_tok - t0) : 32;
+    const int own = we * 32 + fr < E ? we * 32 + fr : E - 1;             // lane l knows expert l % 32 of its wave's group
+    const RowForm own_form = forms[own];
+    const bool real = lane < 32 && we * 32 + fr < E;
+    const uint32_t e_lost = (uint32_t)__ballot(real && own_form.eb < 0);
+    const uint32_t e_stray = (uint32_t)__ballot(real && own_form.eb >= 0 && own_form.stray[0] != kNoStray);
+    const uint32_t t_stray = (uint32_t)__ballot(lane < rows && form[fr].eb >= 0 && form[fr].stray[0] != kNoStray);
+    if (wk == 0) {
+        // accumulator element v: expert (v / 4) * 8 + fq * 4 + v % 4 of the group, token fr
+        const int xe = form[fr].eb;
+        const float own_bias = bias ? bias[own] : 0.f;
+#pragma unroll
+        for (int v = 0; v < 16; ++v) {
+            const int e = (v >> 2) * 8 + fq * 4 + (v & 3);
+            const int s[7] = {acc[0][v], acc[1][v], acc[2][v], acc[3][v], acc[4][v], acc[5][v], acc[6][v]};
+            // (exponents of 29 and more: the power of two is a normal number; of rows that are not held, anything)
+            const double unit = __hiloint2double((1023 + xe + __shfl(own_form.eb, e, 64) - 312) << 20, 0);
+            z[fr * ZLD + we * 32 + e] = join_sums(s) * unit + (double)__shfl(own_bias, e, 64);
+        }
+    }
+    __syncthreads();
+    // ---- remainders: of x first, then of w_router, in ascending k ----
+    if (t_stray != 0) {                  // (one row in a thousand)
+#pragma unroll 1
+        for (uint32_t left = t_stray; left != 0; left &= left - 1) {
+            const int r = __ffs((int)left) - 1;
+            if (r % NW != wave) continue;
+            list_strays(token_row(r), H, &form[r]);
+            __builtin_amdgcn_wave_barrier();
+            const int eb = form[r].eb;
+            if (eb < 0) continue;
+#pragma unroll 1
+            for (int i = 0; i < kStray; ++i) {
+                const uint32_t k = form[r].stray[i];
+                if (k == kNoStray) break;
+                const double rest = remainder_part(token_row(r)[k], eb);
+                for (int e = lane; e < E; e += 64) z[r * ZLD + e] += rest * (double)bf16_to_f32(wr[(int64_t)e * H + k]);
+            }
+        }
+        __syncthreads();
+    }
+    if (wk == 0) {
+#pragma unroll 1
+        for (uint32_t left = e_stray; left != 0; left &= left - 1) {
+            const int e = __ffs((int)left) - 1, eb = __builtin_amdgcn_readlane(own_form.eb, e);
+            const uint32_t ks[kStray] = {(uint32_t)__builtin_amdgcn_readlane((int)own_form.stray[0], e),
+                                         (uint32_t)__builtin_amdgcn_readlane((int)own_form.stray[1], e),
+                                         (uint32_t)__builtin_amdgcn_readlane((int)own_form.stray[2], e)};
+            if (lane < 32 && form[fr].eb >= 0)
+#pragma unroll
+                for (int i = 0; i < kStray; ++i)
+                    if (ks[i] != kNoStray)
+                        z[fr * ZLD + we * 32 + e] += digit_part(token_row(fr)[ks[i]], form[fr].eb) *
+                                                     remainder_part(wr[(int64_t)(we * 32 + e) * H + ks[i]], eb);
+        }
+    }
+    // ---- rows that are not held (a row of x may have turned out to be one above) ----
+    const bool lost = e_lost != 0 || __ballot(lane < rows && form[fr].eb < 0) != 0;
+    if (__syncthreads_or(lost)) {
+#pragma unroll 1
+        for (int tile = 0; tile < 4 * WE; ++tile) {
+            const int a = (tile & 1) * 16, e0 = (tile >> 1) * 16;
+            if (a >= rows || e0 >= E) continue;
+            const bool here = lane < 16 ? a + lane < rows && form[a + lane].eb < 0
+                                        : lane < 32 && e0 + lane - 16 < E && forms[e0 + lane - 16].eb < 0;
+            if (__ballot(here) == 0) continue;          // (the same in every wave)
+            logits_tile<bf16_t, 4>(x, n_tok, H, wr, bias, E, t0 + a, e0, [&](int i, int j, double logit) {
+                if (form[a + i].eb < 0 || forms[e0 + j].eb < 0) z[(a + i) * ZLD + e0 + j] = logit;
+            });
+            __syncthreads();             // its scratch is used again
+        }
+    }
+
+    // ---- top-k: 16 lanes per token ----
+    const int64_t tile0 = t0 * K / kPermTile;        // 32 tokens x K <= 512 assignments touch at most two permutation tiles
+    const int c = lane & 15;
+    constexpr int AT_ONCE = 512 / NT;                // rows tid / 16, tid / 16 + NT / 16, ...
+    const double* zs[AT_ONCE];
+    int my_e[AT_ONCE];
+    float my_w[AT_ONCE];
+#pragma unroll
+    for (int u = 0; u < AT_ONCE; ++u) zs[u] = z + (tid / 16 + u * (NT / 16)) * ZLD;
+    topk_of_rows<WE * 2, AT_ONCE>(zs, E, K, renorm, c, false, my_e, my_w);
+#pragma unroll
+    for (int u = 0; u < AT_ONCE; ++u) {
+        const int64_t t = t0 + tid / 16 + u * (NT / 16);
+        if (t < n_tok && c < K) {
+            idx[t * K + c] = my_e[u];
+            w[t * K + c] = my_w[u];
+            if (tile_hist) atomicAdd(&hist[(t * K + c) / kPermTile - tile0][my_e[u]], 1);
+        }
+    }
+    if (tile_hist) {
+        __syncthreads();
+        for (int i = tid; i < 2 * E; i += NT) {
             const int cnt = hist[i / E][i % E];
             if (cnt) atomicAdd(&tile_hist[(tile0 + i / E) * E + i % E], cnt);
         }
@@ -492,7 +1060,10 @@ __global__ __launch_bounds__(kSmallWaves * 64) void route_small_kernel(
     static_assert(kSmallExperts <= 256, "an expert is one byte of expert_of");
     const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
     const int t0 = (int)blockIdx.x * 16;
-    logits_tile<T, kSmallWaves, true>(x, n_tok, H, wr, bias, E, logits, t0, (int)blockIdx.y * 16);
+    const int e0 = (int)blockIdx.y * 16;
+    logits_tile<T, kSmallWaves>(x, n_tok, H, wr, bias, E, t0, e0, [&](int i, int j, double z) {
+        store_shared(logits + (int64_t)(t0 + i) * E + e0 + j, z);      // (another block of the launch may read it)
+    });
     for (int i = tid; i < E * kSmallWords; i += kSmallWaves * 64) (&chosen[0][0])[i] = 0ull;
     if (tid < E) count[tid] = 0;
     if (tid == 0) twice = 0;
@@ -621,6 +1192,42 @@ hipError_t launch_route_small(int dtype, RowSrc x, int64_t T, int H, const void*
     if (npl <= 2) return go(std::integral_constant<int, 2>{});
     if (npl <= 8) return go(std::integral_constant<int, 8>{});
     return go(std::integral_constant<int, 16>{});
+}
+
+int64_t router_digit_bytes(int H, int E) { return (int64_t)((H + kDigitK - 1) / kDigitK) * ((E + 31) / 32) * 8192; }
+
+hipError_t launch_router_digits(const RouterWeights& w, int layers, int H, int E, uint8_t* digits, void* forms, int32_t* zero_buf,
+                                int64_t zero_n, hipStream_t s)
+{
+    const int rows = (E + 31) / 32 * 32;
+    static_assert(sizeof(RowForm) == 16, "router_form_bytes");
+    router_digits_kernel<<<dim3((unsigned)rows, (unsigned)layers), kPrepThreads, 0, s>>>(
+        w, H, E, digits, router_digit_bytes(H, E), static_cast<RowForm*>(forms), zero_buf, zero_n);
+    return hipGetLastError();
+}
+
+hipError_t launch_route_exact(RowSrc x, int64_t T, int H, const void* w_router, const float* bias, int E, int K, int renorm,
+                              const uint8_t* digits, const void* forms, int32_t* idx, float* w, int32_t* tile_hist,
+                              hipStream_t s)
+{
+    const int64_t tiles = (T + 31) / 32;
+    int cus = 0;
+    const hipError_t e = compute_units(&cus);
+    if (e != hipSuccess) return e;
+    auto go = [&](auto we, auto wk) {
+        constexpr int WE = decltype(we)::value, WK = decltype(wk)::value;
+        route_exact_kernel<WE, WK><<<(unsigned)tiles, WE * WK * 64, 0, s>>>(
+            x, T, H, static_cast<const bf16_t*>(w_router), bias, E, K, renorm, digits, static_cast<const RowForm*>(forms), idx,
+            w, tile_hist);
+        return hipGetLastError();
+    };
+    using std::integral_constant;
+    // With a block per compute unit at most, twice the waves (registers leave room for two per SIMD either way): 2112 tokens,
+    // H = 2048, 128 experts 26.4 us against 29.7, 6000 tokens 35 / 37; 8320 tokens, 260 blocks, 53 / 44.
+    const bool few = tiles <= cus;
+    if (E <= 32) return few ? go(integral_constant<int, 1>{}, integral_constant<int, 8>{}) : go(integral_constant<int, 1>{}, integral_constant<int, 4>{});
+    if (E <= 64) return few ? go(integral_constant<int, 2>{}, integral_constant<int, 4>{}) : go(integral_constant<int, 2>{}, integral_constant<int, 2>{});
+    return few ? go(integral_constant<int, 4>{}, integral_constant<int, 2>{}) : go(integral_constant<int, 4>{}, integral_constant<int, 1>{});
 }
 
 hipError_t launch_router_logits(int dtype, RowSrc x, int64_t T, int H, const void* w_router, const float* bias,

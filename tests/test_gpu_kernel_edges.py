@@ -87,6 +87,59 @@ def test_one_launch_routing_of_long_rows(gpu_lib, H, dtype, T):
         assert torch.equal(torch.cat([yd, yp]), y_steps)
 
 
+# Routing of larger batches through exact integer sums: 32-token tiles, 32-expert groups (1, 2 and 4 of them; up to and above one
+# block per compute unit), 64-value steps (a ragged last one), and rows that the 32-bit fixed point holds with one rest, with
+# three, not at all (four rests; no fp32 scale), of zeros.  Indices are exact; a weight is one rounding to fp32 of a quotient of
+# fp64 values: 2^-23 relative.
+@pytest.mark.parametrize("H,E,K,T", [(2056, 128, 8, 2290), (4104, 17, 5, 4580), (4096, 32, 1, 8225), (8, 128, 16, 586000),
+                                     (16384, 64, 9, 577), (2048, 33, 3, 9190), (2048, 97, 16, 8193)])
+@pytest.mark.parametrize("renorm", [True, False])
+def test_exact_routing(gpu_lib, H, E, K, T, renorm):
+    if H == 8 and not renorm:
+        pytest.skip("one pass over the long batch is enough")
+    w = inputs.Workload("exact", H=H, E=E, K=K, I=8, n_layers=1, D=T, P=0, dtype="bf16", seed=T)
+    x = inputs.randn((T, H), 1.0, w.seed, "x", 0, "bf16").float()
+    wr = inputs.randn((E, H), 0.02, w.seed, "w_router", 0, "bf16").float()
+    some = [0, 1, 31, 32, T - 33, T - 2, T - 1]
+    for i, t in enumerate(some):
+        top = float(x[t].abs().max())
+        for j in range([1, 3, 4, 1, 0, 2, 1][i]):         # values far below the row's largest, with bits to the last
+            x[t, (7 * j + 3 * i) % H] = (-1) ** j * top * 2.0 ** (-23 - 2 * j) * 1.3
+    x[5] = 0
+    x[6] *= 2.0 ** 40
+    x[7] *= 2.0 ** -110
+    wr[2, 1] = float(wr[2].abs().max()) * 2.0 ** -25 * 1.7
+    wr[3, :4] = wr[3].abs().max() * 2.0 ** -26 * 1.9
+    wr[min(11, E - 1)] = 0
+    wr[min(12, E - 1)] = wr[min(14, E - 1)]               # equal logits: the lower index first
+    x, wr = x.bfloat16(), wr.bfloat16()
+    bias = inputs.randn((E,), 0.1, w.seed, "bias", 0, "f32")
+    bias[min(12, E - 1)] = bias[min(14, E - 1)]
+    ctx = gpu_lib.Context(H, E, K, 8, torch.bfloat16, max_tokens=T, renormalize=renorm, device=DEV)
+    idx, wt = ctx.moe_router_topk(x.to(DEV), wr.to(DEV), bias.to(DEV))
+    rows = np.unique(np.concatenate([np.arange(min(T, 64)), np.arange(T - 64, T), np.random.default_rng(1).integers(0, T, 2000)]))
+    o_idx, o_w = oracle.router_topk(inputs.to_numpy(x[rows]), inputs.to_numpy(wr), bias.numpy(), K, renorm)[:2]
+    assert (idx.cpu().numpy()[rows] == o_idx).all()
+    np.testing.assert_allclose(wt.cpu().numpy()[rows], o_w, rtol=2.0 ** -23, atol=0)
+
+
+# ... as part of a pass: the digits of ten layers come in two launches, and the top-k counts the permutation's histograms
+def test_exact_routing_in_a_group(gpu_lib):
+    H, E, K, I, T, n = 2048, 128, 8, 64, 2300, 10
+    w = inputs.Workload("exact", H=H, E=E, K=K, I=I, n_layers=n, D=0, P=T, dtype="bf16", seed=5)
+    layers = [{k: (v.to(DEV) if v is not None else None) for k, v in inputs.make_layer(w, l).items()} for l in range(n)]
+    x = inputs.randn((T, H), 1.0, 5, "x", 0, "bf16").to(DEV)
+    ctx = gpu_lib.Context(H, E, K, I, torch.bfloat16, max_tokens=T, device=DEV)
+    for _ in range(2):
+        _, y = ctx.moe_group_forward(layers, None, x, "layered")
+        z = x
+        for L in layers:
+            idx, wt = ctx.moe_router_topk(z, L["w_router"])
+            counts, offsets, perm, inv, x_perm = ctx.moe_permute(z, idx)
+            z = ctx.moe_combine(ctx.moe_grouped_ffn(x_perm, offsets, L["w_gate_up"], L["w_down"]), inv, wt, residual=z)
+        assert torch.equal(y, z)
+
+
 # Many permutation tiles: from 2^25 histogram words read in all (tiles squared times experts), the tiles' running sums come from
 # a pass of their own; one tile to either side of the border, 64-expert groups that are not whole
 @pytest.mark.parametrize("T,K,E", [(65536, 8, 512), (65537, 8, 512), (300000, 5, 65), (1 << 20, 8, 3)])
