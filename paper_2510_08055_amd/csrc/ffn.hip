@@ -271,15 +271,21 @@ __global__ __launch_bounds__(NW * 64, MINW) void grouped_gemm_bf16_pipe_kernel(
         b_src[p] = We + (int64_t)n * ldw + ((l_chunk ^ swz(rb)) << 3);
     }
     const uint32_t lds0 = lds_address(smem);
-    auto issue_b = [&](int kt, int p) {
+    // (stream: the weights of this tile are read by this block alone; see load_lds.  The wide shape is for many rows per expert.)
+    constexpr bool MAY_STREAM = BM <= 64;
+    auto issue_b = [&](int kt, int p, auto stream) {
         const int kw = (SPLIT && !GATED && kt >= nk_w) ? kt - nk_w : kt;
-        load_lds_16(b_src[p] + kw * PBK, lds0 + B_BASE + (kt % NS) * B_SLOT + (wave + NW * p) * 1024);
+        load_lds_16<decltype(stream)::value>(b_src[p] + kw * PBK, lds0 + B_BASE + (kt % NS) * B_SLOT + (wave + NW * p) * 1024);
     };
+    auto issue_first = [&](auto stream) {
 #pragma unroll
-    for (int st = 0; st < NS - 1; ++st)
-        if (st < nk_)
+        for (int st = 0; st < NS - 1; ++st)
+            if (st < nk_)
 #pragma unroll
-            for (int p = 0; p < B_LPW; ++p) issue_b(st, p);
+                for (int p = 0; p < B_LPW; ++p) issue_b(st, p, stream);
+    };
+    if (MAY_STREAM && tc.alone) issue_first(std::integral_constant<bool, MAY_STREAM>{});
+    else issue_first(std::false_type{});
     if (MAPPED) {
         // the lookups came before the weight loads of the prologue: wait for them alone
         if (nk_ >= NS - 1) wait_vmcnt<(NS - 1) * B_LPW>();
@@ -307,12 +313,12 @@ __global__ __launch_bounds__(NW * 64, MINW) void grouped_gemm_bf16_pipe_kernel(
     auto issue_a = [&](int kt, int p) {
         load_lds_16(a_src[p] + kt * PBK, lds0 + (kt % NS) * A_SLOT + (wave + NW * p) * 1024);
     };
-    auto issue_part = [&](int kt, int part) {
+    auto issue_part = [&](int kt, int part, auto stream) {
 #pragma unroll
         for (int q = 0; q < LPS; ++q) {
             if (q % KS != part) continue;
             if (q < A_LPW) issue_a(kt, q);
-            else issue_b(kt, q - A_LPW);
+            else issue_b(kt, q - A_LPW, stream);
         }
     };
     // ---- LDS byte offsets of the operand rows this lane feeds to the MFMAs ----
@@ -336,7 +342,7 @@ __global__ __launch_bounds__(NW * 64, MINW) void grouped_gemm_bf16_pipe_kernel(
     // the barrier that hands over the next stage, under the reads of that stage's first slice.
     // The body is instantiated for the number TMV of row blocks this wave really has (0..TM), so the
     // hot loop is straight-line code; a wave with no row block still loads and synchronises.
-    auto run = [&](auto tmv_const) {
+    auto run = [&](auto tmv_const, auto stream) {
         constexpr int TMV = decltype(tmv_const)::value;
         constexpr int TMA = TMV > 0 ? TMV : 1;
         float16_t acc[TMA][TN];
@@ -406,11 +412,11 @@ __global__ __launch_bounds__(NW * 64, MINW) void grouped_gemm_bf16_pipe_kernel(
 #pragma unroll
             for (int kk = 0; kk < KS - 1; ++kk) {
                 read_frags(g, kk + 1, (kk + 1) & 1);
-                if (MORE) issue_part(g + NS - 1, kk);
+                if (MORE) issue_part(g + NS - 1, kk, stream);
                 mfma_set(kk & 1);
                 interleave(TMV > 0 ? TMV + TN : 0, MORE ? parts_in(kk) : 0, TMV * TN);
             }
-            if (MORE) issue_part(g + NS - 1, KS - 1);
+            if (MORE) issue_part(g + NS - 1, KS - 1, stream);
             if (NEXT) {
                 if (MORE && NS > 3 && g < NS - 2) wait_vmcnt<WAIT_EARLY>();
                 else if (MORE) wait_vmcnt<WAIT_MAIN>();
@@ -442,11 +448,15 @@ __global__ __launch_bounds__(NW * 64, MINW) void grouped_gemm_bf16_pipe_kernel(
 
     // row blocks wm, wm + WM, ... below rb_valid belong to this wave
     const int tm_valid = (rb_valid - wm + WM - 1) / WM;
-    if (TM >= 4 && tm_valid >= 4) run(std::integral_constant<int, (TM >= 4 ? 4 : 0)>{});
-    else if (TM >= 3 && tm_valid >= 3) run(std::integral_constant<int, (TM >= 3 ? 3 : 0)>{});
-    else if (TM >= 2 && tm_valid >= 2) run(std::integral_constant<int, (TM >= 2 ? 2 : 0)>{});
-    else if (tm_valid >= 1) run(std::integral_constant<int, 1>{});
-    else run(std::integral_constant<int, 0>{});
+    auto run_rows = [&](auto stream) {
+        if (TM >= 4 && tm_valid >= 4) run(std::integral_constant<int, (TM >= 4 ? 4 : 0)>{}, stream);
+        else if (TM >= 3 && tm_valid >= 3) run(std::integral_constant<int, (TM >= 3 ? 3 : 0)>{}, stream);
+        else if (TM >= 2 && tm_valid >= 2) run(std::integral_constant<int, (TM >= 2 ? 2 : 0)>{}, stream);
+        else if (tm_valid >= 1) run(std::integral_constant<int, 1>{}, stream);
+        else run(std::integral_constant<int, 0>{}, stream);
+    };
+    if (MAY_STREAM && tc.alone) run_rows(std::integral_constant<bool, MAY_STREAM>{});
+    else run_rows(std::false_type{});
 }
 
 // ----------------------------------------------------------------------------------------------
@@ -536,175 +546,182 @@ __global__ __launch_bounds__(kBigWaves * 64, 2) void grouped_gemm_bf16_big_kerne
             b_off[p] = (uint32_t)r * (uint32_t)ldw * 2u + l_chunk;
         }
     };
-    auto issue_b = [&](int p, uint32_t slot) {
-        load_lds_16_base(GATED && p >= LPW / 2 ? b_up : b_gate, b_off[p], lds0 + B_BASE + slot + (wave + NW * p) * 1024);
-    };
-    auto advance_b = [&](int stage) {      // after the loads of weight stage `stage` of a tile
-        const int64_t by = (SPLIT && !GATED && stage + 1 == nk_w) ? ROWB - (int64_t)ldw * 2 : ROWB;
-        b_gate += by;
-        if (GATED) b_up += by;
-    };
-    auto next_b_slot = [](uint32_t s) { return s == 2 * SLOT ? 0u : s + SLOT; };
-
-    // ---- LDS addresses of the operand rows this lane feeds to the MFMAs ----
-    // k-slice kk of tile row r sits at r * 128 + ((2 kk + fq) ^ swz(r)) * 16; the row blocks of a wave are constants
-    // apart and go into the read instructions.  (Addresses are integers in the LDS address space: the compiler then
-    // folds those constants instead of adding the array's base at every read.)
-    typedef __attribute__((address_space(3))) const bf16x8_t lds_bf16x8_t;
-    const int fr = lane & 31, fq = lane >> 5;
-    uint32_t k_lane[KS];
-#pragma unroll
-    for (int kk = 0; kk < KS; ++kk) k_lane[kk] = lds0 + fr * ROWB + (((kk * 2 + fq) ^ swz(fr)) << 4);
-    const uint32_t a_wave = wm * 32 * ROWB, b_wave = B_BASE + wn * WNO * ROWB;
-
-    // ---- first tile: two weight stages and one activation stage ----
-    BigTile cur = queue.take(at), nxt = cur;
-    uint32_t a_slot = 0, b_slot = 0;       // slots of the stage being multiplied
-    rows.look_up(cur);
-    use_weights(cur);
-#pragma unroll
-    for (int st = 0; st < 2; ++st) {
-#pragma unroll
-        for (int p = 0; p < LPW; ++p) issue_b(p, st * SLOT);
-        advance_b(st);
-    }
-    wait_vmcnt<2 * LPW>();                 // the look-ups came before the weight loads
-    rows.use(cur);
-    rows.issue(0, lds0);
-    wait_vmcnt<0>();
-    block_barrier();
-    rows.issue(1, lds0 + SLOT);
-
-    // One tile.  On entry stage 0 of both operands is in LDS for every wave, weight stage 1 is in flight and the
-    // activation loads of stage 1 have been issued.  The body is instantiated for the number TMV of row blocks this
-    // wave really has (0..TM), so the hot loop is straight-line code; a wave with no row block still loads and
-    // synchronises.
-    auto run = [&](auto tmv_const) {
-        constexpr int TMV = decltype(tmv_const)::value;
-        constexpr int TMA = TMV > 0 ? TMV : 1;
-        float16_t acc[TMA][TN];
-#pragma unroll
-        for (int i = 0; i < TMA; ++i)
-#pragma unroll
-            for (int j = 0; j < TN; ++j)
-#pragma unroll
-                for (int v = 0; v < 16; ++v) acc[i][j][v] = 0.f;
-        bf16x8_t af[2][TMA], bfr[2][TN];
-        auto read_frags = [&](uint32_t as, uint32_t bs, int kk, int set) {
-            if (TMV == 0) return;
-            const uint32_t av = k_lane[kk] + (as + a_wave), bv = k_lane[kk] + (bs + b_wave);
-#pragma unroll
-            for (int i = 0; i < TMV; ++i) af[set][i] = *(lds_bf16x8_t*)(uintptr_t)(av + i * (WM * 32 * ROWB));
-#pragma unroll
-            for (int j = 0; j < TN; ++j)
-                bfr[set][j] = *(lds_bf16x8_t*)(uintptr_t)(bv + (j < TNO ? j * 32 : NO + (j - TNO) * 32) * ROWB);
+    // The block's walk over its tiles.  STREAM: of weights that no other block reads (see load_lds): whether they are is a
+    // matter of the whole launch, because the policy is part of the load instruction.
+    auto walk = [&](auto stream) {
+        constexpr bool STREAM = decltype(stream)::value;
+        auto issue_b = [&](int p, uint32_t slot) {
+            load_lds_16_base<STREAM>(GATED && p >= LPW / 2 ? b_up : b_gate, b_off[p], lds0 + B_BASE + slot + (wave + NW * p) * 1024);
         };
-        auto mfma_set = [&](int set) {
+        auto advance_b = [&](int stage) {      // after the loads of weight stage `stage` of a tile
+            const int64_t by = (SPLIT && !GATED && stage + 1 == nk_w) ? ROWB - (int64_t)ldw * 2 : ROWB;
+            b_gate += by;
+            if (GATED) b_up += by;
+        };
+        auto next_b_slot = [](uint32_t s) { return s == 2 * SLOT ? 0u : s + SLOT; };
+
+        // ---- LDS addresses of the operand rows this lane feeds to the MFMAs ----
+        // k-slice kk of tile row r sits at r * 128 + ((2 kk + fq) ^ swz(r)) * 16; the row blocks of a wave are constants
+        // apart and go into the read instructions.  (Addresses are integers in the LDS address space: the compiler then
+        // folds those constants instead of adding the array's base at every read.)
+        typedef __attribute__((address_space(3))) const bf16x8_t lds_bf16x8_t;
+        const int fr = lane & 31, fq = lane >> 5;
+        uint32_t k_lane[KS];
 #pragma unroll
-            for (int i = 0; i < TMV; ++i)
+        for (int kk = 0; kk < KS; ++kk) k_lane[kk] = lds0 + fr * ROWB + (((kk * 2 + fq) ^ swz(fr)) << 4);
+        const uint32_t a_wave = wm * 32 * ROWB, b_wave = B_BASE + wn * WNO * ROWB;
+
+        // ---- first tile: two weight stages and one activation stage ----
+        BigTile cur = queue.take(at), nxt = cur;
+        uint32_t a_slot = 0, b_slot = 0;       // slots of the stage being multiplied
+        rows.look_up(cur);
+        use_weights(cur);
+#pragma unroll
+        for (int st = 0; st < 2; ++st) {
+#pragma unroll
+            for (int p = 0; p < LPW; ++p) issue_b(p, st * SLOT);
+            advance_b(st);
+        }
+        wait_vmcnt<2 * LPW>();                 // the look-ups came before the weight loads
+        rows.use(cur);
+        rows.issue(0, lds0);
+        wait_vmcnt<0>();
+        block_barrier();
+        rows.issue(1, lds0 + SLOT);
+
+        // One tile.  On entry stage 0 of both operands is in LDS for every wave, weight stage 1 is in flight and the
+        // activation loads of stage 1 have been issued.  The body is instantiated for the number TMV of row blocks this
+        // wave really has (0..TM), so the hot loop is straight-line code; a wave with no row block still loads and
+        // synchronises.
+        auto run = [&](auto tmv_const) {
+            constexpr int TMV = decltype(tmv_const)::value;
+            constexpr int TMA = TMV > 0 ? TMV : 1;
+            float16_t acc[TMA][TN];
+#pragma unroll
+            for (int i = 0; i < TMA; ++i)
 #pragma unroll
                 for (int j = 0; j < TN; ++j)
-                    // weight rows as the MFMA's row operand, activation rows as its column operand: a lane then
-                    // holds 4 consecutive OUTPUT COLUMNS of one output row
-                    acc[i][j] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(bfr[set][j], af[set][i], acc[i][j], 0, 0, 0);
-        };
-        // Ask the scheduler to issue the LDS reads and the global loads of a region one by one between its MFMAs
-        // (they then execute in the shadow of the matrix pipe) instead of in a clump.
-        auto interleave = [](int n_ds, int n_vmem, int n_mfma) {
 #pragma unroll
-            for (int i = 0; i < 16; ++i) {
-                if (i < n_ds && i < n_mfma) {
-                    __builtin_amdgcn_sched_group_barrier(0x008, 1, 0);   // one MFMA
-                    __builtin_amdgcn_sched_group_barrier(0x100, 1, 0);   // one LDS read
+                    for (int v = 0; v < 16; ++v) acc[i][j][v] = 0.f;
+            bf16x8_t af[2][TMA], bfr[2][TN];
+            auto read_frags = [&](uint32_t as, uint32_t bs, int kk, int set) {
+                if (TMV == 0) return;
+                const uint32_t av = k_lane[kk] + (as + a_wave), bv = k_lane[kk] + (bs + b_wave);
+#pragma unroll
+                for (int i = 0; i < TMV; ++i) af[set][i] = *(lds_bf16x8_t*)(uintptr_t)(av + i * (WM * 32 * ROWB));
+#pragma unroll
+                for (int j = 0; j < TN; ++j)
+                    bfr[set][j] = *(lds_bf16x8_t*)(uintptr_t)(bv + (j < TNO ? j * 32 : NO + (j - TNO) * 32) * ROWB);
+            };
+            auto mfma_set = [&](int set) {
+#pragma unroll
+                for (int i = 0; i < TMV; ++i)
+#pragma unroll
+                    for (int j = 0; j < TN; ++j)
+                        // weight rows as the MFMA's row operand, activation rows as its column operand: a lane then
+                        // holds 4 consecutive OUTPUT COLUMNS of one output row
+                        acc[i][j] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(bfr[set][j], af[set][i], acc[i][j], 0, 0, 0);
+            };
+            // Ask the scheduler to issue the LDS reads and the global loads of a region one by one between its MFMAs
+            // (they then execute in the shadow of the matrix pipe) instead of in a clump.
+            auto interleave = [](int n_ds, int n_vmem, int n_mfma) {
+#pragma unroll
+                for (int i = 0; i < 16; ++i) {
+                    if (i < n_ds && i < n_mfma) {
+                        __builtin_amdgcn_sched_group_barrier(0x008, 1, 0);   // one MFMA
+                        __builtin_amdgcn_sched_group_barrier(0x100, 1, 0);   // one LDS read
+                    }
                 }
-            }
 #pragma unroll
-            for (int i = 0; i < 16; ++i) {
-                if (i < n_vmem && n_ds + i < n_mfma) {
-                    __builtin_amdgcn_sched_group_barrier(0x008, 1, 0);   // one MFMA
-                    __builtin_amdgcn_sched_group_barrier(0x020, 1, 0);   // one global load
+                for (int i = 0; i < 16; ++i) {
+                    if (i < n_vmem && n_ds + i < n_mfma) {
+                        __builtin_amdgcn_sched_group_barrier(0x008, 1, 0);   // one MFMA
+                        __builtin_amdgcn_sched_group_barrier(0x020, 1, 0);   // one global load
+                    }
                 }
-            }
-        };
-        // The k-slices of step s but the last, with the weight loads of the stage two steps on; then the wait for
-        // the next stage and the barrier that hands it over.  On return the last slice's operands are in registers.
-        uint32_t b_ahead = next_b_slot(next_b_slot(b_slot));     // slot of the weight stage two steps on
-        auto step_head = [&](int stage_ahead) {
+            };
+            // The k-slices of step s but the last, with the weight loads of the stage two steps on; then the wait for
+            // the next stage and the barrier that hands it over.  On return the last slice's operands are in registers.
+            uint32_t b_ahead = next_b_slot(next_b_slot(b_slot));     // slot of the weight stage two steps on
+            auto step_head = [&](int stage_ahead) {
 #pragma unroll
-            for (int kk = 0; kk < KS - 1; ++kk) {
-                read_frags(a_slot, b_slot, kk + 1, (kk + 1) & 1);
-                issue_b(kk, b_ahead);
-                mfma_set(kk & 1);
-                interleave(TMV > 0 ? TMV + TN : 0, 1, TMV * TN);
-            }
-            issue_b(KS - 1, b_ahead);
-            advance_b(stage_ahead);
-            // Loads return in issue order.  Everything of the next stage was issued before this step's four weight
-            // loads (its activation loads behind the barrier that began this step), so those four may stay.
-            wait_vmcnt<LPW>();
-            wait_lds_reads();          // all of this wave's reads of the stage have returned before its slots are refilled
-            block_barrier();
-        };
-        auto step_tail = [&](bool read_next) {
-            const uint32_t a_next = a_slot ^ SLOT, b_next = next_b_slot(b_slot);
-            if (read_next) read_frags(a_next, b_next, 0, 0);
-            mfma_set((KS - 1) & 1);
-            interleave(read_next && TMV > 0 ? TMV + TN : 0, 0, TMV * TN);
-            a_slot = a_next;
-            b_ahead = b_slot;
-            b_slot = b_next;
-        };
+                for (int kk = 0; kk < KS - 1; ++kk) {
+                    read_frags(a_slot, b_slot, kk + 1, (kk + 1) & 1);
+                    issue_b(kk, b_ahead);
+                    mfma_set(kk & 1);
+                    interleave(TMV > 0 ? TMV + TN : 0, 1, TMV * TN);
+                }
+                issue_b(KS - 1, b_ahead);
+                advance_b(stage_ahead);
+                // Loads return in issue order.  Everything of the next stage was issued before this step's four weight
+                // loads (its activation loads behind the barrier that began this step), so those four may stay.
+                wait_vmcnt<LPW>();
+                wait_lds_reads();          // all of this wave's reads of the stage have returned before its slots are refilled
+                block_barrier();
+            };
+            auto step_tail = [&](bool read_next) {
+                const uint32_t a_next = a_slot ^ SLOT, b_next = next_b_slot(b_slot);
+                if (read_next) read_frags(a_next, b_next, 0, 0);
+                mfma_set((KS - 1) & 1);
+                interleave(read_next && TMV > 0 ? TMV + TN : 0, 0, TMV * TN);
+                a_slot = a_next;
+                b_ahead = b_slot;
+                b_slot = b_next;
+            };
 
-        read_frags(a_slot, b_slot, 0, 0);
-        for (int s = 0; s < nk - 3; ++s) {
-            step_head(s + 2);
-            rows.issue(s + 2, lds0 + a_slot);
+            read_frags(a_slot, b_slot, 0, 0);
+            for (int s = 0; s < nk - 3; ++s) {
+                step_head(s + 2);
+                rows.issue(s + 2, lds0 + a_slot);
+                step_tail(true);
+            }
+            // step nk - 3: the next tile's rows are looked up.  (Not earlier: the registers the look-ups land on must not
+            // be copied before they have landed, and the shorter they live the less reason the compiler has to; the
+            // build checks the listing.)
+            rows.look_up(nxt);
+            step_head(nk - 1);
+            rows.issue(nk - 1, lds0 + a_slot);
             step_tail(true);
+            // step nk - 2: from here on the loads are those of the next tile
+            use_weights(nxt);
+            rows.use(nxt);
+            step_head(0);
+            rows.issue(0, lds0 + a_slot);
+            step_tail(true);
+            // step nk - 1
+            step_head(1);
+            // every wave has read the last stage: its activation slot takes stage 1 of the next tile, its weight slot
+            // (free until the next tile's first step) is where the epilogue works
+            rows.issue(1, lds0 + a_slot);
+            const uint32_t epi_slot = B_BASE + b_slot;
+            step_tail(false);
+
+            store_tile<GATED, OUT_F32, SPLIT, TMV, TNO, WM>(acc, cur.row0, cur.row_end, wm, cur.n_tile * NO + wn * WNO,
+                                                            smem + epi_slot + wave * (TNO * 2048), Out_, ldo, N);
+        };
+
+        for (;;) {
+            // (the last tile is followed by itself: its first stages are loaded once more and never used)
+            at += stride;
+            const bool more = at < queue.end;
+            if (more) nxt = queue.take(at);
+            const int rb_valid = (cur.row_end - cur.row0 + 31) / 32;
+            // row blocks wm, wm + WM, ... below rb_valid belong to this wave
+            const int tm_valid = (rb_valid - wm + WM - 1) / WM;
+            if (tm_valid >= 4) run(std::integral_constant<int, 4>{});
+            else if (tm_valid >= 3) run(std::integral_constant<int, 3>{});
+            else if (tm_valid >= 2) run(std::integral_constant<int, 2>{});
+            else if (tm_valid >= 1) run(std::integral_constant<int, 1>{});
+            else run(std::integral_constant<int, 0>{});
+            if (!more) break;
+            cur = nxt;
+            wait_lds_reads();
+            block_barrier();       // every wave has read its piece of the epilogue's slot: the next weight loads may overwrite it
         }
-        // step nk - 3: the next tile's rows are looked up.  (Not earlier: the registers the look-ups land on must not
-        // be copied before they have landed, and the shorter they live the less reason the compiler has to; the
-        // build checks the listing.)
-        rows.look_up(nxt);
-        step_head(nk - 1);
-        rows.issue(nk - 1, lds0 + a_slot);
-        step_tail(true);
-        // step nk - 2: from here on the loads are those of the next tile
-        use_weights(nxt);
-        rows.use(nxt);
-        step_head(0);
-        rows.issue(0, lds0 + a_slot);
-        step_tail(true);
-        // step nk - 1
-        step_head(1);
-        // every wave has read the last stage: its activation slot takes stage 1 of the next tile, its weight slot
-        // (free until the next tile's first step) is where the epilogue works
-        rows.issue(1, lds0 + a_slot);
-        const uint32_t epi_slot = B_BASE + b_slot;
-        step_tail(false);
-
-        store_tile<GATED, OUT_F32, SPLIT, TMV, TNO, WM>(acc, cur.row0, cur.row_end, wm, cur.n_tile * NO + wn * WNO,
-                                                        smem + epi_slot + wave * (TNO * 2048), Out_, ldo, N);
+        wait_vmcnt<0>();           // a block must not end with loads into LDS outstanding
     };
-
-    for (;;) {
-        // (the last tile is followed by itself: its first stages are loaded once more and never used)
-        at += stride;
-        const bool more = at < queue.end;
-        if (more) nxt = queue.take(at);
-        const int rb_valid = (cur.row_end - cur.row0 + 31) / 32;
-        // row blocks wm, wm + WM, ... below rb_valid belong to this wave
-        const int tm_valid = (rb_valid - wm + WM - 1) / WM;
-        if (tm_valid >= 4) run(std::integral_constant<int, 4>{});
-        else if (tm_valid >= 3) run(std::integral_constant<int, 3>{});
-        else if (tm_valid >= 2) run(std::integral_constant<int, 2>{});
-        else if (tm_valid >= 1) run(std::integral_constant<int, 1>{});
-        else run(std::integral_constant<int, 0>{});
-        if (!more) break;
-        cur = nxt;
-        wait_lds_reads();
-        block_barrier();       // every wave has read its piece of the epilogue's slot: the next weight loads may overwrite it
-    }
-    wait_vmcnt<0>();           // a block must not end with loads into LDS outstanding
+    if (queue.mostly_alone) walk(std::true_type{});
+    else walk(std::false_type{});
 }
 
 // ----------------------------------------------------------------------------------------------

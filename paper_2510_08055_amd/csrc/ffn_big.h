@@ -59,6 +59,7 @@ struct BigQueue {
     int h;                     // tile height limit in row blocks
     uint32_t h_inv;
     int end;                   // end of the block's range
+    bool mostly_alone;         // nearly every expert with rows has one m-tile: its weight tiles are read by one block
     int expert, before;        // the walk: an expert, tiles of the experts in front of it,
     int lo, hi, mt, per;       // its rows, its number of m-tiles and the row blocks of each
 
@@ -124,7 +125,7 @@ struct BigQueue {
         int* const rb_of = scratch + 64;            // [E] row blocks
 
         // wave k: number of tiles at height 8 - k
-        int rb_sum = 0, t_sum = 0;
+        int rb_sum = 0, t_sum = 0, used = 0;
         float sq_sum = 0.f;                         // sum of the tiles' squared heights
         {
             const int hh = kBigRows / 32 - k >= kBigMinHeight ? kBigRows / 32 - k : kBigMinHeight;
@@ -138,6 +139,7 @@ struct BigQueue {
                 if (k == 0) rb_of[e] = rb;
                 const int m = div_up(rb, hh, inv);
                 rb_sum += rb;
+                used += rb > 0;
                 t_sum += m;
                 sq_sum += rb > 0 ? (float)rb * (float)rb * __builtin_amdgcn_rcpf((float)m) : 0.f;
             }
@@ -145,6 +147,7 @@ struct BigQueue {
         t_sum = last_lane(wave_scan(t_sum));
         sq_sum = last_lane(wave_scan(sq_sum));
         const float rb_all = (float)last_lane(wave_scan(rb_sum)) * (float)n_tiles;
+        used = last_lane(wave_scan(used));
         if (lane == 0) {
             tiles_at[k] = t_sum;
             squares_at[k] = sq_sum;
@@ -167,7 +170,9 @@ struct BigQueue {
         }
         h = __builtin_amdgcn_readfirstlane(h);
         h_inv = height_inverse(h);
-        const int total = __builtin_amdgcn_readfirstlane(tiles_at[kBigRows / 32 - h]) * n_tiles;
+        const int m_tiles = __builtin_amdgcn_readfirstlane(tiles_at[kBigRows / 32 - h]);
+        mostly_alone = m_tiles - used <= used / 16;
+        const int total = m_tiles * n_tiles;
         const float ftotal = fixed * (float)total + rb_all;
 
         // Border k of the eight pieces: after k / 8 of the tiles, or where the running cost passes k / 8 of the total.

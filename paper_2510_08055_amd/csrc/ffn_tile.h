@@ -25,6 +25,7 @@ typedef float float16_t __attribute__((ext_vector_type(16)));
 // ----------------------------------------------------------------------------------------------
 struct TileCoord {
     int expert, row0, row_end, n_tile;   // rows [row0, row_end) of the permuted batch belong to this tile
+    bool alone;                          // no other tile reads its weights (the expert has one m-tile)
     bool valid;
 };
 
@@ -67,7 +68,7 @@ __device__ __forceinline__ TileCoord find_tile(const int32_t* __restrict__ offse
     const int logical = (int)(blockIdx.x % 8) * chunk + slot;
     TileCoord tc;
     tc.valid = __builtin_amdgcn_readfirstlane((slot < chunk) && (logical < total)) != 0;   // uniform: no divergent join below
-    tc.expert = 0; tc.row0 = 0; tc.row_end = 0; tc.n_tile = 0;
+    tc.expert = 0; tc.row0 = 0; tc.row_end = 0; tc.n_tile = 0; tc.alone = true;
     if (!tc.valid) return tc;
     // the lane whose experts contain the tile (tiles of an expert: mt_e * n_tiles, n-major), then the
     // expert among that lane's EPL; the one division happens after the choice
@@ -109,6 +110,7 @@ __device__ __forceinline__ TileCoord find_tile(const int32_t* __restrict__ offse
     tc.row0 = __builtin_amdgcn_readfirstlane(row0);
     tc.row_end = __builtin_amdgcn_readfirstlane(row_end);
     tc.n_tile = __builtin_amdgcn_readfirstlane(n_tile);
+    tc.alone = __builtin_amdgcn_readfirstlane(s_mt) == 1;
     return tc;
 }
 
@@ -157,17 +159,28 @@ __device__ __forceinline__ void block_barrier() { asm volatile("s_barrier" ::: "
 // for the reads just issued for the next slice.  With the asm form the waits carry the exact count.
 // The kernels that use it must not leave anything else in M0 (nothing in them does: LDS instructions
 // need no M0 on this target).
-template <int BYTES> __device__ __forceinline__ void load_lds(const void* src, uint32_t lds_base)
+// STREAM: bytes that nobody asks for again, as a non-temporal load.  A weight tile that one block alone reads is such a stream,
+// and most weight tiles of a batch with few rows per expert are: the loads then leave the L2 to the activations, and memory
+// delivers more of them (6.8 TB/s against 6.1).  gate_up and down, us, plain / non-temporal: 128 experts, H = I = 2880, 256 tokens
+// 697 / 624 and 366 / 338; H = 2048, I = 768, 32 tokens 128 / 114 and 67 / 60, 640 tokens 149 / 139 and 83 / 80.  Weights that several
+// m-tiles share must stay: 520 rows per expert 388 / 437 and 225 / 248.
+template <int BYTES, bool STREAM = false> __device__ __forceinline__ void load_lds(const void* src, uint32_t lds_base)
 {
     static_assert(BYTES == 16 || BYTES == 4 || BYTES == 2, "direct-to-LDS loads move 16, 4 or 2 bytes per lane");
-    if (BYTES == 16)
+    static_assert(!STREAM || BYTES == 16, "streams are read 16 bytes at a time");
+    if (STREAM)
+        asm volatile("s_mov_b32 m0, %1\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %0, off nt" ::"v"(src), "s"(lds_base) : "memory");
+    else if (BYTES == 16)
         asm volatile("s_mov_b32 m0, %1\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %0, off" ::"v"(src), "s"(lds_base) : "memory");
     else if (BYTES == 4)
         asm volatile("s_mov_b32 m0, %1\n\ts_nop 0\n\tglobal_load_lds_dword %0, off" ::"v"(src), "s"(lds_base) : "memory");
     else
         asm volatile("s_mov_b32 m0, %1\n\ts_nop 0\n\tglobal_load_lds_ushort %0, off" ::"v"(src), "s"(lds_base) : "memory");
 }
-__device__ __forceinline__ void load_lds_16(const void* src, uint32_t lds_base) { load_lds<16>(src, lds_base); }
+template <bool STREAM = false> __device__ __forceinline__ void load_lds_16(const void* src, uint32_t lds_base)
+{
+    load_lds<16, STREAM>(src, lds_base);
+}
 // An address that is the same in every lane, as a scalar (the compiler does not see every uniform value as one).
 __device__ __forceinline__ const char* uniform(const char* p)
 {
@@ -176,9 +189,12 @@ __device__ __forceinline__ const char* uniform(const char* p)
                                          (uint64_t)(uint32_t)__builtin_amdgcn_readfirstlane((int)(uint32_t)(b >> 32)) << 32);
 }
 // The same load with a wave-uniform base address and a 32-bit byte offset per lane.
-__device__ __forceinline__ void load_lds_16_base(const void* base, uint32_t offset, uint32_t lds_base)
+template <bool STREAM = false> __device__ __forceinline__ void load_lds_16_base(const void* base, uint32_t offset, uint32_t lds_base)
 {
-    asm volatile("s_mov_b32 m0, %2\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %0, %1" ::"v"(offset), "s"(base), "s"(lds_base) : "memory");
+    if (STREAM)
+        asm volatile("s_mov_b32 m0, %2\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %0, %1 nt" ::"v"(offset), "s"(base), "s"(lds_base) : "memory");
+    else
+        asm volatile("s_mov_b32 m0, %2\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %0, %1" ::"v"(offset), "s"(base), "s"(lds_base) : "memory");
 }
 // LDS byte address of a pointer into the block's dynamic shared memory
 __device__ __forceinline__ uint32_t lds_address(const void* p)

@@ -265,6 +265,26 @@ def test_wide_tiles_grouped_ffn(gpu_lib, H, I, rows):
             assert_close(ref, dense_ffn(x_perm, offsets, L, "bf16", E), "bf16", "wide tiles")
 
 
+# Weight tiles that one block alone reads are loaded as a stream: all experts in one m-tile, some, none, by the shape's tile height
+@pytest.mark.parametrize("shape,H,I,rows", [
+    ("few", 448, 392, [32, 1, 0, 20]), ("few", 384, 64, [33, 32, 5]), ("small", 512, 448, [64, 0, 1, 40]),
+    ("small", 256, 328, [65, 64, 200]), ("big", 512, 328, [256, 1, 0, 130]), ("big", 320, 448, [100] * 17 + [257]),
+    ("big", 320, 448, [257, 256, 90]),
+])
+@pytest.mark.parametrize("fmt", [{}, {"y_perm_f32": True, "act_split": True}])
+def test_streamed_weight_tiles(gpu_lib, shape, H, I, rows, fmt):
+    E, A = len(rows), sum(rows)
+    w = inputs.Workload("stream", H=H, E=E, K=1, I=I, n_layers=1, D=0, P=A, dtype="bf16", seed=A)
+    L = {k: (v.to(DEV) if v is not None else None) for k, v in inputs.make_layer(w, 0).items()}
+    x_perm = inputs.randn((A, H), 1.0, A, "x_perm", 0, "bf16").to(DEV)
+    offsets = torch.tensor(np.concatenate([[0], np.cumsum(rows)]), dtype=torch.int32).to(DEV)
+    ctx = gpu_lib.Context(H, E, 1, I, torch.bfloat16, max_tokens=A, device=DEV, **fmt)
+    ctx.moe_set_ffn_variant("tile128")
+    want = ctx.moe_grouped_ffn(x_perm, offsets, L["w_gate_up"], L["w_down"]).clone()
+    ctx.moe_set_ffn_variant(shape)
+    assert torch.equal(ctx.moe_grouped_ffn(x_perm, offsets, L["w_gate_up"], L["w_down"]), want)
+
+
 # The shape a launch takes is the one moe_ffn_variant names: pinned, or by the rule.  By the rule: a streaming shape up to 56
 # rows per expert, and beyond as long as its tiles are one round (two per compute unit, 512 on 256 units); narrow tiles while
 # these are less than one round.
