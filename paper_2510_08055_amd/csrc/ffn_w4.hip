@@ -568,7 +568,11 @@ __global__ __launch_bounds__(kS4Waves * 64, 4) void grouped_gemm_w4_stream_kerne
                 asm volatile("");
                 a = a > W_last ? W_last : a;
             }
-            load_lds<16>(a, ldsb + B_BASE + (L & 1) * B_SLOT + (wave * B_LPW + k) * 1024);
+            const uint32_t to = ldsb + B_BASE + (L & 1) * B_SLOT + (wave * B_LPW + k) * 1024;
+            // (a stream if no other block reads the row: 128 experts, H = I = 2880, 4 rows each, gate_up 241 -> 217 us, 16 rows
+            // 260 -> 254; 32 experts, 8 rows 68 -> 62; the shapes that fetch half lines lose 5 to 12 % by it and stay plain)
+            if (tc.alone) load_lds<16, true>(a, to);
+            else load_lds<16>(a, to);
         }
     };
     // Loads in flight at the top of stage g that stage g does not need: the lines of stages g-3, g-2, g-1
