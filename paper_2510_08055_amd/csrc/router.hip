@@ -530,7 +530,7 @@ __global__ __launch_bounds__(kTopkWaves * 64) void topk_rows_kernel(const double
 // digits come from a launch of their own (for several layers at once), laid out as the operands' registers.  The logits
 // stay in LDS, where the top-k reads them.
 // Measured (kernel times; logits and top-k before -> this launch, and 5 us for the digits of up to 8 layers), H = 2048,
-// E = 128, top-8: 2112 tokens 36.4 -> 26.4 us, 4128 57.5 -> 29, 8320 100.9 -> 43.7; H = 2880, E = 32, top-4, 8320 tokens
+// E = 128, top-8: 2112 tokens 36.4 -> 26.4 us, 4128 57.5 -> 30, 8320 100.9 -> 43.7; H = 2880, E = 32, top-4, 8320 tokens
 // 45 -> 37.  What bounds it: the MFMAs alone take 10.5 us of the 24 of the k-loop at 8320 tokens; the rest is the 36 KB per
 // step that a compute unit's address unit and L2 deliver (eight loads issued in a row, in place of one by one between the
 // MFMAs, cost 6 us, the branches around four groups of MFMAs in place of one 5 us; the conversions are hidden).  The row maxima
