@@ -139,9 +139,9 @@ moe_status moe_router_topk(moe_ctx *ctx, const void *x, int64_t T, const void *w
  * moe_router_topk for callers that cannot allocate device memory and have no workspace to hand over (code
  * under HIP graph capture, tight serving loops, harnesses that forbid hipMalloc): no context; the logits
  * live in a static device array of the library (4 MiB per GPU, held until the process ends), so
- * T * cfg->E must not exceed 524288 (MOE_ERR_WORKSPACE otherwise, before anything is launched).  Same
- * arithmetic, same kernels and same results as moe_router_topk with a context of this cfg; H, E, K,
- * dtype and renormalize of cfg are read.  The call allocates nothing, on the host or the device.  All
+ * T * cfg->E must not exceed 524288 (MOE_ERR_WORKSPACE otherwise, before anything is launched).  The
+ * results are those of moe_router_topk with a context of this cfg, bit for bit; H, E, K, dtype and
+ * renormalize of cfg are read.  The call allocates nothing, on the host or the device.  All
  * calls on one GPU share the array: calls that overlap in time on one GPU (different streams, or
  * different threads) race; serialise them.
  */

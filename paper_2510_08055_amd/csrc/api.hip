@@ -26,9 +26,11 @@ struct moe_ctx {
     int32_t *idx, *counts, *offsets, *perm, *inv, *tile_hist;
     float* w;
     uint8_t* digits;          // w_router as digits, of digit_slots layers
-    char* digit_forms;          // and what else describes its rows
+    char* digit_forms;        // and what else describes its rows
+    int32_t* listed;          // tokens whose routing the exact sums leave open
     int digit_slots;
-    int64_t tile_hist_words;  // of one slot
+    int64_t slot_words;       // counters of one slot's layer: permutation histograms, then those of the list
+    int64_t hist_words;       // of these, the histograms
     void *xa, *xb, *act, *y_perm;
     // host-side counters (everything the host already knows)
     uint64_t router_bytes, tokens_processed;
@@ -71,9 +73,9 @@ moe_status check_cfg(const moe_config* c)
 }
 
 struct Layout {
-    size_t counters, logits, idx, w, counts, offsets, perm, inv, tile_hist, digits, digit_forms, xa, xb, act, y_perm, total;
+    size_t counters, logits, idx, w, counts, offsets, perm, inv, tile_hist, digits, digit_forms, listed, xa, xb, act, y_perm, total;
     int digit_slots;
-    size_t tile_hist_words;
+    size_t hist_words, slot_words;
 };
 
 Layout carve(const moe_config& c, int64_t Tm)
@@ -99,10 +101,12 @@ Layout carve(const moe_config& c, int64_t Tm)
         const size_t fit = ((size_t)32 << 20) / digit_bytes;
         L.digit_slots = fit < 1 ? 1 : (fit > (size_t)kDigitLayers ? kDigitLayers : (int)fit);
     }
-    L.tile_hist_words = n_tiles * c.E;       // of a layer
-    L.tile_hist = take((L.digit_slots > 1 ? L.digit_slots : 1) * L.tile_hist_words * 4);
+    L.hist_words = n_tiles * c.E;            // of a layer
+    L.slot_words = L.hist_words + (L.digit_slots > 0 ? (size_t)route_list_words(Tm) : 0);
+    L.tile_hist = take((L.digit_slots > 1 ? L.digit_slots : 1) * L.slot_words * 4);
     L.digits = take(L.digit_slots * digit_bytes);
     L.digit_forms = take((size_t)L.digit_slots * router_form_bytes(c.E));
+    L.listed = take(L.digit_slots > 0 ? (size_t)Tm * 4 : 0);
     L.xa = take((size_t)Tm * c.H * esz);
     L.xb = take((size_t)Tm * c.H * esz);
     L.act = take(Am * c.I * esz * (c.act_split ? 2 : 1));
@@ -182,6 +186,13 @@ hipError_t clear_tickets(moe_ctx* c, hipStream_t s)
     return e;
 }
 
+// The list of a slot's layer, behind its histograms.
+RouteList route_list(const moe_ctx* c, int slot)
+{
+    int32_t* const words = c->tile_hist + slot * c->slot_words + c->hist_words;
+    return RouteList{words, reinterpret_cast<uint32_t*>(words + 1), c->listed};
+}
+
 // One layer on the batch `x` [T,H]; output rows [0,rows0) -> y0, the rest -> y1.
 moe_status run_layer(moe_ctx* c, const moe_layer& L, RowSrc x, int64_t T, int slot, void* y0, int64_t rows0, void* y1,
                      hipStream_t s)
@@ -194,7 +205,7 @@ moe_status run_layer(moe_ctx* c, const moe_layer& L, RowSrc x, int64_t T, int sl
     hipError_t e;
     const bool small = route_is_small(T, g.E, g.K);
     const bool exact = route_is_exact(g.dtype, T, g.H, g.E, g.K);
-    int32_t* const tile_hist = c->tile_hist + slot * c->tile_hist_words;
+    int32_t* const tile_hist = c->tile_hist + slot * c->slot_words;
     if (small) {
         // (timed as the router's logits; the other two have no launch of their own)
         e = clear_tickets(c, s);
@@ -207,7 +218,7 @@ moe_status run_layer(moe_ctx* c, const moe_layer& L, RowSrc x, int64_t T, int sl
         if (exact)      // (timed as the router's logits; the top-k has no launch of its own)
             e = launch_route_exact(x, T, g.H, L.w_router, L.router_bias, g.E, g.K, g.renormalize,
                                    c->digits + slot * router_digit_bytes(g.H, g.E), c->digit_forms + slot * router_form_bytes(g.E),
-                                   c->idx, c->w, fused_hist ? tile_hist : nullptr, s);
+                                   route_list(c, slot), c->logits, c->idx, c->w, fused_hist ? tile_hist : nullptr, s);
         else
             e = launch_router_logits(g.dtype, x, T, g.H, L.w_router, L.router_bias, g.E, c->logits, tile_hist,
                                      fused_hist ? n_perm_tiles * g.E : 0, s);
@@ -274,7 +285,7 @@ moe_status run_group(moe_ctx* c, const moe_layer* layers, int n, RowSrc in, int6
             RouterWeights w = {};
             const int here = n - l < slots ? n - l : slots;
             for (int i = 0; i < here; ++i) w.p[i] = layers[l + i].w_router;
-            if (launch_router_digits(w, here, g.H, g.E, c->digits, c->digit_forms, c->tile_hist, here * c->tile_hist_words, s) != hipSuccess) return MOE_ERR_DEVICE;
+            if (launch_router_digits(w, here, g.H, g.E, c->digits, c->digit_forms, c->tile_hist, here * c->slot_words, s) != hipSuccess) return MOE_ERR_DEVICE;
         }
         moe_status st;
         if (l + 1 < n) st = run_layer(c, layers[l], src, T, slot, nxt, T, nxt, s);
@@ -357,8 +368,10 @@ moe_status moe_create(const moe_config* cfg, int64_t max_tokens, void* workspace
     c->tile_hist = reinterpret_cast<int32_t*>(b + L.tile_hist);
     c->digits = reinterpret_cast<uint8_t*>(b + L.digits);
     c->digit_forms = b + L.digit_forms;
+    c->listed = reinterpret_cast<int32_t*>(b + L.listed);
     c->digit_slots = L.digit_slots;
-    c->tile_hist_words = (int64_t)L.tile_hist_words;
+    c->slot_words = (int64_t)L.slot_words;
+    c->hist_words = (int64_t)L.hist_words;
     c->xa = b + L.xa;
     c->xb = b + L.xb;
     c->act = b + L.act;
@@ -396,9 +409,11 @@ moe_status moe_router_topk(moe_ctx* ctx, const void* x, int64_t T, const void* w
     const moe_config& g = ctx->cfg;
     if (route_is_exact(g.dtype, T, g.H, g.E, g.K)) {
         const RouterWeights w = {{w_router}};
-        if (launch_router_digits(w, 1, g.H, g.E, ctx->digits, ctx->digit_forms, nullptr, 0, s) != hipSuccess) return MOE_ERR_DEVICE;
+        const RouteList list = route_list(ctx, 0);
+        if (launch_router_digits(w, 1, g.H, g.E, ctx->digits, ctx->digit_forms, list.count, route_list_words(T), s) != hipSuccess)
+            return MOE_ERR_DEVICE;
         return dev(launch_route_exact(single_src(x), T, g.H, w_router, bias, g.E, g.K, g.renormalize, ctx->digits,
-                                      ctx->digit_forms, topk_idx, topk_w, nullptr, s));
+                                      ctx->digit_forms, list, ctx->logits, topk_idx, topk_w, nullptr, s));
     }
     hipError_t e = launch_router_logits(g.dtype, single_src(x), T, g.H, w_router, bias, g.E, ctx->logits, nullptr, 0, s);
     if (e != hipSuccess) return MOE_ERR_DEVICE;

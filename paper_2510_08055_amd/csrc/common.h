@@ -65,20 +65,27 @@ hipError_t launch_router_logits(int dtype, RowSrc x, int64_t T, int H, const voi
 constexpr int kSmallTokens = 256, kSmallExperts = 256;
 inline bool route_is_small(int64_t T, int E, int K) { return T <= kSmallTokens && E <= kSmallExperts && K <= 16; }
 
-// Router and top-k of larger bf16 batches with logits that are exact integer sums (see router.hip): a launch that makes the
-// digits of the layers' w_router (router_digit_bytes and router_form_bytes for each) and clears zero_n words, then a launch
-// per layer; tile_hist as for launch_topk.
+// Router and top-k of larger bf16 batches by exact integer sums (see router.hip), with the results of the fp64 pass: a launch
+// that makes the digits of the layers' w_router (router_digit_bytes and router_form_bytes for each) and clears zero_n words,
+// then two launches per layer; tile_hist as for launch_topk; logits: [T, E] of scratch.
 constexpr int kDigitLayers = 8;      // layers per digits launch
 struct RouterWeights {
     const void* p[kDigitLayers];
 };
 int64_t router_digit_bytes(int H, int E);
-inline int64_t router_form_bytes(int E) { return (int64_t)((E + 31) / 32 * 32) * 16; }
+inline int64_t router_form_bytes(int E) { return (int64_t)((E + 31) / 32 * 32) * 32; }
 hipError_t launch_router_digits(const RouterWeights& w, int layers, int H, int E, uint8_t* digits, void* forms, int32_t* zero_buf,
                                 int64_t zero_n, hipStream_t s);
+// The tokens that the exact sums leave to the fp64 pass: count and tickets (one per 16 tokens of the batch) are zero before the launch.
+struct RouteList {
+    int32_t* count;
+    uint32_t* tickets;
+    int32_t* tokens;      // [T]
+};
+inline int64_t route_list_words(int64_t T) { return 1 + (T + 15) / 16; }      // count and tickets
 hipError_t launch_route_exact(RowSrc x, int64_t T, int H, const void* w_router, const float* bias, int E, int K, int renorm,
-                              const uint8_t* digits, const void* forms, int32_t* idx, float* w, int32_t* tile_hist,
-                              hipStream_t s);
+                              const uint8_t* digits, const void* forms, const RouteList& list, double* logits, int32_t* idx,
+                              float* w, int32_t* tile_hist, hipStream_t s);
 // (its sums are at most 4 H 2^14; a block holds all experts' logits of its tokens.)  It takes 25 us and more however few the
 // tokens, the fp64 pass grows with T E H.  Logits and top-k, fp64 / exact with the digits of one layer, us: H = 2048, E = 128: 1389
 // tokens 26.6 / 31, 2112 36.4 / 31.2 (as part of a layer, with one launch boundary less or more, the two are level), 4128

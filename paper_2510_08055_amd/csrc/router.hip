@@ -5,10 +5,11 @@
 // agree with an fp64 definition: products of two bf16 (or two fp32) values are
 // exact in fp64 and the summation error (~1e-16 relative) is far below any
 // realistic gap between neighbouring logits.  The reduction order of a token's
-// logits depends only on H, never on the batch.  Large bf16 batches take exact
-// integer sums instead (route_exact_kernel), rounded once: their logits can differ
-// from the fp64 chain's by its own rounding, a part in 10^15, and from nothing else
-// in the batch.
+// logits depends only on H, never on the batch, so routing is batch-invariant:
+// the chunked and the layered schedule route every token identically.  Large bf16
+// batches take exact integer sums instead (route_exact_kernel): tokens whose experts
+// or weights the difference to the fp64 chain (its rounding) could change are found
+// by a bound on it and take the chain after all, so the results are the chain's.
 #include <type_traits>
 
 #include "common.h"
@@ -117,11 +118,26 @@ template <typename V> __device__ __forceinline__ V load_shared(const V* p)
     return __hip_atomic_load(p, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
 }
 
-// The tile of logits at (t0, e0), computed by the first NW waves of the block and stored by wave 0; every thread of the
-// block calls it.  store(i, j, z) takes the logit z of token t0 + i < n_tok and expert e0 + j < E.
-template <typename T, int NW, typename Store>
-__device__ __forceinline__ void logits_tile(const RowSrc& x, int64_t n_tok, int H, const T* __restrict__ wr,
-                                            const float* __restrict__ bias, int E, int64_t t0, int e0, Store store)
+// Draws a ticket for the block once everything it has stored is visible; true for the last of n drawers.
+// Every thread of the block calls it (`flag`: a word of LDS).
+__device__ __forceinline__ bool last_to_arrive(uint32_t* ticket, uint32_t n, int32_t* flag)
+{
+    asm volatile("s_waitcnt vmcnt(0)" ::: "memory");         // this wave's stores have reached the shared level
+    __syncthreads();
+    if (threadIdx.x == 0) {
+        const bool last = __hip_atomic_fetch_add(ticket, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) == n - 1;
+        if (last) store_shared(ticket, 0u);
+        *flag = last;
+    }
+    __syncthreads();
+    return *flag != 0;
+}
+
+// The tile of logits of rows row(0 .. 15) and experts e0 .. e0 + 15, stored by wave 0; every thread of the block calls it.
+// Rows from n_rows on are read and not used.  store(i, j, z) takes the logit z of row i < n_rows and expert e0 + j < E.
+template <typename T, int NW, typename Row, typename Store>
+__device__ __forceinline__ void logits_tile(Row row, int n_rows, int H, const T* __restrict__ wr,
+                                            const float* __restrict__ bias, int E, int e0, Store store)
 {
     constexpr int NACC = 16 / NW;                // partial sums per wave
     static_assert(NW == 4 || NW == 16, "16 partial sums over 4 or 16 waves");
@@ -129,9 +145,8 @@ __device__ __forceinline__ void logits_tile(const RowSrc& x, int64_t n_tok, int 
     const int lane = lane_id();
     const int wave = __builtin_amdgcn_readfirstlane((int)(threadIdx.x >> 6));
     const int r = lane & 15, q = lane >> 4;
-    const int64_t tr = (t0 + r < n_tok) ? (t0 + r) : (n_tok - 1);  // clamp: loads stay in bounds
-    const int er = (e0 + r < E) ? (e0 + r) : (E - 1);
-    const T* xp = row_ptr<T>(x, tr, H) + q * 8;
+    const int er = (e0 + r < E) ? (e0 + r) : (E - 1);              // clamp: loads stay in bounds
+    const T* xp = row(r) + q * 8;
     const T* wp = wr + (int64_t)er * H + q * 8;
 
     double4_t acc[NACC];
@@ -153,8 +168,7 @@ __device__ __forceinline__ void logits_tile(const RowSrc& x, int64_t n_tok, int 
             if (a == i % NACC) multiply(buf, acc[a]);
     };
     const int n_whole = H / 32;                                            // whole 32-wide chunks of a row
-    // of which this wave takes chunks wave, wave + NW, ... (a wave past the first NW none)
-    const int mine = wave < NW && n_whole > wave ? (n_whole - wave + NW - 1) / NW : 0;
+    const int mine = n_whole > wave ? (n_whole - wave + NW - 1) / NW : 0;   // of which this wave takes chunks wave, wave + NW, ...
     auto fetch = [&](int buf, int i) {                                      // this wave's i-th chunk
         const int k0 = (wave + NW * i) * 32;
         xa[buf].load_async(xp + k0);
@@ -196,7 +210,7 @@ __device__ __forceinline__ void logits_tile(const RowSrc& x, int64_t n_tok, int 
     double4_t mysum = acc[0];
 #pragma unroll
     for (int a = 1; a < NACC; ++a) mysum += acc[a];
-    if (wave > 0 && wave < NW) {
+    if (wave > 0) {
 #pragma unroll
         for (int v = 0; v < 4; ++v) part[wave - 1][v][lane] = mysum[v];
     }
@@ -208,7 +222,6 @@ __device__ __forceinline__ void logits_tile(const RowSrc& x, int64_t n_tok, int 
         const double b = bias ? (double)bias[e] : 0.0;
 #pragma unroll
         for (int v = 0; v < 4; ++v) {
-            const int64_t t = t0 + v * 4 + q;
             double z = 0.0;
 #pragma unroll
             for (int p = 0; p < 4; ++p) {        // partial sums p, p + 4, p + 8, p + 12
@@ -217,10 +230,17 @@ __device__ __forceinline__ void logits_tile(const RowSrc& x, int64_t n_tok, int 
                 for (int w = p + 4; w < NW; w += 4) s += part[w - 1][v][lane];
                 z = p == 0 ? s : z + s;
             }
-            if (t < n_tok) store(v * 4 + q, r, z + b);
+            if (v * 4 + q < n_rows) store(v * 4 + q, r, z + b);
         }
     }
 }
+
+// The 16 rows from t0 on, the last row again past the end.
+template <typename T> __device__ __forceinline__ auto rows_from(const RowSrc& x, int64_t t0, int64_t n_tok, int H)
+{
+    return [=](int i) { return row_ptr<T>(x, t0 + i < n_tok ? t0 + i : n_tok - 1, H); };
+}
+__device__ __forceinline__ int rows_left(int64_t t0, int64_t n_tok, int most) { return n_tok - t0 < most ? (int)(n_tok - t0) : most; }
 
 template <typename T>
 __global__ __launch_bounds__(256) void router_logits_kernel(RowSrc x, int64_t n_tok, int H,
@@ -235,7 +255,8 @@ __global__ __launch_bounds__(256) void router_logits_kernel(RowSrc x, int64_t n_
         for (int i = threadIdx.x; i < zero_n; i += 256) zero_buf[i] = 0;
     const int64_t t0 = (int64_t)blockIdx.x * 16;
     const int e0 = (int)blockIdx.y * 16;
-    logits_tile<T, 4>(x, n_tok, H, wr, bias, E, t0, e0, [&](int i, int j, double z) { logits[(t0 + i) * E + e0 + j] = z; });
+    logits_tile<T, 4>(rows_from<T>(x, t0, n_tok, H), rows_left(t0, n_tok, 16), H, wr, bias, E, e0,
+                      [&](int i, int j, double z) { logits[(t0 + i) * E + e0 + j] = z; });
 }
 
 // (value, index) "greater" under the routing order: larger logit first, equal logits by lower index.
@@ -387,11 +408,22 @@ template <int NPL, bool TREE> __device__ __forceinline__ void lane_best(const do
     be = e[0];
 }
 
+// How far the logits of R tokens may be from those of another order of summation (see route_exact_kernel), and what comes of it.
+struct NoMargin {
+    static constexpr bool kCheck = false;
+};
+template <int R> struct Margin {
+    static constexpr bool kCheck = true;
+    double off[R];      // a logit z of the token is at most off + 2^-49 |z| from the other one
+    bool sure[R];       // out, the same in all lanes of the row: indices and weights are the same with the other logits
+};
+
 // Top-k of R tokens by the 16 lanes of a row (c = lane % 16): lane c < K ends with the c-th winner of each and its weight.
 // All lanes of the row hold the same z[0 .. R).  (A round is a chain of dependent instructions; two tokens fill its gaps.)
-template <int NPL, int R>   // logits per lane: experts c + 16 i, i < NPL
+// With a margin K must be less than E.
+template <int NPL, int R, typename M>   // logits per lane: experts c + 16 i, i < NPL
 __device__ __forceinline__ void topk_of_rows(const double* const (&z)[R], int E, int K, int renorm, int c, bool shared,
-                                             int (&my_e)[R], float (&my_w)[R])
+                                             int (&my_e)[R], float (&my_w)[R], M& margin)
 {
     const double NEG = -__builtin_huge_val();
     double v[R][NPL];
@@ -403,14 +435,17 @@ __device__ __forceinline__ void topk_of_rows(const double* const (&z)[R], int E,
             v[r][i] = (e < E) ? (shared ? load_shared(z[r] + e) : z[r][e]) : NEG;
         }
     double esum[R];         // only without renormalisation: this lane's share of sum_e exp(z_e - z_max)
-    double my_z[R], z_max[R];
+    double my_z[R], z_max[R], before_z[R];
+    bool close[R];
 #pragma unroll
     for (int r = 0; r < R; ++r) {
-        esum[r] = z_max[r] = 0.0;
+        esum[r] = z_max[r] = before_z[r] = 0.0;
         my_z[r] = NEG;
         my_e[r] = 0;
+        close[r] = false;
     }
-    for (int j = 0; j < K; ++j) {
+    const int rounds = M::kCheck ? K + 1 : K;        // (the last of K + 1: what the K-th winner is ahead of)
+    for (int j = 0; j < rounds; ++j) {
         double bv[R];
         int be[R];
 #pragma unroll
@@ -436,6 +471,13 @@ __device__ __forceinline__ void topk_of_rows(const double* const (&z)[R], int E,
         }
 #pragma unroll
         for (int r = 0; r < R; ++r) {
+            if constexpr (M::kCheck) {
+                // Each winner ahead of the next by more than both can move.  (A NaN is ahead of nothing.)
+                const double room = 2.0 * margin.off[r] + 0x1p-48 * __builtin_fmax(__builtin_fabs(before_z[r]), __builtin_fabs(bv[r]));
+                if (j > 0 && !(before_z[r] - bv[r] > room)) close[r] = true;
+                before_z[r] = bv[r];
+                if (j == K) continue;
+            }
             if (c == j) { my_z[r] = bv[r]; my_e[r] = be[r]; }
             if ((be[r] & 15) == c) {
                 const int slot = be[r] >> 4;
@@ -453,7 +495,18 @@ __device__ __forceinline__ void topk_of_rows(const double* const (&z)[R], int E,
         denom = row_sum_step<kDppXor2>(denom);
         denom = row_sum_step<kDppHalfMirror>(denom);
         denom = row_sum_step<kDppMirror>(denom);
-        my_w[r] = (float)(p / denom);
+        const double q = p / denom;
+        my_w[r] = (float)q;
+        if constexpr (M::kCheck) {
+            // Logits that move by d move ln q by at most 2 max(d); the roundings of exp, the sum and the quotient on either side and
+            // (without renormalisation) the 2^-49 |z| of the terms far down come to less than 2^-46.  Is the fp32 weight the same at
+            // both ends?
+            const double rel = 4.0 * margin.off[r] + 0x1p-46 * (1.0 + __builtin_fabs(my_z[r]) + __builtin_fabs(z_max[r]));
+            const bool moves = c < K && !((float)(q - q * rel) == (float)(q + q * rel));
+            const uint32_t of_row = (uint32_t)(__ballot(moves) >> (lane_id() & 48)) & 0xffffu;
+            // (off = 0: a row of zeros or a router of zeros, whose logits are the bias in any order)
+            margin.sure[r] = margin.off[r] == 0.0 || (!close[r] && of_row == 0);
+        }
     }
 }
 template <int NPL>
@@ -462,7 +515,8 @@ __device__ __forceinline__ void topk_of_row(const double* z, int E, int K, int r
     const double* zs[1] = {z};
     int e[1];
     float w[1];
-    topk_of_rows<NPL, 1>(zs, E, K, renorm, c, shared, e, w);
+    NoMargin none;
+    topk_of_rows<NPL, 1>(zs, E, K, renorm, c, shared, e, w, none);
     my_e = e[0];
     my_w = w[0];
 }
@@ -515,39 +569,52 @@ __global__ __launch_bounds__(kTopkWaves * 64) void topk_rows_kernel(const double
 // v_mfma_i32_32x32x32_i8 that cannot overflow (7 sums for i + j = 0 .. 6, each at most 4 H 2^14 < 2^31).  Nothing is rounded
 // until the 7 sums meet: one rounding to fp64, closer to the true sum than the fp64 chain's H of them, and the same
 // whatever the tile, the order of the chain or the rest of the batch.
-// The lowest digit of most values is zero (it is used by values 2^13 and more below their row's largest, one in 10^4 of
+// The lowest digit of most values is zero (it is used by values 2^14 and more below their row's largest, one in 10^4 of
 // normally distributed ones): a chunk of 32 k-values whose lowest digits are all zero on either side leaves
 // those products out, which makes 10 of 16.
-// A value with bits below the window (2^22 and more below the row's largest: one in 2 10^6) leaves a remainder that the
-// digits do not hold.  Such values of a row are listed, up to kStray of them, and their remainders times the other
-// operand are added to the logit in fp64.  A row with more of them, with infinities or NaN, or of largest exponents that no
-// fp32 scale reaches, takes its logits from the fp64 pass, tile by tile, at the end of the block.  Which way a logit is
-// made depends on its two rows alone.
+// A value with bits below the window (2^22 and more below the row's largest: one in 2 10^6 of normally distributed ones)
+// leaves a remainder that the digits do not hold.  Such values of a row are listed, up to kStray of them, and their remainders
+// times the other operand are added to the logit in fp64.
+//
+// The fp64 pass takes the sums in another order with a rounding at every step, so its logits are not the same bits, and a
+// token must not change its experts or its weights with the size of its batch.  So a token's top-k is taken from these
+// logits only where it is shown to be what the fp64 logits give.  A logit is at most
+//     off = c |x|_2 max_e |w_e|_2,  c = (products of a partial sum + 40) 2^-52
+// from the fp64 one (sum |x w| <= |x| |w|; a unit in the last place for each of the fp64 chain's additions, the 16 partial
+// sums' among them, and for those of the remainders here), plus 2^-49 of itself for those that have the bias in them.  Where two of
+// the first K + 1 logits are closer than that, or a weight so near the middle between two fp32 values that it could round the
+// other way, the token is listed.  So are rows of x that are not held (more than kStray strays, infinities, NaN, a
+// largest value outside 2^-40 .. 2^40), and all of the batch with a row of w_router that is not.  Listed tokens take
+// the fp64 pass (route_listed_kernel), 16 at a time whichever block they come from: one in 1000 of normally distributed
+// tokens at H = 2048, 128 experts.
 //
 // A block takes 32 tokens and all experts, WE groups of 32; its waves are WE x WK: WK shares of the k-range, in each of
 // them one wave per group; the WE waves of a share turn 32 tokens x 64 k-values at a time into digits (whole 128-byte
 // lines, each value once) and hand them to each other through LDS, a step ahead of the MFMAs that use them.  w_router's
 // digits come from a launch of their own (for several layers at once), laid out as the operands' registers.  The logits
 // stay in LDS, where the top-k reads them.
-// Measured (kernel times; logits and top-k before -> this launch, and 5 us for the digits of up to 8 layers), H = 2048,
-// E = 128, top-8: 2112 tokens 36.4 -> 26.4 us, 4128 57.5 -> 30, 8320 100.9 -> 43.7; H = 2880, E = 32, top-4, 8320 tokens
-// 45 -> 37.  What bounds it: the MFMAs alone take 10.5 us of the 24 of the k-loop at 8320 tokens; the rest is the 36 KB per
-// step that a compute unit's address unit and L2 deliver (eight loads issued in a row, in place of one by one between the
-// MFMAs, cost 6 us, the branches around four groups of MFMAs in place of one 5 us; the conversions are hidden).  The row maxima
-// take 4 us, the sums and the logits 2, the top-k 6.
+// Measured (kernel times, us; logits and top-k of the fp64 pass -> this launch + the listed tokens, and 5 us for the digits of up
+// to 8 layers), H = 2048, E = 128, top-8: 2400 tokens 33 -> 30 + 13, 8320 93 -> 49 + 14.  What bounds it: the MFMAs alone take 10.5 us of the 24 of the k-loop at 8320 tokens; the rest is
+// the 36 KB per step that a compute unit's address unit and L2 deliver (eight loads issued in a row, in place of one by one
+// between the MFMAs, cost 6 us, the branches around four groups of MFMAs in place of one 5 us; the conversions are hidden).
+// Every row listed (more than kStray values below the window in each of them): 143 us in all at 8320 tokens against 97.
 // ----------------------------------------------------------------------------------------------
 typedef int i32x4_t __attribute__((ext_vector_type(4)));
 typedef int i32x16_t __attribute__((ext_vector_type(16)));
 typedef uint16_t u16x2_t __attribute__((ext_vector_type(2)));
+typedef __bf16 bf16x2_t __attribute__((ext_vector_type(2)));
 
 constexpr int kDigitK = 64;           // k-values per step: rows are padded to it with zeros
 constexpr int kWindow = 22;           // exponents below the row's largest that the fixed point holds exactly
-constexpr int kStray = 3;             // values of a row that may lie below it
+constexpr int kStray = 6;             // values of a row that may lie below it
+constexpr int kHeld = 40;             // rows whose largest value is in 2^-40 .. 2^40: their squares stay in the fp32 range
 constexpr uint32_t kBalance = 0x80808080u, kNoStray = 0xffffffffu;
 
-// How a row is held: the biased exponent eb of its scale (-1: not at all), and the k-values whose remainders it misses.
+// How a row is held: the biased exponent eb of its scale (-1: not at all), its 2-norm (or a little more), and the k-values
+// whose remainders the digits miss.
 struct RowForm {
     int eb;
+    float norm;
     uint32_t stray[kStray];           // in ascending order, kNoStray past the last
 };
 // 2^(156 - eb); any scale will do for a row that is not held
@@ -556,14 +623,16 @@ __device__ __forceinline__ float digit_scale(int eb) { return __uint_as_float((u
 __device__ __forceinline__ double digit_part(bf16_t v, int eb) { return (double)truncf(bf16_to_f32(v) * digit_scale(eb)) / digit_scale(eb); }
 __device__ __forceinline__ double remainder_part(bf16_t v, int eb) { return (double)bf16_to_f32(v) - digit_part(v, eb); }
 
-// The largest and the smallest non-zero magnitude of a row, as bf16 bits, gathered 8 values at a time (zero counts as
-// 0xffff on the small side).
+// The largest and the smallest non-zero magnitude of a row, as bf16 bits, and its sum of squares, gathered 8 values at a time
+// (zero counts as 0xffff on the small side).
 struct RowRange {
     u16x2_t top, low;
+    float squares;
     __device__ __forceinline__ void clear()
     {
         top = u16x2_t{0, 0};
         low = u16x2_t{0xffff, 0xffff};
+        squares = 0.f;
     }
     __device__ __forceinline__ void add(const u32x4_t& raw)
     {
@@ -572,32 +641,38 @@ struct RowRange {
             const u16x2_t m = __builtin_bit_cast(u16x2_t, raw[i] & 0x7fff7fffu);
             top = __builtin_elementwise_max(top, m);
             low = __builtin_elementwise_min(low, m - u16x2_t{1, 1});       // zero wraps to 0xffff
+            const bf16x2_t v = __builtin_bit_cast(bf16x2_t, raw[i]);
+            squares = __builtin_amdgcn_fdot2_f32_bf16(v, v, squares, false);
         }
     }
     // Over W neighbouring lanes that hold the row; strays: some value lies below the window.
-    template <int W> __device__ __forceinline__ int exponent(bool& strays) const
+    template <int W> __device__ __forceinline__ RowForm form(bool& strays) const
     {
         int hi = top[0] > top[1] ? top[0] : top[1], lo = low[0] < low[1] ? low[0] : low[1];
+        float sq = squares;
 #pragma unroll
         for (int o = 1; o < W; o <<= 1) {
             const int h2 = __shfl_xor(hi, o, 64), l2 = __shfl_xor(lo, o, 64);
             hi = h2 > hi ? h2 : hi;
             lo = l2 < lo ? l2 : lo;
+            sq += __shfl_xor(sq, o, 64);
         }
         const int eb = hi == 0 ? 127 : hi >> 7;      // (a row of zeros: any)
         strays = ((lo + 1) >> 7) < eb - kWindow;
-        return eb >= 29 && eb <= 254 ? eb : -1;
+        const bool held = eb >= 127 - kHeld && eb < 127 + kHeld;
+        // (the sum of H <= 16384 squares in fp32 is right to a part in 2^9)
+        return RowForm{held ? eb : -1, held ? 1.01f * sqrtf(sq) : 0.f, {kNoStray, kNoStray, kNoStray, kNoStray, kNoStray, kNoStray}};
     }
 };
 
-// Lists the strays of a row; called by one whole wave.  (Rare: short rather than fast.)
-__device__ __forceinline__ void list_strays(const bf16_t* row, int H, RowForm* form)
+// Lists the strays of a row of scale eb, or marks the row as not held; called by one whole wave, written by its lane 0.  (Rare:
+// short rather than fast.)
+__device__ __forceinline__ void list_strays(const bf16_t* row, int H, int eb, RowForm* form)
 {
     const int lane = lane_id();
-    const int eb = form->eb;
     int n = 0;
 #pragma unroll 1
-    for (int k0 = 0; k0 < H; k0 += 512) {
+    for (int k0 = 0; k0 < H && n <= kStray; k0 += 512) {
         const int k = k0 + lane * 8;
         u32x4_t raw = {0, 0, 0, 0};
         if (k < H) raw = *reinterpret_cast<const u32x4_t*>(row + k);
@@ -651,8 +726,9 @@ __global__ __launch_bounds__(kPrepThreads) void router_digits_kernel(RouterWeigh
                                                                       int64_t zero_n)
 {
     __shared__ int s_hi[kPrepThreads / 64], s_lo[kPrepThreads / 64];
+    __shared__ float s_sq[kPrepThreads / 64];
     __shared__ RowForm s_form;
-    // side job: clear the expert histograms that the layers' top-k counts into
+    // side job: clear the counters of the layers' routing
     for (int64_t i = ((int64_t)blockIdx.y * gridDim.x + blockIdx.x) * kPrepThreads + threadIdx.x; i < zero_n;
          i += (int64_t)gridDim.x * gridDim.y * kPrepThreads)
         zero_buf[i] = 0;
@@ -665,25 +741,30 @@ __global__ __launch_bounds__(kPrepThreads) void router_digits_kernel(RouterWeigh
     for (int p = threadIdx.x; p < pieces; p += kPrepThreads) range.add(*reinterpret_cast<const u32x4_t*>(row + p * 8));
     int hi = range.top[0] > range.top[1] ? range.top[0] : range.top[1];
     int lo = range.low[0] < range.low[1] ? range.low[0] : range.low[1];
+    float sq = range.squares;
 #pragma unroll
     for (int o = 1; o < 64; o <<= 1) {
         const int h2 = __shfl_xor(hi, o, 64), l2 = __shfl_xor(lo, o, 64);
         hi = h2 > hi ? h2 : hi;
         lo = l2 < lo ? l2 : lo;
+        sq += __shfl_xor(sq, o, 64);
     }
     if ((threadIdx.x & 63) == 0) {
         s_hi[threadIdx.x >> 6] = hi;
         s_lo[threadIdx.x >> 6] = lo;
+        s_sq[threadIdx.x >> 6] = sq;
     }
     __syncthreads();
+    static_assert(kPrepThreads == 128, "two waves' ranges meet here");
     range.top = u16x2_t{(uint16_t)s_hi[0], (uint16_t)s_hi[1]};
     range.low = u16x2_t{(uint16_t)s_lo[0], (uint16_t)s_lo[1]};
+    range.squares = s_sq[0] + s_sq[1];
     bool strays;
-    const int eb = range.exponent<1>(strays);
+    const RowForm form = range.form<1>(strays);
+    const int eb = form.eb;
     if (threadIdx.x < 64) {
-        if (threadIdx.x == 0) s_form = RowForm{eb, {kNoStray, kNoStray, kNoStray}};
-        if (strays && eb >= 0) list_strays(row, H, &s_form);
-        __builtin_amdgcn_wave_barrier();
+        if (threadIdx.x == 0) s_form = form;
+        if (strays && eb >= 0) list_strays(row, H, eb, &s_form);
         if (threadIdx.x == 0) forms[layer * (int)gridDim.x + e] = s_form;
     }
     const float scale = digit_scale(eb);
@@ -718,8 +799,8 @@ __device__ __forceinline__ void lds_barrier() { asm volatile("s_waitcnt lgkmcnt(
 template <int WE, int WK>
 __global__ __launch_bounds__(WE * WK * 64, 2) void route_exact_kernel(
     RowSrc x, int64_t n_tok, int H, const bf16_t* __restrict__ wr, const float* __restrict__ bias, int E, int K, int renorm,
-    const uint8_t* __restrict__ digits, const RowForm* __restrict__ forms, int32_t* __restrict__ idx, float* __restrict__ w,
-    int32_t* __restrict__ tile_hist)
+    const uint8_t* __restrict__ digits, const RowForm* __restrict__ forms, double chain_error, int32_t* __restrict__ idx,
+    float* __restrict__ w, int32_t* __restrict__ tile_hist, int32_t* n_listed, int32_t* __restrict__ listed)
 {
     constexpr int NW = WE * WK, NT = NW * 64;    // waves, threads
     constexpr int XL = 4 / WE;                   // 16-byte loads per lane and step: 32 rows x 128 bytes over WE waves
@@ -773,11 +854,37 @@ __global__ __launch_bounds__(WE * WK * 64, 2) void route_exact_kernel(
             for (int i = 0; i < AHEAD; ++i) range.add(v[i]);
         }
         bool strays;
-        const int eb = range.exponent<W>(strays);
-        // (a stray, if there is one, is looked for at the end)
-        if (tid % W == 0) form[tid / W] = RowForm{eb, {strays ? 0u : kNoStray, kNoStray, kNoStray}};
+        const RowForm f = range.form<W>(strays);
+        if (tid % W == 0) form[tid / W] = f;
+        // (a row's lanes are neighbours: each wave lists the strays of its own rows)
+        unsigned long long left = __ballot(strays && f.eb >= 0 && tid % W == 0);
+#pragma unroll 1
+        for (; left != 0; left &= left - 1) {
+            const int from = __ffsll((long long)left) - 1, r = (tid - lane + from) / W;
+            list_strays(token_row(r), H, __builtin_amdgcn_readlane(f.eb, from), &form[r]);
+        }
     }
-    lds_barrier();
+    __syncthreads();
+
+    // ---- nothing to do here for a block that holds no row, or with an expert that is not held ----
+    const int rows = rows_left(t0, n_tok, 32);
+    const int e_a = lane < E ? lane : E - 1, e_b = lane + 64 < E ? lane + 64 : E - 1;
+    if (__ballot(forms[e_a].eb < 0 || forms[e_b].eb < 0) != 0 || __ballot(lane < rows && form[lane & 31].eb >= 0) == 0) {
+        if (wave == 0) {
+            int32_t at = 0;
+            if (lane == 0) at = atomicAdd(n_listed, rows);
+            at = __builtin_amdgcn_readfirstlane(at);
+            if (lane < rows) listed[at + lane] = (int32_t)(t0 + lane);
+        }
+        return;
+    }
+    float w_norm = forms[e_a].norm > forms[e_b].norm ? forms[e_a].norm : forms[e_b].norm;      // the largest of all experts'
+#pragma unroll
+    for (int o = 1; o < 64; o <<= 1) {
+        const float other = __shfl_xor(w_norm, o, 64);
+        w_norm = other > w_norm ? other : w_norm;
+    }
+    const double off_unit = chain_error * (double)w_norm;
 
     // ---- x: load p of this wave covers rows (we + WE p) * 8 .. + 7 of the tile, lane = (row, 16-byte piece of the step) ----
     const int piece = lane & 7;
@@ -908,14 +1015,9 @@ __global__ __launch_bounds__(WE * WK * 64, 2) void route_exact_kernel(
     }
     __syncthreads();
     double* const z = reinterpret_cast<double*>(lds);        // [32][ZLD]
-    // what is not in the digits (bit = token row, or expert of this wave's group; the same in every wave of a share)
-    const int rows = n_tok - t0 < 32 ? (int)(n_tok - t0) : 32;
     const int own = we * 32 + fr < E ? we * 32 + fr : E - 1;             // lane l knows expert l % 32 of its wave's group
     const RowForm own_form = forms[own];
     const bool real = lane < 32 && we * 32 + fr < E;
-    const uint32_t e_lost = (uint32_t)__ballot(real && own_form.eb < 0);
-    const uint32_t e_stray = (uint32_t)__ballot(real && own_form.eb >= 0 && own_form.stray[0] != kNoStray);
-    const uint32_t t_stray = (uint32_t)__ballot(lane < rows && form[fr].eb >= 0 && form[fr].stray[0] != kNoStray);
     if (wk == 0) {
         // accumulator element v: expert (v / 4) * 8 + fq * 4 + v % 4 of the group, token fr
         const int xe = form[fr].eb;
@@ -930,21 +1032,18 @@ __global__ __launch_bounds__(WE * WK * 64, 2) void route_exact_kernel(
         }
     }
     __syncthreads();
-    // ---- remainders: of x first, then of w_router, in ascending k ----
-    if (t_stray != 0) {                  // (one row in a thousand)
+    // ---- remainders: of x first, then of w_router, in ascending k (bit = token row, or expert of this wave's group) ----
+    const uint32_t t_stray = (uint32_t)__ballot(lane < rows && form[fr].eb >= 0 && form[fr].stray[0] != kNoStray);
+    if (t_stray != 0) {                  // (the same in every wave)
 #pragma unroll 1
         for (uint32_t left = t_stray; left != 0; left &= left - 1) {
             const int r = __ffs((int)left) - 1;
             if (r % NW != wave) continue;
-            list_strays(token_row(r), H, &form[r]);
-            __builtin_amdgcn_wave_barrier();
-            const int eb = form[r].eb;
-            if (eb < 0) continue;
 #pragma unroll 1
             for (int i = 0; i < kStray; ++i) {
                 const uint32_t k = form[r].stray[i];
                 if (k == kNoStray) break;
-                const double rest = remainder_part(token_row(r)[k], eb);
+                const double rest = remainder_part(token_row(r)[k], form[r].eb);
                 for (int e = lane; e < E; e += 64) z[r * ZLD + e] += rest * (double)bf16_to_f32(wr[(int64_t)e * H + k]);
             }
         }
@@ -952,35 +1051,18 @@ __global__ __launch_bounds__(WE * WK * 64, 2) void route_exact_kernel(
     }
     if (wk == 0) {
 #pragma unroll 1
-        for (uint32_t left = e_stray; left != 0; left &= left - 1) {
+        for (uint32_t left = (uint32_t)__ballot(real && own_form.stray[0] != kNoStray); left != 0; left &= left - 1) {
             const int e = __ffs((int)left) - 1, eb = __builtin_amdgcn_readlane(own_form.eb, e);
-            const uint32_t ks[kStray] = {(uint32_t)__builtin_amdgcn_readlane((int)own_form.stray[0], e),
-                                         (uint32_t)__builtin_amdgcn_readlane((int)own_form.stray[1], e),
-                                         (uint32_t)__builtin_amdgcn_readlane((int)own_form.stray[2], e)};
-            if (lane < 32 && form[fr].eb >= 0)
+            const bf16_t* w_row = wr + (int64_t)(we * 32 + e) * H;
 #pragma unroll
-                for (int i = 0; i < kStray; ++i)
-                    if (ks[i] != kNoStray)
-                        z[fr * ZLD + we * 32 + e] += digit_part(token_row(fr)[ks[i]], form[fr].eb) *
-                                                     remainder_part(wr[(int64_t)(we * 32 + e) * H + ks[i]], eb);
+            for (int i = 0; i < kStray; ++i) {
+                const uint32_t k = (uint32_t)__builtin_amdgcn_readlane((int)own_form.stray[i], e);
+                if (k != kNoStray && lane < 32 && form[fr].eb >= 0)
+                    z[fr * ZLD + we * 32 + e] += digit_part(token_row(fr)[k], form[fr].eb) * remainder_part(w_row[k], eb);
+            }
         }
     }
-    // ---- rows that are not held (a row of x may have turned out to be one above) ----
-    const bool lost = e_lost != 0 || __ballot(lane < rows && form[fr].eb < 0) != 0;
-    if (__syncthreads_or(lost)) {
-#pragma unroll 1
-        for (int tile = 0; tile < 4 * WE; ++tile) {
-            const int a = (tile & 1) * 16, e0 = (tile >> 1) * 16;
-            if (a >= rows || e0 >= E) continue;
-            const bool here = lane < 16 ? a + lane < rows && form[a + lane].eb < 0
-                                        : lane < 32 && e0 + lane - 16 < E && forms[e0 + lane - 16].eb < 0;
-            if (__ballot(here) == 0) continue;          // (the same in every wave)
-            logits_tile<bf16_t, 4>(x, n_tok, H, wr, bias, E, t0 + a, e0, [&](int i, int j, double logit) {
-                if (form[a + i].eb < 0 || forms[e0 + j].eb < 0) z[(a + i) * ZLD + e0 + j] = logit;
-            });
-            __syncthreads();             // its scratch is used again
-        }
-    }
+    __syncthreads();
 
     // ---- top-k: 16 lanes per token ----
     const int64_t tile0 = t0 * K / kPermTile;        // 32 tokens x K <= 512 assignments touch at most two permutation tiles
@@ -989,13 +1071,28 @@ __global__ __launch_bounds__(WE * WK * 64, 2) void route_exact_kernel(
     const double* zs[AT_ONCE];
     int my_e[AT_ONCE];
     float my_w[AT_ONCE];
+    Margin<AT_ONCE> margin;
+    bool held[AT_ONCE];
 #pragma unroll
-    for (int u = 0; u < AT_ONCE; ++u) zs[u] = z + (tid / 16 + u * (NT / 16)) * ZLD;
-    topk_of_rows<WE * 2, AT_ONCE>(zs, E, K, renorm, c, false, my_e, my_w);
+    for (int u = 0; u < AT_ONCE; ++u) {
+        const int r = tid / 16 + u * (NT / 16);
+        zs[u] = z + r * ZLD;
+        margin.off[u] = off_unit * (double)form[r].norm;
+        held[u] = form[r].eb >= 0;
+    }
+    topk_of_rows<WE * 2, AT_ONCE>(zs, E, K, renorm, c, false, my_e, my_w, margin);
 #pragma unroll
     for (int u = 0; u < AT_ONCE; ++u) {
         const int64_t t = t0 + tid / 16 + u * (NT / 16);
-        if (t < n_tok && c < K) {
+        const bool sure = held[u] && margin.sure[u];
+        const unsigned long long open = __ballot(t < n_tok && c == 0 && !sure);
+        if (open != 0) {                 // (rare) on the list
+            int32_t at = 0;
+            if (lane == 0) at = atomicAdd(n_listed, (int32_t)__popcll(open));
+            at = __builtin_amdgcn_readfirstlane(at) + (int32_t)__popcll(open & ((1ull << lane) - 1));
+            if (t < n_tok && c == 0 && !sure) listed[at] = (int32_t)t;
+        }
+        if (t < n_tok && c < K && sure) {
             idx[t * K + c] = my_e[u];
             w[t * K + c] = my_w[u];
             if (tile_hist) atomicAdd(&hist[(t * K + c) / kPermTile - tile0][my_e[u]], 1);
@@ -1007,6 +1104,39 @@ __global__ __launch_bounds__(WE * WK * 64, 2) void route_exact_kernel(
             const int cnt = hist[i / E][i % E];
             if (cnt) atomicAdd(&tile_hist[(tile0 + i / E) * E + i % E], cnt);
         }
+    }
+}
+
+// The tokens that route_exact_kernel listed, 16 to a tile: block (g, e) takes the logits of tiles g, g + gridDim.x, ... and
+// 16 experts from the fp64 pass (the same bits as in any other launch); the last block of a tile does its top-k.
+// tickets: one per 16 tokens of the batch, zero at the start.
+template <int NPL>
+__global__ __launch_bounds__(256, 3) void route_listed_kernel(RowSrc x, int H, const bf16_t* __restrict__ wr,
+                                                           const float* __restrict__ bias, int E, int K, int renorm,
+                                                           const int32_t* __restrict__ n_listed,
+                                                           const int32_t* __restrict__ listed, double* logits, uint32_t* tickets,
+                                                           int32_t* __restrict__ idx, float* __restrict__ w,
+                                                           int32_t* __restrict__ tile_hist)
+{
+    __shared__ int32_t flag;
+    const int n = *n_listed, e0 = (int)blockIdx.y * 16;
+    for (int64_t at = (int64_t)blockIdx.x * 16; at < n; at += (int64_t)gridDim.x * 16) {
+        const int rows = rows_left(at, n, 16);
+        logits_tile<bf16_t, 4>([&](int i) { return row_ptr<bf16_t>(x, listed[at + (i < rows ? i : rows - 1)], H); }, rows, H, wr,
+                               bias, E, e0, [&](int i, int j, double z) { store_shared(logits + (at + i) * E + e0 + j, z); });
+        if (last_to_arrive(tickets + at / 16, gridDim.y, &flag)) {
+            const int c = (int)threadIdx.x & 15, row = (int)threadIdx.x >> 4;
+            int e;
+            float wt;
+            topk_of_row<NPL>(logits + (at + (row < rows ? row : rows - 1)) * E, E, K, renorm, c, true, e, wt);
+            if (row < rows && c < K) {
+                const int64_t f = (int64_t)listed[at + row] * K + c;
+                idx[f] = e;
+                w[f] = wt;
+                if (tile_hist) atomicAdd(&tile_hist[f / kPermTile * E + e], 1);
+            }
+        }
+        __syncthreads();                 // the tile's LDS is used again
     }
 }
 
@@ -1031,21 +1161,6 @@ __global__ __launch_bounds__(WE * WK * 64, 2) void route_exact_kernel(
 constexpr int kSmallWaves = 16;
 constexpr int kSmallWords = kSmallTokens / 64;
 
-// Draws a ticket for the block once everything it has stored is visible; true for the last of n drawers.
-// Every thread of the block calls it (`flag`: a word of LDS).
-__device__ __forceinline__ bool last_to_arrive(uint32_t* ticket, uint32_t n, int32_t* flag)
-{
-    asm volatile("s_waitcnt vmcnt(0)" ::: "memory");         // this wave's stores have reached the shared level
-    __syncthreads();
-    if (threadIdx.x == 0) {
-        const bool last = __hip_atomic_fetch_add(ticket, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) == n - 1;
-        if (last) store_shared(ticket, 0u);
-        *flag = last;
-    }
-    __syncthreads();
-    return *flag != 0;
-}
-
 template <typename T, int NPL>
 __global__ __launch_bounds__(kSmallWaves * 64) void route_small_kernel(
     RowSrc x, int n_tok, int H, const T* __restrict__ wr, const float* __restrict__ bias, int E, int K, int renorm,
@@ -1061,7 +1176,8 @@ __global__ __launch_bounds__(kSmallWaves * 64) void route_small_kernel(
     const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
     const int t0 = (int)blockIdx.x * 16;
     const int e0 = (int)blockIdx.y * 16;
-    logits_tile<T, kSmallWaves>(x, n_tok, H, wr, bias, E, t0, e0, [&](int i, int j, double z) {
+    logits_tile<T, kSmallWaves>(rows_from<T>(x, t0, n_tok, H), rows_left(t0, n_tok, 16), H, wr, bias, E, e0,
+                                [&](int i, int j, double z) {
         store_shared(logits + (int64_t)(t0 + i) * E + e0 + j, z);      // (another block of the launch may read it)
     });
     for (int i = tid; i < E * kSmallWords; i += kSmallWaves * 64) (&chosen[0][0])[i] = 0ull;
@@ -1200,25 +1316,35 @@ hipError_t launch_router_digits(const RouterWeights& w, int layers, int H, int E
                                 int64_t zero_n, hipStream_t s)
 {
     const int rows = (E + 31) / 32 * 32;
-    static_assert(sizeof(RowForm) == 16, "router_form_bytes");
+    static_assert(sizeof(RowForm) == 32, "router_form_bytes");
     router_digits_kernel<<<dim3((unsigned)rows, (unsigned)layers), kPrepThreads, 0, s>>>(
         w, H, E, digits, router_digit_bytes(H, E), static_cast<RowForm*>(forms), zero_buf, zero_n);
     return hipGetLastError();
 }
 
 hipError_t launch_route_exact(RowSrc x, int64_t T, int H, const void* w_router, const float* bias, int E, int K, int renorm,
-                              const uint8_t* digits, const void* forms, int32_t* idx, float* w, int32_t* tile_hist,
-                              hipStream_t s)
+                              const uint8_t* digits, const void* forms, const RouteList& list, double* logits, int32_t* idx,
+                              float* w, int32_t* tile_hist, hipStream_t s)
 {
     const int64_t tiles = (T + 31) / 32;
     int cus = 0;
-    const hipError_t e = compute_units(&cus);
+    hipError_t e = compute_units(&cus);
     if (e != hipSuccess) return e;
+    // (see route_exact_kernel; a partial sum of the fp64 chain has every 16th 32-wide chunk of the row)
+    const double chain_error = 0x1p-52 * 1.02 * (((H + 31) / 32 + 15) / 16 * 32 + 40);
     auto go = [&](auto we, auto wk) {
         constexpr int WE = decltype(we)::value, WK = decltype(wk)::value;
         route_exact_kernel<WE, WK><<<(unsigned)tiles, WE * WK * 64, 0, s>>>(
-            x, T, H, static_cast<const bf16_t*>(w_router), bias, E, K, renorm, digits, static_cast<const RowForm*>(forms), idx,
-            w, tile_hist);
+            x, T, H, static_cast<const bf16_t*>(w_router), bias, E, K, renorm, digits, static_cast<const RowForm*>(forms),
+            chain_error, idx, w, tile_hist, list.count, list.tokens);
+        const hipError_t err = hipGetLastError();
+        if (err != hipSuccess) return err;
+        // Usually none or one tile of 16 tokens; two rounds of the chip when it is all of the batch.
+        const int64_t most = (T + 15) / 16;
+        const unsigned n_e = (unsigned)((E + 15) / 16), per = 8 * (unsigned)cus / n_e + 1;
+        const unsigned n_t = most < per ? (unsigned)most : per;
+        route_listed_kernel<WE * 2><<<dim3(n_t, n_e), 256, 0, s>>>(x, H, static_cast<const bf16_t*>(w_router), bias, E, K, renorm,
+                                                                   list.count, list.tokens, logits, list.tickets, idx, w, tile_hist);
         return hipGetLastError();
     };
     using std::integral_constant;

@@ -123,6 +123,98 @@ def test_exact_routing(gpu_lib, H, E, K, T, renorm):
     np.testing.assert_allclose(wt.cpu().numpy()[rows], o_w, rtol=2.0 ** -23, atol=0)
 
 
+# ... and the same bits as the fp64 pass, which smaller batches take: experts and weights of a token do not depend on its batch.
+# (moe_router_topk_noalloc always takes the fp64 pass.)  Rows and experts for which that is decided by the rounding of a sum, rows
+# and experts that the fixed point cannot hold, values that are not finite, biases that mask experts.
+def _hard_routing(kind, T, H, E, seed):
+    g = torch.Generator(device=DEV).manual_seed(seed)
+    x = torch.randn((T, H), generator=g, device=DEV)
+    wr = torch.randn((E, H), generator=g, device=DEV) * 0.02
+    bias = torch.randn((E,), generator=g, device=DEV) * 0.1
+    rows = torch.randint(0, T, (T // 50,), generator=g, device=DEV)
+    if kind == "ties":            # equal sums of the same products in another order, in a tenth of the rows
+        # (over exponents so wide that the fp64 sums round)
+        x *= 2.0 ** -torch.randint(0, 16, (T, H), generator=g, device=DEV).float()
+        wr *= 2.0 ** -torch.randint(0, 16, (E, H), generator=g, device=DEV).float()
+        rows = torch.randint(0, T, (T // 10,), generator=g, device=DEV)
+        x[rows, H // 2:] = x[rows, :H // 2]
+        for e in range(0, E - 1, 2):
+            wr[e + 1] = wr[e].roll(H // 2)
+            bias[e + 1] = bias[e]
+    elif kind == "outliers":      # one value 10^4 times the others in some rows, 10^6 times in others: none to dozens of rests
+        x[rows, rows % H] = 1e4
+        x[(rows + 1) % T, rows % H] = 1e6
+    elif kind == "all_outliers":  # ... and in every row
+        x[:, 3] = 2e6
+    elif kind == "not_finite":
+        x[rows, rows % H] = torch.tensor([float("nan"), float("inf"), -float("inf")], device=DEV)[rows % 3]
+        x[(rows + 1) % T] = 0
+        x[(rows + 2) % T] *= 2.0 ** 60
+        x[(rows + 3) % T] *= 2.0 ** -60
+    elif kind == "masked":        # fewer finite logits than K in the second half of the experts' order, and zero rows: all logits tie
+        bias[E // 2:] = -float("inf")
+        x[rows] = 0
+        bias[:E // 2] = bias[:E // 2].round(decimals=1)
+    elif kind == "strays":        # experts with as many rests as are listed, and one fewer
+        wr[2, :6] = wr[2].abs().max() * 2.0 ** -25 * 1.7
+        wr[E - 1, H - 5:] = wr[E - 1].abs().max() * -(2.0 ** -27) * 1.9
+    elif kind == "lost_expert":   # with one more; infinite
+        wr[1, :7] = wr[1].abs().max() * 2.0 ** -25 * 1.7
+    elif kind == "infinite_expert":
+        wr[E - 2, 5] = float("inf")
+    elif kind == "zero_router":
+        wr.zero_()
+    return x.bfloat16(), wr.bfloat16(), bias
+
+
+@pytest.mark.parametrize("kind", ["normal", "ties", "outliers", "all_outliers", "not_finite", "masked", "strays", "lost_expert",
+                                  "infinite_expert", "zero_router"])
+@pytest.mark.parametrize("H,E,K,T,renorm", [(2048, 128, 8, 6000, True), (2056, 100, 16, 16421, False), (2880, 64, 4, 17000, True),
+                                            (3080, 33, 3, 16123, False), (1096, 64, 6, 24000, True), (16376, 97, 9, 4800, False)])
+def test_exact_routing_is_the_fp64_pass(gpu_lib, kind, H, E, K, T, renorm):
+    x, wr, bias = _hard_routing(kind, T, H, E, 7 * T + H)
+    ctx = gpu_lib.Context(H, E, K, 8, torch.bfloat16, max_tokens=T, renormalize=renorm, device=DEV)
+    step = (1 << 19) // E
+    for b in (bias, None):
+        want = [gpu_lib.moe_router_topk_noalloc(x[t:t + step], wr, b, K, renormalize=renorm) for t in range(0, T, step)]
+        want_idx, want_w = torch.cat([i for i, _ in want]), torch.cat([w for _, w in want])
+        for _ in range(2):
+            idx, w = ctx.moe_router_topk(x, wr, b)
+            assert torch.equal(idx, want_idx)
+            assert torch.equal(w.view(torch.int32), want_w.view(torch.int32)) or (
+                torch.equal(w.isnan(), want_w.isnan()) and torch.equal(w.nan_to_num(), want_w.nan_to_num()))
+
+
+@pytest.mark.parametrize("kind", ["ties", "outliers", "not_finite", "lost_expert"])
+@pytest.mark.parametrize("H,E,K,T", [(2048, 128, 8, 6000), (2880, 64, 4, 17000)])
+def test_hard_routing_in_a_group(gpu_lib, kind, H, E, K, T):
+    """The histograms behind the permutation hold listed tokens too; a token's outputs are those of a small batch."""
+    I = 64
+    x, wr, bias = _hard_routing(kind, T, H, E, T + H)
+    w = inputs.Workload("hard", H=H, E=E, K=K, I=I, n_layers=1, D=0, P=T, dtype="bf16", seed=9)
+    L = {k: (v.to(DEV) if v is not None else None) for k, v in inputs.make_layer(w, 0).items()}
+    L["w_router"], L["router_bias"] = wr, bias
+    ctx = gpu_lib.Context(H, E, K, I, torch.bfloat16, max_tokens=T, residual=False, device=DEV)
+    for _ in range(2):
+        _, y = ctx.moe_group_forward([L], None, x, "layered")
+        _, part = ctx.moe_group_forward([L], None, x, "chunked", 1000)
+        assert torch.equal(y.view(torch.int16), part.view(torch.int16))
+    idx, wt = ctx.moe_router_topk(x, wr, bias)
+    counts, offsets, perm, inv, x_perm = ctx.moe_permute(x, idx)
+    z = ctx.moe_combine(ctx.moe_grouped_ffn(x_perm, offsets, L["w_gate_up"], L["w_down"]), inv, wt)
+    assert torch.equal(y.view(torch.int16), z.view(torch.int16))
+    packed, out, want = ctx.pack_layers([L]), torch.empty_like(y), y.clone()
+    graph = torch.cuda.CUDAGraph()
+    with torch.cuda.graph(graph):
+        ctx.moe_group_forward([L], None, x, "layered", packed=packed, y_prefill=out)
+    for _ in range(3):               # every replay finds the list empty
+        out.zero_()
+        graph.replay()
+        torch.cuda.synchronize()
+        assert torch.equal(out.view(torch.int16), want.view(torch.int16))
+        ctx.moe_group_forward([L], None, x.roll(1, 0), "layered")
+
+
 # ... as part of a pass: the digits of ten layers come in two launches, and the top-k counts the permutation's histograms
 def test_exact_routing_in_a_group(gpu_lib):
     H, E, K, I, T, n = 2048, 128, 8, 64, 2300, 10
