@@ -86,17 +86,23 @@ inline int64_t route_list_words(int64_t T) { return 1 + (T + 15) / 16; }      //
 hipError_t launch_route_exact(RowSrc x, int64_t T, int H, const void* w_router, const float* bias, int E, int K, int renorm,
                               const uint8_t* digits, const void* forms, const RouteList& list, double* logits, int32_t* idx,
                               float* w, int32_t* tile_hist, hipStream_t s);
-// (its sums are at most 4 H 2^14; a block holds all experts' logits of its tokens.)  It takes 25 us and more however few the
-// tokens, the fp64 pass grows with T E H.  Logits and top-k, fp64 / exact with the digits of one layer, us: H = 2048, E = 128: 1389
-// tokens 26.6 / 31, 2112 36.4 / 31.2 (as part of a layer, with one launch boundary less or more, the two are level), 4128
-// 57.5 / 34; E = 64: 3000 tokens 25.9 / 31, 4128 36.4 / 32; H = 2880, E = 32: 4128 30.6 / 30, 8320 45 / 42.  Up to 16 experts the
-// fp64 pass does a group of 16 where this one does 32: H = 4096, E = 8, 8320 tokens 39 / 61.
-constexpr int kExactMaxH = 16384, kExactExperts = 128;
+// (its sums are at most 4 H 2^14; a block holds all experts' logits of its tokens.)  A block of 32 tokens takes as long as the chip
+// with a block on every unit, and about in proportion to H, while the fp64 pass grows with the 16 x 16 tiles of logits: so the
+// line is a number of logits, at short rows a higher one (the launches' own 20 us).  moe_router_topk, us, fp64 pass / this
+// one with the digits of one layer:
+//   E = 128:  H = 1024: 4000 tokens 31 / 34, 5000 36 / 34;  2048: 3000 40 / 46, 4000 51 / 47, 8320 97 / 64;
+//             4096: 3000 71 / 73, 5000 108 / 88;  16384: 300 56 / 198, 2400 211 / 247, 4800 397 / 297;  512: 5000 25 / 29, 8200 37 / 34
+//   E = 96:   2048: 4000 41 / 46, 5000 50 / 47        E = 64:   2048: 5000 35 / 40, 8200 55 / 50;  16384: 577 55 / 156, 8320 366 / 358
+//   E = 48:   2048: 8200 45 / 49, 12000 56 / 54       E = 32 and less (one group of experts to a block): 2048: 16384 50 / 53,
+//             32768 93 / 86;  4096: 16384 89 / 106, 32768 170 / 170
+constexpr int kExactMaxH = 16384, kExactMinExperts = 33, kExactMaxExperts = 128;
 inline bool route_is_exact(int dtype, int64_t T, int H, int E, int K)
 {
-    return dtype == MOE_BF16 && !route_is_small(T, E, K) && H <= kExactMaxH && E > 16 && E <= kExactExperts && K <= 16 &&
-           T * ((E + 15) / 16 * 16) * H >= (int64_t)600000000;
+    const int64_t logits = T * ((E + 15) / 16 * 16);
+    return dtype == MOE_BF16 && H <= kExactMaxH && E >= kExactMinExperts && E <= kExactMaxExperts && K <= 16 &&
+           (logits - ((int64_t)1 << 19)) * H >= (int64_t)1 << 27;
 }
+static_assert(kSmallTokens * kSmallExperts < 1 << 19, "a batch of the one-launch routing is below the line");
 // tile_hist (or NULL): [ceil(T*K / kPermTile), E] counters, already zero, that receive the expert histogram
 hipError_t launch_topk(const double* logits, int64_t T, int E, int K, int renorm, int32_t* idx, float* w,
                        int32_t* tile_hist, hipStream_t s);

@@ -559,7 +559,7 @@ __global__ __launch_bounds__(kTopkWaves * 64) void topk_rows_kernel(const double
 }
 
 // ----------------------------------------------------------------------------------------------
-// Router and top-k of larger batches of bf16 rows (at most kExactExperts experts, K <= 16): the logits are exact integer
+// Router and top-k of larger batches of bf16 rows (at most kExactMaxExperts experts, K <= 16): the logits are exact integer
 // sums on the i8 matrix cores.
 //
 // The fp64 pass above is bound by the fp64 matrix pipe (two widenings beside every MFMA).  Here a row of x, and a row
@@ -826,8 +826,7 @@ __global__ __launch_bounds__(WE * WK * 64, 2) void route_exact_kernel(
     const int steps = (H + kDigitK - 1) / kDigitK;
     const int mine = (steps + WK - 1) / WK;                  // steps of every share (its last ones may be empty: zeros)
     const uint8_t* w_src = digits + (int64_t)(we < groups ? we : groups - 1) * 8192 + lane * 16;
-    constexpr int WB = WE > 1 ? 2 : 1;           // (one group's waves hold four rows' worth of x: no room for a second step)
-    i32x4_t wd[WB][2][4];
+    i32x4_t wd[2][2][4];
     auto load_w = [&](int i, int buf) {
         const int c = i * WK + wk;
         const uint8_t* p = w_src + (int64_t)(c < steps ? c : steps - 1) * groups * 8192;
@@ -901,8 +900,7 @@ __global__ __launch_bounds__(WE * WK * 64, 2) void route_exact_kernel(
         x_scale[p] = digit_scale(form[r].eb);
         x_dst[p] = slot(r, piece >> 1) + (piece & 1) * 8;
     }
-    constexpr int XB = WE > 1 ? 2 : 1;   // (issued in front of the step's weights, so that waiting for one is not waiting for the other)
-    u32x4_t xr[XB][XL];
+    u32x4_t xr[2][XL];                   // (issued in front of the step's weights, so that waiting for one is not waiting for the other)
     auto load_x = [&](int i, int buf) {
         const int at = (i * WK + wk) * 8 + piece;
         // (past the row: a valid piece, turned into zeros below; a load under a condition would make the compiler wait for
@@ -932,8 +930,8 @@ __global__ __launch_bounds__(WE * WK * 64, 2) void route_exact_kernel(
     auto step = [&](int i, auto buf_const) {
         constexpr int BUF = decltype(buf_const)::value;
         lds_barrier();                   // the digits of step i are there, and those of step i - 1 have been read
-        if (XB == 2) load_x(i + 2, BUF);
-        if (WB == 2) load_w(i + 1, BUF ^ 1);
+        load_x(i + 2, BUF);
+        load_w(i + 1, BUF ^ 1);
         const uint8_t* dig = lds + wk * SHARE + (i & 1) * 8192;
         i32x4_t xd[2][4];
 #pragma unroll
@@ -954,15 +952,14 @@ __global__ __launch_bounds__(WE * WK * 64, 2) void route_exact_kernel(
         // bits 0, 1: lowest digits of the weights' halves that are not zero; 2, 3: of x's
         const int low = (any_of(wd[BUF][0][0]) ? 1 : 0) | (any_of(wd[BUF][1][0]) ? 2 : 0) | (any_of(xd[0][0]) ? 4 : 0) |
                         (any_of(xd[1][0]) ? 8 : 0);
-        store_digits(i + 1, XB == 2 ? BUF ^ 1 : 0);          // (past the last step: zeros nobody reads)
-        if (XB == 1) load_x(i + 2, 0);
+        store_digits(i + 1, BUF ^ 1);    // (past the last step: zeros nobody reads)
         // The loads one by one between the MFMAs: a wave issues in order, and eight loads in a row keep its MFMAs waiting
         // for the address unit, which takes 16 clocks of each of the four waves' loads.
         __builtin_amdgcn_sched_group_barrier(0x100, 4, 0);           // LDS reads of the first half
 #pragma unroll
         for (int n = 0; n < 9; ++n) {
             __builtin_amdgcn_sched_group_barrier(0x008, 1, 0);       // one MFMA
-            if (n < (WB == 2 ? 8 : 0) + (XB == 2 ? XL : 0)) __builtin_amdgcn_sched_group_barrier(0x020, 1, 0);   // one global load
+            if (n < 8 + XL) __builtin_amdgcn_sched_group_barrier(0x020, 1, 0);   // one global load
             if (n < 4) __builtin_amdgcn_sched_group_barrier(0x100, 1, 0);
             __builtin_amdgcn_sched_group_barrier(0x008, 1, 0);
         }
@@ -975,17 +972,15 @@ __global__ __launch_bounds__(WE * WK * 64, 2) void route_exact_kernel(
                 if (w_low && x_low) multiply(half, 0, 0);
             }
         }
-        if (WB == 1) load_w(i + 1, 0);
     };
     load_x(0, 0);
-    if (XB == 2) load_x(1, 1);
+    load_x(1, 1);
     load_w(0, 0);                        // (in the loop's order: the compiler's waits in the loop allow for what comes before it)
     store_digits(0, 0);
-    if (XB == 1) load_x(1, 0);
 #pragma unroll 1
     for (int i = 0; i < mine; i += 2) {
         step(i, std::integral_constant<int, 0>{});
-        step(i + 1, std::integral_constant<int, WB - 1>{});
+        step(i + 1, std::integral_constant<int, 1>{});
     }
 
     // ---- the shares' sums meet, the upper half of them handing theirs to the lower half ----
@@ -1348,12 +1343,10 @@ hipError_t launch_route_exact(RowSrc x, int64_t T, int H, const void* w_router, 
         return hipGetLastError();
     };
     using std::integral_constant;
-    // With a block per compute unit at most, twice the waves (registers leave room for two per SIMD either way): 2112 tokens,
-    // H = 2048, 128 experts 26.4 us against 29.7, 6000 tokens 35 / 37; 8320 tokens, 260 blocks, 53 / 44.
-    const bool few = tiles <= cus;
-    if (E <= 32) return few ? go(integral_constant<int, 1>{}, integral_constant<int, 8>{}) : go(integral_constant<int, 1>{}, integral_constant<int, 4>{});
-    if (E <= 64) return few ? go(integral_constant<int, 2>{}, integral_constant<int, 4>{}) : go(integral_constant<int, 2>{}, integral_constant<int, 2>{});
-    return few ? go(integral_constant<int, 4>{}, integral_constant<int, 2>{}) : go(integral_constant<int, 4>{}, integral_constant<int, 1>{});
+    if (E <= 64) return go(integral_constant<int, 2>{}, integral_constant<int, 2>{});      // (8192 tokens and more)
+    // With a block per compute unit at most, twice the waves (registers leave room for two per SIMD either way), us before the
+    // check of the winners: 2112 tokens, H = 2048, 128 experts 26.4 against 29.7, 6000 tokens 35 / 37; 8320 tokens, 260 blocks, 53 / 44.
+    return tiles <= cus ? go(integral_constant<int, 4>{}, integral_constant<int, 2>{}) : go(integral_constant<int, 4>{}, integral_constant<int, 1>{});
 }
 
 hipError_t launch_router_logits(int dtype, RowSrc x, int64_t T, int H, const void* w_router, const float* bias,

@@ -92,7 +92,8 @@ def test_one_launch_routing_of_long_rows(gpu_lib, H, dtype, T):
 # three, not at all (four rests; no fp32 scale), of zeros.  Indices are exact; a weight is one rounding to fp32 of a quotient of
 # fp64 values: 2^-23 relative.
 @pytest.mark.parametrize("H,E,K,T", [(2056, 128, 8, 2290), (4104, 17, 5, 4580), (4096, 32, 1, 8225), (8, 128, 16, 586000),
-                                     (16384, 64, 9, 577), (2048, 33, 3, 9190), (2048, 97, 16, 8193)])
+                                     (16384, 64, 9, 577), (2048, 33, 3, 9190), (2048, 97, 16, 8193), (2056, 128, 8, 4690),
+                                     (4104, 49, 5, 8705), (512, 96, 1, 8225)])
 @pytest.mark.parametrize("renorm", [True, False])
 def test_exact_routing(gpu_lib, H, E, K, T, renorm):
     if H == 8 and not renorm:
@@ -215,9 +216,25 @@ def test_hard_routing_in_a_group(gpu_lib, kind, H, E, K, T):
         ctx.moe_group_forward([L], None, x.roll(1, 0), "layered")
 
 
+# Which batches take them: a number of logits, whatever the length of the rows (the top-k then has no launch of its own).
+@pytest.mark.parametrize("H,E,T,exact", [(16384, 64, 577, False), (16384, 128, 300, False), (4096, 128, 1200, False),
+                                         (2880, 32, 17000, False), (2048, 128, 4607, False), (2048, 128, 4608, True),
+                                         (2048, 64, 9215, False), (2048, 64, 9216, True), (256, 40, 21844, False),
+                                         (256, 40, 21846, True)])
+def test_exact_routing_rule(gpu_lib, H, E, T, exact):
+    w = inputs.Workload("rule", H=H, E=E, K=2, I=8, n_layers=1, D=0, P=T, dtype="bf16", seed=3)
+    L = {k: (v.to(DEV) if v is not None else None) for k, v in inputs.make_layer(w, 0).items()}
+    x = torch.randn((T, H), dtype=torch.bfloat16, device=DEV)
+    ctx = gpu_lib.Context(H, E, 2, 8, torch.bfloat16, max_tokens=T, device=DEV)
+    ctx.moe_kernel_timing(["topk"])
+    ctx.moe_group_forward([L], None, x, "layered")
+    assert ctx.moe_read_kernel_timing("topk")[1] == (0 if exact else 1)
+
+
 # ... as part of a pass: the digits of ten layers come in two launches, and the top-k counts the permutation's histograms
-def test_exact_routing_in_a_group(gpu_lib):
-    H, E, K, I, T, n = 2048, 128, 8, 64, 2300, 10
+@pytest.mark.parametrize("T", [2300, 4700])
+def test_exact_routing_in_a_group(gpu_lib, T):
+    H, E, K, I, n = 2048, 128, 8, 64, 10
     w = inputs.Workload("exact", H=H, E=E, K=K, I=I, n_layers=n, D=0, P=T, dtype="bf16", seed=5)
     layers = [{k: (v.to(DEV) if v is not None else None) for k, v in inputs.make_layer(w, l).items()} for l in range(n)]
     x = inputs.randn((T, H), 1.0, 5, "x", 0, "bf16").to(DEV)
