@@ -273,6 +273,7 @@ __global__ __launch_bounds__(NW * 64, MINW) void grouped_gemm_bf16_pipe_kernel(
     const uint32_t lds0 = lds_address(smem);
     // (stream: the weights of this tile are read by this block alone; see load_lds.  The wide shape is for many rows per expert.)
     constexpr bool MAY_STREAM = BM <= 64;
+    const bool streamed = MAY_STREAM && tc.alone && whole_lines(W);
     auto issue_b = [&](int kt, int p, auto stream) {
         const int kw = (SPLIT && !GATED && kt >= nk_w) ? kt - nk_w : kt;
         load_lds_16<decltype(stream)::value>(b_src[p] + kw * PBK, lds0 + B_BASE + (kt % NS) * B_SLOT + (wave + NW * p) * 1024);
@@ -284,7 +285,7 @@ __global__ __launch_bounds__(NW * 64, MINW) void grouped_gemm_bf16_pipe_kernel(
 #pragma unroll
                 for (int p = 0; p < B_LPW; ++p) issue_b(st, p, stream);
     };
-    if (MAY_STREAM && tc.alone) issue_first(std::integral_constant<bool, MAY_STREAM>{});
+    if (streamed) issue_first(std::integral_constant<bool, MAY_STREAM>{});
     else issue_first(std::false_type{});
     if (MAPPED) {
         // the lookups came before the weight loads of the prologue: wait for them alone
@@ -455,7 +456,7 @@ __global__ __launch_bounds__(NW * 64, MINW) void grouped_gemm_bf16_pipe_kernel(
         else if (tm_valid >= 1) run(std::integral_constant<int, 1>{}, stream);
         else run(std::integral_constant<int, 0>{}, stream);
     };
-    if (MAY_STREAM && tc.alone) run_rows(std::integral_constant<bool, MAY_STREAM>{});
+    if (streamed) run_rows(std::integral_constant<bool, MAY_STREAM>{});
     else run_rows(std::false_type{});
 }
 
@@ -720,7 +721,7 @@ __global__ __launch_bounds__(kBigWaves * 64, 2) void grouped_gemm_bf16_big_kerne
         }
         wait_vmcnt<0>();           // a block must not end with loads into LDS outstanding
     };
-    if (queue.mostly_alone) walk(std::true_type{});
+    if (queue.mostly_alone && whole_lines(W)) walk(std::true_type{});
     else walk(std::false_type{});
 }
 

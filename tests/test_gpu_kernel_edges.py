@@ -394,6 +394,28 @@ def test_streamed_weight_tiles(gpu_lib, shape, H, I, rows, fmt):
     assert torch.equal(ctx.moe_grouped_ffn(x_perm, offsets, L["w_gate_up"], L["w_down"]), want)
 
 
+# ... unless the weights do not start on a 128-byte line (16 bytes are enough for the library): the same bits from there
+@pytest.mark.parametrize("shape,H,I,rows", [("few", 384, 64, [32, 1, 0, 20]), ("small", 512, 448, [64, 0, 1, 40]),
+                                            ("big", 512, 320, [256, 1, 0, 130])])
+@pytest.mark.parametrize("off", [8, 32, 64])
+def test_streamed_weight_tiles_inside_a_line(gpu_lib, shape, H, I, rows, off):
+    E, A = len(rows), sum(rows)
+    w = inputs.Workload("stream", H=H, E=E, K=1, I=I, n_layers=1, D=0, P=A, dtype="bf16", seed=A)
+    L = {k: (v.to(DEV) if v is not None else None) for k, v in inputs.make_layer(w, 0).items()}
+    x_perm = inputs.randn((A, H), 1.0, A, "x_perm", 0, "bf16").to(DEV)
+    offsets = torch.tensor(np.concatenate([[0], np.cumsum(rows)]), dtype=torch.int32).to(DEV)
+    ctx = gpu_lib.Context(H, E, 1, I, torch.bfloat16, max_tokens=A, device=DEV)
+    ctx.moe_set_ffn_variant(shape)
+    want = ctx.moe_grouped_ffn(x_perm, offsets, L["w_gate_up"], L["w_down"]).clone()
+
+    def moved(t):
+        buf = torch.empty(t.numel() + 128, dtype=t.dtype, device=DEV)
+        at = (-buf.data_ptr() % 128) // 2 + off
+        return buf[at:at + t.numel()].view(t.shape).copy_(t)
+
+    assert torch.equal(ctx.moe_grouped_ffn(x_perm, offsets, moved(L["w_gate_up"]), moved(L["w_down"])), want)
+
+
 # The shape a launch takes is the one moe_ffn_variant names: pinned, or by the rule.  By the rule: a streaming shape up to 56
 # rows per expert, and beyond as long as its tiles are one round (two per compute unit, 512 on 256 units); narrow tiles while
 # these are less than one round.
