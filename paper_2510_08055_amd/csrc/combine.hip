@@ -1,9 +1,9 @@
 // Weighted un-permute and combine: a token's output is the mix of its K selected
 // experts' outputs under the router's weights (Sec. 2.4), plus the residual stream.
 // Pure bandwidth: one block per token, 16-byte loads of the K source rows, fp32
-// accumulation in slot order, one rounding.  The source rows are read once, as non-temporal loads (8320 tokens,
-// top-8, H = 2048, us, plain / so: 65.5 / 56.9; up to 2112 tokens level), except fp32 rows under bf16 output: a lane reads
-// its 32 bytes of those in two pieces, and a line that is gone between them is fetched twice (33.8 / 48).
+// accumulation in slot order, one rounding.
+#include <type_traits>
+
 #include "common.h"
 
 namespace moe {
@@ -40,13 +40,15 @@ template <> struct pack16<float> {
 // y rows [0, rows0) go to y0, rows [rows0, T) to y1 (row t - rows0): lets the layer-group driver
 // write decode rows and prefill rows to their separate output buffers without a copy.
 // YT: element type of y_perm (T, or float when the context keeps the expert outputs in fp32).
-template <typename T, typename YT>
+// STREAM: y_perm as non-temporal loads (each of its rows is read once; see launch_combine).
+template <typename T, typename YT, bool STREAM>
 __global__ __launch_bounds__(256) void combine_kernel(const YT* __restrict__ y_perm, const int32_t* __restrict__ inv,
                                                       const float* __restrict__ w, bool has_residual,
                                                       RowSrc residual, int K, int H, T* y0, int64_t rows0, T* y1)
 {
     typedef pack16<T> P;
     typedef pack16<YT> PY;
+    static_assert(!STREAM || sizeof(T) == sizeof(YT), "a line that is read in two pieces would be fetched twice");
     constexpr int NY = P::N / PY::N;      // 16-byte pieces of y_perm per 16 bytes of output (1, or 2 for fp32 under bf16)
     __shared__ int32_t s_row[kMaxTopK];
     __shared__ float s_w[kMaxTopK];
@@ -68,7 +70,7 @@ __global__ __launch_bounds__(256) void combine_kernel(const YT* __restrict__ y_p
 #pragma unroll
             for (int h = 0; h < NY; ++h) {
                 PY p;
-                if (NY == 1)
+                if (STREAM)
                     p.raw = __builtin_bit_cast(decltype(p.raw), __builtin_nontemporal_load(reinterpret_cast<const chunk16_t*>(src)));
                 else
                     p.raw = *reinterpret_cast<const decltype(p.raw)*>(src + h * PY::N);
@@ -91,20 +93,31 @@ __global__ __launch_bounds__(256) void combine_kernel(const YT* __restrict__ y_p
     }
 }
 
+// Expert outputs of more than this are read as a stream: of fewer, the last-level cache (256 MB) still holds most of what the
+// down GEMM has just written.  Behind it, top-8 unless said otherwise, us, plain / stream: H = 2048: 69 MB (2112 tokens) 18.2 / 18.7,
+// 164 MB 38.7 / 38.0, 197 MB 46.8 / 44.3, 273 MB (8320) 67.1 / 59.3; H = 2880, top-4: 96 MB 29.1 / 29.8, 192 MB 55.5 / 51.0;
+// H = 1160: 154 MB 33.2 / 34.4, 297 MB 71 / 60; H = 8200: 84 MB 23.5 / 26.9, 157 MB 35.8 / 38.8, 315 MB 84.7 / 72.5.  On y_perm that is
+// wholly in the cache a stream is up to 25 % slower.  fp32 rows under bf16 output stay plain: a lane reads its 32 bytes of those
+// in two pieces, and a line that is gone between them is fetched twice (33.8 / 48).
+constexpr int64_t kStreamFrom = (int64_t)160 << 20;
+
 hipError_t launch_combine(int dtype, bool y_perm_f32, const void* y_perm, const int32_t* inv, const float* w,
                           bool has_residual, RowSrc residual, int64_t T, int K, int H, void* y0, int64_t rows0, void* y1,
                           hipStream_t s)
 {
-    if (dtype == MOE_BF16 && y_perm_f32)
-        combine_kernel<bf16_t, float><<<(unsigned)T, 256, 0, s>>>((const float*)y_perm, inv, w, has_residual, residual,
-                                                                  K, H, (bf16_t*)y0, rows0, (bf16_t*)y1);
-    else if (dtype == MOE_BF16)
-        combine_kernel<bf16_t, bf16_t><<<(unsigned)T, 256, 0, s>>>((const bf16_t*)y_perm, inv, w, has_residual, residual,
-                                                                   K, H, (bf16_t*)y0, rows0, (bf16_t*)y1);
-    else
-        combine_kernel<float, float><<<(unsigned)T, 256, 0, s>>>((const float*)y_perm, inv, w, has_residual, residual, K,
-                                                                 H, (float*)y0, rows0, (float*)y1);
-    return hipGetLastError();
+    auto go = [&](auto elem_t, auto y_elem_t, auto stream) {
+        typedef decltype(elem_t) X;
+        typedef decltype(y_elem_t) Y;
+        combine_kernel<X, Y, decltype(stream)::value><<<(unsigned)T, 256, 0, s>>>(
+            static_cast<const Y*>(y_perm), inv, w, has_residual, residual, K, H, static_cast<X*>(y0), rows0, static_cast<X*>(y1));
+        return hipGetLastError();
+    };
+    const std::true_type stream;
+    const std::false_type plain;
+    const int64_t values = T * K * H;
+    if (dtype == MOE_BF16 && y_perm_f32) return go(bf16_t(), float(), plain);
+    if (dtype == MOE_BF16) return values * 2 > kStreamFrom ? go(bf16_t(), bf16_t(), stream) : go(bf16_t(), bf16_t(), plain);
+    return values * 4 > kStreamFrom ? go(float(), float(), stream) : go(float(), float(), plain);
 }
 
 }  // namespace moe

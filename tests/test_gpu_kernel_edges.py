@@ -416,6 +416,26 @@ def test_streamed_weight_tiles_inside_a_line(gpu_lib, shape, H, I, rows, off):
     assert torch.equal(ctx.moe_grouped_ffn(x_perm, offsets, moved(L["w_gate_up"]), moved(L["w_down"])), want)
 
 
+# Expert outputs of more than 160 MiB are read as a stream: the same bits as in pieces below that
+@pytest.mark.parametrize("H,K,T,dtype", [(2048, 8, 5120, "bf16"), (2048, 8, 5121, "bf16"), (1160, 7, 11008, "bf16"), (2056, 3, 7000, "f32")])
+def test_streamed_combine(gpu_lib, H, K, T, dtype):
+    dt = inputs.torch_dtype(dtype)
+    g = torch.Generator(device=DEV).manual_seed(T)
+    y_perm, x = (torch.randn((n, H), generator=g, device=DEV).to(dt) for n in (T * K, T))
+    w = torch.rand((T, K), generator=g, device=DEV)
+    cut = [0, T // 3, T // 2, T]
+    local = [torch.randperm((b - a) * K, generator=g, device=DEV).to(torch.int32).view(-1, K) for a, b in zip(cut, cut[1:])]
+    ctx = gpu_lib.Context(H, 16, K, 8, dt, max_tokens=T, device=DEV)
+    inv = torch.cat([l + a * K for l, a in zip(local, cut)])
+    y = ctx.moe_combine(y_perm, inv, w, residual=x)
+    for l, a, b in zip(local, cut, cut[1:]):
+        part = ctx.moe_combine(y_perm[a * K:b * K], l, w[a:b], residual=x[a:b])
+        assert torch.equal(y[a:b], part)
+    want = (y_perm[inv.long().view(-1)].view(T, K, H).float() * w[:, :, None]).sum(1) + x.float()
+    bound = 2.0 ** -8 if dtype == "bf16" else 2.0 ** -20      # one rounding; K + 1 fp32 sums of values up to 2^3
+    assert ((y.float() - want).abs() <= bound * (want.abs() + 8)).all()
+
+
 # The shape a launch takes is the one moe_ffn_variant names: pinned, or by the rule.  By the rule: a streaming shape up to 56
 # rows per expert, and beyond as long as its tiles are one round (two per compute unit, 512 on 256 units); narrow tiles while
 # these are less than one round.
