@@ -593,10 +593,11 @@ __global__ __launch_bounds__(kTopkWaves * 64) void topk_rows_kernel(const double
 // lines, each value once) and hand them to each other through LDS, a step ahead of the MFMAs that use them.  w_router's
 // digits come from a launch of their own (for several layers at once), laid out as the operands' registers.  The logits
 // stay in LDS, where the top-k reads them.
-// Measured (kernel times, us; logits and top-k of the fp64 pass -> this launch + the listed tokens, and 5 us for the digits of up
-// to 8 layers), H = 2048, E = 128, top-8: 2400 tokens 33 -> 30 + 13, 8320 93 -> 49 + 14.  What bounds it: the MFMAs alone take 10.5 us of the 24 of the k-loop at 8320 tokens; the rest is
-// the 36 KB per step that a compute unit's address unit and L2 deliver (eight loads issued in a row, in place of one by one
-// between the MFMAs, cost 6 us, the branches around four groups of MFMAs in place of one 5 us; the conversions are hidden).
+// Measured, H = 2048, E = 128, top-8: moe_router_topk with the fp64 pass -> this one 60 -> 46 us at 4800 tokens, 97 -> 63 at 8320,
+// of which the digits (of up to 8 layers) 5, this kernel 47, the listed tokens 14.  What bounds it: the MFMAs alone take 10.5 us of
+// the 24 of the k-loop at 8320 tokens; the rest is the 36 KB per step that a compute unit's address unit and L2 deliver (eight
+// loads issued in a row, in place of one by one between the MFMAs, cost 6 us, the branches around four groups of MFMAs in place of
+// one 5 us; the conversions are hidden).
 // Every row listed (more than kStray values below the window in each of them): 143 us in all at 8320 tokens against 97.
 // ----------------------------------------------------------------------------------------------
 typedef int i32x4_t __attribute__((ext_vector_type(4)));
@@ -834,7 +835,13 @@ __global__ __launch_bounds__(WE * WK * 64, 2) void route_exact_kernel(
         for (int d = 0; d < 8; ++d) wd[buf][d / 4][d % 4] = *reinterpret_cast<const i32x4_t*>(p + d * 1024);
     };
 
-    // ---- the form of the token rows: NT / 32 neighbouring lanes per row ----
+    // ---- the form of the token rows: NT / 32 neighbouring lanes per row (the experts' forms come in meanwhile) ----
+    struct EbNorm {
+        int eb;
+        float norm;
+    };
+    auto expert_form = [&](int e) { return *reinterpret_cast<const EbNorm*>(forms + (e < E ? e : E - 1)); };
+    const EbNorm form_a = expert_form(lane), form_b = expert_form(lane + 64);
     for (int i = tid; i < 2 * WE * 32; i += NT) (&hist[0][0])[i] = 0;
     {
         constexpr int W = NT / 32, AHEAD = 8;
@@ -867,8 +874,7 @@ __global__ __launch_bounds__(WE * WK * 64, 2) void route_exact_kernel(
 
     // ---- nothing to do here for a block that holds no row, or with an expert that is not held ----
     const int rows = rows_left(t0, n_tok, 32);
-    const int e_a = lane < E ? lane : E - 1, e_b = lane + 64 < E ? lane + 64 : E - 1;
-    if (__ballot(forms[e_a].eb < 0 || forms[e_b].eb < 0) != 0 || __ballot(lane < rows && form[lane & 31].eb >= 0) == 0) {
+    if (__ballot(form_a.eb < 0 || form_b.eb < 0) != 0 || __ballot(lane < rows && form[lane & 31].eb >= 0) == 0) {
         if (wave == 0) {
             int32_t at = 0;
             if (lane == 0) at = atomicAdd(n_listed, rows);
@@ -877,7 +883,7 @@ __global__ __launch_bounds__(WE * WK * 64, 2) void route_exact_kernel(
         }
         return;
     }
-    float w_norm = forms[e_a].norm > forms[e_b].norm ? forms[e_a].norm : forms[e_b].norm;      // the largest of all experts'
+    float w_norm = form_a.norm > form_b.norm ? form_a.norm : form_b.norm;      // the largest of all experts'
 #pragma unroll
     for (int o = 1; o < 64; o <<= 1) {
         const float other = __shfl_xor(w_norm, o, 64);
@@ -1334,7 +1340,8 @@ hipError_t launch_route_exact(RowSrc x, int64_t T, int H, const void* w_router, 
             chain_error, idx, w, tile_hist, list.count, list.tokens);
         const hipError_t err = hipGetLastError();
         if (err != hipSuccess) return err;
-        // Usually none or one tile of 16 tokens; two rounds of the chip when it is all of the batch.
+        // Usually none or one tile of 16 tokens (14 us); when it is all of the batch, 8320 tokens of 128 experts, 120 us against
+        // 149 with a block's place on the chip each.
         const int64_t most = (T + 15) / 16;
         const unsigned n_e = (unsigned)((E + 15) / 16), per = 8 * (unsigned)cus / n_e + 1;
         const unsigned n_t = most < per ? (unsigned)most : per;
