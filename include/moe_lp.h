@@ -263,7 +263,8 @@ moe_status moe_reset_counters(moe_ctx *ctx, void *stream);
  * moe_read_kernel_timing synchronises `stream` and returns the summed duration (milliseconds) and
  * the number of timed launches of one kernel since the mask was set.  (The permutation may be up to
  * three launches; they are timed as one.  The routing of a small batch is a single launch, timed as
- * MOE_KERNEL_ROUTER_LOGITS.)
+ * MOE_KERNEL_ROUTER_LOGITS; so are the two or three launches that make logits and top-k of a large one.  Either
+ * leaves MOE_KERNEL_TOPK without launches, a small batch MOE_KERNEL_PERMUTE too.)
  */
 typedef enum {
     MOE_KERNEL_ROUTER_LOGITS = 0, MOE_KERNEL_TOPK = 1, MOE_KERNEL_PERMUTE = 2,

@@ -193,10 +193,11 @@ RouteList route_list(const moe_ctx* c, int slot)
     return RouteList{words, reinterpret_cast<uint32_t*>(words + 1), c->listed};
 }
 
-// One layer on the batch `x` [T,H]; output rows [0,rows0) -> y0, the rest -> y1.
-moe_status run_layer(moe_ctx* c, const moe_layer& L, RowSrc x, int64_t T, int slot, void* y0, int64_t rows0, void* y1,
+// Layer l of `layers` [n] on the batch `x` [T,H]; output rows [0,rows0) -> y0, the rest -> y1.
+moe_status run_layer(moe_ctx* c, const moe_layer* layers, int l, int n, RowSrc x, int64_t T, void* y0, int64_t rows0, void* y1,
                      hipStream_t s)
 {
+    const moe_layer& L = layers[l];
     const moe_config& g = c->cfg;
     const int64_t A = T * g.K;
     // with more than one permutation tile the top-k kernel counts the per-tile expert histograms itself
@@ -205,6 +206,7 @@ moe_status run_layer(moe_ctx* c, const moe_layer& L, RowSrc x, int64_t T, int sl
     hipError_t e;
     const bool small = route_is_small(T, g.E, g.K);
     const bool exact = route_is_exact(g.dtype, T, g.H, g.E, g.K);
+    const int slot = exact ? l % c->digit_slots : 0;
     int32_t* const tile_hist = c->tile_hist + slot * c->slot_words;
     if (small) {
         // (timed as the router's logits; the other two have no launch of their own)
@@ -215,6 +217,14 @@ moe_status run_layer(moe_ctx* c, const moe_layer& L, RowSrc x, int64_t T, int sl
                                c->w, c->offsets, c->perm, c->inv, c->d_active_total, c->d_tickets, s);
     } else {
         Timed t(c, MOE_KERNEL_ROUTER_LOGITS, s);
+        e = hipSuccess;
+        if (exact && slot == 0) {       // the digits of this layer and the next ones
+            RouterWeights w = {};
+            const int here = n - l < c->digit_slots ? n - l : c->digit_slots;
+            for (int i = 0; i < here; ++i) w.p[i] = layers[l + i].w_router;
+            e = launch_router_digits(w, here, g.H, g.E, c->digits, c->digit_forms, c->tile_hist, here * c->slot_words, s);
+        }
+        if (e != hipSuccess) return MOE_ERR_DEVICE;
         if (exact)      // (timed as the router's logits; the top-k has no launch of its own)
             e = launch_route_exact(x, T, g.H, L.w_router, L.router_bias, g.E, g.K, g.renormalize,
                                    c->digits + slot * router_digit_bytes(g.H, g.E), c->digit_forms + slot * router_form_bytes(g.E),
@@ -276,20 +286,11 @@ moe_status run_group(moe_ctx* c, const moe_layer* layers, int n, RowSrc in, int6
 {
     char* cur = static_cast<char*>(c->xa);
     char* nxt = static_cast<char*>(c->xb);
-    const moe_config& g = c->cfg;
-    const int slots = route_is_exact(g.dtype, T, g.H, g.E, g.K) ? c->digit_slots : 0;
     for (int l = 0; l < n; ++l) {
         const RowSrc src = (l == 0) ? in : single_src(cur);
-        const int slot = slots > 0 ? l % slots : 0;
-        if (slots > 0 && slot == 0) {
-            RouterWeights w = {};
-            const int here = n - l < slots ? n - l : slots;
-            for (int i = 0; i < here; ++i) w.p[i] = layers[l + i].w_router;
-            if (launch_router_digits(w, here, g.H, g.E, c->digits, c->digit_forms, c->tile_hist, here * c->slot_words, s) != hipSuccess) return MOE_ERR_DEVICE;
-        }
         moe_status st;
-        if (l + 1 < n) st = run_layer(c, layers[l], src, T, slot, nxt, T, nxt, s);
-        else st = run_layer(c, layers[l], src, T, slot, y0, rows0, y1, s);
+        if (l + 1 < n) st = run_layer(c, layers, l, n, src, T, nxt, T, nxt, s);
+        else st = run_layer(c, layers, l, n, src, T, y0, rows0, y1, s);
         if (st != MOE_OK) return st;
         char* t = cur; cur = nxt; nxt = t;
         c->layer_passes += 1;

@@ -231,6 +231,18 @@ def test_exact_routing_rule(gpu_lib, H, E, T, exact):
     assert ctx.moe_read_kernel_timing("topk")[1] == (0 if exact else 1)
 
 
+# What the timing interface counts in such a pass: one launch a layer for each kernel, the digits with the first layer's logits
+def test_timed_launches_of_a_large_batch(gpu_lib):
+    H, E, K, I, T, n = 2048, 128, 8, 8, 4700, 10
+    w = inputs.Workload("timed", H=H, E=E, K=K, I=I, n_layers=n, D=0, P=T, dtype="bf16", seed=5)
+    layers = [{k: (v.to(DEV) if v is not None else None) for k, v in inputs.make_layer(w, l).items()} for l in range(n)]
+    x = inputs.randn((T, H), 1.0, 5, "x", 0, "bf16").to(DEV)
+    ctx = gpu_lib.Context(H, E, K, I, torch.bfloat16, max_tokens=T, device=DEV)
+    ctx.moe_kernel_timing(list(gpu_lib.KERNELS))
+    ctx.moe_group_forward(layers, None, x)
+    assert [ctx.moe_read_kernel_timing(k)[1] for k in gpu_lib.KERNELS] == [n, 0, n, n, n, n]
+
+
 # ... as part of a pass: the digits of ten layers come in two launches, and the top-k counts the permutation's histograms
 @pytest.mark.parametrize("T", [2300, 4700])
 def test_exact_routing_in_a_group(gpu_lib, T):
