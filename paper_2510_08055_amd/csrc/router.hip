@@ -666,9 +666,9 @@ struct RowRange {
     }
 };
 
-// Lists the strays of a row of scale eb, or marks the row as not held; called by one whole wave, written by its lane 0.  (Rare:
-// short rather than fast.)
-__device__ __forceinline__ void list_strays(const bf16_t* row, int H, int eb, RowForm* form)
+// Lists the strays of a row of scale eb, or marks the row as not held.  Called by one whole wave; lane `owner`, which wrote the form,
+// writes to it.  (Rare: short rather than fast.)
+__device__ __forceinline__ void list_strays(const bf16_t* row, int H, int eb, int owner, RowForm* form)
 {
     const int lane = lane_id();
     int n = 0;
@@ -690,11 +690,11 @@ __device__ __forceinline__ void list_strays(const bf16_t* row, int H, int eb, Ro
             uint32_t bits = (uint32_t)__builtin_amdgcn_readlane((int)mine, from);
 #pragma unroll 1
             for (; bits; bits &= bits - 1, ++n)
-                if (n < kStray && lane == 0) form->stray[n] = (uint32_t)(k0 + from * 8 + __ffs((int)bits) - 1);
+                if (n < kStray && lane == owner) form->stray[n] = (uint32_t)(k0 + from * 8 + __ffs((int)bits) - 1);
             hit &= hit - 1;
         }
     }
-    if (n > kStray && lane == 0) form->eb = -1;
+    if (n > kStray && lane == owner) form->eb = -1;
 }
 
 // The digits of 8 consecutive values: digit p of values 0 .. 3 in d[p][0], of values 4 .. 7 in d[p][1].
@@ -765,7 +765,7 @@ __global__ __launch_bounds__(kPrepThreads) void router_digits_kernel(RouterWeigh
     const int eb = form.eb;
     if (threadIdx.x < 64) {
         if (threadIdx.x == 0) s_form = form;
-        if (strays && eb >= 0) list_strays(row, H, eb, &s_form);
+        if (strays && eb >= 0) list_strays(row, H, eb, 0, &s_form);
         if (threadIdx.x == 0) forms[layer * (int)gridDim.x + e] = s_form;
     }
     const float scale = digit_scale(eb);
@@ -867,7 +867,7 @@ __global__ __launch_bounds__(WE * WK * 64, 2) void route_exact_kernel(
 #pragma unroll 1
         for (; left != 0; left &= left - 1) {
             const int from = __ffsll((long long)left) - 1, r = (tid - lane + from) / W;
-            list_strays(token_row(r), H, __builtin_amdgcn_readlane(f.eb, from), &form[r]);
+            list_strays(token_row(r), H, __builtin_amdgcn_readlane(f.eb, from), from, &form[r]);
         }
     }
     __syncthreads();
