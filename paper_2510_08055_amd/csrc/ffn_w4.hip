@@ -377,8 +377,10 @@ __global__ __launch_bounds__(kW4Waves * 64, 2) void grouped_gemm_w4_kernel(
 // (4 MFMAs behind 16 conversions) and the stage is a chain of dependent waits, so the kernel lives on
 // the number of waves per SIMD (4) and on the length of that chain: every instruction on it costs.
 // The load schedule is therefore fixed, with nothing to keep count of.  Stages are taken in pairs, with one block barrier per pair
-// (one per stage: 32 experts, H = I = 2880, 40 rows each, gate_up 99 us against 97, 128 experts, 8 rows 242 / 239).  The top of pair g,
-// g + 1 issues the activations of stages g + 2 and g + 3 into the slots of the pair before; every stage g issues
+// (gate_up + down, us, one per stage / per pair: 128 experts, H = 2048, I = 768, 2 rows each 85 / 73, 16 rows 89 / 82; 32 experts,
+// 4096 x 2048, 8 rows 95 / 82; 128 experts, 2880 x 2880, 2 rows 293 / 286, 8 rows 338 / 332, 16 rows 361 / 353; only 32 experts of 2880 x 2880 with
+// 4 and 8 rows are faster with one per stage, 92 / 94 and 94 / 97, and from 16 rows on they are level).  The top of pair g, g + 1
+// issues the activations of stages g + 2 and g + 3 into the slots of the pair before; every stage g issues
 // line ((c + g) / 4) + 1 of the rows whose class c has (c + g) % 4 = 0; the start-up issues what stages -3, -2, -1
 // would have.  Past a row's end the rule fetches the row's last line once more (into the line slot the row has left for
 // good), past the last stage the activation load repeats the last stage into a free slot: harmless and served by the
@@ -571,8 +573,9 @@ __global__ __launch_bounds__(kS4Waves * 64, 4) void grouped_gemm_w4_stream_kerne
                 a = a > W_last ? W_last : a;
             }
             const uint32_t to = ldsb + B_BASE + (L & 1) * B_SLOT + (wave * B_LPW + k) * 1024;
-            // (a stream if no other block reads the row: 128 experts, H = I = 2880, 4 rows each, gate_up 241 -> 217 us, 16 rows
-            // 260 -> 254; 32 experts, 8 rows 68 -> 62; the shapes that fetch half lines lose 5 to 12 % by it and stay plain)
+            // (a stream if no other block reads the row; gate_up + down, us, plain / so: 128 experts, H = I = 2880, 2 rows each 314 / 293,
+            // 4 rows 339 / 311, 16 rows 372 / 361; 32 experts, 8 rows 105 / 96; wherever in a line the codes start.  The shapes that
+            // fetch half lines lose 5 to 12 % by it and stay plain; so does line 0 of the start-up.)
             if (tc.alone) load_lds<16, true>(a, to);
             else load_lds<16>(a, to);
         }
