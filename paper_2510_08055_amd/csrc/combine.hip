@@ -93,13 +93,18 @@ __global__ __launch_bounds__(256) void combine_kernel(const YT* __restrict__ y_p
     }
 }
 
-// Expert outputs of more than this are read as a stream: of fewer, the last-level cache (256 MB) still holds most of what the
-// down GEMM has just written.  Behind it, top-8 unless said otherwise, us, plain / stream: H = 2048: 69 MB (2112 tokens) 18.2 / 18.7,
-// 164 MB 38.7 / 38.0, 197 MB 46.8 / 44.3, 273 MB (8320) 67.1 / 59.3; H = 2880, top-4: 96 MB 29.1 / 29.8, 192 MB 55.5 / 51.0;
-// H = 1160: 154 MB 33.2 / 34.4, 297 MB 71 / 60; H = 8200: 84 MB 23.5 / 26.9, 157 MB 35.8 / 38.8, 315 MB 84.7 / 72.5.  On y_perm that is
-// wholly in the cache a stream is up to 25 % slower.  fp32 rows under bf16 output stay plain: a lane reads its 32 bytes of those
-// in two pieces, and a line that is gone between them is fetched twice (33.8 / 48).
+// Are the expert outputs read as a stream?  Where their rows are whole 128-byte lines: the kernel is level up to 100 MB of them and
+// faster beyond (behind the down GEMM, top-8, H = 2048, us, plain / stream: 69 MB (2112 tokens) 18.2 / 18.7, 197 MB 46.8 / 44.3,
+// 273 MB (8320) 67.1 / 59.3), and what it leaves in the caches is worth 5 us of the next layer (2112 tokens, 340 / 335).  Where
+// neighbouring blocks share lines, only if there are more of them than the last-level cache (256 MB) holds: it still has most of
+// what the down GEMM has just written, and a line that is gone between its two readers is fetched twice.  H = 8200: 84 MB
+// 23.5 / 26.9, 157 MB 35.8 / 38.8, 315 MB 84.7 / 72.5; H = 1160: 154 MB 33.2 / 34.4, 297 MB 71 / 60.  fp32 rows under bf16 output stay
+// plain: a lane reads its 32 bytes of those in two pieces (33.8 / 48).
 constexpr int64_t kStreamFrom = (int64_t)160 << 20;
+inline bool combine_streams(const void* y_perm, int64_t row_bytes, int64_t rows)
+{
+    return ((reinterpret_cast<uintptr_t>(y_perm) | (uintptr_t)row_bytes) & 127u) == 0 || row_bytes * rows > kStreamFrom;
+}
 
 hipError_t launch_combine(int dtype, bool y_perm_f32, const void* y_perm, const int32_t* inv, const float* w,
                           bool has_residual, RowSrc residual, int64_t T, int K, int H, void* y0, int64_t rows0, void* y1,
@@ -114,10 +119,10 @@ hipError_t launch_combine(int dtype, bool y_perm_f32, const void* y_perm, const 
     };
     const std::true_type stream;
     const std::false_type plain;
-    const int64_t values = T * K * H;
     if (dtype == MOE_BF16 && y_perm_f32) return go(bf16_t(), float(), plain);
-    if (dtype == MOE_BF16) return values * 2 > kStreamFrom ? go(bf16_t(), bf16_t(), stream) : go(bf16_t(), bf16_t(), plain);
-    return values * 4 > kStreamFrom ? go(float(), float(), stream) : go(float(), float(), plain);
+    if (dtype == MOE_BF16)
+        return combine_streams(y_perm, (int64_t)H * 2, T * K) ? go(bf16_t(), bf16_t(), stream) : go(bf16_t(), bf16_t(), plain);
+    return combine_streams(y_perm, (int64_t)H * 4, T * K) ? go(float(), float(), stream) : go(float(), float(), plain);
 }
 
 }  // namespace moe

@@ -428,8 +428,10 @@ def test_streamed_weight_tiles_inside_a_line(gpu_lib, shape, H, I, rows, off):
     assert torch.equal(ctx.moe_grouped_ffn(x_perm, offsets, moved(L["w_gate_up"]), moved(L["w_down"])), want)
 
 
-# Expert outputs of more than 160 MiB are read as a stream: the same bits as in pieces below that
-@pytest.mark.parametrize("H,K,T,dtype", [(2048, 8, 5120, "bf16"), (2048, 8, 5121, "bf16"), (1160, 7, 11008, "bf16"), (2056, 3, 7000, "f32")])
+# Expert outputs whose rows are not whole lines are read as a stream from 160 MiB on: the same bits as in pieces below that, and as
+# from a copy inside a line for those whose rows are
+@pytest.mark.parametrize("H,K,T,dtype", [(2048, 8, 517, "bf16"), (1160, 7, 10330, "bf16"), (1160, 7, 10331, "bf16"), (2056, 3, 7000, "f32"),
+                                         (96, 3, 77, "f32")])
 def test_streamed_combine(gpu_lib, H, K, T, dtype):
     dt = inputs.torch_dtype(dtype)
     g = torch.Generator(device=DEV).manual_seed(T)
@@ -443,6 +445,8 @@ def test_streamed_combine(gpu_lib, H, K, T, dtype):
     for l, a, b in zip(local, cut, cut[1:]):
         part = ctx.moe_combine(y_perm[a * K:b * K], l, w[a:b], residual=x[a:b])
         assert torch.equal(y[a:b], part)
+    inside = torch.empty(T * K * H + 8, dtype=dt, device=DEV)[8:].view(T * K, H).copy_(y_perm)
+    assert torch.equal(ctx.moe_combine(inside, inv, w, residual=x), y)
     want = (y_perm[inv.long().view(-1)].view(T, K, H).float() * w[:, :, None]).sum(1) + x.float()
     bound = 2.0 ** -8 if dtype == "bf16" else 2.0 ** -20      # one rounding; K + 1 fp32 sums of values up to 2^3
     assert ((y.float() - want).abs() <= bound * (want.abs() + 8)).all()
