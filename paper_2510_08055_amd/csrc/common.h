@@ -90,19 +90,21 @@ hipError_t launch_route_exact(RowSrc x, int64_t T, int H, const void* w_router, 
 // with a block on every unit, and about in proportion to H, while the fp64 pass grows with the 16 x 16 tiles of logits: so the
 // line is a number of logits, at short rows a higher one (the launches' own 20 us).  moe_router_topk, us, fp64 pass / this
 // one with the digits of one layer:
-//   E = 128:  H = 1024: 4000 tokens 31 / 34, 5000 36 / 34;  2048: 3000 40 / 46, 4000 51 / 47, 8320 97 / 64;
-//             4096: 3000 71 / 73, 5000 108 / 88;  16384: 300 56 / 198, 2400 211 / 247, 4800 397 / 297;  512: 5000 25 / 29, 8200 37 / 34
-//   E = 96:   2048: 4000 41 / 46, 5000 50 / 47        E = 64:   2048: 5000 35 / 40, 8200 55 / 50;  16384: 577 55 / 156, 8320 366 / 358
-//   E = 48:   2048: 8200 45 / 49, 12000 56 / 54       E = 32 and less (one group of experts to a block): 2048: 16384 50 / 53,
-//             32768 93 / 86;  4096: 16384 89 / 106, 32768 170 / 170
-constexpr int kExactMaxH = 16384, kExactMinExperts = 33, kExactMaxExperts = 128;
+//   E = 128:  H = 512: 3000 tokens 19 / 21, 4100 23 / 22;  1024: 2500 23 / 25, 3500 28 / 27;  2048: 2500 36 / 37, 4100 55 / 36,
+//             8200 97 / 52;  2880: 3000 53 / 56, 3500 59 / 52;  4096: 2500 61 / 65, 4100 98 / 71;  8192: 3000 128 / 123;
+//             16384: 300 56 / 198, 2500 207 / 249, 3500 281 / 262
+//   E = 96:   2048: 3000 35 / 36, 4100 45 / 35;  8192: 4100 146 / 142;  16384: 4100 281 / 303
+//   E = 64:   512: 8200 24 / 24;  2048: 5000 35 / 38, 6500 45 / 37;  4096: 6500 78 / 74;  16384: 577 55 / 156
+//   E = 48 (a fourth of the MFMAs for nothing): 2048: 8200 46 / 46, 16384 72 / 56;  4096: 8200 78 / 86, 12000 99 / 93
+//   E = 32 and less (one group of experts to a block): 2048: 16384 50 / 53;  4096: 16384 89 / 106, 32768 170 / 170
+constexpr int kExactMaxH = 16384, kExactMinExperts = 49, kExactMaxExperts = 128;
 inline bool route_is_exact(int dtype, int64_t T, int H, int E, int K)
 {
     const int64_t logits = T * ((E + 15) / 16 * 16);
     return dtype == MOE_BF16 && H <= kExactMaxH && E >= kExactMinExperts && E <= kExactMaxExperts && K <= 16 &&
-           (logits - ((int64_t)1 << 19)) * H >= (int64_t)1 << 27;
+           (logits - 425984) * H >= (int64_t)1 << 26;
 }
-static_assert(kSmallTokens * kSmallExperts < 1 << 19, "a batch of the one-launch routing is below the line");
+static_assert(kSmallTokens * kSmallExperts < 425984, "a batch of the one-launch routing is below the line");
 // tile_hist (or NULL): [ceil(T*K / kPermTile), E] counters, already zero, that receive the expert histogram
 hipError_t launch_topk(const double* logits, int64_t T, int E, int K, int renorm, int32_t* idx, float* w,
                        int32_t* tile_hist, hipStream_t s);

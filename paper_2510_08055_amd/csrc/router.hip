@@ -408,14 +408,25 @@ template <int NPL, bool TREE> __device__ __forceinline__ void lane_best(const do
     be = e[0];
 }
 
-// How far the logits of R tokens may be from those of another order of summation (see route_exact_kernel), and what comes of it.
+// How far the logits of R tokens may be from those of the fp64 chain (see route_exact_kernel), and what comes of it.
 struct NoMargin {
     static constexpr bool kCheck = false;
 };
-template <int R> struct Margin {
+template <int R, typename Head> struct Margin {
     static constexpr bool kCheck = true;
-    double off[R];      // a logit z of the token is at most off + 2^-49 |z| from the other one
-    bool sure[R];       // out, the same in all lanes of the row: indices and weights are the same with the other logits
+    Head row[R];
+    const Head* experts;
+    double product[R];      // |x| max |w|
+    double chain_error;     // a logit without its bias is at most chain_error * product from the chain's
+    bool sure[R];           // out, the same in all lanes of the row: indices and weights are the same with the chain's logits
+
+    // May the chain round a logit of token r and expert e: 0 nowhere, 1 where its partial sums meet, 2 anywhere?
+    __device__ __forceinline__ int rounds(int r, int e) const
+    {
+        const Head w = experts[e];
+        const float exact = ldexpf(1.f, 53 + row[r].last + w.last);
+        return row[r].norm * w.norm < exact ? 0 : (row[r].part * w.part < exact ? 1 : 2);
+    }
 };
 
 // Top-k of R tokens by the 16 lanes of a row (c = lane % 16): lane c < K ends with the c-th winner of each and its weight.
@@ -473,7 +484,7 @@ __device__ __forceinline__ void topk_of_rows(const double* const (&z)[R], int E,
         for (int r = 0; r < R; ++r) {
             if constexpr (M::kCheck) {
                 // Each winner ahead of the next by more than both can move.  (A NaN is ahead of nothing.)
-                const double room = 2.0 * margin.off[r] + 0x1p-48 * __builtin_fmax(__builtin_fabs(before_z[r]), __builtin_fabs(bv[r]));
+                const double room = 2.0 * margin.chain_error * margin.product[r] + 0x1p-48 * __builtin_fmax(__builtin_fabs(before_z[r]), __builtin_fabs(bv[r]));
                 if (j > 0 && !(before_z[r] - bv[r] > room)) close[r] = true;
                 before_z[r] = bv[r];
                 if (j == K) continue;
@@ -498,14 +509,18 @@ __device__ __forceinline__ void topk_of_rows(const double* const (&z)[R], int E,
         const double q = p / denom;
         my_w[r] = (float)q;
         if constexpr (M::kCheck) {
-            // Logits that move by d move ln q by at most 2 max(d); the roundings of exp, the sum and the quotient on either side and
-            // (without renormalisation) the 2^-49 |z| of the terms far down come to less than 2^-46.  Is the fp32 weight the same at
-            // both ends?
-            const double rel = 4.0 * margin.off[r] + 0x1p-46 * (1.0 + __builtin_fabs(my_z[r]) + __builtin_fabs(z_max[r]));
-            const bool moves = c < K && !((float)(q - q * rel) == (float)(q + q * rel));
-            const uint32_t of_row = (uint32_t)(__ballot(moves) >> (lane_id() & 48)) & 0xffffu;
-            // (off = 0: a row of zeros or a router of zeros, whose logits are the bias in any order)
-            margin.sure[r] = margin.off[r] == 0.0 || (!close[r] && of_row == 0);
+            // Without a rounding in the K logits q is the same number.  (Without renormalisation it has all E in it.)
+            auto of_row = [](bool p) { return (uint32_t)(__ballot(p) >> (lane_id() & 48)) & 0xffffu; };
+            const int how = renorm ? (c < K ? margin.rounds(r, my_e[r]) : 0) : 2;
+            const uint32_t some = of_row(how > 0), any = of_row(how > 1);
+            const double d = (any != 0 ? margin.chain_error : 8.0 * 1.03 * 0x1p-53) * margin.product[r];
+            // Logits that move by d move ln q by at most 2 d.  The bias moves them by 2^-49 |z|, and the roundings of the differences,
+            // exp, the sum and the quotient, on either side, come to less than 2^-52 (2 |z| + 2 |z_max| + 16).  Is the fp32 weight the
+            // same at both ends?
+            const double rel = 2.0 * d + 0x1p-47 * (1.0 + __builtin_fabs(my_z[r]) + __builtin_fabs(z_max[r]));
+            const uint32_t moves = of_row(c < K && !((float)(q - q * rel) == (float)(q + q * rel)));
+            // (a product of 0: a row of zeros or a router of zeros, whose logits are the bias in any order)
+            margin.sure[r] = margin.product[r] == 0.0 || (!close[r] && (some == 0 || moves == 0));
         }
     }
 }
@@ -578,27 +593,29 @@ __global__ __launch_bounds__(kTopkWaves * 64) void topk_rows_kernel(const double
 //
 // The fp64 pass takes the sums in another order with a rounding at every step, so its logits are not the same bits, and a
 // token must not change its experts or its weights with the size of its batch.  So a token's top-k is taken from these
-// logits only where it is shown to be what the fp64 logits give.  A logit is at most
-//     off = c |x|_2 max_e |w_e|_2,  c = (products of a partial sum + 40) 2^-52
-// from the fp64 one (sum |x w| <= |x| |w|; a unit in the last place for each of the fp64 chain's additions, the 16 partial
-// sums' among them, and for those of the remainders here), plus 2^-49 of itself for those that have the bias in them.  Where two of
-// the first K + 1 logits are closer than that, or a weight so near the middle between two fp32 values that it could round the
-// other way, the token is listed.  So are rows of x that are not held (more than kStray strays, infinities, NaN, a
-// largest value outside 2^-40 .. 2^40), and all of the batch with a row of w_router that is not.  Listed tokens take
-// the fp64 pass (route_listed_kernel), 16 at a time whichever block they come from: one in 1000 of normally distributed
-// tokens at H = 2048, 128 experts.
+// logits only where it is shown to be what the fp64 logits give.  A product is a multiple of 2^l, l the last places of the two
+// rows' smallest values added up, so a sum below 2^(53 + l) is not rounded in any order, and |x|_2 |w|_2 bounds the sums (of all
+// products, or of those of one partial sum of the chain).  The two logits before the bias are then at most this far apart:
+//     0                   where no sum can be rounded: 96 % of the pairs of normally distributed rows at H = 2048,
+//     8 |x| |w| 2^-53     where only those can that add up the 16 partial sums (6 additions on the way to a logit, and 1 rounding here),
+//     off = (products of a partial sum + 40) |x| max |w| 2^-52    else (a unit in the last place for each addition),
+// and the bias rounds either by 2^-53 of itself.  Where two of the first K + 1 logits are closer than that by the last line, or a
+// weight so near the middle between two fp32 values that it could round the other way, the token is listed.  So are rows of
+// x that are not held (more than kStray strays, infinities, NaN, a largest value outside 2^-40 .. 2^40), and all of the batch
+// with a row of w_router that is not.  Listed tokens take the fp64 pass (route_listed_kernel), 16 at a time whichever block
+// they come from: of normally distributed tokens one in 30000 at H = 2048, 128 experts (in 800 by the last line alone).
 //
 // A block takes 32 tokens and all experts, WE groups of 32; its waves are WE x WK: WK shares of the k-range, in each of
 // them one wave per group; the WE waves of a share turn 32 tokens x 64 k-values at a time into digits (whole 128-byte
 // lines, each value once) and hand them to each other through LDS, a step ahead of the MFMAs that use them.  w_router's
 // digits come from a launch of their own (for several layers at once), laid out as the operands' registers.  The logits
 // stay in LDS, where the top-k reads them.
-// Measured, H = 2048, E = 128, top-8: moe_router_topk with the fp64 pass -> this one 60 -> 46 us at 4800 tokens, 97 -> 63 at 8320,
-// of which the digits (of up to 8 layers) 5, this kernel 47, the listed tokens 14.  What bounds it: the MFMAs alone take 10.5 us of
-// the 24 of the k-loop at 8320 tokens; the rest is the 36 KB per step that a compute unit's address unit and L2 deliver (eight
-// loads issued in a row, in place of one by one between the MFMAs, cost 6 us, the branches around four groups of MFMAs in place of
-// one 5 us; the conversions are hidden).
-// Every row listed (more than kStray values below the window in each of them): 143 us in all at 8320 tokens against 97.
+// Measured, H = 2048, E = 128, top-8: moe_router_topk with the fp64 pass -> this one 55 -> 36 us at 4100 tokens, 97 -> 52 at 8200,
+// of which the digits (of up to 8 layers) 5, this kernel 47 (8320 tokens; 44 without the rows' forms and the test of the winners),
+// the empty list 4.5 (with a token on it 14).  What bounds it: the MFMAs alone take 10.5 us of the 24 of the k-loop; the rest is the
+// 36 KB per step that a compute unit's address unit and L2 deliver (eight loads issued in a row, in place of one by one between
+// the MFMAs, cost 6 us, the branches around four groups of MFMAs in place of one 5 us; the conversions are hidden).
+// Every row listed (more than kStray values below the window in each of them): 141 us in all at 8320 tokens against 97.
 // ----------------------------------------------------------------------------------------------
 typedef int i32x4_t __attribute__((ext_vector_type(4)));
 typedef int i32x16_t __attribute__((ext_vector_type(16)));
@@ -607,16 +624,19 @@ typedef __bf16 bf16x2_t __attribute__((ext_vector_type(2)));
 
 constexpr int kDigitK = 64;           // k-values per step: rows are padded to it with zeros
 constexpr int kWindow = 22;           // exponents below the row's largest that the fixed point holds exactly
-constexpr int kStray = 6;             // values of a row that may lie below it
+constexpr int kStray = 4;             // values of a row that may lie below it
 constexpr int kHeld = 40;             // rows whose largest value is in 2^-40 .. 2^40: their squares stay in the fp32 range
 constexpr uint32_t kBalance = 0x80808080u, kNoStray = 0xffffffffu;
 
-// How a row is held: the biased exponent eb of its scale (-1: not at all), its 2-norm (or a little more), and the k-values
-// whose remainders the digits miss.
-struct RowForm {
+// How a row is held: the biased exponent eb of its scale (-1: not at all); its 2-norm and the largest one of the values that belong
+// to one partial sum of the fp64 chain (or a little more); all its values are multiples of 2^last (with strays: some small number).
+struct RowHead {
     int eb;
-    float norm;
-    uint32_t stray[kStray];           // in ascending order, kNoStray past the last
+    float norm, part;
+    int last;
+};
+struct RowForm : RowHead {
+    uint32_t stray[kStray];           // the k-values whose remainders the digits miss, in ascending order, kNoStray past the last
 };
 // 2^(156 - eb); any scale will do for a row that is not held
 __device__ __forceinline__ float digit_scale(int eb) { return __uint_as_float((uint32_t)(283 - (eb < 0 ? 127 : eb)) << 23); }
@@ -624,18 +644,17 @@ __device__ __forceinline__ float digit_scale(int eb) { return __uint_as_float((u
 __device__ __forceinline__ double digit_part(bf16_t v, int eb) { return (double)truncf(bf16_to_f32(v) * digit_scale(eb)) / digit_scale(eb); }
 __device__ __forceinline__ double remainder_part(bf16_t v, int eb) { return (double)bf16_to_f32(v) - digit_part(v, eb); }
 
-// The largest and the smallest non-zero magnitude of a row, as bf16 bits, and its sum of squares, gathered 8 values at a time
-// (zero counts as 0xffff on the small side).
+// The largest and the smallest non-zero magnitude of a row, as bf16 bits, gathered 8 values at a time (zero counts as
+// 0xffff on the small side).
 struct RowRange {
     u16x2_t top, low;
-    float squares;
     __device__ __forceinline__ void clear()
     {
         top = u16x2_t{0, 0};
         low = u16x2_t{0xffff, 0xffff};
-        squares = 0.f;
     }
-    __device__ __forceinline__ void add(const u32x4_t& raw)
+    // returns sum + the squares of the values
+    __device__ __forceinline__ float add(const u32x4_t& raw, float sum)
     {
 #pragma unroll
         for (int i = 0; i < 4; ++i) {
@@ -643,26 +662,33 @@ struct RowRange {
             top = __builtin_elementwise_max(top, m);
             low = __builtin_elementwise_min(low, m - u16x2_t{1, 1});       // zero wraps to 0xffff
             const bf16x2_t v = __builtin_bit_cast(bf16x2_t, raw[i]);
-            squares = __builtin_amdgcn_fdot2_f32_bf16(v, v, squares, false);
+            sum = __builtin_amdgcn_fdot2_f32_bf16(v, v, sum, false);
         }
+        return sum;
     }
-    // Over W neighbouring lanes that hold the row; strays: some value lies below the window.
-    template <int W> __device__ __forceinline__ RowForm form(bool& strays) const
+    // Over W neighbouring lanes that hold the row, of these sums of squares; strays: some value lies below the window.
+    template <int W> __device__ __forceinline__ RowForm form(float squares, float part_squares, bool& strays) const
     {
         int hi = top[0] > top[1] ? top[0] : top[1], lo = low[0] < low[1] ? low[0] : low[1];
-        float sq = squares;
 #pragma unroll
         for (int o = 1; o < W; o <<= 1) {
             const int h2 = __shfl_xor(hi, o, 64), l2 = __shfl_xor(lo, o, 64);
             hi = h2 > hi ? h2 : hi;
             lo = l2 < lo ? l2 : lo;
-            sq += __shfl_xor(sq, o, 64);
         }
         const int eb = hi == 0 ? 127 : hi >> 7;      // (a row of zeros: any)
-        strays = ((lo + 1) >> 7) < eb - kWindow;
+        const int e_low = (lo + 1) >> 7;             // of the smallest value (or 512)
+        strays = e_low < eb - kWindow;
         const bool held = eb >= 127 - kHeld && eb < 127 + kHeld;
         // (the sum of H <= 16384 squares in fp32 is right to a part in 2^9)
-        return RowForm{held ? eb : -1, held ? 1.01f * sqrtf(sq) : 0.f, {kNoStray, kNoStray, kNoStray, kNoStray, kNoStray, kNoStray}};
+        RowForm f;
+        f.eb = held ? eb : -1;
+        f.norm = held ? 1.01f * sqrtf(squares) : 0.f;
+        f.part = held ? 1.01f * sqrtf(part_squares) : 0.f;
+        f.last = strays ? -512 : (hi == 0 ? 0 : e_low - 134);
+#pragma unroll
+        for (int i = 0; i < kStray; ++i) f.stray[i] = kNoStray;
+        return f;
     }
 };
 
@@ -727,7 +753,7 @@ __global__ __launch_bounds__(kPrepThreads) void router_digits_kernel(RouterWeigh
                                                                       int64_t zero_n)
 {
     __shared__ int s_hi[kPrepThreads / 64], s_lo[kPrepThreads / 64];
-    __shared__ float s_sq[kPrepThreads / 64];
+    __shared__ float s_sq[kPrepThreads / 64][16];
     __shared__ RowForm s_form;
     // side job: clear the counters of the layers' routing
     for (int64_t i = ((int64_t)blockIdx.y * gridDim.x + blockIdx.x) * kPrepThreads + threadIdx.x; i < zero_n;
@@ -739,29 +765,36 @@ __global__ __launch_bounds__(kPrepThreads) void router_digits_kernel(RouterWeigh
     const u32x4_t zero = {0, 0, 0, 0};
     RowRange range;
     range.clear();
-    for (int p = threadIdx.x; p < pieces; p += kPrepThreads) range.add(*reinterpret_cast<const u32x4_t*>(row + p * 8));
+    float sq = 0.f;                      // all of one partial sum: piece p is of chunk p / 4, which is of partial sum p / 4 % 16
+    static_assert(kPrepThreads == 128, "two waves' ranges meet here; a thread's pieces are 32 chunks apart");
+    for (int p = threadIdx.x; p < pieces; p += kPrepThreads) sq = range.add(*reinterpret_cast<const u32x4_t*>(row + p * 8), sq);
     int hi = range.top[0] > range.top[1] ? range.top[0] : range.top[1];
     int lo = range.low[0] < range.low[1] ? range.low[0] : range.low[1];
-    float sq = range.squares;
 #pragma unroll
     for (int o = 1; o < 64; o <<= 1) {
         const int h2 = __shfl_xor(hi, o, 64), l2 = __shfl_xor(lo, o, 64);
         hi = h2 > hi ? h2 : hi;
         lo = l2 < lo ? l2 : lo;
-        sq += __shfl_xor(sq, o, 64);
     }
+    sq += __shfl_xor(sq, 1, 64);
+    sq += __shfl_xor(sq, 2, 64);
+    if ((threadIdx.x & 3) == 0) s_sq[threadIdx.x >> 6][(threadIdx.x & 63) >> 2] = sq;
     if ((threadIdx.x & 63) == 0) {
         s_hi[threadIdx.x >> 6] = hi;
         s_lo[threadIdx.x >> 6] = lo;
-        s_sq[threadIdx.x >> 6] = sq;
     }
     __syncthreads();
-    static_assert(kPrepThreads == 128, "two waves' ranges meet here");
     range.top = u16x2_t{(uint16_t)s_hi[0], (uint16_t)s_hi[1]};
     range.low = u16x2_t{(uint16_t)s_lo[0], (uint16_t)s_lo[1]};
-    range.squares = s_sq[0] + s_sq[1];
+    float squares = 0.f, part_squares = 0.f;
+#pragma unroll
+    for (int p = 0; p < 16; ++p) {
+        const float of_p = s_sq[0][p] + s_sq[1][p];
+        squares += of_p;
+        part_squares = of_p > part_squares ? of_p : part_squares;
+    }
     bool strays;
-    const RowForm form = range.form<1>(strays);
+    const RowForm form = range.form<1>(squares, part_squares, strays);
     const int eb = form.eb;
     if (threadIdx.x < 64) {
         if (threadIdx.x == 0) s_form = form;
@@ -811,6 +844,7 @@ __global__ __launch_bounds__(WE * WK * 64, 2) void route_exact_kernel(
     constexpr int LDS = SUMS > WK * SHARE ? SUMS : WK * SHARE;
     __shared__ __attribute__((aligned(16))) uint8_t lds[LDS > LOGITS ? LDS : LOGITS];
     __shared__ RowForm form[32];                 // of the token rows
+    __shared__ RowHead head[WE * 32];            // of the experts
     __shared__ int32_t hist[2][WE * 32];
     const int tid = threadIdx.x, lane = tid & 63;
     const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
@@ -836,18 +870,22 @@ __global__ __launch_bounds__(WE * WK * 64, 2) void route_exact_kernel(
     };
 
     // ---- the form of the token rows: NT / 32 neighbouring lanes per row (the experts' forms come in meanwhile) ----
-    struct EbNorm {
-        int eb;
-        float norm;
-    };
-    auto expert_form = [&](int e) { return *reinterpret_cast<const EbNorm*>(forms + (e < E ? e : E - 1)); };
-    const EbNorm form_a = expert_form(lane), form_b = expert_form(lane + 64);
+    const RowHead form_a = forms[lane < E ? lane : E - 1], form_b = forms[lane + 64 < E ? lane + 64 : E - 1];
+    if (wave == 0) {
+        head[lane] = form_a;
+        if (WE > 2) head[lane + 64] = form_b;
+    }
     for (int i = tid; i < 2 * WE * 32; i += NT) (&hist[0][0])[i] = 0;
     {
         constexpr int W = NT / 32, AHEAD = 8;
+        constexpr int PARTS = 64 / W;            // partial sums a lane's pieces fall into: every PARTS-th piece into the same
+        static_assert(AHEAD % PARTS == 0, "the pieces of a round begin with the same partial sum");
         const bf16_t* row = token_row(tid / W);
         RowRange range;
         range.clear();
+        float sq[PARTS];
+#pragma unroll
+        for (int i = 0; i < PARTS; ++i) sq[i] = 0.f;
 #pragma unroll 1
         for (int p0 = tid % W; p0 < pieces; p0 += AHEAD * W) {
             u32x4_t v[AHEAD];
@@ -857,10 +895,24 @@ __global__ __launch_bounds__(WE * WK * 64, 2) void route_exact_kernel(
                 v[i] = *reinterpret_cast<const u32x4_t*>(row + p * 8);
             }
 #pragma unroll
-            for (int i = 0; i < AHEAD; ++i) range.add(v[i]);
+            for (int i = 0; i < AHEAD; ++i) sq[i % PARTS] = range.add(v[i], sq[i % PARTS]);
+        }
+        float squares = 0.f, part_squares = 0.f;
+#pragma unroll
+        for (int i = 0; i < PARTS; ++i) {        // four neighbouring lanes have a chunk
+            sq[i] += __shfl_xor(sq[i], 1, 64);
+            sq[i] += __shfl_xor(sq[i], 2, 64);
+            squares += sq[i];
+            part_squares = sq[i] > part_squares ? sq[i] : part_squares;
+        }
+#pragma unroll
+        for (int o = 4; o < W; o <<= 1) {
+            squares += __shfl_xor(squares, o, 64);
+            const float other = __shfl_xor(part_squares, o, 64);
+            part_squares = other > part_squares ? other : part_squares;
         }
         bool strays;
-        const RowForm f = range.form<W>(strays);
+        const RowForm f = range.form<W>(squares, part_squares, strays);
         if (tid % W == 0) form[tid / W] = f;
         // (a row's lanes are neighbours: each wave lists the strays of its own rows)
         unsigned long long left = __ballot(strays && f.eb >= 0 && tid % W == 0);
@@ -889,7 +941,6 @@ __global__ __launch_bounds__(WE * WK * 64, 2) void route_exact_kernel(
         const float other = __shfl_xor(w_norm, o, 64);
         w_norm = other > w_norm ? other : w_norm;
     }
-    const double off_unit = chain_error * (double)w_norm;
 
     // ---- x: load p of this wave covers rows (we + WE p) * 8 .. + 7 of the tile, lane = (row, 16-byte piece of the step) ----
     const int piece = lane & 7;
@@ -1072,15 +1123,18 @@ __global__ __launch_bounds__(WE * WK * 64, 2) void route_exact_kernel(
     const double* zs[AT_ONCE];
     int my_e[AT_ONCE];
     float my_w[AT_ONCE];
-    Margin<AT_ONCE> margin;
+    Margin<AT_ONCE, RowHead> margin;
     bool held[AT_ONCE];
 #pragma unroll
     for (int u = 0; u < AT_ONCE; ++u) {
         const int r = tid / 16 + u * (NT / 16);
         zs[u] = z + r * ZLD;
-        margin.off[u] = off_unit * (double)form[r].norm;
+        margin.row[u] = form[r];
+        margin.product[u] = (double)w_norm * (double)form[r].norm;
         held[u] = form[r].eb >= 0;
     }
+    margin.experts = head;
+    margin.chain_error = chain_error;
     topk_of_rows<WE * 2, AT_ONCE>(zs, E, K, renorm, c, false, my_e, my_w, margin);
 #pragma unroll
     for (int u = 0; u < AT_ONCE; ++u) {
@@ -1350,7 +1404,7 @@ hipError_t launch_route_exact(RowSrc x, int64_t T, int H, const void* w_router, 
         return hipGetLastError();
     };
     using std::integral_constant;
-    if (E <= 64) return go(integral_constant<int, 2>{}, integral_constant<int, 2>{});      // (8192 tokens and more)
+    if (E <= 64) return go(integral_constant<int, 2>{}, integral_constant<int, 2>{});      // (6700 tokens and more)
     // With a block per compute unit at most, twice the waves (registers leave room for two per SIMD either way), us before the
     // check of the winners: 2112 tokens, H = 2048, 128 experts 26.4 against 29.7, 6000 tokens 35 / 37; 8320 tokens, 260 blocks, 53 / 44.
     return tiles <= cus ? go(integral_constant<int, 4>{}, integral_constant<int, 2>{}) : go(integral_constant<int, 4>{}, integral_constant<int, 1>{});

@@ -157,21 +157,24 @@ def _hard_routing(kind, T, H, E, seed):
         x[rows] = 0
         bias[:E // 2] = bias[:E // 2].round(decimals=1)
     elif kind == "strays":        # experts with as many rests as are listed, and one fewer
-        wr[2, :6] = wr[2].abs().max() * 2.0 ** -25 * 1.7
-        wr[E - 1, H - 5:] = wr[E - 1].abs().max() * -(2.0 ** -27) * 1.9
+        wr[2, :4] = wr[2].abs().max() * 2.0 ** -25 * 1.7
+        wr[E - 1, H - 3:] = wr[E - 1].abs().max() * -(2.0 ** -27) * 1.9
     elif kind == "lost_expert":   # with one more; infinite
-        wr[1, :7] = wr[1].abs().max() * 2.0 ** -25 * 1.7
+        wr[1, :5] = wr[1].abs().max() * 2.0 ** -25 * 1.7
     elif kind == "infinite_expert":
         wr[E - 2, 5] = float("inf")
+    elif kind == "wide":          # values over 14 powers of two: sums that are rounded in some places, in all, in none
+        x *= 2.0 ** -torch.randint(0, 15, (T, H), generator=g, device=DEV).float()
+        wr[::2] *= 2.0 ** -torch.randint(0, 15, (E, H), generator=g, device=DEV).float()[::2]
     elif kind == "zero_router":
         wr.zero_()
     return x.bfloat16(), wr.bfloat16(), bias
 
 
 @pytest.mark.parametrize("kind", ["normal", "ties", "outliers", "all_outliers", "not_finite", "masked", "strays", "lost_expert",
-                                  "infinite_expert", "zero_router"])
+                                  "infinite_expert", "zero_router", "wide"])
 @pytest.mark.parametrize("H,E,K,T,renorm", [(2048, 128, 8, 6000, True), (2056, 100, 16, 16421, False), (2880, 64, 4, 17000, True),
-                                            (3080, 33, 3, 16123, False), (1096, 64, 6, 24000, True), (16376, 97, 9, 4800, False)])
+                                            (3080, 50, 3, 12345, False), (1096, 64, 6, 24000, True), (16376, 97, 9, 4800, False)])
 def test_exact_routing_is_the_fp64_pass(gpu_lib, kind, H, E, K, T, renorm):
     x, wr, bias = _hard_routing(kind, T, H, E, 7 * T + H)
     ctx = gpu_lib.Context(H, E, K, 8, torch.bfloat16, max_tokens=T, renormalize=renorm, device=DEV)
@@ -218,9 +221,9 @@ def test_hard_routing_in_a_group(gpu_lib, kind, H, E, K, T):
 
 # Which batches take them: a number of logits, whatever the length of the rows (the top-k then has no launch of its own).
 @pytest.mark.parametrize("H,E,T,exact", [(16384, 64, 577, False), (16384, 128, 300, False), (4096, 128, 1200, False),
-                                         (2880, 32, 17000, False), (2048, 128, 4607, False), (2048, 128, 4608, True),
-                                         (2048, 64, 9215, False), (2048, 64, 9216, True), (256, 40, 21844, False),
-                                         (256, 40, 21846, True)])
+                                         (2880, 48, 17000, False), (2048, 128, 3583, False), (2048, 128, 3584, True),
+                                         (2048, 64, 7167, False), (2048, 64, 7168, True), (256, 50, 10751, False),
+                                         (256, 50, 10752, True)])
 def test_exact_routing_rule(gpu_lib, H, E, T, exact):
     w = inputs.Workload("rule", H=H, E=E, K=2, I=8, n_layers=1, D=0, P=T, dtype="bf16", seed=3)
     L = {k: (v.to(DEV) if v is not None else None) for k, v in inputs.make_layer(w, 0).items()}
