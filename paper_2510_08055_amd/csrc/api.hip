@@ -23,6 +23,7 @@ struct moe_ctx {
     bool tickets_clear;       // cleared in front of every later pass
     bool tickets_clear_now;   // the call in progress finds them clear
     double* logits;
+    double* sums;             // of the one-launch routing
     int32_t *idx, *counts, *offsets, *perm, *inv, *tile_hist;
     float* w;
     uint8_t* digits;          // w_router as digits, of digit_slots layers
@@ -73,7 +74,7 @@ moe_status check_cfg(const moe_config* c)
 }
 
 struct Layout {
-    size_t counters, logits, idx, w, counts, offsets, perm, inv, tile_hist, digits, digit_forms, listed, xa, xb, act, y_perm, total;
+    size_t counters, logits, idx, w, counts, offsets, perm, inv, tile_hist, digits, digit_forms, listed, sums, xa, xb, act, y_perm, total;
     int digit_slots;
     size_t hist_words, slot_words;
 };
@@ -107,6 +108,8 @@ Layout carve(const moe_config& c, int64_t Tm)
     L.digits = take(L.digit_slots * digit_bytes);
     L.digit_forms = take((size_t)L.digit_slots * router_form_bytes(c.E));
     L.listed = take(L.digit_slots > 0 ? (size_t)Tm * 4 : 0);
+    const int64_t small_T = Tm < kSmallTokens ? Tm : kSmallTokens;
+    L.sums = take(route_is_small(small_T, c.E, c.K) ? (size_t)small_T * c.E * kSmallSumBytes : 0);
     L.xa = take((size_t)Tm * c.H * esz);
     L.xb = take((size_t)Tm * c.H * esz);
     L.act = take(Am * c.I * esz * (c.act_split ? 2 : 1));
@@ -213,7 +216,7 @@ moe_status run_layer(moe_ctx* c, const moe_layer* layers, int l, int n, RowSrc x
         e = clear_tickets(c, s);
         if (e != hipSuccess) return MOE_ERR_DEVICE;
         Timed t(c, MOE_KERNEL_ROUTER_LOGITS, s);
-        e = launch_route_small(g.dtype, x, T, g.H, L.w_router, L.router_bias, g.E, g.K, g.renormalize, c->logits, c->idx,
+        e = launch_route_small(g.dtype, x, T, g.H, L.w_router, L.router_bias, g.E, g.K, g.renormalize, c->sums, c->idx,
                                c->w, c->offsets, c->perm, c->inv, c->d_active_total, c->d_tickets, s);
     } else {
         Timed t(c, MOE_KERNEL_ROUTER_LOGITS, s);
@@ -370,6 +373,7 @@ moe_status moe_create(const moe_config* cfg, int64_t max_tokens, void* workspace
     c->digits = reinterpret_cast<uint8_t*>(b + L.digits);
     c->digit_forms = b + L.digit_forms;
     c->listed = reinterpret_cast<int32_t*>(b + L.listed);
+    c->sums = reinterpret_cast<double*>(b + L.sums);
     c->digit_slots = L.digit_slots;
     c->slot_words = (int64_t)L.slot_words;
     c->hist_words = (int64_t)L.hist_words;

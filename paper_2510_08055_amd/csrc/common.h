@@ -4,6 +4,7 @@
 #include <stdint.h>
 
 #include <atomic>
+#include <type_traits>
 
 #include "moe_lp.h"
 
@@ -40,6 +41,28 @@ template <> struct elem<bf16_t> {
 };
 
 __device__ __forceinline__ int lane_id() { return (int)(threadIdx.x & 63); }
+
+typedef __attribute__((address_space(3))) void lds_ptr_t;
+typedef __attribute__((address_space(1))) const void glb_ptr_t;
+
+// Inclusive scan over the wave's lanes in six register-to-register steps (row shifts, then the last lane of a row to
+// the next row, then lane 31 to the upper half).
+template <typename V> __device__ __forceinline__ V wave_scan(V v)
+{
+    auto step = [&](auto ctrl, auto row_mask) {
+        const int o = __builtin_amdgcn_update_dpp(0, __builtin_bit_cast(int, v), decltype(ctrl)::value,
+                                                  decltype(row_mask)::value, 0xF, true);
+        v += __builtin_bit_cast(V, o);
+    };
+    using std::integral_constant;
+    step(integral_constant<int, 0x111>{}, integral_constant<int, 0xF>{});      // from 1, 2, 4 and 8 lanes below, within 16
+    step(integral_constant<int, 0x112>{}, integral_constant<int, 0xF>{});
+    step(integral_constant<int, 0x114>{}, integral_constant<int, 0xF>{});
+    step(integral_constant<int, 0x118>{}, integral_constant<int, 0xF>{});
+    step(integral_constant<int, 0x142>{}, integral_constant<int, 0xA>{});      // rows 1 and 3: last lane of the row below
+    step(integral_constant<int, 0x143>{}, integral_constant<int, 0xC>{});      // upper half: lane 31
+    return v;
+}
 
 // A batch of rows that lives in two buffers: rows [0, n0) in p0, the rest in p1 (row t - n0).  The
 // layer-group driver reads the first layer's input straight from x_decode / x_prefill this way instead
@@ -110,9 +133,10 @@ hipError_t launch_topk(const double* logits, int64_t T, int E, int K, int renorm
                        int32_t* tile_hist, hipStream_t s);
 
 // tickets: kSmallTickets counters, zero before the first launch; every launch leaves them at zero
-constexpr int kSmallTickets = 1 + kSmallTokens / 16;
+// sums: scratch of kSmallSumBytes per logit
+constexpr int kSmallTickets = 1 + kSmallTokens / 16, kSmallSumBytes = 32;
 hipError_t launch_route_small(int dtype, RowSrc x, int64_t T, int H, const void* w_router, const float* bias, int E, int K,
-                              int renorm, double* logits, int32_t* idx, float* w, int32_t* offsets, int32_t* perm, int32_t* inv,
+                              int renorm, double* sums, int32_t* idx, float* w, int32_t* offsets, int32_t* perm, int32_t* inv,
                               unsigned long long* active_total, uint32_t* tickets, hipStream_t s);
 
 // permute.hip

@@ -12,24 +12,6 @@ constexpr int kBigRows = 256, kBigBN = 256, kBigWaves = 8, kBigMinHeight = 4;
 // (epilogue, change of tile); the rest are waits inside the k-loop that the MFMAs of the blocks do not cover.
 __device__ __forceinline__ float big_tile_fixed(int nk) { return 48.0f / (float)nk + 0.35f; }
 
-// Inclusive scan over the wave's lanes in six register-to-register steps (row shifts, then the last lane of a row to
-// the next row, then lane 31 to the upper half).
-template <typename V> __device__ __forceinline__ V wave_scan(V v)
-{
-    auto step = [&](auto ctrl, auto row_mask) {
-        const int o = __builtin_amdgcn_update_dpp(0, __builtin_bit_cast(int, v), decltype(ctrl)::value,
-                                                  decltype(row_mask)::value, 0xF, true);
-        v += __builtin_bit_cast(V, o);
-    };
-    using std::integral_constant;
-    step(integral_constant<int, 0x111>{}, integral_constant<int, 0xF>{});      // from 1, 2, 4 and 8 lanes below, within 16
-    step(integral_constant<int, 0x112>{}, integral_constant<int, 0xF>{});
-    step(integral_constant<int, 0x114>{}, integral_constant<int, 0xF>{});
-    step(integral_constant<int, 0x118>{}, integral_constant<int, 0xF>{});
-    step(integral_constant<int, 0x142>{}, integral_constant<int, 0xA>{});      // rows 1 and 3: last lane of the row below
-    step(integral_constant<int, 0x143>{}, integral_constant<int, 0xC>{});      // upper half: lane 31
-    return v;
-}
 __device__ __forceinline__ int last_lane(int v) { return __builtin_amdgcn_readlane(v, 63); }
 __device__ __forceinline__ float last_lane(float v)
 {

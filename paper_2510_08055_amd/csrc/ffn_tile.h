@@ -2,8 +2,6 @@
 // the device-side tile search, the SwiGLU epilogue function and the helpers of the direct-to-LDS
 // software pipeline.
 #pragma once
-#include <type_traits>
-
 #include "common.h"
 
 namespace moe {
@@ -136,9 +134,6 @@ __device__ __forceinline__ float opaque(float v)
     asm volatile("" : "+v"(v));
     return v;
 }
-
-typedef __attribute__((address_space(3))) void lds_ptr_t;
-typedef __attribute__((address_space(1))) const void glb_ptr_t;
 
 // Waits and barriers of the software pipeline are inline asm with a memory clobber: the compiler must
 // not move LDS reads or the direct-to-LDS loads across them (the bare s_barrier intrinsic is not a

@@ -33,6 +33,7 @@ template <> struct vec8<bf16_t> {
     {
         asm volatile("global_load_dwordx4 %0, %1, off" : "=v"(raw) : "v"(p) : "memory");
     }
+    __device__ __forceinline__ void load_lds(const char* p) { raw = *reinterpret_cast<const u32x4_t*>(p); }      // a load's 1 KB apart
     __device__ __forceinline__ void zero() { raw = u32x4_t{0, 0, 0, 0}; }
     __device__ __forceinline__ double get(int j) const
     {
@@ -52,6 +53,11 @@ template <> struct vec8<float> {
     {
         asm volatile("global_load_dwordx4 %0, %1, off" : "=v"(a) : "v"(p) : "memory");
         asm volatile("global_load_dwordx4 %0, %1, off offset:16" : "=v"(b) : "v"(p) : "memory");
+    }
+    __device__ __forceinline__ void load_lds(const char* p)
+    {
+        a = *reinterpret_cast<const f32x4_t*>(p);
+        b = *reinterpret_cast<const f32x4_t*>(p + 1024);
     }
     __device__ __forceinline__ void zero() { a = b = f32x4_t{0.f, 0.f, 0.f, 0.f}; }
     __device__ __forceinline__ double get(int j) const
@@ -92,13 +98,9 @@ __device__ __forceinline__ void wait_ring(vec8<float> (&x)[4], vec8<float> (&w)[
 // One block: a 16-token x 16-expert tile of logits with v_mfma_f64_16x16x4.  The hidden dimension is cut
 // into 32-wide chunks, chunk c belongs to partial sum c % 16, and the 16 partial sums are added in a fixed
 // tree (p, p + 4, p + 8, p + 12 in order for p = 0..3, then those four in order), so the summation order of a
-// logit is fixed by H alone, whichever of the two block shapes computes it:
-//   NW = 4:  wave w holds partial sums w, w + 4, w + 8, w + 12 (four independent MFMA chains).  The shape of the
-//            stand-alone logits kernel (16 waves per block were no faster there at 272 to 640 tokens: 11.5 against
-//            11.9 us and 16.4 against 18.4 us).
-//   NW = 16: one partial sum per wave.  The shape of the one-launch routing of a decode batch, whose few blocks are
-//            a serial chain of load latencies and 64-clock MFMAs: 1 us shorter than with 4 waves at H = 2048, 2 us
-//            at H = 2880.
+// logit is fixed by H alone.  Wave w holds partial sums w, w + 4, w + 8, w + 12: four independent MFMA chains.  (16 waves per
+// block were no faster at 272 to 640 tokens: 11.5 against 11.9 us and 16.4 against 18.4 us.  Decode batches have a kernel of
+// their own, see route_small_kernel, with the same order of summation.)
 // Lane l supplies row (l % 16) of both operands; its quarter q = l / 16 owns the 8 consecutive
 // k-values [c*32 + q*8, c*32 + q*8 + 8) of chunk c and feeds them to 8 successive MFMAs (any fixed
 // pairing of k-slots is a valid summation order).  The raw operands of the next chunks are fetched
@@ -130,17 +132,16 @@ __device__ __forceinline__ bool last_to_arrive(uint32_t* ticket, uint32_t n, int
         *flag = last;
     }
     __syncthreads();
-    return *flag != 0;
+    return __builtin_amdgcn_readfirstlane(*flag) != 0;
 }
 
 // The tile of logits of rows row(0 .. 15) and experts e0 .. e0 + 15, stored by wave 0; every thread of the block calls it.
 // Rows from n_rows on are read and not used.  store(i, j, z) takes the logit z of row i < n_rows and expert e0 + j < E.
-template <typename T, int NW, typename Row, typename Store>
+template <typename T, typename Row, typename Store>
 __device__ __forceinline__ void logits_tile(Row row, int n_rows, int H, const T* __restrict__ wr,
                                             const float* __restrict__ bias, int E, int e0, Store store)
 {
-    constexpr int NACC = 16 / NW;                // partial sums per wave
-    static_assert(NW == 4 || NW == 16, "16 partial sums over 4 or 16 waves");
+    constexpr int NW = 4, NACC = 4;              // waves, partial sums per wave
     __shared__ double part[NW - 1][4][64];       // [wave-1][element v][lane]: a wave's partial sums, already added up
     const int lane = lane_id();
     const int wave = __builtin_amdgcn_readfirstlane((int)(threadIdx.x >> 6));
@@ -225,9 +226,7 @@ __device__ __forceinline__ void logits_tile(Row row, int n_rows, int H, const T*
             double z = 0.0;
 #pragma unroll
             for (int p = 0; p < 4; ++p) {        // partial sums p, p + 4, p + 8, p + 12
-                double s = p == 0 ? mysum[v] : part[p - 1][v][lane];
-#pragma unroll
-                for (int w = p + 4; w < NW; w += 4) s += part[w - 1][v][lane];
+                const double s = p == 0 ? mysum[v] : part[p - 1][v][lane];
                 z = p == 0 ? s : z + s;
             }
             if (v * 4 + q < n_rows) store(v * 4 + q, r, z + b);
@@ -255,7 +254,7 @@ __global__ __launch_bounds__(256) void router_logits_kernel(RowSrc x, int64_t n_
         for (int i = threadIdx.x; i < zero_n; i += 256) zero_buf[i] = 0;
     const int64_t t0 = (int64_t)blockIdx.x * 16;
     const int e0 = (int)blockIdx.y * 16;
-    logits_tile<T, 4>(rows_from<T>(x, t0, n_tok, H), rows_left(t0, n_tok, 16), H, wr, bias, E, e0,
+    logits_tile<T>(rows_from<T>(x, t0, n_tok, H), rows_left(t0, n_tok, 16), H, wr, bias, E, e0,
                       [&](int i, int j, double z) { logits[(t0 + i) * E + e0 + j] = z; });
 }
 
@@ -353,9 +352,9 @@ __global__ __launch_bounds__(kTopkWaves * 64) void topk_kernel(const double* __r
 
 // ----------------------------------------------------------------------------------------------
 // Top-k for K <= 16: one token per 16-lane row, four tokens per wave.  Lane c of a row holds the
-// logits of experts c, c+16, c+32, ...; a round takes the lane's best, then an all-reduce over the
-// row in four DPP steps (lane ^ 1, lane ^ 2, mirror within 8, mirror within 16: register-to-register
-// moves, no LDS), under the same total order (logit desc, index asc), so every lane of the row ends
+// logits of experts c, c+16, c+32, ...; a round takes the row's largest logit and then the lowest index that has it, either an
+// all-reduce over the row in four DPP steps (lane ^ 1, lane ^ 2, mirror within 8, mirror within 16: register-to-register
+// moves, no LDS), which is the same total order (logit desc, index asc); every lane of the row ends
 // with the same winner.  Lane j of the row keeps winner j.
 // ----------------------------------------------------------------------------------------------
 template <int CTRL> __device__ __forceinline__ int dpp_mov(int v)
@@ -368,44 +367,20 @@ template <int CTRL> __device__ __forceinline__ double dpp_mov(double v)
 }
 constexpr int kDppXor1 = 0xB1, kDppXor2 = 0x4E, kDppHalfMirror = 0x141, kDppMirror = 0x140;
 
-template <int CTRL> __device__ __forceinline__ void row_best_step(double& bv, int& be)
-{
-    const double ov = dpp_mov<CTRL>(bv);
-    const int oe = dpp_mov<CTRL>(be);
-    if (before(ov, oe, bv, be)) { bv = ov; be = oe; }
-}
 template <int CTRL> __device__ __forceinline__ double row_sum_step(double v) { return v + dpp_mov<CTRL>(v); }
-
-// The best of a lane's logits, experts c + 16 i; the lower index stays among equal values.  TREE: as a tree over i in place of a
-// chain (shorter, but more instructions: worth it where several tokens share the lanes).  As in the chain, a NaN is best
-// as the first of them and never elsewhere: in the tree the others count as -infinity.
-template <int NPL, bool TREE> __device__ __forceinline__ void lane_best(const double (&v)[NPL], int c, double& bv, int& be)
+template <int CTRL> __device__ __forceinline__ double row_max_step(double v) { return __builtin_fmax(v, dpp_mov<CTRL>(v)); }
+template <int CTRL> __device__ __forceinline__ int row_min_step(int v)
 {
-    if (!TREE) {
-        bv = v[0];
-        be = c;
-#pragma unroll
-        for (int i = 1; i < NPL; ++i)
-            if (v[i] > bv) { bv = v[i]; be = c + 16 * i; }
-        return;
-    }
-    double t[NPL];
-    int e[NPL];
-#pragma unroll
-    for (int i = 0; i < NPL; ++i) {
-        t[i] = i == 0 ? v[i] : __builtin_fmax(v[i], -__builtin_huge_val());
-        e[i] = c + 16 * i;
-    }
-#pragma unroll
-    for (int d = 1; d < NPL; d *= 2)
-#pragma unroll
-        for (int i = 0; i + d < NPL; i += 2 * d)
-            if (t[i + d] > t[i]) {
-                t[i] = t[i + d];
-                e[i] = e[i + d];
-            }
-    bv = t[0];
-    be = e[0];
+    const int o = dpp_mov<CTRL>(v);
+    return o < v ? o : v;
+}
+__device__ __forceinline__ double row_max(double v)
+{
+    return row_max_step<kDppMirror>(row_max_step<kDppHalfMirror>(row_max_step<kDppXor2>(row_max_step<kDppXor1>(v))));
+}
+__device__ __forceinline__ int row_min(int v)
+{
+    return row_min_step<kDppMirror>(row_min_step<kDppHalfMirror>(row_min_step<kDppXor2>(row_min_step<kDppXor1>(v))));
 }
 
 // How far the logits of R tokens may be from those of the fp64 chain (see route_exact_kernel), and what comes of it.
@@ -430,11 +405,11 @@ template <int R, typename Head> struct Margin {
 };
 
 // Top-k of R tokens by the 16 lanes of a row (c = lane % 16): lane c < K ends with the c-th winner of each and its weight.
-// All lanes of the row hold the same z[0 .. R).  (A round is a chain of dependent instructions; two tokens fill its gaps.)
+// logit(r, e): that of token r and expert e < E.  (A round is a chain of dependent instructions; two tokens fill its gaps.)
 // With a margin K must be less than E.
-template <int NPL, int R, typename M>   // logits per lane: experts c + 16 i, i < NPL
-__device__ __forceinline__ void topk_of_rows(const double* const (&z)[R], int E, int K, int renorm, int c, bool shared,
-                                             int (&my_e)[R], float (&my_w)[R], M& margin)
+template <int NPL, int R, typename M, typename Logit>   // logits per lane: experts c + 16 i, i < NPL
+__device__ __forceinline__ void topk_of_rows(Logit logit, int E, int K, int renorm, int c, int (&my_e)[R], float (&my_w)[R],
+                                             M& margin)
 {
     const double NEG = -__builtin_huge_val();
     double v[R][NPL];
@@ -443,7 +418,7 @@ __device__ __forceinline__ void topk_of_rows(const double* const (&z)[R], int E,
 #pragma unroll
         for (int i = 0; i < NPL; ++i) {
             const int e = c + 16 * i;
-            v[r][i] = (e < E) ? (shared ? load_shared(z[r] + e) : z[r][e]) : NEG;
+            v[r][i] = (e < E) ? logit(r, e) : NEG;
         }
     double esum[R];         // only without renormalisation: this lane's share of sum_e exp(z_e - z_max)
     double my_z[R], z_max[R], before_z[R];
@@ -457,18 +432,29 @@ __device__ __forceinline__ void topk_of_rows(const double* const (&z)[R], int E,
     }
     const int rounds = M::kCheck ? K + 1 : K;        // (the last of K + 1: what the K-th winner is ahead of)
     for (int j = 0; j < rounds; ++j) {
+        // The largest logit, then the lowest of the experts that have it: a maximum is one instruction where a comparison
+        // of (value, index) pairs is eight, and it does not wait for a condition.
         double bv[R];
         int be[R];
 #pragma unroll
-        for (int r = 0; r < R; ++r) lane_best<NPL, (R > 1)>(v[r], c, bv[r], be[r]);
+        for (int r = 0; r < R; ++r) {
+            double m[NPL];
 #pragma unroll
-        for (int r = 0; r < R; ++r) row_best_step<kDppXor1>(bv[r], be[r]);
+            for (int i = 0; i < NPL; ++i) m[i] = v[r][i];
 #pragma unroll
-        for (int r = 0; r < R; ++r) row_best_step<kDppXor2>(bv[r], be[r]);
+            for (int d = 1; d < NPL; d *= 2)
 #pragma unroll
-        for (int r = 0; r < R; ++r) row_best_step<kDppHalfMirror>(bv[r], be[r]);
+                for (int i = 0; i + d < NPL; i += 2 * d) m[i] = __builtin_fmax(m[i], m[i + d]);
+            bv[r] = row_max(m[0]);
+        }
 #pragma unroll
-        for (int r = 0; r < R; ++r) row_best_step<kDppMirror>(bv[r], be[r]);
+        for (int r = 0; r < R; ++r) {
+            int e = kMaxExperts;
+#pragma unroll
+            for (int i = NPL - 1; i >= 0; --i) e = v[r][i] == bv[r] ? c + 16 * i : e;
+            e = row_min(e);
+            be[r] = e < E ? e : 0;       // (only if all that is left is NaN)
+        }
         if (j == 0) {
 #pragma unroll
             for (int r = 0; r < R; ++r) {
@@ -490,12 +476,8 @@ __device__ __forceinline__ void topk_of_rows(const double* const (&z)[R], int E,
                 if (j == K) continue;
             }
             if (c == j) { my_z[r] = bv[r]; my_e[r] = be[r]; }
-            if ((be[r] & 15) == c) {
-                const int slot = be[r] >> 4;
 #pragma unroll
-                for (int i = 0; i < NPL; ++i)
-                    if (i == slot) v[r][i] = NEG;
-            }
+            for (int i = 0; i < NPL; ++i) v[r][i] = be[r] == c + 16 * i ? NEG : v[r][i];
         }
     }
 #pragma unroll
@@ -524,14 +506,13 @@ __device__ __forceinline__ void topk_of_rows(const double* const (&z)[R], int E,
         }
     }
 }
-template <int NPL>
-__device__ __forceinline__ void topk_of_row(const double* z, int E, int K, int renorm, int c, bool shared, int& my_e, float& my_w)
+template <int NPL, typename Logit>
+__device__ __forceinline__ void topk_of_row(Logit logit, int E, int K, int renorm, int c, int& my_e, float& my_w)
 {
-    const double* zs[1] = {z};
     int e[1];
     float w[1];
     NoMargin none;
-    topk_of_rows<NPL, 1>(zs, E, K, renorm, c, shared, e, w, none);
+    topk_of_rows<NPL, 1>([&](int, int e) { return logit(e); }, E, K, renorm, c, e, w, none);
     my_e = e[0];
     my_w = w[0];
 }
@@ -558,7 +539,7 @@ __global__ __launch_bounds__(kTopkWaves * 64) void topk_rows_kernel(const double
     const int64_t tl = live ? t : n_tok - 1;      // rows past the end work on a copy of the last token, store nothing
     int my_e;
     float my_w;
-    topk_of_row<NPL>(logits + tl * E, E, K, renorm, c, false, my_e, my_w);
+    topk_of_row<NPL>([&](int e) { return logits[tl * E + e]; }, E, K, renorm, c, my_e, my_w);
     if (live && c < K) {
         idx[t * K + c] = my_e;
         w[t * K + c] = my_w;
@@ -1135,7 +1116,7 @@ __global__ __launch_bounds__(WE * WK * 64, 2) void route_exact_kernel(
     }
     margin.experts = head;
     margin.chain_error = chain_error;
-    topk_of_rows<WE * 2, AT_ONCE>(zs, E, K, renorm, c, false, my_e, my_w, margin);
+    topk_of_rows<WE * 2, AT_ONCE>([&](int u, int e) { return zs[u][e]; }, E, K, renorm, c, my_e, my_w, margin);
 #pragma unroll
     for (int u = 0; u < AT_ONCE; ++u) {
         const int64_t t = t0 + tid / 16 + u * (NT / 16);
@@ -1177,13 +1158,14 @@ __global__ __launch_bounds__(256, 3) void route_listed_kernel(RowSrc x, int H, c
     const int n = *n_listed, e0 = (int)blockIdx.y * 16;
     for (int64_t at = (int64_t)blockIdx.x * 16; at < n; at += (int64_t)gridDim.x * 16) {
         const int rows = rows_left(at, n, 16);
-        logits_tile<bf16_t, 4>([&](int i) { return row_ptr<bf16_t>(x, listed[at + (i < rows ? i : rows - 1)], H); }, rows, H, wr,
+        logits_tile<bf16_t>([&](int i) { return row_ptr<bf16_t>(x, listed[at + (i < rows ? i : rows - 1)], H); }, rows, H, wr,
                                bias, E, e0, [&](int i, int j, double z) { store_shared(logits + (at + i) * E + e0 + j, z); });
         if (last_to_arrive(tickets + at / 16, gridDim.y, &flag)) {
             const int c = (int)threadIdx.x & 15, row = (int)threadIdx.x >> 4;
             int e;
             float wt;
-            topk_of_row<NPL>(logits + (at + (row < rows ? row : rows - 1)) * E, E, K, renorm, c, true, e, wt);
+            const double* z = logits + (at + (row < rows ? row : rows - 1)) * E;
+            topk_of_row<NPL>([&](int e) { return load_shared(z + e); }, E, K, renorm, c, e, wt);
             if (row < rows && c < K) {
                 const int64_t f = (int64_t)listed[at + row] * K + c;
                 idx[f] = e;
@@ -1198,83 +1180,200 @@ __global__ __launch_bounds__(256, 3) void route_listed_kernel(RowSrc x, int H, c
 // ----------------------------------------------------------------------------------------------
 // Router, top-k and permutation of a decode batch (at most kSmallTokens tokens, K <= 16) in one launch.
 //
-// On such a batch the three kernels are a chain of launches with almost nothing in each: one token through
-// E = 128 took 8.1 + 5.0 + 8.9 us, of which the arithmetic is a microsecond.  Here every block computes its
-// tile of logits and takes a ticket of its 16 tokens; the block that draws the last one finds their logits
-// written and does their top-k; of those blocks, the one that draws the last ticket of the batch does the
-// permutation (no block ever waits for another).  A token's experts are distinct as long as K of its logits are finite;
-// the stable rank of an assignment inside its expert is then the number of earlier tokens that chose the expert: one
-// bit per token and expert in LDS, counted with popcounts.  A bit that is set twice (a removed expert and one with a
-// logit of -infinity compare equal, NaN compares with nothing) sends the batch to a count of the earlier assignments
-// one by one.  What crosses between blocks goes past the XCD's caches by itself
-// (store_shared / load_shared): a fence would write back and drop the whole L2, 2 us with a few blocks and 15 us
-// with a hundred.  Every last drawer puts its counter back to zero.
-// Measured (H = 2048, E = 128, top-8; events around the launches, three launches -> one): 1 token 28.9 -> 15.4 us,
-// 32 tokens 29.3 -> 17.8 us, 128 tokens 30.2 -> 19.0 us; 256 tokens at H = 2880, top-4 31.0 -> 20.8 us.  A last
-// block that does the top-k of all tokens was slower from 32 tokens on (26 us; 46 us at 128).
+// On such a batch the three kernels are a chain of launches with almost nothing in each.  Here the blocks of a 16-token tile
+// compute its logits and take a ticket; the one that draws the last finds them written and does the top-k of the tile; of
+// those blocks, the one that draws the last ticket of the batch does the permutation (no block ever waits for another).
+//
+// What bounds it are three chains, one behind the other: the fp64 matrix pipes, instruction fetches, and the trips to the level
+// that all blocks see.  (1) A tile of 16 x 16 logits is H / 4 MFMAs of 64 clocks, whatever the number of tokens, so it is cut into
+// the kClasses sums of four partial sums each that the tree of a logit ends in (see logits_tile), a block each: its four
+// summing waves hold one partial sum each, one to a SIMD.  A class has its own value in memory, [class][token][expert]; who does
+// the top-k adds the four in order, the same bits.  (2) Code that runs once comes in at the speed of its misses, about a
+// microsecond per KB, so loops are kept loops (the operands of a wave's chunks wait in LDS, not in as many registers), and
+// the first of the other waves walks through the top-k once, on whatever the buffers hold, while the sums are formed: its
+// instructions are there when they are needed.  (3) What crosses between blocks goes past the XCD's caches by
+// itself (store_shared, load_shared): a fence would write back and drop the whole L2, 2 us with a few blocks and 15 us with a
+// hundred.  Every last drawer puts its counter back to zero.
+//
+// Measured with clocks in the kernel, us from its start until the sums are stored, the last ticket is drawn, the winners are known, the
+// end; 128 experts, H = 2048, top-8: one token 3.3, 4.0, 6.5, 8.0, 32 tokens 3.7, 4.8, 8.5, 11.2.  With one block to a tile, no walk,
+// unrolled loops and rounds that compare (value, index) pairs: one token 6.5, 7.5, 11, 12.7, 32 tokens 7.9, 8.9, 12.4, 15.6; a pass of
+// four layers over one token 162 us then, 147 now.  256 tokens, H = 2880, top-4, two classes to a block, take 17 us either way.
+//
+// A token's experts are distinct as long as K of its logits are finite; the stable rank of an assignment inside its expert is then the
+// number of earlier tokens that chose the expert: one bit per token and expert in LDS, counted with popcounts.  A bit that is set twice
+// (a removed expert and one with a logit of -infinity compare equal, NaN compares with nothing) sends the batch to a count of
+// the earlier assignments one by one.
 // ----------------------------------------------------------------------------------------------
-constexpr int kSmallWaves = 16;
+constexpr int kClasses = 4;
+static_assert(kSmallSumBytes == kClasses * (int)sizeof(double), "a logit's sums");
+constexpr int kSmallWaves = 8, kSumWaves = 4;
 constexpr int kSmallWords = kSmallTokens / 64;
+
+// One partial sum (p of 16) of a 16 x 16 tile of logits by a wave: chunks p, p + 16, ... of the rows, a group of them at a
+// time.  x_row and w_row: the lane's rows (lane % 16); stage: the wave's LDS, 1 KB per load and chunk of a group.
+template <typename T, int GROUP>
+__device__ __forceinline__ double4_t partial_sum(const T* x_row, const T* w_row, int H, int p, char* stage)
+{
+    constexpr int LOADS = (int)sizeof(T) / 2;        // 16-byte loads for the lane's 8 values of a chunk
+    constexpr int PER = 16 / (int)sizeof(T);         // values in one
+    const int lane = lane_id(), q = lane >> 4;
+    const int n_whole = H / 32, mine = n_whole > p ? (n_whole - p + 15) / 16 : 0;
+    const char* const own = stage + lane * 16;
+    double4_t acc = {0.0, 0.0, 0.0, 0.0};
+    auto multiply = [&](auto value) {        // value(operand, j): the j-th of the lane's 8 values
+#pragma unroll
+        for (int j = 0; j < 8; ++j) acc = __builtin_amdgcn_mfma_f64_16x16x4f64(value(0, j), value(1, j), acc, 0, 0, 0);
+    };
+#pragma unroll 1
+    for (int i0 = 0; i0 < mine; i0 += GROUP) {
+        const int n = mine - i0 < GROUP ? mine - i0 : GROUP;
+#pragma unroll 1
+        for (int i = 0; i < n; ++i) {
+            const int k = (p + 16 * (i0 + i)) * 32 + q * 8;
+#pragma unroll
+            for (int l = 0; l < LOADS; ++l) {
+                char* const to = stage + (i * 2 * LOADS + l) * 1024;
+                __builtin_amdgcn_global_load_lds((glb_ptr_t*)(x_row + k + l * PER), (lds_ptr_t*)to, 16, 0, 0);
+                __builtin_amdgcn_global_load_lds((glb_ptr_t*)(w_row + k + l * PER), (lds_ptr_t*)(to + LOADS * 1024), 16, 0, 0);
+            }
+        }
+        asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
+#pragma unroll 1
+        for (int i = 0; i < n; ++i) {
+            vec8<T> o[2];
+#pragma unroll
+            for (int x = 0; x < 2; ++x) o[x].load_lds(own + (i * 2 + x) * LOADS * 1024);
+            multiply([&](int x, int j) { return o[x].get(j); });
+        }
+        asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");       // (the stage is filled again)
+    }
+    if (H % 32 != 0 && p == n_whole % 16) {      // the row's partial chunk: lanes past the end feed zeros
+        const int k = n_whole * 32 + q * 8;
+        vec8<T> o[2];
+        o[0].zero();
+        o[1].zero();
+        if (k < H) {
+            o[0].load(x_row + k);
+            o[1].load(w_row + k);
+        }
+        multiply([&](int x, int j) { return o[x].get(j); });
+    }
+    return acc;
+}
 
 template <typename T, int NPL>
 __global__ __launch_bounds__(kSmallWaves * 64) void route_small_kernel(
-    RowSrc x, int n_tok, int H, const T* __restrict__ wr, const float* __restrict__ bias, int E, int K, int renorm,
-    double* logits, int32_t* idx, float* __restrict__ w, int32_t* __restrict__ offsets, int32_t* __restrict__ perm,
+    RowSrc x, int n_tok, int H, const T* __restrict__ wr, const float* __restrict__ bias, int E, uint32_t e_inverse, int K,
+    uint32_t k_inverse, int renorm, double* sums, int32_t* idx, float* __restrict__ w, int32_t* __restrict__ offsets, int32_t* __restrict__ perm,
     int32_t* __restrict__ inv, unsigned long long* __restrict__ active_total, uint32_t* tickets)
 {
+    constexpr int NT = kSmallWaves * 64;
+    constexpr int GROUP = 12 / (int)sizeof(T), STAGE = GROUP * (int)sizeof(T) * 1024;      // chunks at a time; their bytes
+    constexpr int ZLD = NPL * 16 + 1;                // logits per token
+    constexpr int LDS = kSumWaves * STAGE > 16 * ZLD * 8 ? kSumWaves * STAGE : 16 * ZLD * 8;
+    __shared__ __attribute__((aligned(1024))) char lds[LDS];               // the summing waves' stages, then the tile's logits
+    double* const z = reinterpret_cast<double*>(lds);
     __shared__ unsigned long long chosen[kSmallExperts][kSmallWords];      // bit t of an expert: token t chose it
     __shared__ int32_t count[kSmallExperts], start[kSmallExperts];
-    __shared__ int32_t own[16 * 16];                                       // the experts of this block's 16 tokens
-    __shared__ uint8_t expert_of[kSmallTokens * 16];                       // only when a token chose an expert twice
+    __shared__ uint8_t expert_of[kSmallTokens * 16];
     __shared__ int32_t flag, twice;
     static_assert(kSmallExperts <= 256, "an expert is one byte of expert_of");
-    const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
-    const int t0 = (int)blockIdx.x * 16;
-    const int e0 = (int)blockIdx.y * 16;
-    logits_tile<T, kSmallWaves>(rows_from<T>(x, t0, n_tok, H), rows_left(t0, n_tok, 16), H, wr, bias, E, e0,
-                                [&](int i, int j, double z) {
-        store_shared(logits + (int64_t)(t0 + i) * E + e0 + j, z);      // (another block of the launch may read it)
-    });
-    for (int i = tid; i < E * kSmallWords; i += kSmallWaves * 64) (&chosen[0][0])[i] = 0ull;
-    if (tid < E) count[tid] = 0;
-    if (tid == 0) twice = 0;
-    if (!last_to_arrive(tickets + 1 + blockIdx.x, gridDim.y, &flag)) return;
-
-    // top-k of this block's 16 tokens: 16 lanes per token, four waves
+    const int tid = threadIdx.x, lane = tid & 63;
+    const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+    const int t0 = (int)blockIdx.x * 16, e0 = (int)blockIdx.y * 16;
+    const int r = lane & 15, q = lane >> 4;
     const bool single = gridDim.x == 1;       // a batch of one token tile: nothing to hand to another block
-    if (wave < 4) {
-        const int c = lane & 15, row = wave * 4 + (lane >> 4);
-        const int t = t0 + row;
-        int e;
-        float wt;
-        topk_of_row<NPL>(logits + (int64_t)(t < n_tok ? t : n_tok - 1) * E, E, K, renorm, c, true, e, wt);
-        if (t < n_tok && c < K) {
-            w[t * K + c] = wt;
-            if (single) own[row * K + c] = e;
-            else store_shared(idx + t * K + c, (int32_t)e);
+    char* const stage = lds + (wave < kSumWaves ? wave * STAGE : 0);
+
+    // Turn 0, of the first wave that has no sums to form: its way through the top-k.  Turn 1: the work.
+    int turn = wave == kSumWaves ? 0 : 1;
+#pragma unroll 1
+    for (;; turn = 1) {
+        asm volatile("" : "+v"(turn));       // (or the compiler would write the top-k down twice)
+        turn = __builtin_amdgcn_readfirstlane(turn);
+        if (turn != 0) {
+            if (wave >= kSumWaves) {
+                for (int i = tid - kSumWaves * 64; i < E * kSmallWords; i += NT - kSumWaves * 64) (&chosen[0][0])[i] = 0ull;
+                if (tid - kSumWaves * 64 < E) count[tid - kSumWaves * 64] = 0;
+                if (tid == kSumWaves * 64) twice = 0;
+            }
+#pragma unroll 1
+            for (int cls = (int)blockIdx.z; cls < kClasses; cls += (int)gridDim.z) {
+                double4_t acc;
+                if (wave < kSumWaves) {
+                    const T* const w_row = wr + (int64_t)(e0 + r < E ? e0 + r : E - 1) * H;      // clamp: loads stay in bounds
+                    acc = partial_sum<T, GROUP>(row_ptr<T>(x, t0 + r < n_tok ? t0 + r : n_tok - 1, H), w_row, H, cls + 4 * wave, stage);
+                    if (wave > 0) {
+#pragma unroll
+                        for (int v = 0; v < 4; ++v) reinterpret_cast<double*>(stage)[v * 64 + lane] = acc[v];
+                    }
+                }
+                __syncthreads();
+                if (wave == 0 && e0 + r < E) {
+                    // D layout of the f64 16x16x4 MFMA: lane l, element v holds row 4*v + l/16 (token), column l % 16 (expert).
+#pragma unroll
+                    for (int v = 0; v < 4; ++v) {
+                        double s = acc[v];
+#pragma unroll
+                        for (int o = 1; o < kSumWaves; ++o) s += reinterpret_cast<const double*>(lds + o * STAGE)[v * 64 + lane];
+                        const int t = t0 + v * 4 + q;
+                        if (t < n_tok) store_shared(sums + ((int64_t)cls * n_tok + t) * E + e0 + r, s);
+                    }
+                }
+                if (cls + (int)gridDim.z < kClasses) __syncthreads();       // the stages are filled again
+            }
+            if (!last_to_arrive(tickets + 1 + blockIdx.x, gridDim.y * gridDim.z, &flag)) return;
+            // The tile's logits: all threads load, whole lines of the four classes.  (Read by the lanes that need them, a 16-lane row
+            // per token, the same bytes took 2.8 us in place of 0.6 to 1.8.)
+            const int rows = n_tok - t0 < 16 ? n_tok - t0 : 16;
+#pragma unroll 4
+            for (int i = tid; i < rows * E; i += NT) {
+                const int row = (int)((uint32_t)i * e_inverse >> 20), e = i - row * E;
+                const double* const from = sums + (int64_t)t0 * E + i;
+                double s[kClasses];
+#pragma unroll
+                for (int c = 0; c < kClasses; ++c) s[c] = load_shared(from + (int64_t)c * n_tok * E);
+                z[row * ZLD + e] = (((s[0] + s[1]) + s[2]) + s[3]) + (bias ? (double)bias[e] : 0.0);
+            }
+            __syncthreads();
         }
+        // top-k of this block's 16 tokens: 16 lanes per token, four waves
+        const int row = (wave & 3) * 4 + q, t = t0 + row;
+        if (turn == 0 || (wave < 4 && t0 + wave * 4 < n_tok)) {
+            int e;
+            float wt;
+            const double* const own = z + (t < n_tok ? row : 0) * ZLD;
+            topk_of_row<NPL>([&](int x) { return own[x]; }, E, turn == 0 ? 1 : K, renorm, r, e, wt);
+            if (turn != 0 && t < n_tok && r < K) {
+                w[t * K + r] = wt;
+                if (single) expert_of[t * K + r] = (uint8_t)e;
+                else store_shared(idx + t * K + r, (int32_t)e);
+            }
+            asm volatile("" ::"v"(e), "v"(wt));
+        }
+        if (turn != 0) break;
     }
     if (single) __syncthreads();
     else if (!last_to_arrive(tickets, gridDim.x, &flag)) return;
 
     const int A = n_tok * K;
-    constexpr int PER = kSmallTokens * 16 / (kSmallWaves * 64);            // assignments per thread, at most
-    int my_e[PER];
+    auto token_of = [&](int f) { return (int)((uint32_t)f * k_inverse >> 16); };      // f / K: k_inverse = ceil(2^16 / K)
+    if (!single) {
+        constexpr int PER = kSmallTokens * 16 / NT;            // assignments per thread, at most
+        int32_t my_e[PER];
 #pragma unroll
-    for (int p = 0; p < PER; ++p) {
-        const int f = p * kSmallWaves * 64 + tid;
-        my_e[p] = -1;
-        if (f < A) my_e[p] = single ? own[f] : load_shared(idx + f);
+        for (int p = 0; p < PER; ++p) my_e[p] = p * NT + tid < A ? load_shared(idx + p * NT + tid) : 0;
+#pragma unroll
+        for (int p = 0; p < PER; ++p) expert_of[p * NT + tid] = (uint8_t)my_e[p];
+        // (a thread reads its own)
     }
-#pragma unroll
-    for (int p = 0; p < PER; ++p) {
-        const int f = p * kSmallWaves * 64 + tid;
-        if (my_e[p] >= 0) {
-            const int t = f / K;
-            const unsigned long long bit = 1ull << (t & 63);
-            if (atomicOr(&chosen[my_e[p]][t >> 6], bit) & bit) twice = 1;
-            atomicAdd(&count[my_e[p]], 1);
-        }
+#pragma unroll 1
+    for (int f = tid; f < A; f += NT) {
+        const int t = token_of(f), e = expert_of[f];
+        const unsigned long long bit = 1ull << (t & 63);
+        if (atomicOr(&chosen[e][t >> 6], bit) & bit) twice = 1;
+        atomicAdd(&count[e], 1);
     }
     __syncthreads();
     // exclusive scan of the expert counts by wave 0: lane l owns experts [4 l, 4 l + 4)
@@ -1286,53 +1385,33 @@ __global__ __launch_bounds__(kSmallWaves * 64) void route_small_kernel(
             const int e = lane * EPL + i;
             cnt[i] = e < E ? count[e] : 0;
             sum += cnt[i];
-            act += cnt[i] > 0;
+            act += (int)__popcll(__ballot(cnt[i] > 0));
         }
-        int incl = sum;
-#pragma unroll
-        for (int off = 1; off < 64; off <<= 1) {
-            const int o = __shfl_up(incl, off, 64);
-            if (lane >= off) incl += o;
-        }
-        int run = incl - sum;
+        int run = wave_scan(sum) - sum;
 #pragma unroll
         for (int i = 0; i < EPL; ++i) {
             const int e = lane * EPL + i;
-            if (e < E) {
-                start[e] = run;
-                offsets[e] = run;
-            }
+            if (e <= E) offsets[e] = run;       // (lanes behind the experts hold the total: the first of them has entry E)
+            if (e < E) start[e] = run;
             run += cnt[i];
         }
-        if (lane == 63) offsets[E] = incl;
-#pragma unroll
-        for (int off = 32; off >= 1; off >>= 1) act += __shfl_xor(act, off, 64);
+        if (lane == 63 && E == kSmallExperts) offsets[E] = run;
         if (lane == 0) atomicAdd(active_total, (unsigned long long)act);
     }
     __syncthreads();
-    const bool recount = twice != 0;
-#pragma unroll
-    for (int p = 0; p < PER; ++p) {
-        const int f = p * kSmallWaves * 64 + tid;
-        const int e = my_e[p];
-        if (e < 0) continue;
-        const int t = f / K;
-        int pos = start[e];
-        for (int j = 0; j <= (t >> 6); ++j) {
-            const unsigned long long m = chosen[e][j];
-            pos += __popcll(j < (t >> 6) ? m : m & ((1ull << (t & 63)) - 1));
-        }
-        if (recount) continue;                // (asked this late: the answer is here when the position is)
-        perm[pos] = f;
-        inv[f] = pos;
-    }
-    if (__builtin_expect(recount, 0)) {
-#pragma unroll
-        for (int p = 0; p < PER; ++p)
-            if (my_e[p] >= 0) expert_of[p * kSmallWaves * 64 + tid] = (uint8_t)my_e[p];
-        __syncthreads();
+    if (__builtin_expect(twice == 0, 1)) {
 #pragma unroll 1
-        for (int f = tid; f < A; f += kSmallWaves * 64) {
+        for (int f = tid; f < A; f += NT) {
+            const int t = token_of(f), e = expert_of[f];
+            int pos = start[e] + (int)__popcll(chosen[e][t >> 6] & ((1ull << (t & 63)) - 1));
+#pragma unroll 1
+            for (int j = 0; j < t >> 6; ++j) pos += (int)__popcll(chosen[e][j]);
+            perm[pos] = f;
+            inv[f] = pos;
+        }
+    } else {
+#pragma unroll 1
+        for (int f = tid; f < A; f += NT) {
             const int e = expert_of[f];
             int pos = start[e];
             for (int g = 0; g < f; ++g) pos += expert_of[g] == e;
@@ -1343,20 +1422,27 @@ __global__ __launch_bounds__(kSmallWaves * 64) void route_small_kernel(
 }
 
 hipError_t launch_route_small(int dtype, RowSrc x, int64_t T, int H, const void* w_router, const float* bias, int E, int K,
-                              int renorm, double* logits, int32_t* idx, float* w, int32_t* offsets, int32_t* perm, int32_t* inv,
+                              int renorm, double* sums, int32_t* idx, float* w, int32_t* offsets, int32_t* perm, int32_t* inv,
                               unsigned long long* active_total, uint32_t* tickets, hipStream_t s)
 {
     if (!route_is_small(T, E, K)) return hipErrorInvalidValue;
-    const dim3 grid((unsigned)((T + 15) / 16), (unsigned)((E + 15) / 16));
-    const int npl = (E + 15) / 16;
+    int cus = 0;
+    const hipError_t err = compute_units(&cus);
+    if (err != hipSuccess) return err;
+    const int npl = (E + 15) / 16, tiles = (int)((T + 15) / 16) * npl;
+    // the classes of a tile share a block where they would not all find a compute unit
+    const dim3 grid((unsigned)((T + 15) / 16), (unsigned)npl, tiles * 4 <= cus ? 4 : tiles * 2 <= cus ? 2 : 1);
+    const uint32_t k_inverse = (65536u + K - 1) / K, e_inverse = ((1u << 20) + E - 1) / E;
+    static_assert(kSmallTokens * 16 * 15 < 65536, "f / K for f < 256 K, K <= 16");
+    static_assert(16 * kSmallExperts * (kSmallExperts - 1) < 1 << 20, "i / E for i < 16 E, E <= 256");
     auto go = [&](auto npl_const) {
         constexpr int NPL = decltype(npl_const)::value;
         if (dtype == MOE_BF16)
             route_small_kernel<bf16_t, NPL><<<grid, kSmallWaves * 64, 0, s>>>(
-                x, (int)T, H, (const bf16_t*)w_router, bias, E, K, renorm, logits, idx, w, offsets, perm, inv, active_total, tickets);
+                x, (int)T, H, (const bf16_t*)w_router, bias, E, e_inverse, K, k_inverse, renorm, sums, idx, w, offsets, perm, inv, active_total, tickets);
         else
             route_small_kernel<float, NPL><<<grid, kSmallWaves * 64, 0, s>>>(
-                x, (int)T, H, (const float*)w_router, bias, E, K, renorm, logits, idx, w, offsets, perm, inv, active_total, tickets);
+                x, (int)T, H, (const float*)w_router, bias, E, e_inverse, K, k_inverse, renorm, sums, idx, w, offsets, perm, inv, active_total, tickets);
         return hipGetLastError();
     };
     if (npl <= 1) return go(std::integral_constant<int, 1>{});

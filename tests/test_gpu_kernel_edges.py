@@ -623,3 +623,24 @@ def test_w4_big_tiles_against_the_oracle(gpu_lib):
     ref, _, _ = oracle.moe_layer(inputs.to_numpy(x), n["w_router"], None, n["w_gate_up"], n["w_down"], K, residual=False,
                                  s_gate_up=n["s_gate_up"], s_down=n["s_down"])
     assert_close(y, ref, "bf16", "w4 big tiles")
+
+
+# The one-launch routing: the four sums of a logit in four blocks, in two, in one (by the number of 16 x 16 tiles; 256 compute
+# units), rows shorter and longer than a wave's stage, with a partial chunk and without, against the separate launches
+@pytest.mark.parametrize("dtype,E,K,H,T", [
+    ("bf16", 16, 4, 40, 1), ("bf16", 128, 8, 2048, 17), ("bf16", 130, 3, 32 * 16 * 6 + 40, 96), ("bf16", 200, 5, 520, 100),
+    ("bf16", 256, 16, 72, 256), ("bf16", 32, 16, 32 * 16 * 12, 15), ("f32", 64, 4, 32 * 16 * 3 + 8, 33), ("f32", 250, 2, 200, 250),
+])
+def test_one_launch_routing_in_one_to_four_blocks(gpu_lib, dtype, E, K, H, T):
+    w = inputs.Workload("one", H=H, E=E, K=K, I=64, n_layers=1, D=T, P=0, dtype=dtype, seed=H + T)
+    L = inputs.make_layer(w, 0, device=DEV)
+    L["router_bias"] = inputs.randn((E,), 0.5, w.seed, "bias", 0, "f32", DEV)
+    dt = inputs.torch_dtype(dtype)
+    for s in range(2):
+        x = inputs.randn((T, H), 1.0, w.seed + s, "x", 0, dtype, DEV)
+        ctx = gpu_lib.Context(H, E, K, 64, dt, max_tokens=T, residual=False, device=DEV, renormalize=bool(s))
+        idx, wt = ctx.moe_router_topk(x, L["w_router"], L["router_bias"])
+        _, offsets, _, inv, x_perm = ctx.moe_permute(x, idx)
+        want = ctx.moe_combine(ctx.moe_grouped_ffn(x_perm, offsets, L["w_gate_up"], L["w_down"]), inv, wt)
+        for _ in range(2):
+            assert torch.equal(ctx.moe_group_forward([L], x, None)[0], want)
