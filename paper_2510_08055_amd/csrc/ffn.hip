@@ -190,7 +190,7 @@ __global__ __launch_bounds__(256) void grouped_gemm_bf16_kernel(
 // their wait, a round trip to L2 at the start of every tile, are left out altogether.
 template <int RBM, int BN, int WM, int NS, int MINW, int NW, bool GATED, bool OUT_F32, bool SPLIT, bool MAPPED>
 __global__ __launch_bounds__(NW * 64, MINW) void grouped_gemm_bf16_pipe_kernel(
-    RowSrc X, int ldx, const int32_t* __restrict__ row_map, int map_div,
+    RowSrc X, int ldx, const int32_t* __restrict__ row_map, int map_div, uint32_t map_magic,
     const int32_t* __restrict__ offsets, int E, const bf16_t* __restrict__ W, int64_t w_expert_stride, int N, int K,
     void* __restrict__ Out_, int ldo, int a_rows)
 {
@@ -294,9 +294,7 @@ __global__ __launch_bounds__(NW * 64, MINW) void grouped_gemm_bf16_pipe_kernel(
 #pragma unroll
         for (int p = 0; p < A_LPW; ++p) {
             asm volatile("" : "+v"(a_row_id[p])::"memory");
-            // a row map holds indices below a_rows; the clamp keeps a bad entry from becoming a wild address
-            int32_t id = a_row_id[p] < 0 ? 0 : a_row_id[p];
-            a_row_id[p] = id < a_rows ? id : a_rows - 1;
+            a_row_id[p] = (int32_t)mapped_row(a_row_id[p], a_rows, map_div, map_magic);
         }
     } else {
 #pragma unroll
@@ -306,8 +304,7 @@ __global__ __launch_bounds__(NW * 64, MINW) void grouped_gemm_bf16_pipe_kernel(
 #pragma unroll
     for (int p = 0; p < A_LPW; ++p) {
         const int tr = (wave + NW * p) * RPL + l_row;      // row inside the tile
-        const int64_t src = MAPPED ? (int64_t)(a_row_id[p] / map_div) : (int64_t)a_row_id[p];
-        a_src[p] = row_ptr<bf16_t>(X, src, ldx) + ((l_chunk ^ swz(tr)) << 3);
+        a_src[p] = row_ptr<bf16_t>(X, (int64_t)a_row_id[p], ldx) + ((l_chunk ^ swz(tr)) << 3);
     }
     // Loads of one stage, cut into KS parts that are issued in the shadow of the MFMAs of the KS
     // k-slices of the stage being multiplied: load q of the step (activation loads first) goes with slice q % KS.
@@ -943,7 +940,7 @@ static hipError_t launch_pipe(RowSrc X, int ldx, const int32_t* row_map, int map
     const int64_t m_tiles_max = (A + BM - 1) / BM + (A < E ? A : E);
     const int64_t grid = ((m_tiles_max * n_tiles + 7) / 8) * 8;
     if (grid >= ((int64_t)1 << 31)) return hipErrorInvalidValue;   // the device-side tile search counts in 32 bits
-    kern<<<(unsigned)grid, NW * 64, lds_bytes, s>>>(X, ldx, row_map, map_div, offsets, E, W, w_expert_stride, N, K, Out,
+    kern<<<(unsigned)grid, NW * 64, lds_bytes, s>>>(X, ldx, row_map, map_div, map_magic_of(map_div), offsets, E, W, w_expert_stride, N, K, Out,
                                                 ldo, (int)A);
     return hipGetLastError();
 }

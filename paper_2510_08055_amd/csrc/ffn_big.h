@@ -286,14 +286,7 @@ template <bool MAPPED> struct BigRows {
         for (int p = 0; p < LPW; ++p) {
             if constexpr (MAPPED) {
                 asm volatile("" : "+v"(row_id[p])::"memory");
-                // a row map holds indices below a_rows; the clamp keeps a bad entry from becoming a wild address
-                uint32_t id = row_id[p] < 0 ? 0u : (uint32_t)row_id[p];
-                id = id < (uint32_t)a_rows ? id : (uint32_t)a_rows - 1;
-                if (map_div > 1) {       // id / map_div: map_magic = ceil(2^32 / map_div) overshoots by at most one
-                    uint32_t q = __umulhi(id, map_magic);
-                    if (q * (uint32_t)map_div > id) q -= 1;
-                    id = q;
-                }
+                const uint32_t id = mapped_row(row_id[p], a_rows, map_div, map_magic);
                 src[p] = reinterpret_cast<const char*>(row_ptr<bf16_t>(X, (int64_t)id, ldx)) + l_chunk;
             } else {
                 int r = (wave + kBigWaves * p) * 8 + l_row;
@@ -330,11 +323,6 @@ inline hipError_t big_grid(int* grid)
 inline bool big_list_fits(int64_t A, int E, int64_t n_tiles)
 {
     return A < ((int64_t)1 << 28) && ((A + 127) / 128 + (A < E ? A : E)) * n_tiles < ((int64_t)1 << 24);
-}
-
-inline uint32_t map_magic_of(int map_div)
-{
-    return map_div > 1 ? (uint32_t)((((uint64_t)1 << 32) + map_div - 1) / map_div) : 0;
 }
 
 }  // namespace moe

@@ -34,10 +34,15 @@ struct TileCoord {
 // Offsets are trusted to be a non-decreasing sequence in [0, max_rows]; they are clamped to that range and
 // negative counts to zero all the same, so that offsets gone wrong (a caller's bug, an uninitialised buffer)
 // give wrong results inside the output's rows, never a store outside them.
-template <int BM>
-__device__ __forceinline__ TileCoord find_tile(const int32_t* __restrict__ offsets, int E, int n_tiles, int max_rows)
+//
+// Every block of a launch runs it before it can load anything, and code that runs once costs its instruction misses, about 1 us
+// per KB: so it is short for up to 128 experts (two to a lane), what a tile needs is taken from its lane as scalars, and an expert
+// with one m-tile needs no division.  Of a block's time at H = 2048, 128 experts, it takes 0.9 us; with eight experts to a lane, shuffles
+// and divisions 1.5 to 2.0.  The two launches of 32 tokens: 111.5 + 58.8 -> 109.4 + 53.4 us; a pass of two layers 406 -> 392, of two 4-bit
+// layers (2880 x 2880, 256 tokens) 726 -> 697, of one fp32 layer of 64 tokens 26.0 -> 24.1.
+template <int BM, int EPL>
+__device__ __forceinline__ TileCoord find_tile_in(const int32_t* __restrict__ offsets, int E, int n_tiles, int max_rows)
 {
-    constexpr int EPL = kMaxExperts / 64;
     const int lane = lane_id();
     int off[EPL + 1];
 #pragma unroll
@@ -54,62 +59,79 @@ __device__ __forceinline__ TileCoord find_tile(const int32_t* __restrict__ offse
         mt[i] = (cnt + BM - 1) / BM;
         sum += mt[i];
     }
-    int incl = sum;
-#pragma unroll
-    for (int o = 1; o < 64; o <<= 1) {
-        const int v = __shfl_up(incl, o, 64);
-        if (lane >= o) incl += v;
-    }
-    const int total = __shfl(incl, 63, 64) * n_tiles;
+    const int incl = wave_scan(sum);
+    const int total = __builtin_amdgcn_readlane(incl, 63) * n_tiles;
     const int chunk = (total + 7) / 8;
     const int slot = blockIdx.x / 8;
     const int logical = (int)(blockIdx.x % 8) * chunk + slot;
     TileCoord tc;
-    tc.valid = __builtin_amdgcn_readfirstlane((slot < chunk) && (logical < total)) != 0;   // uniform: no divergent join below
+    tc.valid = slot < chunk && logical < total;
     tc.expert = 0; tc.row0 = 0; tc.row_end = 0; tc.n_tile = 0; tc.alone = true;
     if (!tc.valid) return tc;
-    // the lane whose experts contain the tile (tiles of an expert: mt_e * n_tiles, n-major), then the
-    // expert among that lane's EPL; the one division happens after the choice
+    // the lane whose experts contain the tile (tiles of an expert: mt_e * n_tiles, n-major), then the expert among that lane's
     const unsigned long long hit = __ballot(logical < incl * n_tiles);
     const int src = __ffsll((long long)hit) - 1;
-    int rem = logical - (incl - sum) * n_tiles;   // meaningful on lane src only
-    int s_e = 0, s_lo = 0, s_hi = 0, s_mt = 1, s_rem = 0;
-    bool found = false;
+    int rem = logical - __builtin_amdgcn_readlane(incl - sum, src) * n_tiles;
+    int lo = __builtin_amdgcn_readlane(off[0], src), hi = lo, m = 0;
 #pragma unroll
     for (int i = 0; i < EPL; ++i) {
-        const int cnt = mt[i] * n_tiles;
-        const bool here = !found && rem < cnt;
-        if (here) {
-            s_e = lane * EPL + i;
-            s_lo = off[i];
-            s_hi = off[i + 1];
-            s_mt = mt[i];
-            s_rem = rem;
-            found = true;
+        const int m_i = __builtin_amdgcn_readlane(mt[i], src), end = __builtin_amdgcn_readlane(off[i + 1], src);
+        if (m == 0) {
+            if (rem < m_i * n_tiles) {
+                m = m_i;
+                hi = end;
+                tc.expert = src * EPL + i;
+            } else {
+                rem -= m_i * n_tiles;
+                lo = end;
+            }
         }
-        rem -= cnt;
     }
-    s_e = __shfl(s_e, src, 64);
-    s_lo = __shfl(s_lo, src, 64);
-    s_hi = __shfl(s_hi, src, 64);
-    s_mt = __shfl(s_mt, src, 64);
-    s_rem = __shfl(s_rem, src, 64);
-    const int n_tile = s_rem / s_mt;
-    const int t = s_rem - n_tile * s_mt;
-    const int rb = (s_hi - s_lo + 31) / 32;                 // 32-row blocks of this expert
-    const int per = (rb + s_mt - 1) / s_mt;                 // row blocks per tile
-    int row0 = s_lo + t * per * 32;
-    int row_end = row0 + per * 32;
-    if (row_end > s_hi) row_end = s_hi;
-    if (row0 > row_end) row0 = row_end;                     // cannot happen: per * (mt - 1) < rb
+    tc.n_tile = rem;
+    tc.row0 = lo;
+    tc.row_end = hi;
+    tc.alone = m == 1;
+    if (!tc.alone) {
+        tc.n_tile = rem / m;
+        const int t = rem - tc.n_tile * m;
+        const int rb = (hi - lo + 31) / 32;                 // 32-row blocks of this expert
+        const int per = (rb + m - 1) / m;                   // row blocks per tile
+        tc.row0 = lo + t * per * 32;
+        tc.row_end = tc.row0 + per * 32;
+        if (tc.row_end > hi) tc.row_end = hi;
+        if (tc.row0 > tc.row_end) tc.row0 = tc.row_end;     // cannot happen: per * (m - 1) < rb
+    }
     // the same in every lane: handed out as scalars, so that what the kernels derive from them (base
     // addresses, row counts, the bookkeeping of the load pipeline) stays in scalar registers
-    tc.expert = __builtin_amdgcn_readfirstlane(s_e);
-    tc.row0 = __builtin_amdgcn_readfirstlane(row0);
-    tc.row_end = __builtin_amdgcn_readfirstlane(row_end);
-    tc.n_tile = __builtin_amdgcn_readfirstlane(n_tile);
-    tc.alone = __builtin_amdgcn_readfirstlane(s_mt) == 1;
+    tc.expert = __builtin_amdgcn_readfirstlane(tc.expert);
+    tc.row0 = __builtin_amdgcn_readfirstlane(tc.row0);
+    tc.row_end = __builtin_amdgcn_readfirstlane(tc.row_end);
+    tc.n_tile = __builtin_amdgcn_readfirstlane(tc.n_tile);
     return tc;
+}
+template <int BM>
+__device__ __forceinline__ TileCoord find_tile(const int32_t* __restrict__ offsets, int E, int n_tiles, int max_rows)
+{
+    if (E <= 128) return find_tile_in<BM, 2>(offsets, E, n_tiles, max_rows);
+    return find_tile_in<BM, kMaxExperts / 64>(offsets, E, n_tiles, max_rows);
+}
+
+// Entry `id` of a row map, below `rows`, as the row it stands for: id / div, with magic = map_magic_of(div).
+__device__ __forceinline__ uint32_t mapped_row(int32_t id, int rows, int div, uint32_t magic)
+{
+    // (a row map holds indices below `rows`; the clamp keeps a bad entry from becoming a wild address)
+    uint32_t r = id < 0 ? 0u : (uint32_t)id;
+    r = r < (uint32_t)rows ? r : (uint32_t)rows - 1;
+    if (div > 1) {       // ceil(2^32 / div) overshoots by at most one
+        uint32_t q = __umulhi(r, magic);
+        if (q * (uint32_t)div > r) q -= 1;
+        r = q;
+    }
+    return r;
+}
+inline uint32_t map_magic_of(int map_div)
+{
+    return map_div > 1 ? (uint32_t)((((uint64_t)1 << 32) + map_div - 1) / map_div) : 0;
 }
 
 // Host side: tiles of `rows` rows a launch is expected to have when its A rows spread evenly over the experts (an

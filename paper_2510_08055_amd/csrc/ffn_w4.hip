@@ -96,7 +96,8 @@ template <int SH> __device__ __forceinline__ float e8m0_byte_to_float(uint32_t w
 // OUT_F32: the output is stored as float (down GEMM of a context that keeps y_perm in fp32).
 template <bool GATED, bool OUT_F32>
 __global__ __launch_bounds__(kW4Waves * 64, 2) void grouped_gemm_w4_kernel(
-    RowSrc X, int ldx, const int32_t* __restrict__ row_map, int map_div, const int32_t* __restrict__ offsets, int E,
+    RowSrc X, int ldx, const int32_t* __restrict__ row_map, int map_div, uint32_t map_magic,
+    const int32_t* __restrict__ offsets, int E,
     const uint8_t* __restrict__ W, const uint8_t* __restrict__ S, int64_t rows_per_expert, int N, int K,
     void* __restrict__ Out_, int ldo, int a_rows)
 {
@@ -142,8 +143,7 @@ __global__ __launch_bounds__(kW4Waves * 64, 2) void grouped_gemm_w4_kernel(
     for (int p = 0; p < A_LPW; ++p) {
         int r = tc.row0 + (wave + NW * p) * 8 + a_lrow;
         if (r >= tc.row_end) r = tc.row_end - 1;
-        int id = row_map ? row_map[r] : r;
-        a_row_id[p] = id < 0 ? 0 : (id < a_rows ? id : a_rows - 1);      // a bad map entry must not become a wild address
+        a_row_id[p] = row_map ? (int32_t)mapped_row(row_map[r], a_rows, map_div, map_magic) : r;
     }
     // weights: the wave's load covers tile rows wave * 32 .. + 31, lane = (row, 16-byte MX block of the stage)
     auto weight_row = [&](int rb) {       // tile row -> row of the expert's weight matrix
@@ -225,8 +225,7 @@ __global__ __launch_bounds__(kW4Waves * 64, 2) void grouped_gemm_w4_kernel(
 #pragma unroll
     for (int p = 0; p < A_LPW; ++p) {
         const int tr = (wave + NW * p) * 8 + a_lrow;
-        const int64_t src = row_map ? (int64_t)(a_row_id[p] / map_div) : (int64_t)a_row_id[p];
-        a_src[p] = row_ptr<bf16_t>(X, src, ldx) + ((a_chunk ^ swz(tr)) << 3);
+        a_src[p] = row_ptr<bf16_t>(X, (int64_t)a_row_id[p], ldx) + ((a_chunk ^ swz(tr)) << 3);
     }
     // A load whose 8 tile rows all lie past the tile's last row is left out (a decode batch puts a
     // handful of rows into a 64-row tile; with 4-bit weights the activation tile would otherwise be most
@@ -408,7 +407,8 @@ __device__ __forceinline__ void settle(u32x4_t& v) { asm volatile("" : "+v"(v)::
 // (second launch bound: waves per SIMD; two blocks of 8 waves per compute unit = 4)
 template <bool GATED, bool ODD, bool OUT_F32>
 __global__ __launch_bounds__(kS4Waves * 64, 4) void grouped_gemm_w4_stream_kernel(
-    RowSrc X, int ldx, const int32_t* __restrict__ row_map, int map_div, const int32_t* __restrict__ offsets, int E,
+    RowSrc X, int ldx, const int32_t* __restrict__ row_map, int map_div, uint32_t map_magic,
+    const int32_t* __restrict__ offsets, int E,
     const uint8_t* __restrict__ W, const uint8_t* __restrict__ S, int64_t rows_per_expert, int N, int K,
     void* __restrict__ Out_, int ldo, int a_rows)
 {
@@ -615,16 +615,12 @@ __global__ __launch_bounds__(kS4Waves * 64, 4) void grouped_gemm_w4_stream_kerne
         // down to this lane's bytes
         wait_vmcnt<B_LPW>();
         asm volatile("" : "+v"(a_row_id)::"memory");
-        {      // a row map holds indices below a_rows; the clamp keeps a bad entry from becoming a wild address
-            int32_t id = a_row_id < 0 ? 0 : a_row_id;
-            id = id < a_rows ? id : a_rows - 1;
-            a_row_id = row_map ? id : a_own;
-        }
+        const uint32_t mapped = mapped_row(a_row_id, a_rows, map_div, map_magic);
+        a_row_id = row_map ? (int32_t)mapped : a_own;
 #pragma unroll
         for (int i = 0; i < 8; ++i) keep_piece(s_raw[i], i < s_row_pieces ? i : s_row_pieces - 1, s_lo[i], s_hi[i]);
         const int tr = wave * 8 + a_lrow;
-        const int64_t src = row_map ? (int64_t)(a_row_id / map_div) : (int64_t)a_row_id;
-        a_src = row_ptr<bf16_t>(X, src, ldx) + ((a_chunk ^ swz(tr)) << 3);
+        a_src = row_ptr<bf16_t>(X, (int64_t)a_row_id, ldx) + ((a_chunk ^ swz(tr)) << 3);
     }
     issue_lines(-3);
     issue_rows(0, 0);
@@ -1153,8 +1149,8 @@ hipError_t launch_w4(int variant, RowSrc X, int ldx, const int32_t* row_map, int
     const int64_t m_tiles_max = (A + tile_rows - 1) / tile_rows + (A < E ? A : E);
     const int64_t grid = ((m_tiles_max * n_tiles + 7) / 8) * 8;
     if (grid >= ((int64_t)1 << 31)) return hipErrorInvalidValue;   // the device-side tile search counts in 32 bits
-    kern<<<(unsigned)grid, (stream ? kS4Waves : kW4Waves) * 64, lds_bytes, s>>>(X, ldx, row_map, map_div, offsets, E, W, S, rows_per_expert, N, K,
-                                                          Out, ldo, (int)A);
+    kern<<<(unsigned)grid, (stream ? kS4Waves : kW4Waves) * 64, lds_bytes, s>>>(X, ldx, row_map, map_div, map_magic_of(map_div), offsets, E, W, S,
+                                                                                  rows_per_expert, N, K, Out, ldo, (int)A);
     return hipGetLastError();
 }
 

@@ -644,3 +644,39 @@ def test_one_launch_routing_in_one_to_four_blocks(gpu_lib, dtype, E, K, H, T):
         want = ctx.moe_combine(ctx.moe_grouped_ffn(x_perm, offsets, L["w_gate_up"], L["w_down"]), inv, wt)
         for _ in range(2):
             assert torch.equal(ctx.moe_group_forward([L], x, None)[0], want)
+
+
+# The search for a block's tile: two experts to a lane and eight, experts without rows at the ends and between, one m-tile and
+# several of each height.  Through the gather of the layer (row map, divided by K) and without.
+@pytest.mark.parametrize("shape", ["small", "few", "tile128"])
+@pytest.mark.parametrize("E,big", [(1, [0]), (2, [1]), (128, [0, 63, 127]), (129, [128]), (130, [1, 64]), (512, [7, 8, 511])])
+def test_tile_search(gpu_lib, shape, E, big):
+    H, I = 64, 72
+    rows = [(e * 7 + 1) % 3 if e % 5 else 0 for e in range(E)]
+    for e in big:
+        rows[e] = 150 + e % 3
+    A = sum(rows)
+    w = inputs.Workload("search", H=H, E=E, K=1, I=I, n_layers=1, D=0, P=A, dtype="bf16", seed=E)
+    L = inputs.make_layer(w, 0)
+    x_perm = inputs.randn((A, H), 1.0, E, "x_perm", 0, "bf16")
+    offsets = torch.tensor(np.concatenate([[0], np.cumsum(rows)]), dtype=torch.int32)
+    ctx = gpu_lib.Context(H, E, 1, I, torch.bfloat16, max_tokens=A, device=DEV)
+    ctx.moe_set_ffn_variant(shape)
+    got = ctx.moe_grouped_ffn(x_perm.to(DEV), offsets.to(DEV), L["w_gate_up"].to(DEV), L["w_down"].to(DEV))
+    assert_close(got, dense_ffn(x_perm, offsets, L, "bf16", E), "bf16", f"search {E} {shape}")
+
+
+@pytest.mark.parametrize("K", [1, 3, 8, 13])
+def test_row_map_division(gpu_lib, K):
+    """The layer's gather (entry / K of the permutation) against rows gathered by the permutation's own call."""
+    E, H, I, T = 16, 64, 64, 300
+    w = inputs.Workload("map", H=H, E=E, K=K, I=I, n_layers=1, D=T, P=0, dtype="bf16", seed=K)
+    L = inputs.make_layer(w, 0, device=DEV)
+    x = inputs.randn((T, H), 1.0, K, "x", 0, "bf16", DEV)
+    ctx = gpu_lib.Context(H, E, K, I, torch.bfloat16, max_tokens=T, residual=False, device=DEV)
+    idx, wt = ctx.moe_router_topk(x, L["w_router"])
+    _, offsets, _, inv, x_perm = ctx.moe_permute(x, idx)
+    for shape in ("small", "few", "tile128"):
+        ctx.moe_set_ffn_variant(shape)
+        want = ctx.moe_combine(ctx.moe_grouped_ffn(x_perm, offsets, L["w_gate_up"], L["w_down"]), inv, wt)
+        assert torch.equal(ctx.moe_group_forward([L], x, None)[0], want)
