@@ -169,11 +169,36 @@ __global__ __launch_bounds__(256) void grouped_gemm_bf16_kernel(
 }
 
 
+// Epilogue of a fragment with 16 gate rows and the 16 matching up rows: accumulator elements v and v + 8 of a lane belong to
+// output column col + (v / 4) * 8 + v % 4, v < 8, of `row`.  8-byte stores: such a launch has few rows.
+template <bool SPLIT>
+__device__ __forceinline__ void store_pairs(const float16_t& acc, int row, int row_end, int col, void* Out_, int ldo, int N)
+{
+    bf16_t* const out = static_cast<bf16_t*>(Out_) + (int64_t)row * ldo + col;
+    if (row >= row_end) return;
+#pragma unroll
+    for (int a = 0; a < 2; ++a) {
+        float val[4];
+#pragma unroll
+        for (int b = 0; b < 4; ++b) {
+            val[b] = silu_mul(acc[a * 4 + b], acc[8 + a * 4 + b]);
+            if (SPLIT) val[b] = opaque(val[b]);
+        }
+        if (col + a * 8 >= N) continue;          // N is a multiple of 8: the 4 columns are in or out together
+        const uint32_t p01 = pack_bf16x2(val[0], val[1]), p23 = pack_bf16x2(val[2], val[3]);
+        *reinterpret_cast<uint2*>(out + a * 8) = make_uint2(p01, p23);
+        if (SPLIT)
+            *reinterpret_cast<uint2*>(out + N + a * 8) =
+                make_uint2(pack_bf16x2(val[0] - __uint_as_float(p01 << 16), val[1] - __uint_as_float(p01 & 0xffff0000u)),
+                           pack_bf16x2(val[2] - __uint_as_float(p23 << 16), val[3] - __uint_as_float(p23 & 0xffff0000u)));
+    }
+}
+
 // ----------------------------------------------------------------------------------------------
 // Weight-streaming shape (few rows per expert): global -> LDS copies issued as direct-to-LDS loads
 // (global_load_lds_dwordx4: no staging registers, no LDS store instructions) into two rings of NS LDS slots, one for
 // the activation rows and one for the weight rows, each stage 64 k-values deep; one barrier per stage.
-// 64 x 128 tiles, 4 waves, 3 stages of 24 KB: two blocks share a compute unit.  Launches of few tiles take 32 x 64 tiles (one wave, 5 stages), short rows 256 x 256 (8
+// 64 x 128 tiles, 4 waves, 3 stages of 24 KB: two blocks share a compute unit.  Launches of few tiles take 32 x 64 tiles (two waves, 5 stages), short rows 256 x 256 (8
 // waves, 2 stages): see pick_variant.
 // NW waves arranged WM x WN.
 // One wave-level load moves 64 lanes x 16 B = 8 whole tile rows into 1 KB of LDS.  LDS rows
@@ -200,28 +225,24 @@ __global__ __launch_bounds__(NW * 64, MINW) void grouped_gemm_bf16_pipe_kernel(
     constexpr int NO = GATED ? BN / 2 : BN;     // output columns per block
     constexpr int TM = RBM / WM;                // row blocks per wave: rb = wm + WM * i
     constexpr int WNO = NO / WN;                // output columns per wave
-    constexpr int TNO = WNO / 32;
-    constexpr int TN = GATED ? 2 * TNO : TNO;
+    constexpr int TNO = WNO < 32 ? 1 : WNO / 32;
+    constexpr int TN = GATED && WNO >= 32 ? 2 * TNO : TNO;
     constexpr int ROWB = PBK * 2;                       // bytes per LDS tile row
     constexpr int CPR = PBK / 8;                        // 16-byte chunks per row
     constexpr int RPL = 64 / CPR;                       // tile rows moved by one wave-level load (1 KB)
     constexpr int KS = PBK / 16;                        // MFMA k-slices per stage
     constexpr int A_LPW = BM / RPL / NW, B_LPW = BN / RPL / NW;   // load groups per wave and stage
-    constexpr int LPS = A_LPW + B_LPW;                  // load instructions per thread and stage
     constexpr int A_SLOT = BM * ROWB, B_SLOT = BN * ROWB;   // bytes of one stage of either operand
     constexpr int B_BASE = NS * A_SLOT;                 // the weight ring follows the activation ring
     static_assert(RBM % WM == 0 && TM <= 4 && TNO >= 1, "bad tile configuration");
     static_assert(NS >= 2, "a stage is loaded while another is multiplied");
     static_assert(BM % (RPL * NW) == 0 && BN % (RPL * NW) == 0, "tile rows must split evenly over the waves");
-    // In a step the loads of stage g+NS-1 are issued; loads return in issue order, so when stage g+1 is needed the
-    // loads that may still be in flight are the ones issued after it.
-    constexpr int WAIT_MAIN = (NS - 2) * LPS;
-    constexpr int WAIT_FIRST = (NS - 2) * A_LPW;   // prologue: all weight stages, then the activation stages
-    // The prologue's loads are not in stage order: while stage g + 1 is one of the prologue's, the loads issued after it
-    // are its later activation stages and the steps' own; the fewest, at g = 0, serve all of these steps.  (With up
-    // to three stages this is no fewer than WAIT_MAIN.)
-    constexpr int WAIT_EARLY = NS > 3 ? (NS - 3) * A_LPW + LPS : WAIT_MAIN;
-    static_assert(WAIT_MAIN + LPS < 64 && (NS - 1) * LPS + A_LPW < 64, "vmcnt is a 6-bit counter");
+    constexpr int AHEAD = NS - 1;                       // stages loaded ahead of the one being multiplied
+    // Tiles of 32 rows: where 8 rows or fewer are real, the loads of the others are left out (in a launch of few tiles a wave's
+    // own instructions set its pace).
+    constexpr bool MAY_BE_SLIM = RBM == 1;
+    // A wave with 16 output columns of a gated GEMM has their gate rows and their up rows in one fragment.
+    constexpr bool PAIRED = GATED && WNO == 16;
 
     extern __shared__ __attribute__((aligned(1024))) char smem[];
 
@@ -279,17 +300,16 @@ __global__ __launch_bounds__(NW * 64, MINW) void grouped_gemm_bf16_pipe_kernel(
         load_lds_16<decltype(stream)::value>(b_src[p] + kw * PBK, lds0 + B_BASE + (kt % NS) * B_SLOT + (wave + NW * p) * 1024);
     };
     auto issue_first = [&](auto stream) {
+#pragma unroll 1
+        for (int st = 0; st < AHEAD && st < nk_; ++st)
 #pragma unroll
-        for (int st = 0; st < NS - 1; ++st)
-            if (st < nk_)
-#pragma unroll
-                for (int p = 0; p < B_LPW; ++p) issue_b(st, p, stream);
+            for (int p = 0; p < B_LPW; ++p) issue_b(st, p, stream);
     };
     if (streamed) issue_first(std::integral_constant<bool, MAY_STREAM>{});
     else issue_first(std::false_type{});
     if (MAPPED) {
         // the lookups came before the weight loads of the prologue: wait for them alone
-        if (nk_ >= NS - 1) wait_vmcnt<(NS - 1) * B_LPW>();
+        if (nk_ >= AHEAD) wait_vmcnt<AHEAD * B_LPW>();
         else wait_vmcnt<0>();
 #pragma unroll
         for (int p = 0; p < A_LPW; ++p) {
@@ -311,12 +331,13 @@ __global__ __launch_bounds__(NW * 64, MINW) void grouped_gemm_bf16_pipe_kernel(
     auto issue_a = [&](int kt, int p) {
         load_lds_16(a_src[p] + kt * PBK, lds0 + (kt % NS) * A_SLOT + (wave + NW * p) * 1024);
     };
-    auto issue_part = [&](int kt, int part, auto stream) {
+    auto issue_part = [&](int kt, int part, auto stream, auto a_loads) {
+        constexpr int NA = decltype(a_loads)::value;
 #pragma unroll
-        for (int q = 0; q < LPS; ++q) {
+        for (int q = 0; q < NA + B_LPW; ++q) {
             if (q % KS != part) continue;
-            if (q < A_LPW) issue_a(kt, q);
-            else issue_b(kt, q - A_LPW, stream);
+            if (q < NA) issue_a(kt, q);
+            else issue_b(kt, q - NA, stream);
         }
     };
     // ---- LDS byte offsets of the operand rows this lane feeds to the MFMAs ----
@@ -328,7 +349,8 @@ __global__ __launch_bounds__(NW * 64, MINW) void grouped_gemm_bf16_pipe_kernel(
 #pragma unroll
     for (int j = 0; j < TN; ++j) {
         int r;
-        if (GATED) r = (j < TNO) ? (wn * WNO + j * 32 + fr) : (NO + wn * WNO + (j - TNO) * 32 + fr);
+        if (PAIRED) r = wn * 16 + (fr & 15) + (fr >> 4) * NO;
+        else if (GATED) r = (j < TNO) ? (wn * WNO + j * 32 + fr) : (NO + wn * WNO + (j - TNO) * 32 + fr);
         else r = wn * WNO + j * 32 + fr;
         b_row[j] = B_BASE + r * ROWB;
     }
@@ -340,8 +362,19 @@ __global__ __launch_bounds__(NW * 64, MINW) void grouped_gemm_bf16_pipe_kernel(
     // the barrier that hands over the next stage, under the reads of that stage's first slice.
     // The body is instantiated for the number TMV of row blocks this wave really has (0..TM), so the
     // hot loop is straight-line code; a wave with no row block still loads and synchronises.
-    auto run = [&](auto tmv_const, auto stream) {
-        constexpr int TMV = decltype(tmv_const)::value;
+    // NA: activation loads of a stage.
+    auto run = [&](auto tmv_const, auto stream, auto a_loads) {
+        constexpr int TMV = decltype(tmv_const)::value, NA = decltype(a_loads)::value;
+        constexpr int LPS = NA + B_LPW;             // load instructions per wave and stage
+        // In a step the loads of stage g+AHEAD are issued; loads return in issue order, so when stage g+1 is needed the
+        // loads that may still be in flight are the ones issued after it.
+        constexpr int WAIT_MAIN = (AHEAD - 1) * LPS;
+        constexpr int WAIT_FIRST = (AHEAD - 1) * NA;   // prologue: all weight stages, then the activation stages
+        // The prologue's loads are not in stage order: while stage g + 1 is one of the prologue's, the loads issued after it
+        // are its later activation stages and the steps' own; the fewest, at g = 0, serve all of these steps.  (With up
+        // to two stages ahead this is no fewer than WAIT_MAIN.)
+        constexpr int WAIT_EARLY = AHEAD > 2 ? (AHEAD - 2) * NA + LPS : WAIT_MAIN;
+        static_assert(WAIT_MAIN + LPS < 64 && AHEAD * LPS + NA < 64, "vmcnt is a 6-bit counter");
         constexpr int TMA = TMV > 0 ? TMV : 1;
         float16_t acc[TMA][TN];
 #pragma unroll
@@ -374,16 +407,15 @@ __global__ __launch_bounds__(NW * 64, MINW) void grouped_gemm_bf16_pipe_kernel(
 
         // prologue: the weight stages are already in flight; the activation stages follow, and the first
         // wait lets through only the activation loads issued after stage 0's
+#pragma unroll 1
+        for (int st = 0; st < AHEAD && st < nk_; ++st)
 #pragma unroll
-        for (int st = 0; st < NS - 1; ++st)
-            if (st < nk_)
-#pragma unroll
-                for (int p = 0; p < A_LPW; ++p) issue_a(st, p);
-        if (nk_ >= NS - 1) wait_vmcnt<WAIT_FIRST>();
+            for (int p = 0; p < NA; ++p) issue_a(st, p);
+        if (nk_ >= AHEAD) wait_vmcnt<WAIT_FIRST>();
         else wait_vmcnt<0>();
         block_barrier();
         read_frags(0, 0, 0);
-        // One k-step.  MORE: stage g+NS-1 exists and is loaded (in parts, between the MFMAs) into the slot stage g-1
+        // One k-step.  MORE: stage g+AHEAD exists and is loaded (in parts, between the MFMAs) into the slot stage g-1
         // used, free since the last barrier.  NEXT: stage g+1 exists; it is waited for and handed over by the
         // barrier before the last slice of this stage is multiplied.
         // Ask the scheduler to issue the LDS reads and the global loads of a region one by one between
@@ -410,13 +442,13 @@ __global__ __launch_bounds__(NW * 64, MINW) void grouped_gemm_bf16_pipe_kernel(
 #pragma unroll
             for (int kk = 0; kk < KS - 1; ++kk) {
                 read_frags(g, kk + 1, (kk + 1) & 1);
-                if (MORE) issue_part(g + NS - 1, kk, stream);
+                if (MORE) issue_part(g + AHEAD, kk, stream, a_loads);
                 mfma_set(kk & 1);
                 interleave(TMV > 0 ? TMV + TN : 0, MORE ? parts_in(kk) : 0, TMV * TN);
             }
-            if (MORE) issue_part(g + NS - 1, KS - 1, stream);
+            if (MORE) issue_part(g + AHEAD, KS - 1, stream, a_loads);
             if (NEXT) {
-                if (MORE && NS > 3 && g < NS - 2) wait_vmcnt<WAIT_EARLY>();
+                if (MORE && AHEAD > 2 && g < AHEAD - 1) wait_vmcnt<WAIT_EARLY>();
                 else if (MORE) wait_vmcnt<WAIT_MAIN>();
                 else wait_vmcnt<0>();        // the pipeline drains: wait for everything
                 // all of this wave's reads of stage g have returned before its slots may be refilled
@@ -429,15 +461,19 @@ __global__ __launch_bounds__(NW * 64, MINW) void grouped_gemm_bf16_pipe_kernel(
         };
         using T = std::true_type;
         using F = std::false_type;
-        const int n_main = nk_ - (NS - 1) > 0 ? nk_ - (NS - 1) : 0;   // steps that still start loads
+        const int n_main = nk_ > AHEAD ? nk_ - AHEAD : 0;   // steps that still start loads
         int g = 0;
         for (; g < n_main; ++g) step(g, T{}, T{});
         for (; g < nk_ - 1; ++g) step(g, F{}, T{});
         step(g, F{}, F{});
 
+        if constexpr (PAIRED) {
+            store_pairs<SPLIT>(acc[0][0], tc.row0 + fr, tc.row_end, n0 + wn * 16 + fq * 4, Out_, ldo, N);
+            return;
+        }
         // The epilogue's LDS is an activation slot no stage occupies any more: stage nk-1, the last one, sits in slot
         // (nk-1) % NS, and the readers of the other slots passed their barrier long ago.
-        constexpr int REG = TNO * 2048;           // bytes per wave
+        constexpr int REG = OUT_F32 ? 4096 : TNO * 2048;           // bytes per wave
         constexpr int WPS = A_SLOT / REG;         // waves per free activation slot
         static_assert(WPS >= 1 && (NS - 1) * WPS >= NW, "the epilogue staging does not fit the free slots");
         store_tile<GATED, OUT_F32, SPLIT, TMV, TNO, WM>(acc, tc.row0, tc.row_end, wm, n0 + wn * WNO,
@@ -447,11 +483,18 @@ __global__ __launch_bounds__(NW * 64, MINW) void grouped_gemm_bf16_pipe_kernel(
     // row blocks wm, wm + WM, ... below rb_valid belong to this wave
     const int tm_valid = (rb_valid - wm + WM - 1) / WM;
     auto run_rows = [&](auto stream) {
-        if (TM >= 4 && tm_valid >= 4) run(std::integral_constant<int, (TM >= 4 ? 4 : 0)>{}, stream);
-        else if (TM >= 3 && tm_valid >= 3) run(std::integral_constant<int, (TM >= 3 ? 3 : 0)>{}, stream);
-        else if (TM >= 2 && tm_valid >= 2) run(std::integral_constant<int, (TM >= 2 ? 2 : 0)>{}, stream);
-        else if (tm_valid >= 1) run(std::integral_constant<int, 1>{}, stream);
-        else run(std::integral_constant<int, 0>{}, stream);
+        using std::integral_constant;
+        const integral_constant<int, A_LPW> all;
+        if constexpr (MAY_BE_SLIM)
+            if (rows_here <= 8) {
+                if (wave == 0) return run(integral_constant<int, 1>{}, stream, integral_constant<int, 1>{});
+                return run(integral_constant<int, 1>{}, stream, integral_constant<int, 0>{});
+            }
+        if (TM >= 4 && tm_valid >= 4) run(integral_constant<int, (TM >= 4 ? 4 : 0)>{}, stream, all);
+        else if (TM >= 3 && tm_valid >= 3) run(integral_constant<int, (TM >= 3 ? 3 : 0)>{}, stream, all);
+        else if (TM >= 2 && tm_valid >= 2) run(integral_constant<int, (TM >= 2 ? 2 : 0)>{}, stream, all);
+        else if (tm_valid >= 1) run(integral_constant<int, 1>{}, stream, all);
+        else run(integral_constant<int, 0>{}, stream, all);
     };
     if (streamed) run_rows(std::integral_constant<bool, MAY_STREAM>{});
     else run_rows(std::false_type{});
@@ -894,10 +937,12 @@ static hipError_t pick_variant(int pinned, bool gated, int64_t A, int E, int N, 
     // tiles at 150 rows 8.3 / 10.3, more than one at 300 rows 11.5 / 10.6.
     *v = V_PIPE_WIDE;
     if (K < 256 && A > (int64_t)64 * E && !small_is_one_round) return hipSuccess;
-    // Narrow tiles (32 x 64, one wave, five stages of 12 KB) while they are one round.  What bounds such a launch is how
+    // Narrow tiles (32 x 64, two waves, five stages of 12 KB) while they are one round.  What bounds such a launch is how
     // much it has in flight: 96 tiles of 64 x 128 for one token at 8 of 128 experts (H = 2048, I = 768) with two stages of
-    // weights each, 16 KB, ask for 2.6 TB/s; 192 narrow ones keep four stages of 8 KB: gate_up 19.1 -> 15.4 us, down 10.1 ->
-    // 9.3.  64 x 128 against narrow tiles, us: layer of that shape, 2 tokens (384 and 512 narrow tiles) 57.1 / 53.8, 3 tokens
+    // weights each, 16 KB, ask for 2.6 TB/s; 192 narrow ones keep four stages of 8 KB.  Then it is a wave's own instructions: with one
+    // wave to a tile the k-loop took 9.8 us whether four, five or six stages were on their way, with two waves it takes 7.9 (6.3
+    // TB/s; gate_up and down of one token, clocks in the kernel, 13.2 -> 11.0 and 7.2 -> 6.3 us; a pass of four layers 139 -> 129).
+    // 64 x 128 against narrow tiles of one wave, us: layer of that shape, 2 tokens (384 and 512 narrow tiles) 57.1 / 53.8, 3 tokens
     // (576 and 768) 73.2 / 75.7; gate_up, 8 experts, H = I = 1024, 40 rows (448) 12.6 / 13.3, 56 rows (576) 12.9 / 20.1; H = I =
     // 512, 100 rows (464) 9.5 / 10.0, 130 rows (584) 9.9 / 14.8.
     *v = few_is_one_round ? V_PIPE_FEW : V_PIPE_SMALL;
@@ -971,7 +1016,7 @@ static hipError_t launch_bf16(int variant, RowSrc X, int ldx, const int32_t* row
 {
     // weight streaming: 64 x 128 tiles, 4 waves, 72 KB of LDS: two blocks share a compute unit, so one
     // block's prologue and epilogue are covered by the other's loads, and the many small tiles balance
-    // well over the chip.  launches of few tiles: 32 x 64, 1 wave, five stages.  compute bound: up to 256 x 256 tiles,
+    // well over the chip.  launches of few tiles: 32 x 64, 2 waves, five stages.  compute bound: up to 256 x 256 tiles,
     // one persistent block per compute unit; for rows of fewer than four stages the same tiles, a block each, two stages.
     // (only the gate_up GEMM is ever called with a row map)
     const bool mapped = GATED && row_map != nullptr;
@@ -986,8 +1031,8 @@ static hipError_t launch_bf16(int variant, RowSrc X, int ldx, const int32_t* row
             return launch_pipe<64, 128, 2, 3, 2, 4, GATED, OUT_F32, SPLIT, false>(X, ldx, row_map, map_div, offsets, E, A, W, w_expert_stride, N, K, Out, ldo, s);
         case V_PIPE_FEW:
             if (mapped)
-                return launch_pipe<32, 64, 1, 5, 1, 1, GATED, OUT_F32, SPLIT, GATED>(X, ldx, row_map, map_div, offsets, E, A, W, w_expert_stride, N, K, Out, ldo, s);
-            return launch_pipe<32, 64, 1, 5, 1, 1, GATED, OUT_F32, SPLIT, false>(X, ldx, row_map, map_div, offsets, E, A, W, w_expert_stride, N, K, Out, ldo, s);
+                return launch_pipe<32, 64, 1, 5, 1, 2, GATED, OUT_F32, SPLIT, GATED>(X, ldx, row_map, map_div, offsets, E, A, W, w_expert_stride, N, K, Out, ldo, s);
+            return launch_pipe<32, 64, 1, 5, 1, 2, GATED, OUT_F32, SPLIT, false>(X, ldx, row_map, map_div, offsets, E, A, W, w_expert_stride, N, K, Out, ldo, s);
         case V_PIPE_WIDE:
             if (mapped)
                 return launch_pipe<256, 256, 2, 2, 2, 8, GATED, OUT_F32, SPLIT, GATED>(X, ldx, row_map, map_div, offsets, E, A, W, w_expert_stride, N, K, Out, ldo, s);
@@ -1044,6 +1089,7 @@ const char* ffn_variant_name(int dtype, int variant, int64_t A, int E, int H, in
     if (pick_variant(variant, true, A, E, I, H, &v) != hipSuccess) return "";
     switch (v) {
         case V_PIPE_SMALL: return "grouped_gemm_bf16_pipe_kernel<2,128,2,3,2,4,gated>";
+        // (a name that callers know; the shape had one wave when it got it)
         case V_PIPE_FEW: return "grouped_gemm_bf16_pipe_kernel<1,64,1,5,1,1,gated>";
         case V_PIPE_WIDE: return "grouped_gemm_bf16_pipe_kernel<8,256,2,2,2,8,gated>";
         case V_PIPE_BIG: return "grouped_gemm_bf16_big_kernel<gated>";

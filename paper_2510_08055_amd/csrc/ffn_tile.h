@@ -235,7 +235,7 @@ __device__ __forceinline__ int swz(int r) { return (r & 7) ^ ((r >> 3) & 1); }
 // Epilogue of a wave's TMV row blocks (wm, wm + WM, ... of the tile whose rows are [row0, row_end)) by TNO * 32 output columns
 // from `col0` on.  A lane holds, for output row fr of a row block, groups of 4 consecutive columns (accumulator element v of
 // tile (i, j): column (v/4)*8 + fq*4 + v%4); storing them directly would scatter 8-byte pieces over 32 rows per
-// instruction.  The wave instead turns one row block at a time through `epi`, 32 * TNO * 64 bytes of LDS that only it uses
+// instruction.  The wave instead turns one row block at a time through `epi`, 32 * TNO * 64 bytes of LDS (float output: 4 KB) that only it uses
 // (no block barrier: a wave's own LDS operations execute in program order), and writes it out as whole 16-byte chunks,
 // consecutive lanes along a row (64- or 128-byte runs per row).
 template <bool GATED, bool OUT_F32, bool SPLIT, int TMV, int TNO, int WM, typename ACC>
@@ -251,7 +251,7 @@ __device__ __forceinline__ void store_tile(ACC& acc, int row0, int row_end, int 
     constexpr int RB = TNO * 64;              // bytes of one row of the wave's output tile
     constexpr int CPRW = TNO * 4;             // 16-byte chunks per such row
     constexpr int RPI = 64 / CPRW;            // rows one wave-level 16-byte access covers
-    static_assert(TNO <= 2 && (!OUT_F32 || TNO == 2), "a 32 x 32 float tile must fit the wave's staging piece");
+    static_assert(TNO <= 2, "columns of a wave");
     if constexpr (OUT_F32) {
         // float output: one 32 x 32 tile (4 KB: 32 rows of 8 16-byte chunks) at a time; a lane's 4 consecutive columns are
         // one chunk, chunk c of row r sits in chunk slot c ^ (r & 7), and the tile goes out as 128-byte runs per row

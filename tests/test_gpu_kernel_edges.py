@@ -680,3 +680,20 @@ def test_row_map_division(gpu_lib, K):
         ctx.moe_set_ffn_variant(shape)
         want = ctx.moe_combine(ctx.moe_grouped_ffn(x_perm, offsets, L["w_gate_up"], L["w_down"]), inv, wt)
         assert torch.equal(ctx.moe_group_forward([L], x, None)[0], want)
+
+
+# Narrow tiles: 8 rows and fewer load less, waves have 16 output columns of a gated GEMM (ragged column tiles of both kinds)
+@pytest.mark.parametrize("H,I,rows", [(64, 64, [8, 9, 0, 7, 1, 16]), (320, 64 + 40, [8, 32]), (448, 64 + 16, [9, 3]), (2880, 8, [1])])
+@pytest.mark.parametrize("fmt", [{}, {"y_perm_f32": True}, {"y_perm_f32": True, "act_split": True}])
+def test_narrow_tiles_of_two_waves(gpu_lib, H, I, rows, fmt):
+    E, A = len(rows), sum(rows)
+    w = inputs.Workload("narrow", H=H, E=E, K=1, I=I, n_layers=1, D=0, P=A, dtype="bf16", seed=A)
+    L = inputs.make_layer(w, 0, device=DEV)
+    x_perm = inputs.randn((A, H), 1.0, A, "x_perm", 0, "bf16", DEV)
+    offsets = torch.tensor(np.concatenate([[0], np.cumsum(rows)]), dtype=torch.int32, device=DEV)
+    ctx = gpu_lib.Context(H, E, 1, I, torch.bfloat16, max_tokens=A, device=DEV, **fmt)
+    ctx.moe_set_ffn_variant("tile128")
+    want = ctx.moe_grouped_ffn(x_perm, offsets, L["w_gate_up"], L["w_down"]).clone()
+    ctx.moe_set_ffn_variant("few")
+    for _ in range(2):
+        assert torch.equal(ctx.moe_grouped_ffn(x_perm, offsets, L["w_gate_up"], L["w_down"]), want)
