@@ -612,21 +612,22 @@ __global__ __launch_bounds__(kBigWaves * 64, 2) void grouped_gemm_bf16_big_kerne
         for (int kk = 0; kk < KS; ++kk) k_lane[kk] = lds0 + fr * ROWB + (((kk * 2 + fq) ^ swz(fr)) << 4);
         const uint32_t a_wave = wm * 32 * ROWB, b_wave = B_BASE + wn * WNO * ROWB;
 
-        // ---- first tile: two weight stages and one activation stage ----
+        // ---- first tile: its first weight stage, first activation stage and second weight stage, in this order: all units start at
+        // once and wait for what they have asked memory for, so nothing is asked for ahead of what is multiplied first ----
         BigTile cur = queue.take(at), nxt = cur;
         uint32_t a_slot = 0, b_slot = 0;       // slots of the stage being multiplied
         rows.look_up(cur);
         use_weights(cur);
 #pragma unroll
-        for (int st = 0; st < 2; ++st) {
-#pragma unroll
-            for (int p = 0; p < LPW; ++p) issue_b(p, st * SLOT);
-            advance_b(st);
-        }
-        wait_vmcnt<2 * LPW>();                 // the look-ups came before the weight loads
+        for (int p = 0; p < LPW; ++p) issue_b(p, 0);
+        advance_b(0);
+        wait_vmcnt<LPW>();                     // the look-ups came before the weight loads
         rows.use(cur);
         rows.issue(0, lds0);
-        wait_vmcnt<0>();
+#pragma unroll
+        for (int p = 0; p < LPW; ++p) issue_b(p, SLOT);
+        advance_b(1);
+        wait_vmcnt<LPW>();
         block_barrier();
         rows.issue(1, lds0 + SLOT);
 

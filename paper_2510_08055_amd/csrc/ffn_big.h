@@ -18,6 +18,18 @@ __device__ __forceinline__ float last_lane(float v)
     return __builtin_bit_cast(float, __builtin_amdgcn_readlane(__builtin_bit_cast(int, v), 63));
 }
 
+// The largest of the values of 8 neighbouring lanes, in all of them.
+__device__ __forceinline__ float eight_max(float v)
+{
+    auto step = [&](auto ctrl) {
+        v = fmaxf(v, __builtin_bit_cast(float, __builtin_amdgcn_update_dpp(0, __builtin_bit_cast(int, v), decltype(ctrl)::value, 0xF, 0xF, true)));
+    };
+    step(std::integral_constant<int, 0xB1>{});       // lane ^ 1, lane ^ 2, mirrored within 8
+    step(std::integral_constant<int, 0x4E>{});
+    step(std::integral_constant<int, 0x141>{});
+    return v;
+}
+
 struct BigTile {
     int expert, row0, row_end, n_tile;
 };
@@ -34,7 +46,9 @@ __device__ __forceinline__ int div_up(int x, int h, uint32_t inverse) { return (
 //
 // Every block works the list out for itself.  What that costs is instruction fetch (cold straight-line code runs at
 // about 1 KB per us: a first version, unrolled over the 8 experts of a lane, was 11 KB and took 10 us of every
-// launch), hence the loops that are kept loops and the walk over the experts in place of a search.
+// launch), hence the loops that are kept loops and the walk over the experts in place of a search; then trips to memory one
+// behind the other, hence two experts' offsets at a time and the first tile's expert by a scan.  128 experts 3.0 to 3.4 us, 32
+// experts 2.3 (4.2 to 4.5 and 3.0 with a trip per 64 experts, a loop over the heights and a walk to the first tile).
 struct BigQueue {
     const int32_t* offsets;
     int E, max_rows, n_tiles;
@@ -55,7 +69,10 @@ struct BigQueue {
         hi = (int)(uint32_t)(pair >> 32);
         lo = lo < 0 ? 0 : (lo > max_rows ? max_rows : lo);
         hi = hi < lo ? lo : (hi > max_rows ? max_rows : hi);
-        const int rb = (hi - lo + 31) / 32;
+        set_expert((hi - lo + 31) / 32);
+    }
+    __device__ __forceinline__ void set_expert(int rb)
+    {
         mt = div_up(rb, h, h_inv);
         per = mt > 1 ? quotient(rb + mt - 1, mt) : rb;
     }
@@ -89,7 +106,8 @@ struct BigQueue {
         return tile;
     }
 
-    // Every wave of the block calls it, with `scratch` a piece of LDS nothing else uses.  Returns the block's first tile.
+    // Every wave of the block calls it, with `scratch` a piece of LDS nothing else uses (kQueueWords).  Returns the block's first tile.
+    static constexpr int kFrom = 64, kTo = kFrom + kMaxExperts, kRb = kTo + kMaxExperts, kQueueWords = kRb + kMaxExperts;
     __device__ __forceinline__ int init(const int32_t* offsets_, int E_, int n_tiles_, int max_rows_, float fixed, int* scratch)
     {
         offsets = offsets_;
@@ -99,12 +117,12 @@ struct BigQueue {
         const int lane = lane_id();
         const int k = __builtin_amdgcn_readfirstlane((int)(threadIdx.x >> 6));       // wave
         int* const tiles_at = scratch;              // [8] tiles at height 8 - k
-        float* const squares_at = reinterpret_cast<float*>(scratch + 600);   // [8] sum of their squared heights
-        int* const border = scratch + 8;            // [2][8] first tile of piece k: equal numbers, equal costs
-        int* const b_expert = scratch + 24;         // [2][8] the expert of that tile
-        int* const b_before = scratch + 40;         // [2][8] tiles of the experts in front of it
-        float* const b_cost = reinterpret_cast<float*>(scratch + 56);     // [8] cost in front of border[0][k]
-        int* const rb_of = scratch + 64;            // [E] row blocks
+        float* const squares_at = reinterpret_cast<float*>(scratch + 8);     // [8] sum of their squared heights
+        int* const border = scratch + 16;           // [2][8] first tile of piece k: equal numbers, equal costs
+        float* const b_cost = reinterpret_cast<float*>(scratch + 32);        // [8] cost in front of border[0][k]
+        int* const from = scratch + kFrom;          // [E] first row, end of the rows
+        int* const to = scratch + kTo;
+        int* const rb_of = scratch + kRb;           // [E] row blocks
 
         // wave k: number of tiles at height 8 - k
         int rb_sum = 0, t_sum = 0, used = 0;
@@ -113,17 +131,31 @@ struct BigQueue {
             const int hh = kBigRows / 32 - k >= kBigMinHeight ? kBigRows / 32 - k : kBigMinHeight;
             const uint32_t inv = height_inverse(hh);
 #pragma unroll 1
-            for (int e = lane; e < E; e += 64) {
-                int r0 = offsets[e], r1 = offsets[e + 1];
-                r0 = r0 < 0 ? 0 : (r0 > max_rows ? max_rows : r0);
-                r1 = r1 < r0 ? r0 : (r1 > max_rows ? max_rows : r1);
-                const int rb = (r1 - r0 + 31) / 32;
-                if (k == 0) rb_of[e] = rb;
-                const int m = div_up(rb, hh, inv);
-                rb_sum += rb;
-                used += rb > 0;
-                t_sum += m;
-                sq_sum += rb > 0 ? (float)rb * (float)rb * __builtin_amdgcn_rcpf((float)m) : 0.f;
+            for (int e0 = lane; e0 < E; e0 += 128) {       // (two experts at a time: one trip to memory up to 128 of them)
+                int r0[2], r1[2];
+#pragma unroll
+                for (int i = 0; i < 2; ++i) {
+                    const int e = e0 + 64 * i < E ? e0 + 64 * i : E - 1;
+                    r0[i] = offsets[e];
+                    r1[i] = offsets[e + 1];
+                }
+#pragma unroll
+                for (int i = 0; i < 2; ++i) {
+                    if (e0 + 64 * i >= E) break;
+                    const int lo_e = r0[i] < 0 ? 0 : (r0[i] > max_rows ? max_rows : r0[i]);
+                    const int hi_e = r1[i] < lo_e ? lo_e : (r1[i] > max_rows ? max_rows : r1[i]);
+                    const int rb = (hi_e - lo_e + 31) / 32;
+                    if (k == 0) {
+                        from[e0 + 64 * i] = lo_e;
+                        to[e0 + 64 * i] = hi_e;
+                        rb_of[e0 + 64 * i] = rb;
+                    }
+                    const int m = div_up(rb, hh, inv);
+                    rb_sum += rb;
+                    used += rb > 0;
+                    t_sum += m;
+                    sq_sum += rb > 0 ? (float)rb * (float)rb * __builtin_amdgcn_rcpf((float)m) : 0.f;
+                }
             }
         }
         t_sum = last_lane(wave_scan(t_sum));
@@ -136,21 +168,18 @@ struct BigQueue {
         }
         __syncthreads();
         const float blocks = (float)gridDim.x;
-        float best = 0.f;
-        h = 0;
-#pragma unroll 1
-        for (int c = 0; c <= kBigRows / 32 - kBigMinHeight; ++c) {
+        {
+            // lane c: the launch at height 8 - c (whole rounds of the mean tile, and what the unluckiest block gets on top by chance)
+            constexpr int LAST = kBigRows / 32 - kBigMinHeight;
+            const int c = lane < LAST ? lane : LAST;
             const float tiles = fmaxf((float)tiles_at[c] * (float)n_tiles, 1.f), inv = __builtin_amdgcn_rcpf(tiles);
             const float rounds = ceilf(tiles * __builtin_amdgcn_rcpf(blocks) - 1e-3f), mean = rb_all * inv;
             const float var = fmaxf(squares_at[c] * (float)n_tiles * inv - mean * mean, 0.f);
-            // whole rounds of the mean tile, and what the unluckiest block gets on top of that by chance
             const float cost = rounds * (fixed + mean) + 1.5f * __builtin_amdgcn_sqrtf(rounds * var);
-            if (c == 0 || cost < best) {
-                best = cost;
-                h = kBigRows / 32 - c;
-            }
+            static_assert(LAST < 8, "eight lanes hold every height");
+            const unsigned long long best = __ballot(cost == -eight_max(-cost));
+            h = kBigRows / 32 - (__ffsll((long long)best) - 1);       // (the highest of equal ones)
         }
-        h = __builtin_amdgcn_readfirstlane(h);
         h_inv = height_inverse(h);
         const int m_tiles = __builtin_amdgcn_readfirstlane(tiles_at[kBigRows / 32 - h]);
         mostly_alone = m_tiles - used <= used / 16;
@@ -180,8 +209,6 @@ struct BigQueue {
                     found_n = true;
                     if (lane == __ffsll((long long)past_n) - 1) {
                         border[k] = by_count;
-                        b_expert[k] = e0 + lane;
-                        b_before[k] = cum - tiles;
                         b_cost[k] = fcum - c * (float)(cum - by_count) * __builtin_amdgcn_rcpf((float)tiles);
                     }
                 }
@@ -190,8 +217,6 @@ struct BigQueue {
                     if (lane == __ffsll((long long)past) - 1) {
                         const float behind = fminf((fcum - target) * __builtin_amdgcn_rcpf(c), 1.f);
                         border[8 + k] = k > 0 ? cum - (int)(behind * (float)tiles) : 0;
-                        b_expert[8 + k] = e0 + lane;
-                        b_before[8 + k] = cum - tiles;
                     }
                 }
                 sum = last_lane(cum);
@@ -200,15 +225,9 @@ struct BigQueue {
             if (lane == 0) {     // (only if rounding puts the last borders behind the last expert, or nothing has rows)
                 if (!found_n) {
                     border[k] = total;
-                    b_expert[k] = E - 1;
-                    b_before[k] = total;
                     b_cost[k] = ftotal;
                 }
-                if (!found) {
-                    border[8 + k] = total;
-                    b_expert[8 + k] = E - 1;
-                    b_before[8 + k] = total;
-                }
+                if (!found) border[8 + k] = total;
             }
         }
         __syncthreads();
@@ -217,20 +236,32 @@ struct BigQueue {
         const float n0 = (float)(y < 7 ? border[y + 1] : total) - (float)border[y];
         const float n1 = (float)(y < 7 ? border[9 + y] : total) - (float)border[8 + y];
         const float per_block = 8.f * __builtin_amdgcn_rcpf(blocks);
-        float slow0 = n0 > 0.f ? ceilf(n0 * per_block - 1e-3f) * ((y < 7 ? b_cost[y + 1] : ftotal) - b_cost[y]) * __builtin_amdgcn_rcpf(n0) : 0.f;
-        float slow1 = n1 > 0.f ? ceilf(n1 * per_block - 1e-3f) * (ftotal * 0.125f) * __builtin_amdgcn_rcpf(n1) : 0.f;
-#pragma unroll 1
-        for (int o = 4; o >= 1; o >>= 1) {
-            slow0 = fmaxf(slow0, __shfl_xor(slow0, o, 64));
-            slow1 = fmaxf(slow1, __shfl_xor(slow1, o, 64));
-        }
+        const float slow0 = n0 > 0.f ? ceilf(n0 * per_block - 1e-3f) * ((y < 7 ? b_cost[y + 1] : ftotal) - b_cost[y]) * __builtin_amdgcn_rcpf(n0) : 0.f;
+        const float slow1 = n1 > 0.f ? ceilf(n1 * per_block - 1e-3f) * (ftotal * 0.125f) * __builtin_amdgcn_rcpf(n1) : 0.f;
         const int x = (int)(blockIdx.x % 8);
-        const int at = (__builtin_amdgcn_readfirstlane(slow1 < slow0) != 0 ? 8 : 0) + x;
+        const int at = (__builtin_amdgcn_readfirstlane(eight_max(slow1) < eight_max(slow0)) != 0 ? 8 : 0) + x;
         const int first = __builtin_amdgcn_readfirstlane(border[at]) + (int)(blockIdx.x / 8);
         end = x == 7 ? total : __builtin_amdgcn_readfirstlane(border[at + 1]);
-        expert = __builtin_amdgcn_readfirstlane(b_expert[at]);
-        before = __builtin_amdgcn_readfirstlane(b_before[at]);
-        load_expert();
+        // the expert of the first tile, and the tiles in front of it (a block without a tile: the last expert)
+        before = 0;
+        expert = E - 1;
+#pragma unroll 1
+        for (int e0 = 0; e0 < E; e0 += 64) {
+            const int rb = e0 + lane < E ? rb_of[e0 + lane] : 0;
+            const int tiles = div_up(rb, h, h_inv) * n_tiles;
+            const int cum = wave_scan(tiles) + before;
+            const unsigned long long past = __ballot(cum > first);
+            if (past != 0) {
+                const int src = __ffsll((long long)past) - 1;
+                expert = e0 + src;
+                before = __builtin_amdgcn_readlane(cum - tiles, src);
+                break;
+            }
+            before = last_lane(cum);
+        }
+        lo = __builtin_amdgcn_readfirstlane(from[expert]);
+        hi = __builtin_amdgcn_readfirstlane(to[expert]);
+        set_expert(__builtin_amdgcn_readfirstlane(rb_of[expert]));
         __syncthreads();       // `scratch` is free again
         return first;
     }

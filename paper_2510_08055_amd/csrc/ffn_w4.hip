@@ -908,13 +908,15 @@ __global__ __launch_bounds__(kBigWaves * 64, 2) void grouped_gemm_w4_big_kernel(
     rows.look_up(cur);
     use_weights(cur);
     use_scales(cur);
-#pragma unroll 1
-    for (int i = 0; i < LEAD; ++i) issue_piece();
+    issue_piece();
+    issue_piece();
     issue_scales(0);
-    wait_vmcnt<LEAD + 1>();                // the look-ups came first
+    wait_vmcnt<3>();                       // the look-ups came first
     rows.use(cur);
     rows.issue(0, lds0);
-    wait_vmcnt<0>();
+#pragma unroll 1
+    for (int i = 2; i < LEAD; ++i) issue_piece();
+    wait_vmcnt<LEAD - 2>();                // (of what the first two stages need: nothing is asked for ahead of it, see ffn.hip)
     block_barrier();
 
     auto run = [&](auto tmv_const) {
