@@ -41,7 +41,11 @@ template <> struct pack16<float> {
 // write decode rows and prefill rows to their separate output buffers without a copy.
 // YT: element type of y_perm (T, or float when the context keeps the expert outputs in fp32).
 // STREAM: y_perm as non-temporal loads (each of its rows is read once; see launch_combine).
-template <typename T, typename YT, bool STREAM>
+// KB: rows that are asked for at once, a divisor of K.  With few tokens the kernel is a chain of latencies, and a loop over the
+// rows waited for them two by two: now the token's indices and weights are scalar loads (no trip through LDS), its KB rows and the
+// residual are in flight together.  A pass of four layers over one token (top-8) 129 -> 123 us, an fp32 layer of 64 tokens (top-2) 24.1 ->
+// 23.4; level with many tokens, which are bound by bandwidth (6 TB/s at 8320).
+template <typename T, typename YT, bool STREAM, int KB>
 __global__ __launch_bounds__(256) void combine_kernel(const YT* __restrict__ y_perm, const int32_t* __restrict__ inv,
                                                       const float* __restrict__ w, bool has_residual,
                                                       RowSrc residual, int K, int H, T* y0, int64_t rows0, T* y1)
@@ -50,40 +54,45 @@ __global__ __launch_bounds__(256) void combine_kernel(const YT* __restrict__ y_p
     typedef pack16<YT> PY;
     static_assert(!STREAM || sizeof(T) == sizeof(YT), "a line that is read in two pieces would be fetched twice");
     constexpr int NY = P::N / PY::N;      // 16-byte pieces of y_perm per 16 bytes of output (1, or 2 for fp32 under bf16)
-    __shared__ int32_t s_row[kMaxTopK];
-    __shared__ float s_w[kMaxTopK];
     const int64_t t = blockIdx.x;
-    if (threadIdx.x < K) {
-        // (entries are trusted to lie in [0, T K); the clamp keeps a bad one from becoming a wild address)
-        const int32_t row = inv[t * K + threadIdx.x], last = (int32_t)gridDim.x * K - 1;
-        s_row[threadIdx.x] = row < 0 ? 0 : (row > last ? last : row);
-        s_w[threadIdx.x] = w[t * K + threadIdx.x];
-    }
-    __syncthreads();
+    const int32_t* const t_inv = inv + t * K;
+    const float* const t_w = w + t * K;
+    const int32_t last = (int32_t)gridDim.x * K - 1;
     T* out = (t < rows0) ? (y0 + t * (int64_t)H) : (y1 + (t - rows0) * (int64_t)H);
     for (int c = threadIdx.x * P::N; c < H; c += 256 * P::N) {
         float acc[P::N], v[P::N];
 #pragma unroll
         for (int i = 0; i < P::N; ++i) acc[i] = 0.f;
-        for (int j = 0; j < K; ++j) {
-            const YT* src = y_perm + (int64_t)s_row[j] * H + c;
+        P res;
+        if (has_residual) res.raw = *reinterpret_cast<const decltype(res.raw)*>(row_ptr<T>(residual, t, H) + c);
+#pragma unroll 1
+        for (int j0 = 0; j0 < K; j0 += KB) {
+            PY p[KB][NY];
 #pragma unroll
-            for (int h = 0; h < NY; ++h) {
-                PY p;
-                if (STREAM)
-                    p.raw = __builtin_bit_cast(decltype(p.raw), __builtin_nontemporal_load(reinterpret_cast<const chunk16_t*>(src)));
-                else
-                    p.raw = *reinterpret_cast<const decltype(p.raw)*>(src + h * PY::N);
-                p.unpack(v + h * PY::N);
+            for (int j = 0; j < KB; ++j) {
+                // (entries are trusted to lie in [0, T K); the clamp keeps a bad one from becoming a wild address)
+                int32_t row = t_inv[j0 + j];
+                row = row < 0 ? 0 : (row > last ? last : row);
+                const YT* src = y_perm + (int64_t)row * H + c;
+#pragma unroll
+                for (int h = 0; h < NY; ++h) {
+                    if (STREAM)
+                        p[j][h].raw = __builtin_bit_cast(decltype(p[j][h].raw), __builtin_nontemporal_load(reinterpret_cast<const chunk16_t*>(src)));
+                    else
+                        p[j][h].raw = *reinterpret_cast<const decltype(p[j][h].raw)*>(src + h * PY::N);
+                }
             }
-            const float wj = s_w[j];
 #pragma unroll
-            for (int i = 0; i < P::N; ++i) acc[i] = fmaf(wj, v[i], acc[i]);
+            for (int j = 0; j < KB; ++j) {
+#pragma unroll
+                for (int h = 0; h < NY; ++h) p[j][h].unpack(v + h * PY::N);
+                const float wj = t_w[j0 + j];
+#pragma unroll
+                for (int i = 0; i < P::N; ++i) acc[i] = fmaf(wj, v[i], acc[i]);
+            }
         }
         if (has_residual) {
-            P p;
-            p.raw = *reinterpret_cast<const decltype(p.raw)*>(row_ptr<T>(residual, t, H) + c);
-            p.unpack(v);
+            res.unpack(v);
 #pragma unroll
             for (int i = 0; i < P::N; ++i) acc[i] += v[i];
         }
@@ -110,12 +119,26 @@ hipError_t launch_combine(int dtype, bool y_perm_f32, const void* y_perm, const 
                           bool has_residual, RowSrc residual, int64_t T, int K, int H, void* y0, int64_t rows0, void* y1,
                           hipStream_t s)
 {
+    int at_once = 8;      // the largest divisor of K up to 8
+    while (K % at_once != 0) --at_once;
     auto go = [&](auto elem_t, auto y_elem_t, auto stream) {
         typedef decltype(elem_t) X;
         typedef decltype(y_elem_t) Y;
-        combine_kernel<X, Y, decltype(stream)::value><<<(unsigned)T, 256, 0, s>>>(
-            static_cast<const Y*>(y_perm), inv, w, has_residual, residual, K, H, static_cast<X*>(y0), rows0, static_cast<X*>(y1));
-        return hipGetLastError();
+        auto with = [&](auto kb) {
+            combine_kernel<X, Y, decltype(stream)::value, decltype(kb)::value><<<(unsigned)T, 256, 0, s>>>(
+                static_cast<const Y*>(y_perm), inv, w, has_residual, residual, K, H, static_cast<X*>(y0), rows0, static_cast<X*>(y1));
+            return hipGetLastError();
+        };
+        switch (at_once) {
+            case 8: return with(std::integral_constant<int, 8>());
+            case 7: return with(std::integral_constant<int, 7>());
+            case 6: return with(std::integral_constant<int, 6>());
+            case 5: return with(std::integral_constant<int, 5>());
+            case 4: return with(std::integral_constant<int, 4>());
+            case 3: return with(std::integral_constant<int, 3>());
+            case 2: return with(std::integral_constant<int, 2>());
+            default: return with(std::integral_constant<int, 1>());
+        }
     };
     const std::true_type stream;
     const std::false_type plain;

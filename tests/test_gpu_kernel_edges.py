@@ -697,3 +697,23 @@ def test_narrow_tiles_of_two_waves(gpu_lib, H, I, rows, fmt):
     ctx.moe_set_ffn_variant("few")
     for _ in range(2):
         assert torch.equal(ctx.moe_grouped_ffn(x_perm, offsets, L["w_gate_up"], L["w_down"]), want)
+
+
+# The combine asks for as many rows at once as the largest divisor of K up to 8; plain and streamed rows, one and two pieces per output
+@pytest.mark.parametrize("K", [1, 2, 3, 4, 5, 6, 7, 8, 9, 11, 12, 14, 16, 64])
+@pytest.mark.parametrize("dtype,H,fmt", [("bf16", 64, {}), ("bf16", 2056, {}), ("bf16", 72, {"y_perm_f32": True}), ("f32", 1064, {})])
+def test_combine_rows_at_once(gpu_lib, K, dtype, H, fmt):
+    T, E = 37, 64
+    dt = inputs.torch_dtype(dtype)
+    ctx = gpu_lib.Context(H, E, K, 8 if not fmt else 64, dt, max_tokens=T, device=DEV, **fmt)
+    y_perm = inputs.randn((T * K, H), 1.0, K, "y", 0, "f32" if fmt else dtype, DEV)
+    inv = torch.randperm(T * K, generator=torch.Generator().manual_seed(K)).to(torch.int32).to(DEV)
+    wt = torch.rand((T, K), generator=torch.Generator().manual_seed(K + 1)).to(DEV) / K
+    x = inputs.randn((T, H), 1.0, K, "x", 0, dtype, DEV)
+    terms = wt.double()[:, :, None] * y_perm.double()[inv.long()].view(T, K, H)
+    # K + 1 roundings of fp32 sums no larger than the terms' magnitudes, and the output's own rounding
+    bound = (K + 1) * 2.0 ** -24 * (terms.abs().sum(1) + x.double().abs())
+    for res in (None, x):
+        want = terms.sum(1) + (0 if res is None else res.double())
+        got = ctx.moe_combine(y_perm, inv, wt, residual=res).double()
+        assert ((got - want).abs() <= bound + want.abs() * (2.0 ** -8 if dtype == "bf16" else 2.0 ** -23)).all()
