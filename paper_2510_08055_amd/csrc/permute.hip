@@ -87,32 +87,46 @@ __global__ __launch_bounds__(kPermThreads) void permute_scatter_kernel(
     __shared__ int32_t start[kMaxExperts];              // first permuted row of this tile inside expert e
     __shared__ int32_t wave_cnt[kPermWaves][kMaxExperts];
 
-    const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
+    const int tid = threadIdx.x, lane = tid & 63;
+    const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
     const int tile = blockIdx.x;
     const int64_t base = (int64_t)tile * kPermTile;
 
+    // all of this thread's expert ids are fetched up front: one memory latency, under that of the histograms
+    int my_e[kPermRounds], my_rank[kPermRounds];
+#pragma unroll
+    for (int r = 0; r < kPermRounds; ++r) {
+        const int64_t f = base + (int64_t)wave * (kPermRounds * 64) + r * 64 + lane;
+        my_e[r] = f < A ? idx[f] : -1;
+    }
     for (int e = tid; e < E; e += kPermThreads) {
         total[e] = 0;
         start[e] = 0;
     }
-    for (int i = tid; i < kPermWaves * kMaxExperts; i += kPermThreads) (&wave_cnt[0][0])[i] = 0;
+    for (int e = lane; e < E; e += 64) wave_cnt[wave][e] = 0;
     __syncthreads();
+#pragma unroll
+    for (int r = 0; r < kPermRounds; ++r) {
+        const int64_t f = base + (int64_t)wave * (kPermRounds * 64) + r * 64 + lane;
+        my_e[r] = f < A ? clamp_expert(my_e[r], E) : -1;
+    }
     if (SCANNED) {
         for (int e = tid; e < E; e += kPermThreads) {
             total[e] = tile_hist[(int64_t)n_tiles * E + e];
             start[e] = tile_hist[(int64_t)tile * E + e];
         }
     } else if (n_tiles == 1) {
-        for (int i = tid; i < kPermTile; i += kPermThreads)
-            if (base + i < A) atomicAdd(&total[clamp_expert(idx[base + i], E)], 1);
+#pragma unroll
+        for (int r = 0; r < kPermRounds; ++r)
+            if (my_e[r] >= 0) atomicAdd(&total[my_e[r]], 1);
     } else {
         // the threads share out the (expert, eighth of the tiles) pairs: a few loads in flight per thread, not a
         // chain of n_tiles; integer sums do not depend on the order of the atomics
         for (int i = tid; i < 8 * E; i += kPermThreads) {
-            const int e = i % E;
+            const int eighth = i / E, e = i - eighth * E;
             int tot = 0, before = 0;
 #pragma unroll 4
-            for (int t = i / E; t < n_tiles; t += 8) {
+            for (int t = eighth; t < n_tiles; t += 8) {
                 const int h = tile_hist[(int64_t)t * E + e];
                 tot += h;
                 before += t < tile ? h : 0;
@@ -122,57 +136,34 @@ __global__ __launch_bounds__(kPermThreads) void permute_scatter_kernel(
         }
     }
     __syncthreads();
-    // exclusive scan over experts by wave 0: lane l owns experts [l*8, l*8+8)
+    // exclusive scan over experts by wave 0, 64 at a time
     if (wave == 0) {
-        int loc[kMaxExperts / 64];
-        int sum = 0;
-#pragma unroll
-        for (int i = 0; i < kMaxExperts / 64; ++i) {
-            const int e = lane * (kMaxExperts / 64) + i;
-            loc[i] = (e < E) ? total[e] : 0;
-            sum += loc[i];
-        }
-        int incl = sum;
-#pragma unroll
-        for (int off = 1; off < 64; off <<= 1) {
-            const int o = __shfl_up(incl, off, 64);
-            if (lane >= off) incl += o;
-        }
-        int run = incl - sum;
-        int act = 0;
-#pragma unroll
-        for (int i = 0; i < kMaxExperts / 64; ++i) {
-            const int e = lane * (kMaxExperts / 64) + i;
+        int before = 0, act = 0;
+#pragma unroll 1
+        for (int e0 = 0; e0 < E; e0 += 64) {
+            const int e = e0 + lane, n = e < E ? total[e] : 0;
+            const int incl = wave_scan(n) + before;
             if (e < E) {
-                start[e] += run;
+                start[e] += incl - n;
                 if (tile == 0) {
-                    counts[e] = loc[i];
-                    offsets[e] = run;
+                    counts[e] = n;
+                    offsets[e] = incl - n;
                 }
-                act += (loc[i] > 0);
             }
-            run += loc[i];
+            act += (int)__popcll(__ballot(n > 0));
+            before = __builtin_amdgcn_readlane(incl, 63);
         }
-        if (tile == 0) {
-            if (lane == 63) offsets[E] = incl;
-#pragma unroll
-            for (int off = 32; off >= 1; off >>= 1) act += __shfl_xor(act, off, 64);
-            if (lane == 0 && active_total) atomicAdd(active_total, (unsigned long long)act);
+        if (tile == 0 && lane == 0) {
+            offsets[E] = before;
+            if (active_total) atomicAdd(active_total, (unsigned long long)act);
         }
     }
-    __syncthreads();
 
     // Rank inside the wave's region of kPermRounds * 64 assignments, chunk by chunk in index order.
     int nbits = 0;
     while ((1 << nbits) < E) ++nbits;
-    int my_e[kPermRounds], my_rank[kPermRounds];
+    // (wave 0 meanwhile scans the counts: wave_cnt is the wave's own, and `start` is not read before the barrier behind this.)
     const uint64_t lt_mask = (lane == 0) ? 0ull : (~0ull >> (64 - lane));
-    // all of this thread's expert ids are fetched up front: one memory latency, not one per round
-#pragma unroll
-    for (int r = 0; r < kPermRounds; ++r) {
-        const int64_t f = base + (int64_t)wave * (kPermRounds * 64) + r * 64 + lane;
-        my_e[r] = (f < A) ? clamp_expert(idx[f], E) : -1;
-    }
 #pragma unroll
     for (int r = 0; r < kPermRounds; ++r) {
         const bool valid = my_e[r] >= 0;
