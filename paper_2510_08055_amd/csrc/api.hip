@@ -203,9 +203,9 @@ moe_status run_layer(moe_ctx* c, const moe_layer* layers, int l, int n, RowSrc x
     const moe_layer& L = layers[l];
     const moe_config& g = c->cfg;
     const int64_t A = T * g.K;
-    // with more than one permutation tile the top-k kernel counts the per-tile expert histograms itself
+    // with many permutation tiles the top-k kernel counts the per-tile expert histograms itself
     const int n_perm_tiles = (int)((A + kPermTile - 1) / kPermTile);
-    const bool fused_hist = n_perm_tiles > 1;
+    const bool fused_hist = !permute_counts(A, g.E);
     hipError_t e;
     const bool small = route_is_small(T, g.E, g.K);
     const bool exact = route_is_exact(g.dtype, T, g.H, g.E, g.K);

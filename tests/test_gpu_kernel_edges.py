@@ -717,3 +717,25 @@ def test_combine_rows_at_once(gpu_lib, K, dtype, H, fmt):
         want = terms.sum(1) + (0 if res is None else res.double())
         got = ctx.moe_combine(y_perm, inv, wt, residual=res).double()
         assert ((got - want).abs() <= bound + want.abs() * (2.0 ** -8 if dtype == "bf16" else 2.0 ** -23)).all()
+
+
+# The permutation by itself counts up to 12288 assignments in every block of the scatter, fewer than 16 experts only one tile of
+# 2048; beyond, the top-k's histograms or a pass of its own.  Against a stable sort, and as part of a layer.
+@pytest.mark.parametrize("E,T,K", [(15, 512, 4), (15, 683, 3), (16, 2049, 1), (128, 1536, 8), (128, 1537, 8), (512, 4096, 3), (300, 12289, 1)])
+def test_permutation_counts(gpu_lib, E, T, K):
+    H, I, A = 64, 64, T * K
+    w = inputs.Workload("count", H=H, E=E, K=K, I=I, n_layers=1, D=0, P=T, dtype="bf16", seed=A, residual=False)
+    L = inputs.make_layer(w, 0, device=DEV)
+    x = inputs.randn((T, H), 1.0, A, "x", 0, "bf16", DEV)
+    ctx = gpu_lib.Context(H, E, K, I, torch.bfloat16, max_tokens=T, residual=False, device=DEV)
+    idx, wt = ctx.moe_router_topk(x, L["w_router"])
+    counts, offsets, perm, inv, x_perm = ctx.moe_permute(x, idx)
+    flat = idx.view(-1).long()
+    want = torch.sort(flat, stable=True).indices.to(torch.int32)
+    assert torch.equal(perm.view(-1), want)
+    assert torch.equal(counts.long(), torch.bincount(flat, minlength=E))
+    assert torch.equal(offsets[1:].long(), torch.cumsum(counts.long(), 0)) and int(offsets[0]) == 0
+    assert torch.equal(inv.view(-1)[want.long()], torch.arange(A, dtype=torch.int32, device=DEV))
+    y = ctx.moe_combine(ctx.moe_grouped_ffn(x_perm, offsets, L["w_gate_up"], L["w_down"]), inv, wt)
+    for _ in range(2):
+        assert torch.equal(ctx.moe_group_forward([L], None, x)[1], y)
