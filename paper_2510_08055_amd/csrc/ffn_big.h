@@ -329,16 +329,17 @@ template <bool MAPPED> struct BigRows {
         live = n < 0 ? 0 : (n > LPW ? LPW : n);
     }
     // (a load whose 8 rows all lie past the tile's last row is left out: no wait count may include an activation load)
-    __device__ __forceinline__ void issue(int stage, uint32_t lds_slot) const
+    __device__ __forceinline__ void issue_at(uint32_t byte, uint32_t lds_slot) const      // of the row
     {
 #pragma unroll
         for (int p = 0; p < LPW; ++p)
             if (p < live) {
                 const uint32_t at = lds_slot + (wave + kBigWaves * p) * 1024;
-                if constexpr (MAPPED) load_lds_16(src[p] + (uint32_t)(stage * ROWB), at);
-                else load_lds_16_base(base + (uint32_t)(stage * ROWB), off[p], at);
+                if constexpr (MAPPED) load_lds_16(src[p] + byte, at);
+                else load_lds_16_base(base + byte, off[p], at);
             }
     }
+    __device__ __forceinline__ void issue(int stage, uint32_t lds_slot) const { issue_at((uint32_t)(stage * ROWB), lds_slot); }
 };
 
 // Host side: blocks of a launch (one per compute unit, the same number on every XCD), and whether the tile list is short

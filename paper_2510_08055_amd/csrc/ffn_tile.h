@@ -181,9 +181,7 @@ __device__ __forceinline__ void block_barrier() { asm volatile("s_barrier" ::: "
 // delivers more of them (6.8 TB/s against 6.1).  gate_up and down, us, plain / non-temporal: 128 experts, H = I = 2880, 256 tokens
 // 697 / 624 and 366 / 338; H = 2048, I = 768, 32 tokens 128 / 114 and 67 / 60, 640 tokens 149 / 139 and 83 / 80.  Weights that several
 // m-tiles share must stay: 520 rows per expert 388 / 437 and 225 / 248.  So must weights whose stage rows are not whole 128-byte
-// lines (see whole_lines): a line that is gone between its two pieces is fetched twice.  (The down GEMM of a split intermediate
-// reads its weights twice, half a tile apart, and gains all the same: gate_up + down, 8 experts, 4096 x 14336, 16 rows each 649 / 577,
-// 130 rows 878 / 861; 32 experts, 2880 x 2880, 16 rows 371 / 346, 64 and 250 rows level.)
+// lines (see whole_lines): a line that is gone between its two pieces is fetched twice.
 template <int BYTES, bool STREAM = false> __device__ __forceinline__ void load_lds(const void* src, uint32_t lds_base)
 {
     static_assert(BYTES == 16 || BYTES == 4 || BYTES == 2, "direct-to-LDS loads move 16, 4 or 2 bytes per lane");

@@ -739,3 +739,20 @@ def test_permutation_counts(gpu_lib, E, T, K):
     y = ctx.moe_combine(ctx.moe_grouped_ffn(x_perm, offsets, L["w_gate_up"], L["w_down"]), inv, wt)
     for _ in range(2):
         assert torch.equal(ctx.moe_group_forward([L], None, x)[1], y)
+
+
+# A split intermediate: a weight stage serves a step of hi and a step of lo values; the shortest rows the persistent kernel takes, an
+# odd number of weight stages, blocks with one tile and with two (280 and 300 tiles on 256 units), row blocks per wave from none to four
+@pytest.mark.parametrize("H,I,rows", [(512, 256, [35] * 140), (264, 320, [40, 1, 300] * 50), (768, 448, [256, 129, 0, 64])])
+def test_split_weight_stages(gpu_lib, H, I, rows):
+    E, A = len(rows), sum(rows)
+    w = inputs.Workload("pairs", H=H, E=E, K=1, I=I, n_layers=1, D=0, P=A, dtype="bf16", seed=A)
+    L = inputs.make_layer(w, 0, device=DEV)
+    x_perm = inputs.randn((A, H), 1.0, A, "x_perm", 0, "bf16", DEV)
+    offsets = torch.tensor(np.concatenate([[0], np.cumsum(rows)]), dtype=torch.int32, device=DEV)
+    ctx = gpu_lib.Context(H, E, 1, I, torch.bfloat16, max_tokens=A, device=DEV, y_perm_f32=True, act_split=True)
+    ctx.moe_set_ffn_variant("tile128")
+    want = ctx.moe_grouped_ffn(x_perm, offsets, L["w_gate_up"], L["w_down"]).clone()
+    for shape in ("big", "small", "wide", "big"):
+        ctx.moe_set_ffn_variant(shape)
+        assert torch.equal(ctx.moe_grouped_ffn(x_perm, offsets, L["w_gate_up"], L["w_down"]), want), shape
