@@ -41,11 +41,14 @@ template <> struct pack16<float> {
 // write decode rows and prefill rows to their separate output buffers without a copy.
 // YT: element type of y_perm (T, or float when the context keeps the expert outputs in fp32).
 // STREAM: y_perm as non-temporal loads (each of its rows is read once; see launch_combine).
-// KB: rows that are asked for at once, a divisor of K.  With few tokens the kernel is a chain of latencies, and a loop over the
-// rows waited for them two by two: now the token's indices and weights are scalar loads (no trip through LDS), its KB rows and the
-// residual are in flight together.  A pass of four layers over one token (top-8) 129 -> 123 us, an fp32 layer of 64 tokens (top-2) 24.1 ->
-// 23.4; level with many tokens, which are bound by bandwidth (6 TB/s at 8320).
-template <typename T, typename YT, bool STREAM, int KB>
+// KB, TAIL: a token's K rows are asked for KB at once, and TAIL = K % KB of them at the end.  With few tokens the kernel is a chain of
+// latencies, and a loop over the rows waited for them two by two: now the token's indices and weights are scalar loads (no trip through
+// LDS), KB rows and the residual are in flight together.  A pass of four layers over one token (top-8) 129 -> 123 us, an fp32 layer of
+// 64 tokens (top-2) 24.1 -> 23.4; level with many tokens, which are bound by bandwidth (6 TB/s at 8320).  A group that divides K would leave 11,
+// 13, 17 ... rows to be waited for one by one; us, two by two / by the largest divisor / as now, H = 2048, bf16: one token, top-9 3.3 / 2.8 / 2.6,
+// top-13 3.7 / 4.1 / 2.7, top-29 5.6 / 6.8 / 3.6; 256 tokens 4.9 / 4.5 / 3.7, 5.8 / 6.8 / 4.0, 11.2 / 15.4 / 6.3; 2112 tokens, top-11 21.0 /
+// 22.3 / 18.8, top-13 24.6 / 26.0 / 22.0; fp32 rows under bf16 output, 256 tokens, top-8 4.0 / 3.7 / 3.0, top-13 6.4 / 6.5 / 4.0.
+template <typename T, typename YT, bool STREAM, int KB, int TAIL>
 __global__ __launch_bounds__(256) void combine_kernel(const YT* __restrict__ y_perm, const int32_t* __restrict__ inv,
                                                       const float* __restrict__ w, bool has_residual,
                                                       RowSrc residual, int K, int H, T* y0, int64_t rows0, T* y1)
@@ -65,15 +68,14 @@ __global__ __launch_bounds__(256) void combine_kernel(const YT* __restrict__ y_p
         for (int i = 0; i < P::N; ++i) acc[i] = 0.f;
         P res;
         if (has_residual) res.raw = *reinterpret_cast<const decltype(res.raw)*>(row_ptr<T>(residual, t, H) + c);
-#pragma unroll 1
-        for (int j0 = 0; j0 < K; j0 += KB) {
-            PY p[KB][NY];
+        auto add_rows = [&](int j0, auto n_const) {
+            constexpr int N = decltype(n_const)::value;
+            PY p[N][NY];
 #pragma unroll
-            for (int j = 0; j < KB; ++j) {
+            for (int j = 0; j < N; ++j) {
                 // (entries are trusted to lie in [0, T K); the clamp keeps a bad one from becoming a wild address)
-                int32_t row = t_inv[j0 + j];
-                row = row < 0 ? 0 : (row > last ? last : row);
-                const YT* src = y_perm + (int64_t)row * H + c;
+                const int32_t row = max(min(t_inv[j0 + j], last), 0);
+                const YT* src = y_perm + (uint64_t)(uint32_t)row * (uint32_t)H + c;
 #pragma unroll
                 for (int h = 0; h < NY; ++h) {
                     if (STREAM)
@@ -83,14 +85,17 @@ __global__ __launch_bounds__(256) void combine_kernel(const YT* __restrict__ y_p
                 }
             }
 #pragma unroll
-            for (int j = 0; j < KB; ++j) {
+            for (int j = 0; j < N; ++j) {
 #pragma unroll
                 for (int h = 0; h < NY; ++h) p[j][h].unpack(v + h * PY::N);
                 const float wj = t_w[j0 + j];
 #pragma unroll
                 for (int i = 0; i < P::N; ++i) acc[i] = fmaf(wj, v[i], acc[i]);
             }
-        }
+        };
+#pragma unroll 1
+        for (int j0 = 0; j0 < K - TAIL; j0 += KB) add_rows(j0, std::integral_constant<int, KB>());
+        if constexpr (TAIL > 0) add_rows(K - TAIL, std::integral_constant<int, TAIL>());
         if (has_residual) {
             res.unpack(v);
 #pragma unroll
@@ -119,25 +124,36 @@ hipError_t launch_combine(int dtype, bool y_perm_f32, const void* y_perm, const 
                           bool has_residual, RowSrc residual, int64_t T, int K, int H, void* y0, int64_t rows0, void* y1,
                           hipStream_t s)
 {
-    int at_once = 8;      // the largest divisor of K up to 8
-    while (K % at_once != 0) --at_once;
     auto go = [&](auto elem_t, auto y_elem_t, auto stream) {
         typedef decltype(elem_t) X;
         typedef decltype(y_elem_t) Y;
-        auto with = [&](auto kb) {
-            combine_kernel<X, Y, decltype(stream)::value, decltype(kb)::value><<<(unsigned)T, 256, 0, s>>>(
+        auto with = [&](auto kb, auto tail) {
+            combine_kernel<X, Y, decltype(stream)::value, decltype(kb)::value, decltype(tail)::value><<<(unsigned)T, 256, 0, s>>>(
                 static_cast<const Y*>(y_perm), inv, w, has_residual, residual, K, H, static_cast<X*>(y0), rows0, static_cast<X*>(y1));
             return hipGetLastError();
         };
-        switch (at_once) {
-            case 8: return with(std::integral_constant<int, 8>());
-            case 7: return with(std::integral_constant<int, 7>());
-            case 6: return with(std::integral_constant<int, 6>());
-            case 5: return with(std::integral_constant<int, 5>());
-            case 4: return with(std::integral_constant<int, 4>());
-            case 3: return with(std::integral_constant<int, 3>());
-            case 2: return with(std::integral_constant<int, 2>());
-            default: return with(std::integral_constant<int, 1>());
+        auto even = [&](auto kb) { return with(kb, std::integral_constant<int, 0>()); };
+        auto eights = [&](auto tail) { return with(std::integral_constant<int, 8>(), tail); };
+        // Up to 8 rows at once, up to 16 in two equal groups where there are such, of more 8 and then the rest.
+        switch (K <= 8 ? K : K <= 16 && K % 2 == 0 ? K / 2 : 0) {
+            case 8: return even(std::integral_constant<int, 8>());
+            case 7: return even(std::integral_constant<int, 7>());
+            case 6: return even(std::integral_constant<int, 6>());
+            case 5: return even(std::integral_constant<int, 5>());
+            case 4: return even(std::integral_constant<int, 4>());
+            case 3: return even(std::integral_constant<int, 3>());
+            case 2: return even(std::integral_constant<int, 2>());
+            case 1: return even(std::integral_constant<int, 1>());
+        }
+        switch (K % 8) {
+            case 7: return eights(std::integral_constant<int, 7>());
+            case 6: return eights(std::integral_constant<int, 6>());
+            case 5: return eights(std::integral_constant<int, 5>());
+            case 4: return eights(std::integral_constant<int, 4>());
+            case 3: return eights(std::integral_constant<int, 3>());
+            case 2: return eights(std::integral_constant<int, 2>());
+            case 1: return eights(std::integral_constant<int, 1>());
+            default: return eights(std::integral_constant<int, 0>());
         }
     };
     const std::true_type stream;

@@ -699,7 +699,8 @@ def test_narrow_tiles_of_two_waves(gpu_lib, H, I, rows, fmt):
         assert torch.equal(ctx.moe_grouped_ffn(x_perm, offsets, L["w_gate_up"], L["w_down"]), want)
 
 
-# The combine asks for as many rows at once as the largest divisor of K up to 8; plain and streamed rows, one and two pieces per output
+# The combine asks for up to 8 rows at once, for up to 16 in two equal groups, for others in eights and the rest; plain and streamed rows, one
+# and two pieces per output
 @pytest.mark.parametrize("K", [1, 2, 3, 4, 5, 6, 7, 8, 9, 11, 12, 14, 16, 64])
 @pytest.mark.parametrize("dtype,H,fmt", [("bf16", 64, {}), ("bf16", 2056, {}), ("bf16", 72, {"y_perm_f32": True}), ("f32", 1064, {})])
 def test_combine_rows_at_once(gpu_lib, K, dtype, H, fmt):
@@ -717,6 +718,12 @@ def test_combine_rows_at_once(gpu_lib, K, dtype, H, fmt):
         want = terms.sum(1) + (0 if res is None else res.double())
         got = ctx.moe_combine(y_perm, inv, wt, residual=res).double()
         assert ((got - want).abs() <= bound + want.abs() * (2.0 ** -8 if dtype == "bf16" else 2.0 ** -23)).all()
+
+
+@pytest.mark.parametrize("K", [10, 13, 15, 17, 18, 20, 21, 22, 23, 63])
+@pytest.mark.parametrize("dtype,H,fmt", [("bf16", 2056, {}), ("bf16", 72, {"y_perm_f32": True}), ("f32", 1064, {})])
+def test_combine_eights_and_the_rest(gpu_lib, K, dtype, H, fmt):
+    test_combine_rows_at_once(gpu_lib, K, dtype, H, fmt)
 
 
 # The permutation by itself counts up to 12288 assignments in every block of the scatter, fewer than 16 experts only one tile of
