@@ -205,7 +205,7 @@ moe_status run_layer(moe_ctx* c, const moe_layer* layers, int l, int n, RowSrc x
     const int64_t A = T * g.K;
     // with many permutation tiles the top-k kernel counts the per-tile expert histograms itself
     const int n_perm_tiles = (int)((A + kPermTile - 1) / kPermTile);
-    const bool fused_hist = !permute_counts(A, g.E);
+    const bool fused_hist = topk_counts(A);
     hipError_t e;
     const bool small = route_is_small(T, g.E, g.K);
     const bool exact = route_is_exact(g.dtype, T, g.H, g.E, g.K);

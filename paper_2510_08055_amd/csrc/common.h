@@ -141,10 +141,11 @@ hipError_t launch_route_small(int dtype, RowSrc x, int64_t T, int H, const void*
 
 // permute.hip
 constexpr int kPermTile = 2048;  // assignments per block of the permutation kernels
-// Batches whose expert counts every block of the scatter takes from the assignments themselves (see launch_permute).
-constexpr int kCountTiles = 6, kCountExperts = 16;
-inline bool permute_counts(int64_t A, int E) { return A <= (int64_t)kCountTiles * kPermTile && (A <= kPermTile || E >= kCountExperts); }
-// hist_ready: tile_hist already holds the per-tile histograms (the top-k kernel counted them; not with permute_counts)
+// Batches whose expert counts every block of the scatter takes from the assignments themselves (see launch_permute): in a call of its own,
+// and behind a top-k, which could count them too.
+constexpr int kCountTiles = 6, kCountTilesBehindTopk = 4;
+inline bool topk_counts(int64_t A) { return A > (int64_t)kCountTilesBehindTopk * kPermTile; }
+// hist_ready: tile_hist already holds the per-tile histograms (the top-k kernel counted them)
 hipError_t launch_permute(const int32_t* idx, int64_t A, int E, int32_t* counts, int32_t* offsets,
                           int32_t* perm, int32_t* inv, int32_t* tile_hist, bool hist_ready,
                           unsigned long long* active_total, hipStream_t s);

@@ -77,6 +77,13 @@ __global__ __launch_bounds__(kPermThreads) void permute_scan_kernel(int32_t* __r
 // start of its own tile inside each expert, then ranks and scatters its assignments.
 // COUNT: the block counts all assignments itself (a single tile, or few: see launch_permute) and pass 1 is skipped.
 // SCANNED: the sums over the tiles are already in tile_hist.
+//
+// COUNT: an LDS atomic takes a turn per lane that shares its address, 0.7 ns each, and under skewed routing a wave's 64 assignments are of few
+// experts.  So an expert has kCopies counters, one to eight neighbouring lanes (of neighbouring banks), and a counter's upper half is the
+// count in front of the tile: one atomic per assignment, not two.  moe_permute of 12288 assignments, top-1, us, one counter for the
+// count and one for what is in front / these: 16 experts, all of one of them 22.4 / 6.4, skewed (rank^-1.2) 10.7 / 5.8, even 7.1 / 5.6;
+// 128 experts 22.9 / 6.9, 9.8 / 6.4, 6.7 / 6.3; 512 experts 24.2 / 8.3, 10.6 / 7.7, 8.0 / 7.8.
+constexpr int kCopies = 8;
 template <bool SCANNED, bool COUNT>
 __global__ __launch_bounds__(kPermThreads) void permute_scatter_kernel(
     const int32_t* __restrict__ idx, int64_t A, int E, int n_tiles, const int32_t* __restrict__ tile_hist,
@@ -84,6 +91,7 @@ __global__ __launch_bounds__(kPermThreads) void permute_scatter_kernel(
     int32_t* __restrict__ inv, unsigned long long* __restrict__ active_total)
 {
     __shared__ int32_t total[kMaxExperts];              // assignments per expert, whole batch
+    __shared__ uint32_t copies[COUNT ? kMaxExperts * kCopies : 1];
     __shared__ int32_t start[kMaxExperts];              // first permuted row of this tile inside expert e
     __shared__ int32_t wave_cnt[kPermWaves][kMaxExperts];
 
@@ -99,9 +107,13 @@ __global__ __launch_bounds__(kPermThreads) void permute_scatter_kernel(
         const int64_t f = base + (int64_t)wave * (kPermRounds * 64) + r * 64 + lane;
         my_e[r] = f < A ? idx[f] : -1;
     }
-    for (int e = tid; e < E; e += kPermThreads) {
-        total[e] = 0;
-        start[e] = 0;
+    if (COUNT) {
+        for (int i = tid; i < E * kCopies; i += kPermThreads) copies[i] = 0;
+    } else {
+        for (int e = tid; e < E; e += kPermThreads) {
+            total[e] = 0;
+            start[e] = 0;
+        }
     }
     for (int e = lane; e < E; e += 64) wave_cnt[wave][e] = 0;
     __syncthreads();
@@ -117,6 +129,9 @@ __global__ __launch_bounds__(kPermThreads) void permute_scatter_kernel(
         }
     } else if (COUNT) {
         constexpr int AT_ONCE = 8;
+        static_assert(kCountTiles * kPermTile < 1 << 16, "a half of a counter holds them all");
+        uint32_t* const mine = copies + (lane >> 3);
+        static_assert(kCopies == 8, "one to eight lanes of 64");
 #pragma unroll 1
         for (int64_t f0 = tid; f0 < A; f0 += AT_ONCE * kPermThreads) {
             int e[AT_ONCE];
@@ -126,9 +141,7 @@ __global__ __launch_bounds__(kPermThreads) void permute_scatter_kernel(
             for (int i = 0; i < AT_ONCE; ++i) {
                 const int64_t f = f0 + i * kPermThreads;
                 if (f >= A) break;
-                const int c = clamp_expert(e[i], E);
-                atomicAdd(&total[c], 1);
-                if (f < base) atomicAdd(&start[c], 1);
+                atomicAdd(mine + clamp_expert(e[i], E) * kCopies, f < base ? 0x10001u : 1u);
             }
         }
     } else {
@@ -153,10 +166,21 @@ __global__ __launch_bounds__(kPermThreads) void permute_scatter_kernel(
         int before = 0, act = 0;
 #pragma unroll 1
         for (int e0 = 0; e0 < E; e0 += 64) {
-            const int e = e0 + lane, n = e < E ? total[e] : 0;
+            const int e = e0 + lane;
+            int n = 0, in_front = 0;
+            if (COUNT && e < E) {
+                uint32_t both = 0;
+#pragma unroll
+                for (int i = 0; i < kCopies; ++i) both += copies[e * kCopies + i];
+                n = (int)(both & 0xffffu);
+                in_front = (int)(both >> 16);
+            } else if (e < E) {
+                n = total[e];
+                in_front = start[e];
+            }
             const int incl = wave_scan(n) + before;
             if (e < E) {
-                start[e] += incl - n;
+                start[e] = in_front + incl - n;
                 if (tile == 0) {
                     counts[e] = n;
                     offsets[e] = incl - n;
@@ -241,10 +265,12 @@ hipError_t launch_permute(const int32_t* idx, int64_t A, int E, int32_t* counts,
                           hipStream_t s)
 {
     const int n_tiles = (int)((A + kPermTile - 1) / kPermTile);
-    // Few tiles are counted by every block of the scatter: a launch less in a call of its own (4116 assignments, 32 experts 11.2 -> 5.4
-    // us), and no histograms for the top-k to write (5120 assignments, 128 experts 7.6 -> 6.6 us, 11112 level, 16896 7.6 -> 8.1).  Not those
-    // of few experts, whose counters too many assignments of a wave share.
-    if (!hist_ready && permute_counts(A, E)) {
+    // Few tiles are counted by every block of the scatter.  In a call of its own that is a launch less, us, with it / without, 12288 assignments,
+    // even routing: 2 experts 5.5 / 6.3, 16 experts 5.6 / 6.4, 128 experts 6.3 / 7.5, 512 experts 7.8 / 10.1; all of one expert 5.9 / 6.9, 6.4 /
+    // 7.3, 6.9 / 7.9, 8.3 / 10.4.  Behind a top-k it is its histogram that is saved, which costs less (a pass over rows of 64 values, top-1,
+    // 128 experts, even routing / all of one expert): 4096 assignments 27.5 / 28.7 and 27.3 / 27.6, 8192 35.9 / 36.5 and 35.8 / 34.9,
+    // 12288 38.2 / 38.2 and 38.4 / 36.5; 8 experts 22.1 / 23.3 and 22.0 / 22.7, 24.6 / 25.3 and 24.8 / 24.6, 27.9 / 28.7 and 28.3 / 27.9.
+    if (!hist_ready && A <= (int64_t)kCountTiles * kPermTile) {
         permute_scatter_kernel<false, true><<<n_tiles, kPermThreads, 0, s>>>(idx, A, E, n_tiles, tile_hist, counts, offsets, perm, inv,
                                                                              active_total);
         return hipGetLastError();

@@ -726,8 +726,8 @@ def test_combine_eights_and_the_rest(gpu_lib, K, dtype, H, fmt):
     test_combine_rows_at_once(gpu_lib, K, dtype, H, fmt)
 
 
-# The permutation by itself counts up to 12288 assignments in every block of the scatter, fewer than 16 experts only one tile of
-# 2048; beyond, the top-k's histograms or a pass of its own.  Against a stable sort, and as part of a layer.
+# The permutation by itself counts up to 12288 assignments in every block of the scatter, in a pass up to 8192; beyond, a pass of its
+# own or the top-k's histograms.  Against a stable sort, and as part of a layer.
 @pytest.mark.parametrize("E,T,K", [(15, 512, 4), (15, 683, 3), (16, 2049, 1), (128, 1536, 8), (128, 1537, 8), (512, 4096, 3), (300, 12289, 1)])
 def test_permutation_counts(gpu_lib, E, T, K):
     H, I, A = 64, 64, T * K
@@ -763,3 +763,38 @@ def test_split_weight_stages(gpu_lib, H, I, rows):
     for shape in ("big", "small", "wide", "big"):
         ctx.moe_set_ffn_variant(shape)
         assert torch.equal(ctx.moe_grouped_ffn(x_perm, offsets, L["w_gate_up"], L["w_down"]), want), shape
+
+
+# The counters of the scatter under skewed routing, eight of each expert with the assignments in front of a tile in their upper halves: the last
+# assignment and the first of a tile, all of one expert and of two, the fewest experts and the most
+@pytest.mark.parametrize("A", [1, 2047, 2049, 8192, 12287, 12288, 12289])
+@pytest.mark.parametrize("E,kind", [(1, "one"), (2, "two"), (15, "one"), (16, "last"), (100, "zipf"), (512, "one"), (512, "two")])
+def test_permutation_of_skewed_choices(gpu_lib, E, kind, A):
+    g = torch.Generator().manual_seed(A + E)
+    f = torch.arange(A)
+    flat = {"one": torch.full((A,), E // 2), "last": torch.full((A,), E - 1), "two": torch.where(f % 3 == 0, 0, E - 1),
+            "zipf": (torch.rand(A, generator=g) ** 4 * E).long().clamp(max=E - 1)}[kind]
+    ctx = gpu_lib.Context(64, E, 1, 64, torch.bfloat16, max_tokens=A, device=DEV)
+    x = torch.zeros((A, 64), dtype=torch.bfloat16, device=DEV)
+    counts, offsets, perm, inv, _ = ctx.moe_permute(x, flat.to(torch.int32).view(A, 1).to(DEV), want_x_perm=False)
+    want = torch.sort(flat, stable=True).indices
+    assert torch.equal(perm.cpu().long(), want)
+    assert torch.equal(inv.cpu().long()[want], f)
+    assert torch.equal(counts.cpu().long(), torch.bincount(flat, minlength=E))
+    assert torch.equal(offsets.cpu().long(), torch.cat([torch.zeros(1, dtype=torch.int64), torch.cumsum(counts.cpu().long(), 0)]))
+
+
+# Behind a top-k up to 8192 assignments are counted by the scatter, whatever the number of experts, more by the top-k
+@pytest.mark.parametrize("E,T,K", [(2, 8192, 1), (2, 8193, 1), (15, 2048, 4), (15, 2049, 4), (128, 1024, 8), (128, 1025, 8)])
+def test_who_counts_behind_a_topk(gpu_lib, E, T, K):
+    H, I = 64, 64
+    w = inputs.Workload("counts", H=H, E=E, K=K, I=I, n_layers=1, D=0, P=T, dtype="bf16", seed=T, residual=False)
+    L = inputs.make_layer(w, 0, device=DEV)
+    L["router_bias"] = -1.2 * torch.log(torch.arange(1, E + 1, dtype=torch.float32, device=DEV))
+    x = inputs.randn((T, H), 1.0, T, "x", 0, "bf16", DEV)
+    ctx = gpu_lib.Context(H, E, K, I, torch.bfloat16, max_tokens=T, residual=False, device=DEV)
+    idx, wt = ctx.moe_router_topk(x, L["w_router"], L["router_bias"])
+    _, offsets, _, inv, x_perm = ctx.moe_permute(x, idx)
+    y = ctx.moe_combine(ctx.moe_grouped_ffn(x_perm, offsets, L["w_gate_up"], L["w_down"]), inv, wt)
+    for _ in range(2):
+        assert torch.equal(ctx.moe_group_forward([L], None, x)[1], y)

@@ -57,3 +57,15 @@ def test_combine_of_any_number_of_rows(gpu_lib, dtype, H, few, many):
 
     a, b = times(call(few), call(many))
     assert a <= 1.2 * b, (a, b)
+
+
+# Counting the assignments of one popular expert takes no turns of all lanes at one counter (12288 to one of 128 experts, us, one counter /
+# eight: 22.9 / 6.9, evenly routed 6.7 / 6.3)
+@pytest.mark.parametrize("E,A", [(128, 12288), (16, 12288), (16, 8192), (512, 4096)])
+def test_permutation_of_skewed_routing(gpu_lib, E, A):
+    ctx = gpu_lib.Context(64, E, 1, 64, torch.bfloat16, max_tokens=A, device=DEV)
+    x = torch.ones((A, 64), dtype=torch.bfloat16, device=DEV)
+    even = (torch.randperm(A, generator=torch.Generator().manual_seed(A)) % E).to(torch.int32).view(A, 1).to(DEV)
+    one = torch.full((A, 1), E // 2, dtype=torch.int32, device=DEV)
+    a, b = times(lambda: ctx.moe_permute(x, one, want_x_perm=False), lambda: ctx.moe_permute(x, even, want_x_perm=False))
+    assert a <= 1.35 * b, (a, b)
