@@ -22,7 +22,7 @@ FLAGS = ["--offload-arch=gfx950", "-O3", "-std=c++17", "-fPIC", "-Wall",
 # The register allocator takes such a result for ready at once: if it ever spilled one, it would save a
 # register the load has not written yet, and the load would later land on whatever the register holds by
 # then (an address, say).  So these kernels must compile without any scratch memory; the build checks it.
-NO_SCRATCH = {"router.hip": ("router_logits_kernel", "route_listed_kernel", "route_small_kernel"), "ffn_w4.hip": ("grouped_gemm_w4_stream_kernel", "grouped_gemm_w4_big_kernel"),
+NO_SCRATCH = {"router.hip": ("router_logits_kernel", "route_listed_kernel", "route_small_kernel", "route_small_tile_kernel"), "ffn_w4.hip": ("grouped_gemm_w4_stream_kernel", "grouped_gemm_w4_big_kernel"),
               "ffn.hip": ("grouped_gemm_bf16_pipe_kernel", "grouped_gemm_bf16_big_kernel")}
 
 

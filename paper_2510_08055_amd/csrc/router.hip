@@ -98,9 +98,11 @@ __device__ __forceinline__ void wait_ring(vec8<float> (&x)[4], vec8<float> (&w)[
 // One block: a 16-token x 16-expert tile of logits with v_mfma_f64_16x16x4.  The hidden dimension is cut
 // into 32-wide chunks, chunk c belongs to partial sum c % 16, and the 16 partial sums are added in a fixed
 // tree (p, p + 4, p + 8, p + 12 in order for p = 0..3, then those four in order), so the summation order of a
-// logit is fixed by H alone.  Wave w holds partial sums w, w + 4, w + 8, w + 12: four independent MFMA chains.  (16 waves per
-// block were no faster at 272 to 640 tokens: 11.5 against 11.9 us and 16.4 against 18.4 us.  Decode batches have a kernel of
-// their own, see route_small_kernel, with the same order of summation.)
+// logit is fixed by H alone, whichever of the two block shapes computes it:
+//   NW = 4:  wave w holds partial sums w, w + 4, w + 8, w + 12: four independent MFMA chains.  (16 waves per block were no faster at 272 to
+//            640 tokens: 11.5 against 11.9 us and 16.4 against 18.4 us.)
+//   NW = 16: one partial sum per wave.  The shape of a decode batch's one-launch routing where a block has a whole tile of logits
+//            (see route_small_tile_kernel; where it has a fourth of one, route_small_kernel, with the same order of summation).
 // Lane l supplies row (l % 16) of both operands; its quarter q = l / 16 owns the 8 consecutive
 // k-values [c*32 + q*8, c*32 + q*8 + 8) of chunk c and feeds them to 8 successive MFMAs (any fixed
 // pairing of k-slots is a valid summation order).  The raw operands of the next chunks are fetched
@@ -137,11 +139,12 @@ __device__ __forceinline__ bool last_to_arrive(uint32_t* ticket, uint32_t n, int
 
 // The tile of logits of rows row(0 .. 15) and experts e0 .. e0 + 15, stored by wave 0; every thread of the block calls it.
 // Rows from n_rows on are read and not used.  store(i, j, z) takes the logit z of row i < n_rows and expert e0 + j < E.
-template <typename T, typename Row, typename Store>
+template <typename T, int NW, typename Row, typename Store>
 __device__ __forceinline__ void logits_tile(Row row, int n_rows, int H, const T* __restrict__ wr,
                                             const float* __restrict__ bias, int E, int e0, Store store)
 {
-    constexpr int NW = 4, NACC = 4;              // waves, partial sums per wave
+    constexpr int NACC = 16 / NW;                // partial sums per wave
+    static_assert(NW == 4 || NW == 16, "16 partial sums over 4 or 16 waves");
     __shared__ double part[NW - 1][4][64];       // [wave-1][element v][lane]: a wave's partial sums, already added up
     const int lane = lane_id();
     const int wave = __builtin_amdgcn_readfirstlane((int)(threadIdx.x >> 6));
@@ -226,7 +229,9 @@ __device__ __forceinline__ void logits_tile(Row row, int n_rows, int H, const T*
             double z = 0.0;
 #pragma unroll
             for (int p = 0; p < 4; ++p) {        // partial sums p, p + 4, p + 8, p + 12
-                const double s = p == 0 ? mysum[v] : part[p - 1][v][lane];
+                double s = p == 0 ? mysum[v] : part[p - 1][v][lane];
+#pragma unroll
+                for (int w = p + 4; w < NW; w += 4) s += part[w - 1][v][lane];
                 z = p == 0 ? s : z + s;
             }
             if (v * 4 + q < n_rows) store(v * 4 + q, r, z + b);
@@ -254,7 +259,7 @@ __global__ __launch_bounds__(256) void router_logits_kernel(RowSrc x, int64_t n_
         for (int i = threadIdx.x; i < zero_n; i += 256) zero_buf[i] = 0;
     const int64_t t0 = (int64_t)blockIdx.x * 16;
     const int e0 = (int)blockIdx.y * 16;
-    logits_tile<T>(rows_from<T>(x, t0, n_tok, H), rows_left(t0, n_tok, 16), H, wr, bias, E, e0,
+    logits_tile<T, 4>(rows_from<T>(x, t0, n_tok, H), rows_left(t0, n_tok, 16), H, wr, bias, E, e0,
                       [&](int i, int j, double z) { logits[(t0 + i) * E + e0 + j] = z; });
 }
 
@@ -1158,7 +1163,7 @@ __global__ __launch_bounds__(256, 3) void route_listed_kernel(RowSrc x, int H, c
     const int n = *n_listed, e0 = (int)blockIdx.y * 16;
     for (int64_t at = (int64_t)blockIdx.x * 16; at < n; at += (int64_t)gridDim.x * 16) {
         const int rows = rows_left(at, n, 16);
-        logits_tile<bf16_t>([&](int i) { return row_ptr<bf16_t>(x, listed[at + (i < rows ? i : rows - 1)], H); }, rows, H, wr,
+        logits_tile<bf16_t, 4>([&](int i) { return row_ptr<bf16_t>(x, listed[at + (i < rows ? i : rows - 1)], H); }, rows, H, wr,
                                bias, E, e0, [&](int i, int j, double z) { store_shared(logits + (at + i) * E + e0 + j, z); });
         if (last_to_arrive(tickets + at / 16, gridDim.y, &flag)) {
             const int c = (int)threadIdx.x & 15, row = (int)threadIdx.x >> 4;
@@ -1198,7 +1203,16 @@ __global__ __launch_bounds__(256, 3) void route_listed_kernel(RowSrc x, int H, c
 // Measured with clocks in the kernel, us from its start until the sums are stored, the last ticket is drawn, the winners are known, the
 // end; 128 experts, H = 2048, top-8: one token 3.3, 4.0, 6.5, 8.0, 32 tokens 3.7, 4.8, 8.5, 11.2.  With one block to a tile, no walk,
 // unrolled loops and rounds that compare (value, index) pairs: one token 6.5, 7.5, 11, 12.7, 32 tokens 7.9, 8.9, 12.4, 15.6; a pass of
-// four layers over one token 162 us then, 147 now.  256 tokens, H = 2880, top-4, two classes to a block, take 17 us either way.
+// four layers over one token 162 us then, 147 now.
+//
+// Where a tile is not cut, route_small_tile_kernel has a block of 16 waves for it, one partial sum to a wave, and its code is not walked:
+// that is the shorter way where the rows are short (the MFMAs are soon done, the walk is not), where there are many experts (the
+// last block of a tile reads kClasses times as many sums) and where the blocks would not all find a compute unit.  This kernel / that one,
+// us (kernel trace, caches as a pass leaves them), top-8, bf16: 64 experts, 16 tokens, H = 512 9.2 / 8.4, 1024 10.1 / 10.2, 2048 10.8 / 13.3;
+// 128 experts, 16 tokens, 512 10.1 / 8.7, 1024 10.8 / 10.6, 2048 11.0 / 12.8, 128 tokens, 1024 13.6 / 12.0, 2048 14.3 / 14.7, 4096 16.7 / 19.5;
+// 256 experts, 16 tokens, 1024 14.1 / 11.9, 2048 14.0 / 14.7, 64 tokens, 2048 17.5 / 16.4, 4096 19.8 / 20.8; with four classes to a block,
+// 256 tokens, 2048 27.1 / 18.8, 4096 36.6 / 24.1; 128 experts, 200 tokens, two classes, 2880 19.1 / 18.0.  fp32: 128 experts, 16 tokens, 256
+// 11.1 / 8.9, 1024 10.7 / 11.5, 2048 11.9 / 18.8, 200 tokens, two classes, 2048 18.9 / 20.9.
 //
 // A token's experts are distinct as long as K of its logits are finite; the stable rank of an assignment inside its expert is then the
 // number of earlier tokens that chose the expert: one bit per token and expert in LDS, counted with popcounts.  A bit that is set twice
@@ -1207,8 +1221,95 @@ __global__ __launch_bounds__(256, 3) void route_listed_kernel(RowSrc x, int H, c
 // ----------------------------------------------------------------------------------------------
 constexpr int kClasses = 4;
 static_assert(kSmallSumBytes == kClasses * (int)sizeof(double), "a logit's sums");
-constexpr int kSmallWaves = 8, kSumWaves = 4;
+constexpr int kSmallWaves = 8, kSumWaves = 4, kTileWaves = 16;
 constexpr int kSmallWords = kSmallTokens / 64;
+
+// The choices of a batch, and its permutation by one block.
+struct SmallLists {
+    unsigned long long chosen[kSmallExperts][kSmallWords];      // bit t of an expert: token t chose it
+    int32_t count[kSmallExperts], start[kSmallExperts];
+    uint8_t expert_of[kSmallTokens * 16];
+    int32_t twice;
+    static_assert(kSmallExperts <= 256, "an expert is one byte of expert_of");
+
+    // by n threads, of which this is thread i
+    __device__ __forceinline__ void clear(int E, int i, int n)
+    {
+        for (int j = i; j < E * kSmallWords; j += n) (&chosen[0][0])[j] = 0ull;
+        for (int j = i; j < E; j += n) count[j] = 0;
+        if (i == 0) twice = 0;
+    }
+
+    // single: expert_of holds the choices already (idx otherwise)
+    template <int NT>
+    __device__ __forceinline__ void permute(const int32_t* idx, bool single, int n_tok, int E, int K, uint32_t k_inverse,
+                                            int32_t* __restrict__ offsets, int32_t* __restrict__ perm, int32_t* __restrict__ inv,
+                                            unsigned long long* __restrict__ active_total)
+    {
+        const int tid = threadIdx.x, lane = tid & 63, A = n_tok * K;
+        auto token_of = [&](int f) { return (int)((uint32_t)f * k_inverse >> 16); };      // f / K: k_inverse = ceil(2^16 / K)
+        if (!single) {
+            constexpr int PER = kSmallTokens * 16 / NT;            // assignments per thread, at most
+            int32_t my_e[PER];
+#pragma unroll
+            for (int p = 0; p < PER; ++p) my_e[p] = p * NT + tid < A ? load_shared(idx + p * NT + tid) : 0;
+#pragma unroll
+            for (int p = 0; p < PER; ++p) expert_of[p * NT + tid] = (uint8_t)my_e[p];
+            // (a thread reads its own)
+        }
+#pragma unroll 1
+        for (int f = tid; f < A; f += NT) {
+            const int t = token_of(f), e = expert_of[f];
+            const unsigned long long bit = 1ull << (t & 63);
+            if (atomicOr(&chosen[e][t >> 6], bit) & bit) twice = 1;
+            atomicAdd(&count[e], 1);
+        }
+        __syncthreads();
+        // exclusive scan of the expert counts by wave 0: lane l owns experts [4 l, 4 l + 4)
+        if (tid < 64) {
+            constexpr int EPL = kSmallExperts / 64;
+            int cnt[EPL], sum = 0, act = 0;
+#pragma unroll
+            for (int i = 0; i < EPL; ++i) {
+                const int e = lane * EPL + i;
+                cnt[i] = e < E ? count[e] : 0;
+                sum += cnt[i];
+                act += (int)__popcll(__ballot(cnt[i] > 0));
+            }
+            int run = wave_scan(sum) - sum;
+#pragma unroll
+            for (int i = 0; i < EPL; ++i) {
+                const int e = lane * EPL + i;
+                if (e <= E) offsets[e] = run;       // (lanes behind the experts hold the total: the first of them has entry E)
+                if (e < E) start[e] = run;
+                run += cnt[i];
+            }
+            if (lane == 63 && E == kSmallExperts) offsets[E] = run;
+            if (lane == 0) atomicAdd(active_total, (unsigned long long)act);
+        }
+        __syncthreads();
+        if (__builtin_expect(twice == 0, 1)) {
+#pragma unroll 1
+            for (int f = tid; f < A; f += NT) {
+                const int t = token_of(f), e = expert_of[f];
+                int pos = start[e] + (int)__popcll(chosen[e][t >> 6] & ((1ull << (t & 63)) - 1));
+#pragma unroll 1
+                for (int j = 0; j < t >> 6; ++j) pos += (int)__popcll(chosen[e][j]);
+                perm[pos] = f;
+                inv[f] = pos;
+            }
+        } else {
+#pragma unroll 1
+            for (int f = tid; f < A; f += NT) {
+                const int e = expert_of[f];
+                int pos = start[e];
+                for (int g = 0; g < f; ++g) pos += expert_of[g] == e;
+                perm[pos] = f;
+                inv[f] = pos;
+            }
+        }
+    }
+};
 
 // One partial sum (p of 16) of a 16 x 16 tile of logits by a wave: chunks p, p + 16, ... of the rows, a group of them at a
 // time.  x_row and w_row: the lane's rows (lane % 16); stage: the wave's LDS, 1 KB per load and chunk of a group.
@@ -1274,11 +1375,8 @@ __global__ __launch_bounds__(kSmallWaves * 64) void route_small_kernel(
     constexpr int LDS = kSumWaves * STAGE > 16 * ZLD * 8 ? kSumWaves * STAGE : 16 * ZLD * 8;
     __shared__ __attribute__((aligned(1024))) char lds[LDS];               // the summing waves' stages, then the tile's logits
     double* const z = reinterpret_cast<double*>(lds);
-    __shared__ unsigned long long chosen[kSmallExperts][kSmallWords];      // bit t of an expert: token t chose it
-    __shared__ int32_t count[kSmallExperts], start[kSmallExperts];
-    __shared__ uint8_t expert_of[kSmallTokens * 16];
-    __shared__ int32_t flag, twice;
-    static_assert(kSmallExperts <= 256, "an expert is one byte of expert_of");
+    __shared__ SmallLists lists;
+    __shared__ int32_t flag;
     const int tid = threadIdx.x, lane = tid & 63;
     const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
     const int t0 = (int)blockIdx.x * 16, e0 = (int)blockIdx.y * 16;
@@ -1293,11 +1391,7 @@ __global__ __launch_bounds__(kSmallWaves * 64) void route_small_kernel(
         asm volatile("" : "+v"(turn));       // (or the compiler would write the top-k down twice)
         turn = __builtin_amdgcn_readfirstlane(turn);
         if (turn != 0) {
-            if (wave >= kSumWaves) {
-                for (int i = tid - kSumWaves * 64; i < E * kSmallWords; i += NT - kSumWaves * 64) (&chosen[0][0])[i] = 0ull;
-                if (tid - kSumWaves * 64 < E) count[tid - kSumWaves * 64] = 0;
-                if (tid == kSumWaves * 64) twice = 0;
-            }
+            if (wave >= kSumWaves) lists.clear(E, tid - kSumWaves * 64, NT - kSumWaves * 64);
 #pragma unroll 1
             for (int cls = (int)blockIdx.z; cls < kClasses; cls += (int)gridDim.z) {
                 double4_t acc;
@@ -1347,7 +1441,7 @@ __global__ __launch_bounds__(kSmallWaves * 64) void route_small_kernel(
             topk_of_row<NPL>([&](int x) { return own[x]; }, E, turn == 0 ? 1 : K, renorm, r, e, wt);
             if (turn != 0 && t < n_tok && r < K) {
                 w[t * K + r] = wt;
-                if (single) expert_of[t * K + r] = (uint8_t)e;
+                if (single) lists.expert_of[t * K + r] = (uint8_t)e;
                 else store_shared(idx + t * K + r, (int32_t)e);
             }
             asm volatile("" ::"v"(e), "v"(wt));
@@ -1357,68 +1451,42 @@ __global__ __launch_bounds__(kSmallWaves * 64) void route_small_kernel(
     if (single) __syncthreads();
     else if (!last_to_arrive(tickets, gridDim.x, &flag)) return;
 
-    const int A = n_tok * K;
-    auto token_of = [&](int f) { return (int)((uint32_t)f * k_inverse >> 16); };      // f / K: k_inverse = ceil(2^16 / K)
-    if (!single) {
-        constexpr int PER = kSmallTokens * 16 / NT;            // assignments per thread, at most
-        int32_t my_e[PER];
-#pragma unroll
-        for (int p = 0; p < PER; ++p) my_e[p] = p * NT + tid < A ? load_shared(idx + p * NT + tid) : 0;
-#pragma unroll
-        for (int p = 0; p < PER; ++p) expert_of[p * NT + tid] = (uint8_t)my_e[p];
-        // (a thread reads its own)
-    }
-#pragma unroll 1
-    for (int f = tid; f < A; f += NT) {
-        const int t = token_of(f), e = expert_of[f];
-        const unsigned long long bit = 1ull << (t & 63);
-        if (atomicOr(&chosen[e][t >> 6], bit) & bit) twice = 1;
-        atomicAdd(&count[e], 1);
-    }
-    __syncthreads();
-    // exclusive scan of the expert counts by wave 0: lane l owns experts [4 l, 4 l + 4)
-    if (wave == 0) {
-        constexpr int EPL = kSmallExperts / 64;
-        int cnt[EPL], sum = 0, act = 0;
-#pragma unroll
-        for (int i = 0; i < EPL; ++i) {
-            const int e = lane * EPL + i;
-            cnt[i] = e < E ? count[e] : 0;
-            sum += cnt[i];
-            act += (int)__popcll(__ballot(cnt[i] > 0));
-        }
-        int run = wave_scan(sum) - sum;
-#pragma unroll
-        for (int i = 0; i < EPL; ++i) {
-            const int e = lane * EPL + i;
-            if (e <= E) offsets[e] = run;       // (lanes behind the experts hold the total: the first of them has entry E)
-            if (e < E) start[e] = run;
-            run += cnt[i];
-        }
-        if (lane == 63 && E == kSmallExperts) offsets[E] = run;
-        if (lane == 0) atomicAdd(active_total, (unsigned long long)act);
-    }
-    __syncthreads();
-    if (__builtin_expect(twice == 0, 1)) {
-#pragma unroll 1
-        for (int f = tid; f < A; f += NT) {
-            const int t = token_of(f), e = expert_of[f];
-            int pos = start[e] + (int)__popcll(chosen[e][t >> 6] & ((1ull << (t & 63)) - 1));
-#pragma unroll 1
-            for (int j = 0; j < t >> 6; ++j) pos += (int)__popcll(chosen[e][j]);
-            perm[pos] = f;
-            inv[f] = pos;
-        }
-    } else {
-#pragma unroll 1
-        for (int f = tid; f < A; f += NT) {
-            const int e = expert_of[f];
-            int pos = start[e];
-            for (int g = 0; g < f; ++g) pos += expert_of[g] == e;
-            perm[pos] = f;
-            inv[f] = pos;
+    lists.permute<NT>(idx, single, n_tok, E, K, k_inverse, offsets, perm, inv, active_total);
+}
+
+// The same where a block has a tile's logits whole, with a partial sum to a wave.
+template <typename T, int NPL>
+__global__ __launch_bounds__(kTileWaves * 64) void route_small_tile_kernel(
+    RowSrc x, int n_tok, int H, const T* __restrict__ wr, const float* __restrict__ bias, int E, int K, uint32_t k_inverse, int renorm,
+    double* logits, int32_t* idx, float* __restrict__ w, int32_t* __restrict__ offsets, int32_t* __restrict__ perm,
+    int32_t* __restrict__ inv, unsigned long long* __restrict__ active_total, uint32_t* tickets)
+{
+    constexpr int NT = kTileWaves * 64;
+    __shared__ SmallLists lists;
+    __shared__ int32_t flag;
+    const int tid = threadIdx.x;
+    const int t0 = (int)blockIdx.x * 16, e0 = (int)blockIdx.y * 16;
+    const bool single = gridDim.x == 1;
+    logits_tile<T, kTileWaves>(rows_from<T>(x, t0, n_tok, H), rows_left(t0, n_tok, 16), H, wr, bias, E, e0,
+                               [&](int i, int j, double z) { store_shared(logits + (int64_t)(t0 + i) * E + e0 + j, z); });
+    lists.clear(E, tid, NT);
+    if (!last_to_arrive(tickets + 1 + blockIdx.x, gridDim.y, &flag)) return;
+
+    const int r = tid & 15, row = tid >> 4, t = t0 + row;
+    if (row < 16 && t0 + (row & ~3) < n_tok) {      // (whole waves)
+        int e;
+        float wt;
+        const double* const own = logits + (int64_t)(t < n_tok ? t : n_tok - 1) * E;
+        topk_of_row<NPL>([&](int x) { return load_shared(own + x); }, E, K, renorm, r, e, wt);
+        if (t < n_tok && r < K) {
+            w[t * K + r] = wt;
+            if (single) lists.expert_of[t * K + r] = (uint8_t)e;
+            else store_shared(idx + t * K + r, (int32_t)e);
         }
     }
+    if (single) __syncthreads();
+    else if (!last_to_arrive(tickets, gridDim.x, &flag)) return;
+    lists.permute<NT>(idx, single, n_tok, E, K, k_inverse, offsets, perm, inv, active_total);
 }
 
 hipError_t launch_route_small(int dtype, RowSrc x, int64_t T, int H, const void* w_router, const float* bias, int E, int K,
@@ -1430,21 +1498,29 @@ hipError_t launch_route_small(int dtype, RowSrc x, int64_t T, int H, const void*
     const hipError_t err = compute_units(&cus);
     if (err != hipSuccess) return err;
     const int npl = (E + 15) / 16, tiles = (int)((T + 15) / 16) * npl;
-    // the classes of a tile share a block where they would not all find a compute unit
-    const dim3 grid((unsigned)((T + 15) / 16), (unsigned)npl, tiles * 4 <= cus ? 4 : tiles * 2 <= cus ? 2 : 1);
+    // A tile's sums in kClasses blocks, each on a compute unit of its own, where that shortens the chain of MFMAs by more than its costs
+    // (figures at route_small_kernel; the line is drawn through the lengths at which the two were level, from 1 to 256 tokens and 8 to
+    // 256 experts).  fp32 rows, twice the bytes, gain twice as much, and with two classes to a block too.
+    const int length = dtype == MOE_BF16 ? H : 2 * H, rows = T < 16 ? (int)T : 16;
+    int blocks = 0;      // of a tile's sums; none: a block has the tile
+    if (length >= 512 + E * (rows + 4) / 4 + 11 * tiles)
+        blocks = tiles * kClasses <= cus ? kClasses : dtype == MOE_F32 && tiles * 2 <= cus ? 2 : 0;
     const uint32_t k_inverse = (65536u + K - 1) / K, e_inverse = ((1u << 20) + E - 1) / E;
     static_assert(kSmallTokens * 16 * 15 < 65536, "f / K for f < 256 K, K <= 16");
     static_assert(16 * kSmallExperts * (kSmallExperts - 1) < 1 << 20, "i / E for i < 16 E, E <= 256");
-    auto go = [&](auto npl_const) {
+    auto launch = [&](auto elem_t, auto npl_const) {
+        typedef decltype(elem_t) X;
         constexpr int NPL = decltype(npl_const)::value;
-        if (dtype == MOE_BF16)
-            route_small_kernel<bf16_t, NPL><<<grid, kSmallWaves * 64, 0, s>>>(
-                x, (int)T, H, (const bf16_t*)w_router, bias, E, e_inverse, K, k_inverse, renorm, sums, idx, w, offsets, perm, inv, active_total, tickets);
+        const X* const wr = static_cast<const X*>(w_router);
+        if (blocks > 0)
+            route_small_kernel<X, NPL><<<dim3((unsigned)((T + 15) / 16), (unsigned)npl, (unsigned)blocks), kSmallWaves * 64, 0, s>>>(
+                x, (int)T, H, wr, bias, E, e_inverse, K, k_inverse, renorm, sums, idx, w, offsets, perm, inv, active_total, tickets);
         else
-            route_small_kernel<float, NPL><<<grid, kSmallWaves * 64, 0, s>>>(
-                x, (int)T, H, (const float*)w_router, bias, E, e_inverse, K, k_inverse, renorm, sums, idx, w, offsets, perm, inv, active_total, tickets);
+            route_small_tile_kernel<X, NPL><<<dim3((unsigned)((T + 15) / 16), (unsigned)npl), kTileWaves * 64, 0, s>>>(
+                x, (int)T, H, wr, bias, E, K, k_inverse, renorm, sums, idx, w, offsets, perm, inv, active_total, tickets);
         return hipGetLastError();
     };
+    auto go = [&](auto npl_const) { return dtype == MOE_BF16 ? launch(bf16_t(), npl_const) : launch(float(), npl_const); };
     if (npl <= 1) return go(std::integral_constant<int, 1>{});
     if (npl <= 2) return go(std::integral_constant<int, 2>{});
     if (npl <= 8) return go(std::integral_constant<int, 8>{});

@@ -798,3 +798,45 @@ def test_who_counts_behind_a_topk(gpu_lib, E, T, K):
     y = ctx.moe_combine(ctx.moe_grouped_ffn(x_perm, offsets, L["w_gate_up"], L["w_down"]), inv, wt)
     for _ in range(2):
         assert torch.equal(ctx.moe_group_forward([L], None, x)[1], y)
+
+
+# The one-launch routing: a tile's sums in four blocks, in two (fp32) or whole in one.  Both sides of the line (the last length of the one shape,
+# the first of the other), the most tiles of either, ragged rows; against the separate launches
+@pytest.mark.parametrize("dtype,E,K,T,H", [
+    ("bf16", 16, 2, 16, 600), ("bf16", 16, 2, 16, 608),            # 1 tile
+    ("bf16", 128, 8, 1, 752), ("bf16", 128, 8, 1, 760),
+    ("bf16", 256, 16, 64, 2488), ("bf16", 256, 8, 64, 2496),       # 64 tiles: 256 blocks
+    ("bf16", 256, 8, 65, 4096), ("bf16", 130, 3, 256, 4104),       # 80 and 144
+    ("f32", 128, 8, 200, 1144), ("f32", 128, 8, 200, 1152),        # 104 tiles, two classes to a block
+    ("f32", 32, 16, 33, 1000), ("f32", 250, 5, 256, 520),
+])
+def test_one_launch_routing_whole_and_cut_tiles(gpu_lib, dtype, E, K, T, H):
+    w = inputs.Workload("cut", H=H, E=E, K=K, I=64, n_layers=1, D=T, P=0, dtype=dtype, seed=H + T)
+    L = inputs.make_layer(w, 0, device=DEV)
+    L["router_bias"] = inputs.randn((E,), 0.5, w.seed, "bias", 0, "f32", DEV)
+    for s in range(2):
+        x = inputs.randn((T, H), 1.0, w.seed + s, "x", 0, dtype, DEV)
+        ctx = gpu_lib.Context(H, E, K, 64, inputs.torch_dtype(dtype), max_tokens=T, residual=False, device=DEV, renormalize=bool(s))
+        idx, wt = ctx.moe_router_topk(x, L["w_router"], L["router_bias"])
+        _, offsets, _, inv, x_perm = ctx.moe_permute(x, idx)
+        want = ctx.moe_combine(ctx.moe_grouped_ffn(x_perm, offsets, L["w_gate_up"], L["w_down"]), inv, wt)
+        for _ in range(2):
+            assert torch.equal(ctx.moe_group_forward([L], x, None)[0], want)
+
+
+@pytest.mark.parametrize("dtype,E,K,T,H", [("bf16", 40, 16, 16, 1024), ("bf16", 128, 8, 70, 2048), ("f32", 128, 8, 200, 1152)])
+def test_cut_tiles_of_logits_that_are_not_finite(gpu_lib, dtype, E, K, T, H):
+    w = inputs.Workload("odd", H=H, E=E, K=K, I=64, n_layers=1, D=T, P=0, dtype=dtype, seed=T + E)
+    L = inputs.make_layer(w, 0, device=DEV)
+    x = inputs.randn((T, H), 1.0, w.seed, "x", 0, dtype, DEV)
+    x[::3, 5] = float("nan")
+    x[1::3] = x[1::3].abs()
+    L["w_router"][2] = float("inf")
+    L["router_bias"] = torch.full((E,), float("-inf"), device=DEV)
+    L["router_bias"][[1, 2, E - 1]] = 0.25
+    ctx = gpu_lib.Context(H, E, K, 64, inputs.torch_dtype(dtype), max_tokens=T, residual=False, device=DEV)
+    idx, wt = ctx.moe_router_topk(x, L["w_router"], L["router_bias"])
+    _, offsets, _, inv, x_perm = ctx.moe_permute(x, idx)
+    want = ctx.moe_combine(ctx.moe_grouped_ffn(x_perm, offsets, L["w_gate_up"], L["w_down"]), inv, wt)
+    bits = torch.int16 if dtype == "bf16" else torch.int32
+    assert torch.equal(ctx.moe_group_forward([L], x, None)[0].view(bits), want.view(bits))
