@@ -1138,8 +1138,7 @@ const char* ffn_variant_name(int dtype, int variant, int64_t A, int E, int H, in
     if (pick_variant(variant, true, A, E, I, H, &v) != hipSuccess) return "";
     switch (v) {
         case V_PIPE_SMALL: return "grouped_gemm_bf16_pipe_kernel<2,128,2,3,2,4,gated>";
-        // (a name that callers know; the shape had one wave when it got it)
-        case V_PIPE_FEW: return "grouped_gemm_bf16_pipe_kernel<1,64,1,5,1,1,gated>";
+        case V_PIPE_FEW: return "grouped_gemm_bf16_pipe_kernel<1,64,1,5,1,2,gated>";
         case V_PIPE_WIDE: return "grouped_gemm_bf16_pipe_kernel<8,256,2,2,2,8,gated>";
         case V_PIPE_BIG: return "grouped_gemm_bf16_big_kernel<gated>";
         default: return "grouped_gemm_bf16_kernel<128,128,gated>";

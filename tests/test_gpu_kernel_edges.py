@@ -333,7 +333,7 @@ def test_routing_of_logits_that_are_not_finite(gpu_lib, E, K, T, kind):
 
 
 # The two streaming shapes: 64 x 128 tiles (four waves, a ring of three stages) and, taken when the launch has few tiles, 32 x 64
-# (one wave, five stages).  k-extents around the length of the ring, row and column edges, a plain and a split
+# (two waves, five stages).  k-extents around the length of the ring, row and column edges, a plain and a split
 # intermediate.  Against the register-staged kernel bit for bit (the order of a sum is the same in every shape) and against
 # the oracle.
 @pytest.mark.parametrize("H,I,rows", [
@@ -458,7 +458,7 @@ def test_streamed_combine(gpu_lib, H, K, T, dtype):
 # The shape a launch takes is the one moe_ffn_variant names: pinned, or by the rule.  By the rule: a streaming shape up to 56
 # rows per expert, and beyond as long as its tiles are one round (two per compute unit, 512 on 256 units); narrow tiles while
 # these are less than one round.
-FEW, SMALL, BIG, WIDE = "<1,64,1,5,1,1,", "<2,128,2,3,2,4,", "big", "<8,256,2,2,2,8,"
+FEW, SMALL, BIG, WIDE = "<1,64,1,5,1,2,", "<2,128,2,3,2,4,", "big", "<8,256,2,2,2,8,"
 
 
 @pytest.mark.parametrize("H,E,K,I,T,want", [
