@@ -749,8 +749,10 @@ def test_permutation_counts(gpu_lib, E, T, K):
 
 
 # A split intermediate: a weight stage serves a step of hi and a step of lo values; the shortest rows the persistent kernel takes, an
-# odd number of weight stages, blocks with one tile and with two (280 and 300 tiles on 256 units), row blocks per wave from none to four
-@pytest.mark.parametrize("H,I,rows", [(512, 256, [35] * 140), (264, 320, [40, 1, 300] * 50), (768, 448, [256, 129, 0, 64])])
+# odd number of weight stages, row blocks per wave from none to four, blocks with one tile (12 on 256 units), two (280, and 400 or 500 by the
+# height of the tiles) and up to four (800 of four and of five weight stages: the ring of three slots goes on where the tile before left it)
+@pytest.mark.parametrize("H,I,rows", [(512, 256, [35] * 140), (264, 320, [40, 1, 300] * 50), (768, 448, [256, 129, 0, 64]),
+                                      (264, 256, [9, 40] * 200), (264, 320, [33] * 400)])
 def test_split_weight_stages(gpu_lib, H, I, rows):
     E, A = len(rows), sum(rows)
     w = inputs.Workload("pairs", H=H, E=E, K=1, I=I, n_layers=1, D=0, P=A, dtype="bf16", seed=A)
