@@ -411,7 +411,7 @@ __global__ __launch_bounds__(NW * 64, MINW) void grouped_gemm_bf16_pipe_kernel(
         };
 
         // prologue: the weight stages are already in flight; the activation stages follow, and the first
-        // wait lets through only the activation loads issued after stage 0's
+        // wait lets through only the activation loads issued after stage 0's (so all weight stages of the prologue have landed then)
 #pragma unroll 1
         for (int st = 0; st < AHEAD && st < nk_; ++st)
 #pragma unroll
@@ -988,12 +988,15 @@ static hipError_t pick_variant(int pinned, bool gated, int64_t A, int E, int N, 
     if (K < 256 && A > (int64_t)64 * E && !small_is_one_round) return hipSuccess;
     // Narrow tiles (32 x 64, two waves, five stages of 12 KB) while they are one round.  What bounds such a launch is how
     // much it has in flight: 96 tiles of 64 x 128 for one token at 8 of 128 experts (H = 2048, I = 768) with two stages of
-    // weights each, 16 KB, ask for 2.6 TB/s; 192 narrow ones keep four stages of 8 KB.  Then it is a wave's own instructions: with one
+    // weights each, 16 KB, ask for 2.6 TB/s; 192 narrow ones ask for four stages of 8 KB.  Then it is a wave's own instructions: with one
     // wave to a tile the k-loop took 9.8 us whether four, five or six stages were on their way, with two waves it takes 7.9 (6.3
     // TB/s; gate_up and down of one token, clocks in the kernel, 13.2 -> 11.0 and 7.2 -> 6.3 us; a pass of four layers 139 -> 129).
-    // 64 x 128 against narrow tiles of one wave, us: layer of that shape, 2 tokens (384 and 512 narrow tiles) 57.1 / 53.8, 3 tokens
-    // (576 and 768) 73.2 / 75.7; gate_up, 8 experts, H = I = 1024, 40 rows (448) 12.6 / 13.3, 56 rows (576) 12.9 / 20.1; H = I =
-    // 512, 100 rows (464) 9.5 / 10.0, 130 rows (584) 9.9 / 14.8.
+    // 64 x 128 against narrow tiles, us (kernel trace, weights from memory).  Tiles of one row are level at one round: gate_up of that
+    // shape, 8 experts (192 narrow tiles) 18.6 / 12.6, 16 (384) 20.4 / 19.0, 21 (504) 25.0 / 23.6, 24 (576) 32.1 / 31.3, 28 (672) 35.1 /
+    // 36.4; down, 8 (256) 8.6 / 7.1, 16 (512) 10.8 / 11.0, 18 (576) 13.6 / 14.8; H = I = 2880, gate_up, 4 (360) 25.8 / 25.4, 5 (450) 27.5 /
+    // 28.3, down, 4 (180) 23.2 / 13.9, 8 (360) 25.3 / 24.9.  Full tiles, whose activations two column tiles read where one did, lose a
+    // little ahead of it and much behind it: gate_up, 8 experts, H = I = 1024, 24 rows (256) 11.3 / 8.8, 40 rows (512, 448 expected) 11.5 /
+    // 12.2, 80 rows (768) 12.1 / 16.9; H = I = 512, 100 rows (512, 464 expected) 6.6 / 7.7, 130 rows (640) 6.8 / 11.2.
     *v = few_is_one_round ? V_PIPE_FEW : V_PIPE_SMALL;
     return hipSuccess;
 }

@@ -412,6 +412,8 @@ template <int R, typename Head> struct Margin {
 // Top-k of R tokens by the 16 lanes of a row (c = lane % 16): lane c < K ends with the c-th winner of each and its weight.
 // logit(r, e): that of token r and expert e < E.  (A round is a chain of dependent instructions; two tokens fill its gaps.)
 // With a margin K must be less than E.
+// Whatever the logits are, it ends after its rounds, with indices below E, and waits for no other wave: route_small_kernel has one wave walk
+// through it over LDS that loads still write.  So no barrier and no loop whose end hangs on a logit may come in.
 template <int NPL, int R, typename M, typename Logit>   // logits per lane: experts c + 16 i, i < NPL
 __device__ __forceinline__ void topk_of_rows(Logit logit, int E, int K, int renorm, int c, int (&my_e)[R], float (&my_w)[R],
                                              M& margin)
